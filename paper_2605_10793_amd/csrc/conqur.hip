@@ -710,8 +710,9 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       g.np_out = np_t; g.np_out_n = np_n;
       g.Xadd = add_x ? ctx->PX : nullptr;
       g.C32 = out32;
-      e = launch_gemm_nt(g, EPI_XOUT, h, s);
-      mfma_flop += gemm_issued_flop(g, EPI_XOUT, h);
+      const GemmEpilogue epi = (add_x && out32 && np_t == 0 && np_n == 0) ? EPI_XADD : EPI_XOUT;   // no operand planes wanted: the sum alone
+      e = launch_gemm_nt(g, epi, h, s);
+      mfma_flop += gemm_issued_flop(g, epi, h);
     }
     cur ^= 1;
     return e;
@@ -727,14 +728,14 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     g.M = g.N = g.K = dh;
     g.nseg = 1;   // D^2 is second order small: single bf16 planes are ample
     g.ldc = dh; g.batchC = blk; g.Pn = ctx->PW2; g.np_out = 2; g.plane_out = plane;
-    g.Padd = ctx->PW; g.np_add = 2; g.coef_i = 0.0f; g.coef_g = 1.5f;
+    g.Padd = ctx->PW; g.coef_g = 1.5f;
     g.symmetric = 1;
+    g.Pacc = ctx->PW2 + 2 * plane;   // D^2 itself, third plane of the buffer
+    g.resid_part = keep_square ? ctx->resid_part : nullptr;
     sq_slot = -1;
     mfma_flop += gemm_issued_flop(g, EPI_SQUARE, h);
-    if (!keep_square) return launch_gemm_nt(g, EPI_GRAMW, h, s);
-    g.Pacc = ctx->PW2 + 2 * plane;   // D^2 itself, third plane of the buffer
-    g.resid_part = ctx->resid_part;
     hipError_t e = launch_gemm_nt(g, EPI_SQUARE, h, s);
+    if (!keep_square) return e;
     if (e == hipSuccess) e = launch_sum_partials(ctx->resid_part, ctx->resid_parts, h, ctx->resid + (size_t)slot * h, s);
     if (e == hipSuccess)
       e = hipMemcpyAsync(ctx->host_res + (size_t)slot * h, ctx->resid + (size_t)slot * h, h * sizeof(double), hipMemcpyDeviceToHost, s);

@@ -14,8 +14,8 @@ enum GemmEpilogue : int {
   EPI_SIGN = 0,  // corner signs, transposed: St[n][m] = +-1 (bf16 or fp16)
   EPI_ACT = 1,   // Y[m][n] = acc, stored as bf16 or fp32 (rotated activations for the quantiser score)
   EPI_F32 = 2,   // C[m][n] = out_scale * acc (+ C[m][n] if accumulate), fp32
-  EPI_GRAMW = 3, // acc = Gram matrix G: W = coef_i*I + coef_g*G (+ the planes Padd) written as np_out bf16 split
-                 // planes (natural layout) and per-wavefront partial sums of (G - I)^2
+  EPI_GRAMW = 3, // acc = Gram matrix G: W = coef_i*I + coef_g*G written as np_out bf16 split planes (natural
+                 // layout) and per-wavefront partial sums of (G - I)^2
   EPI_XOUT = 4,  // acc = X' (+ Xadd): written as fp32 (C32) and/or np_out bf16 split planes in natural (Pn)
                  // and transposed (Pt) layout -- the operands of the next Gram / apply GEMMs
   EPI_SQUARE = 5, // acc = D^2 (D symmetric, given as two planes Padd): writes acc as one bf16 plane (Pacc) and
@@ -32,6 +32,7 @@ enum GemmEpilogue : int {
                   // output columns read as input channels), scales each row by w, converts to fp16 and stores it
                   // transposed, Xt[channel][token], through the same LDS staging as the signs; the first tile column
                   // counts the rows (w != 0 / w == 0) into cnt.  Saves the separate transposing launch.
+  EPI_XADD = 10, // C32[m][n] = acc + Xadd[m][n], fp32: the last correction of an update, written straight into the rotation
 };
 
 constexpr int kMaxSegments = 6;
@@ -68,8 +69,7 @@ struct GemmArgs {
   int np_out;              // EPI_GRAMW: planes of W written; EPI_XOUT: transposed planes (Pt) written (1..3);
                            // plane p holds the p-th bf16 split term
   int np_out_n;            // EPI_XOUT: natural planes (Pn) written (<= 3)
-  const bf16_bits* Padd;   // EPI_GRAMW: np_add planes [m][n] (same pitch / plane offset) whose sum is added to W,
-  int np_add;              //            or null: W = coef_i*I + coef_g*acc + sum_p Padd[p]
+  const bf16_bits* Padd;   // EPI_SQUARE: the two planes of D, [m][n] (same pitch / plane offset as the outputs)
   int64_t plane_out;       //   element offset between output planes
   bf16_bits* Pn;           // EPI_GRAMW: W planes; EPI_XOUT: X' planes, natural [m][n] (may be null)
   bf16_bits* Pt;           // EPI_XOUT: X' planes, transposed [n][m] (may be null)

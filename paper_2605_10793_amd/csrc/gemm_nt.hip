@@ -1,10 +1,17 @@
 // bf16 MFMA "NT" GEMM with fused epilogues (see gemm_nt.h).
 //
 // Tiling: a workgroup of WGM x WGN wavefronts owns a BM x BN tile of the output; each
-// 64-lane wavefront owns (BM/WGM) x (BN/WGN) as a grid of 32x32 MFMA tiles
-// (v_mfma_f32_32x32x16_bf16 / _f16, fp32 accumulators).  The large tiles run 8
-// wavefronts (2 per SIMD) so that one wave's MFMAs cover the other's LDS / barrier /
-// load-issue latencies.
+// 64-lane wavefront owns (BM/WGM) x (BN/WGN) as a grid of 16x16 MFMA tiles
+// (v_mfma_f32_16x16x32_bf16 / _f16, fp32 accumulators), 4 wavefronts (1 per SIMD) in
+// every tile.
+//
+// These kernels are limited by power and by LDS reads, so both choices are about what a
+// multiply-add costs besides the MFMA itself.  A 128 x 128 wavefront tile reads 128 KiB of
+// LDS per K step of a 256 x 256 workgroup tile, 8 wavefronts of 128 x 64 read 192 KiB (1536
+// of the 2048 cycles the MFMAs take); a 16x16x32 MFMA updates 4 accumulator registers per
+// 8192 multiply-adds, a 32x32x16 one 16 per 16384.  Plain bf16 product, us (TFLOP/s), 8
+// wavefronts and 32x32x16 -> 8 and 16x16x32 -> 4 and 16x16x32: 4096^3 107 (1280) -> 98 -> 96
+// (1420); 8192^3 805 (1365) -> 784 -> 732 (1500); 4 wavefronts and 32x32x16: 110 and 820.
 //
 // Operand path: HBM/L2 -> LDS directly (buffer_load ... lds, 16 bytes per lane, no
 // register staging), 2 or 3 LDS stages of 64 K-elements (what fits in 160 KiB), fragments
@@ -43,6 +50,19 @@ __device__ __forceinline__ void wait_vmcnt() {
 // the compiler from moving LDS accesses across the barrier.
 __device__ __forceinline__ void pipeline_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
+// Forms of a conversion and of a constant that the compiler cannot merge with an earlier identical one.  The epilogues walk
+// over up to 256 accumulators per lane several times (a plane in two layouts, several planes); merged, the walks' common
+// values would have to stay live from one to the next, and the kernels spill hundreds of bytes per lane.
+__device__ __forceinline__ uint32_t cvt_bf16x2_again(float lo, float hi) {
+  uint32_t r;
+  asm volatile("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(r) : "v"(lo), "v"(hi));
+  return r;
+}
+__device__ __forceinline__ float again(float x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
 // K-tail / invalid-row loads are pointed past the end of the buffer descriptor, where
 // the hardware returns zeros (also for loads whose destination is LDS).
 constexpr uint32_t kOobOffset = 0x80000000u;
@@ -52,10 +72,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   static_assert(!SYM || (BM == BN && (EPI == EPI_GRAMW || EPI == EPI_SQUARE || EPI == EPI_FRO2)),
                 "mirrored tiles: square tiles, symmetric results");
   constexpr int NW = WGM * WGN;                 // wavefronts per workgroup
-  constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 32, TN = WN / 32;
+  constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
   constexpr int NLA = BM / 8, NLB = BN / 8;     // wave-wide 1 KiB loads per stage (8 tile rows each)
   constexpr int QA = NLA / NW, QB = NLB / NW;   // ... per wavefront
-  static_assert(NLA % NW == 0 && NLB % NW == 0 && WM % 32 == 0 && WN % 32 == 0, "tile shape");
+  static_assert(NLA % NW == 0 && NLB % NW == 0 && WM % 16 == 0 && WN % 16 == 0, "tile shape");
   constexpr int STAGE = (BM + BN) * 128;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // Optional clock probe (g.clk != null): wall-clock ticks (100 MHz) of the prologue, main loop and epilogue
@@ -66,7 +86,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave / WGN, wn = wave % WGN;
-  const int half = lane >> 5, col = lane & 31;
+  const int kg = lane >> 4, col = lane & 15;    // operand fragments: row (or column) col, K elements 8 kg .. 8 kg + 7 of 32
 
   // Workgroups are dealt round-robin to the 8 XCDs (bid % 8), each with its own L2, and
   // an XCD runs 32 of them at a time.  Map the 32 workgroups that are co-resident on an
@@ -179,45 +199,51 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
     }
   };
 
-  f32x16 acc[TM][TN];
+  f32x4 acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.0f;
 
   // Software pipeline.  LDS holds NSTAGE tiles; tile t lives in stage t % NSTAGE.
   // Operand fragments are double buffered in registers: while the MFMAs of K-substep
-  // kk run, the fragments of substep kk+1 are read from LDS (one ds_read per MFMA, so
-  // the reads issue in the MFMA's shadow).  The step's only synchronisation sits in the
-  // middle of its last substep: wait for this wave's loads of the next tile (vmcnt
-  // counts outstanding loads, which retire in order), barrier (now every wave's part of
-  // the next tile is visible and every wave has finished reading the current stage),
-  // refill the current stage with tile it+NSTAGE, read the first fragments of the next
-  // tile, and cover that latency with the second half of the substep's MFMAs.
+  // kk run, the fragments of substep kk+1 are read from LDS, spread over the substep (one
+  // read per 4 MFMAs for the largest tile), so that they issue in the MFMAs' shadow.  The
+  // step's only synchronisation sits in the middle of its last substep: wait for this
+  // wave's loads of the next tile (vmcnt counts outstanding loads, which retire in order),
+  // barrier (now every wave's part of the next tile is visible and every wave has finished
+  // reading the current stage), refill the current stage with tile it+NSTAGE, read the
+  // first fragments of the next tile, and cover that latency with the second half of the
+  // substep's MFMAs.
   constexpr int LPT = QA + QB;   // loads per thread per tile
-  constexpr int KS = BK / 16;    // MFMA K-substeps per tile
-  constexpr int NMF = TM * TN;
-  constexpr int LQ0 = NMF - NMF / 2;   // loads issued behind the second half of a step's last substep; the rest of the
-                                       // tile's loads follow behind the first MFMAs of the next step
-  static_assert(KS % 2 == 0, "fragment double buffering assumes an even number of substeps");
+  constexpr int KS = BK / 32;    // MFMA K-substeps per tile
+  constexpr int NMF = TM * TN, HALF = NMF / 2, NR = TM + TN;
+  constexpr int RS = NMF / NR > 1 ? NMF / NR : 1;       // MFMAs between two fragment reads of a full substep
+  constexpr int RH = HALF / NR > 1 ? HALF / NR : 1;     // ... of the half substep behind the barrier
+  constexpr int R0 = NR > HALF ? NR - HALF : 0;         // reads issued ahead of that half (small tiles: more reads than MFMAs)
+  constexpr int LQ2 = LPT / 2, LQ1 = LPT - LQ2;         // a tile's loads: LQ2 behind the barrier, LQ1 in the next step's first substep
+  constexpr int S2 = HALF / LQ2 > 1 ? HALF / LQ2 : 1;   // ... S2 and S1 MFMAs apart (early in the step: what is issued late
+  constexpr int S1 = NMF / LQ1 > 4 ? 4 : (NMF / LQ1 > 1 ? NMF / LQ1 : 1);   // has less time to land before the next barrier)
+  static_assert(KS == 2, "fragment double buffering: the two substeps of a step take one buffer each");
+  static_assert(LQ2 * S2 <= HALF + S2 - 1 && LQ1 * S1 <= NMF + S1 - 1 && NR <= NMF, "every load and read has its MFMA");
   bf16x8 fa[2][TM], fb[2][TN];
 
   auto read_frag = [&](int buf, int r, const unsigned char* sa, int kk) {
     // read number r of a substep, in the order the MFMAs need them: a0, b0..b(TN-1), a1..a(TM-1)
     const unsigned char* sb = sa + BM * 128;
-    if (r == 0) fa[buf][0] = *reinterpret_cast<const bf16x8*>(sa + lds_off(wm * WM + col, kk * 2 + half));
-    else if (r <= TN) fb[buf][r - 1] = *reinterpret_cast<const bf16x8*>(sb + lds_off(wn * WN + (r - 1) * 32 + col, kk * 2 + half));
-    else fa[buf][r - TN] = *reinterpret_cast<const bf16x8*>(sa + lds_off(wm * WM + (r - TN) * 32 + col, kk * 2 + half));
+    if (r == 0) fa[buf][0] = *reinterpret_cast<const bf16x8*>(sa + lds_off(wm * WM + col, kk * 4 + kg));
+    else if (r <= TN) fb[buf][r - 1] = *reinterpret_cast<const bf16x8*>(sb + lds_off(wn * WN + (r - 1) * 16 + col, kk * 4 + kg));
+    else fa[buf][r - TN] = *reinterpret_cast<const bf16x8*>(sa + lds_off(wm * WM + (r - TN) * 16 + col, kk * 4 + kg));
   };
   auto mfma = [&](int buf, int m) {
     const int i = m / TN, j = m % TN;
     if constexpr (F16)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, fa[buf][i]), __builtin_bit_cast(f16x8, fb[buf][j]),
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, fa[buf][i]), __builtin_bit_cast(f16x8, fb[buf][j]),
                                                          acc[i][j], 0, 0, 0);
     else
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[buf][i], fb[buf][j], acc[i][j], 0, 0, 0);
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[buf][i], fb[buf][j], acc[i][j], 0, 0, 0);
   };
 
 #pragma unroll
@@ -229,56 +255,48 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   wait_vmcnt<(NSTAGE - 1) * LPT>();   // tile 0 has landed
   pipeline_barrier();
 #pragma unroll
-  for (int r = 0; r < TM + TN; ++r) read_frag(0, r, smem, 0);
+  for (int r = 0; r < NR; ++r) read_frag(0, r, smem, 0);
 
   const unsigned long long pr_w1 = g.clk ? wall_clock64() : 0, pr_c1 = g.clk ? clock64() : 0;
   int stage = 0;   // it % NSTAGE
   for (int it = 0; it < nit; ++it) {
     const int prev_stage = stage == 0 ? NSTAGE - 1 : stage - 1, next_stage = stage == NSTAGE - 1 ? 0 : stage + 1;
     const unsigned char* sa = smem + stage * STAGE;
+    // first substep
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      const int cur = kk & 1, nxt = cur ^ 1;
-      if (kk + 1 < KS) {
+    for (int m = 0; m < NMF; ++m) {
+      mfma(0, m);
+      if (m % RS == 0 && m / RS < NR) read_frag(1, m / RS, sa, 1);
+      // the loads of tile it-1+NSTAGE that were left over behind the previous step's barrier
+      if (it > 0 && m % S1 == S1 / 2 && m / S1 < LQ1) issue_one(LQ2 + m / S1, prev_stage);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // last substep
+    issue_prep();   // tile it+NSTAGE refills the stage being consumed; scalar work, hidden behind the MFMAs
 #pragma unroll
-        for (int m = 0; m < NMF; ++m) {
-          mfma(cur, m);
-          if (m < TM + TN) read_frag(nxt, m, sa, kk + 1);
-          // the loads of tile it-1+NSTAGE that did not fit behind the previous step's last MFMAs
-          if (kk == 0 && it > 0 && LQ0 + m < LPT) issue_one(LQ0 + m, prev_stage);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+    for (int m = 0; m < HALF; ++m) mfma(1, m);
+    __builtin_amdgcn_sched_barrier(0);
+    // tiles up to it+NSTAGE-1 have been issued; all but the newest NSTAGE-2 have landed => tile it+1 is in LDS
+    wait_vmcnt<(NSTAGE - 2) * LPT>();
+    pipeline_barrier();
+    const unsigned char* sn = smem + next_stage * STAGE;
 #pragma unroll
-        for (int r = NMF; r < TM + TN; ++r) read_frag(nxt, r, sa, kk + 1);
-      } else {
-        issue_prep();   // tile it+NSTAGE refills the stage being consumed; scalar work, hidden behind the MFMAs
+    for (int r = 0; r < R0; ++r) read_frag(0, r, sn, 0);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int m = 0; m < NMF / 2; ++m) mfma(cur, m);
-        __builtin_amdgcn_sched_barrier(0);
-        // tiles up to it+NSTAGE-1 have been issued; all but the newest NSTAGE-2 have landed => tile it+1 is in LDS
-        wait_vmcnt<(NSTAGE - 2) * LPT>();
-        pipeline_barrier();
-        const unsigned char* sn = smem + next_stage * STAGE;
-#pragma unroll
-        for (int r = 0; r < TM + TN; ++r) read_frag(nxt, r, sn, 0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int m = NMF / 2; m < NMF; ++m) {
-          mfma(cur, m);
-          if (m - NMF / 2 < LPT) issue_one(m - NMF / 2, stage);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int q = LQ0 + NMF; q < LPT; ++q) issue_one(q, stage);   // (none for the tile shapes in use)
-      }
+    for (int m = HALF; m < NMF; ++m) {
+      mfma(1, m);
+      if ((m - HALF) % RH == 0 && R0 + (m - HALF) / RH < NR) read_frag(0, R0 + (m - HALF) / RH, sn, 0);
+      if ((m - HALF) % S2 == S2 / 2 && (m - HALF) / S2 < LQ2) issue_one((m - HALF) / S2, stage);
+      __builtin_amdgcn_sched_barrier(0);
     }
     stage = next_stage;
   }
   const unsigned long long pr_w2 = g.clk ? wall_clock64() : 0, pr_c2 = g.clk ? clock64() : 0;
   wait_vmcnt<0>();   // drain the padding loads before the epilogue reuses nothing of LDS (keeps exit clean)
 
-  // Accumulator element e = 4*j + i of tile (im, in) is output row
-  //   m = m0 + wm*WM + im*32 + 8*j + 4*half + i,   column n = n0 + wn*WN + in*32 + col.
+  // Accumulator element r of tile (i, j) is output row
+  //   m = m0 + wm*WM + 16*i + 4*kg + r,   column n = n0 + wn*WN + 16*j + col.
   const int mw = m0 + wm * WM, nw = n0 + wn * WN;
 
   // Addressing of the epilogues that write matrices [row][ldc]: buffer instructions with 32-bit byte offsets, so that
@@ -291,18 +309,18 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   //   transposed layout  [n][m]: byte offset tr_off(j, rows below the lane's first), 4 consecutive m = 8 bytes
   [[maybe_unused]] const uint32_t ldc_u = (uint32_t)g.ldc;
   [[maybe_unused]] const uint32_t nat_rows = (uint32_t)g.M * ldc_u, tr_rows = (uint32_t)g.N * ldc_u;   // elements
-  [[maybe_unused]] const int mlim = g.M - (mw + 4 * half);   // rows ml .. ml + 3 of this lane exist iff ml < mlim
+  [[maybe_unused]] const int mlim = g.M - (mw + 4 * kg);   // rows ml .. ml + 3 of this lane exist iff ml < mlim
   [[maybe_unused]] bool n_ok[TN];
   [[maybe_unused]] uint32_t nat2[TN], nat4[TN], tr2[TN];
   {
-    const uint32_t lane_nat = (uint32_t)(mw + 4 * half) * ldc_u + (uint32_t)(nw + col);
-    const uint32_t lane_tr = (uint32_t)(nw + col) * ldc_u + (uint32_t)(mw + 4 * half);
+    const uint32_t lane_nat = (uint32_t)(mw + 4 * kg) * ldc_u + (uint32_t)(nw + col);
+    const uint32_t lane_tr = (uint32_t)(nw + col) * ldc_u + (uint32_t)(mw + 4 * kg);
 #pragma unroll
     for (int j = 0; j < TN; ++j) {
-      n_ok[j] = nw + 32 * j + col < g.N;
-      nat2[j] = n_ok[j] ? (lane_nat + 32u * j) * 2u : kOobOffset;
-      nat4[j] = n_ok[j] ? (lane_nat + 32u * j) * 4u : kOobOffset;
-      tr2[j] = (lane_tr + 32u * j * ldc_u) * 2u;   // columns n >= N are rows past the end of the transposed array
+      n_ok[j] = nw + 16 * j + col < g.N;
+      nat2[j] = n_ok[j] ? (lane_nat + 16u * j) * 2u : kOobOffset;
+      nat4[j] = n_ok[j] ? (lane_nat + 16u * j) * 4u : kOobOffset;
+      tr2[j] = (lane_tr + 16u * j * ldc_u) * 2u;   // columns n >= N are rows past the end of the transposed array
     }
   }
   [[maybe_unused]] auto row_off = [&](int ml) { return (uint32_t)ml * ldc_u; };
@@ -314,8 +332,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   [[maybe_unused]] auto ld32 = [](__amdgpu_buffer_rsrc_t r, uint32_t off) {
     return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
   };
-  [[maybe_unused]] auto ld16 = [](__amdgpu_buffer_rsrc_t r, uint32_t off) {
-    return (bf16_bits)__builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0);
+  [[maybe_unused]] auto ld64 = [](__amdgpu_buffer_rsrc_t r, uint32_t off) {
+    return __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
   };
   [[maybe_unused]] auto st32 = [](__amdgpu_buffer_rsrc_t r, uint32_t off, float v) {
     __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), r, off, 0, 0);
@@ -333,47 +351,194 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
     __builtin_amdgcn_raw_buffer_store_b16((unsigned short)t.y, r, off + 2u * rb, 0, 0);
     __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(t.y >> 16), r, off + 3u * rb, 0, 0);
   };
+  // Large tiles write their matrices through LDS: each wavefront lays its block out in its own slice of the (now idle)
+  // stage memory and stores whole rows of it, 16 bytes per lane.  Straight from the accumulators a natural-layout store
+  // instruction writes four rows' segments of 16 values and the L2s see every 128-byte line in four pieces (two in a
+  // transposed layout).  Both bf16 layouts of a 4096^3 product: 101 us straight, 97 staged; of an 8192^3 one 785 and 726.
+  // A 64 x 64 tile, whose launches are bound by latency, has 4 accumulators per lane and layout and stores them directly.
+  constexpr bool STAGED = BM >= 128;
+  constexpr int SLICE = NSTAGE * STAGE / NW;
+  [[maybe_unused]] unsigned char* const slice = smem + wave * SLICE;
+  // Rows staged at a time: a row is padded by 16 bytes, which spreads the accumulators' 4 rows (2- and 4-byte writes) and 16
+  // columns (8-byte writes) over the banks.
+  [[maybe_unused]] constexpr auto pass_rows = [](int rows, int pitch) constexpr { while (rows * pitch > SLICE) rows /= 2; return rows; };
+  [[maybe_unused]] auto st128 = [](__amdgpu_buffer_rsrc_t r, uint32_t off, const uint4& t) {
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = {t.x, t.y, t.z, t.w};
+    __builtin_amdgcn_raw_buffer_store_b128(v, r, off, 0, 0);
+  };
+  [[maybe_unused]] auto stage_begin = [&]() {
+    if constexpr (STAGED) __syncthreads();   // every wavefront has finished reading operand tiles, its loads have landed
+  };
+  // 16-bit plane in the natural layout: row m of the block at byte offset origin + m * 2 pitch; quad(i, j) gives the 4 packed
+  // values of accumulator (i, j).  (Column counts are multiples of 8: a chunk of 8 is inside or outside as a whole.)
+  [[maybe_unused]] auto store_nat16 = [&](__amdgpu_buffer_rsrc_t r, uint32_t origin, uint32_t pitch, auto&& quad) {
+    constexpr int ROWB = WN * 2 + 16, ROWS = pass_rows(WM, ROWB), CPR = WN / 8;
+    static_assert(ROWS % 16 == 0 && (ROWS * CPR) % 64 == 0, "whole accumulator rows and wavefronts per pass");
+#pragma unroll
+    for (int h = 0; h < WM / ROWS; ++h) {
+#pragma unroll
+      for (int i = 0; i < ROWS / 16; ++i) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const uint2 t = quad(h * (ROWS / 16) + i, j);
+          unsigned char* d = slice + (16 * i + 4 * kg) * ROWB + (16 * j + col) * 2;
+          *reinterpret_cast<unsigned short*>(d) = (unsigned short)t.x;
+          *reinterpret_cast<unsigned short*>(d + ROWB) = (unsigned short)(t.x >> 16);
+          *reinterpret_cast<unsigned short*>(d + 2 * ROWB) = (unsigned short)t.y;
+          *reinterpret_cast<unsigned short*>(d + 3 * ROWB) = (unsigned short)(t.y >> 16);
+        }
+        __builtin_amdgcn_sched_barrier(0);   // (bounds what the scheduler keeps live: without these the kernels spill)
+      }
+#pragma unroll
+      for (int q = 0; q < ROWS * CPR / 64; ++q) {
+        const int idx = q * 64 + lane, row = idx / CPR, c = idx % CPR;
+        const uint4 v = *reinterpret_cast<const uint4*>(slice + row * ROWB + c * 16);
+        st128(r, nw + 8 * c < g.N ? origin + ((uint32_t)(h * ROWS + row) * pitch + 8u * c) * 2u : kOobOffset, v);
+        if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // the same plane transposed, row n of the block at origin + n * 2 pitch
+  [[maybe_unused]] auto store_tr16 = [&](__amdgpu_buffer_rsrc_t r, uint32_t origin, uint32_t pitch, auto&& quad) {
+    constexpr int ROWB = WM * 2 + 16, ROWS = pass_rows(WN, ROWB), CPR = WM / 8;
+    static_assert(ROWS % 16 == 0 && (ROWS * CPR) % 64 == 0, "whole accumulator columns and wavefronts per pass");
+#pragma unroll
+    for (int h = 0; h < WN / ROWS; ++h) {
+#pragma unroll
+      for (int j = 0; j < ROWS / 16; ++j) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+          *reinterpret_cast<uint2*>(slice + (16 * j + col) * ROWB + (16 * i + 4 * kg) * 2) = quad(i, h * (ROWS / 16) + j);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int q = 0; q < ROWS * CPR / 64; ++q) {
+        const int idx = q * 64 + lane, row = idx / CPR, c = idx % CPR;
+        const uint4 v = *reinterpret_cast<const uint4*>(slice + row * ROWB + c * 16);
+        st128(r, mw + 8 * c < g.M ? origin + ((uint32_t)(h * ROWS + row) * pitch + 8u * c) * 2u : kOobOffset, v);
+        if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // fp32 in the natural layout, straight from the accumulators (16 lanes write 64 contiguous bytes of a row; through LDS, which
+  // holds a quarter of the block at a time, the 4096^2 M of the accumulate GEMM took 10 us instead of 6).  add: the array at
+  // radd (same addressing) is added first, its loads one row of accumulators ahead of their use.
+  [[maybe_unused]] auto store_f32 = [&](__amdgpu_buffer_rsrc_t r, auto add, __amdgpu_buffer_rsrc_t radd, auto&& val) {
+    constexpr bool ADD = decltype(add)::value;
+    [[maybe_unused]] f32x4 more[2][ADD ? TN : 1];
+    auto fetch = [&](int i) {
+      if constexpr (ADD) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) more[i & 1][j][e] = ld32(radd, nat4[j] + row_off(16 * i + e) * 4u);
+      }
+    };
+    fetch(0);
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+      if (i + 1 < TM) fetch(i + 1);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        f32x4 v = val(i, j);
+        if constexpr (ADD) v += more[i & 1][j];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) st32(r, nat4[j] + row_off(16 * i + e) * 4u, v[e]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // byte offsets of this wavefront's block in the [row][ldc] arrays, natural (2- and 4-byte elements) and transposed
+  [[maybe_unused]] const uint32_t blk_nat = (uint32_t)mw * ldc_u + (uint32_t)nw, blk_tr = (uint32_t)nw * ldc_u + (uint32_t)mw;
+  // Split plane p of the values val(i, j) (f32x4): fp16 or bf16 rounding for p = 0; what the planes before leave over, rounded
+  // to bf16, for the next ones.
+  [[maybe_unused]] auto split16 = [&](auto plane, f32x4 a) {
+    constexpr int P = decltype(plane)::value;
+    if constexpr (F16 && EPI != EPI_XLAST) {
+      static_assert(P == 0, "fp16 operands: one plane");
+      return make_uint2(f32x2_to_f16x2(a[0], a[1]), f32x2_to_f16x2(a[2], a[3]));
+    } else {
+      uint2 t = make_uint2(cvt_bf16x2_again(a[0], a[1]), cvt_bf16x2_again(a[2], a[3]));
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        a[0] -= __uint_as_float(t.x << 16); a[1] -= __uint_as_float(t.x & 0xffff0000u);
+        a[2] -= __uint_as_float(t.y << 16); a[3] -= __uint_as_float(t.y & 0xffff0000u);
+        t = make_uint2(cvt_bf16x2_again(a[0], a[1]), cvt_bf16x2_again(a[2], a[3]));
+      }
+      return t;
+    }
+  };
+  [[maybe_unused]] auto acc_val = [&](int i, int j) { return acc[i][j]; };
+  // split plane `plane` of val(i, j) in the natural layout (nat), the transposed one (tr), or both
+  [[maybe_unused]] auto store_plane = [&](auto plane, auto&& val, __amdgpu_buffer_rsrc_t rn, bool nat, __amdgpu_buffer_rsrc_t rt, bool tr) {
+    auto quad = [&](int i, int j) { return split16(plane, val(i, j)); };
+    if constexpr (STAGED) {
+      if (nat) store_nat16(rn, blk_nat * 2u, ldc_u, quad);
+      if (tr) store_tr16(rt, blk_tr * 2u, ldc_u, quad);
+    } else {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const uint2 t = quad(i, j);
+          if (nat) st_rows4(rn, nat2[j] + row_off(16 * i) * 2u, t);
+          if (tr) st64(rt, tr_off(j, 16 * i), t);
+        }
+    }
+  };
+  using Plane0 = std::integral_constant<int, 0>;
+  using Plane1 = std::integral_constant<int, 1>;
+  using Plane2 = std::integral_constant<int, 2>;
+
   // The accumulators as activations Y[m][n] (bf16 or fp32 by g.c_is_f32), row pitch `pitch`: the pitch is the caller's,
   // so the offsets are taken relative to the tile's first row (at most BM rows x pitch x 4 bytes, which the launcher
-  // keeps below 2^31); rows past M lie beyond the range, columns past N are masked.
+  // keeps below 2^31); rows past M lie beyond the range, columns past N are masked.  The staged form stores 16 bytes per
+  // lane and needs rows aligned to them; a caller's Y need not be (conqur_rotate asks for its element size only).
   [[maybe_unused]] auto store_act = [&](void* base, int64_t pitch, int64_t batch_off) {
     const uint32_t pu = (uint32_t)pitch;
     const uint32_t rows = (uint32_t)(g.M - m0 < BM ? g.M - m0 : BM);
-    const uint32_t lane_el = (uint32_t)(wm * WM + 4 * half) * pu + (uint32_t)(nw + col);
+    const uint32_t lane_el = (uint32_t)(wm * WM + 4 * kg) * pu + (uint32_t)(nw + col);
+    const uint32_t blk_el = (uint32_t)(wm * WM) * pu + (uint32_t)nw;
     const int64_t tile_el = (int64_t)bz * batch_off + (int64_t)m0 * pitch;
     if (g.c_is_f32) {
-      const auto r = out_rsrc(reinterpret_cast<float*>(base) + tile_el, rows * pu * 4u);
+      float* const tile = reinterpret_cast<float*>(base) + tile_el;
+      const auto r = out_rsrc(tile, rows * pu * 4u);
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          const uint32_t o = n_ok[j] ? (lane_el + 32u * j) * 4u : kOobOffset;
+          const uint32_t o = n_ok[j] ? (lane_el + 16u * j) * 4u : kOobOffset;
 #pragma unroll
-          for (int e = 0; e < 16; ++e) st32(r, o + (uint32_t)(32 * i + 8 * (e >> 2) + (e & 3)) * pu * 4u, acc[i][j][e]);
+          for (int e = 0; e < 4; ++e) st32(r, o + (uint32_t)(16 * i + e) * pu * 4u, acc[i][j][e]);
         }
     } else {
-      const auto r = out_rsrc(reinterpret_cast<bf16_bits*>(base) + tile_el, rows * pu * 2u);
+      bf16_bits* const tile = reinterpret_cast<bf16_bits*>(base) + tile_el;
+      const auto r = out_rsrc(tile, rows * pu * 2u);
+      if (STAGED && (((uintptr_t)tile | (uintptr_t)(pu * 2u)) & 15) == 0) {
+        if constexpr (STAGED) store_nat16(r, blk_el * 2u, pu, [&](int i, int j) { return split16(Plane0{}, acc[i][j]); });
+        return;
+      }
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          const uint32_t o = n_ok[j] ? (lane_el + 32u * j) * 2u : kOobOffset;
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            uint2 t;
-            t.x = f32x2_to_bf16x2(acc[i][j][4 * q], acc[i][j][4 * q + 1]);
-            t.y = f32x2_to_bf16x2(acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]);
-            const uint32_t oq = o + (uint32_t)(32 * i + 8 * q) * pu * 2u, rb = 2u * pu;
-            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)t.x, r, oq, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(t.x >> 16), r, oq + rb, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)t.y, r, oq + 2u * rb, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(t.y >> 16), r, oq + 3u * rb, 0, 0);
-          }
+          const uint32_t o = n_ok[j] ? (lane_el + 16u * j) * 2u : kOobOffset;
+          const uint2 t = split16(Plane0{}, acc[i][j]);
+          const uint32_t oq = o + (uint32_t)(16 * i) * pu * 2u, rb = 2u * pu;
+          __builtin_amdgcn_raw_buffer_store_b16((unsigned short)t.x, r, oq, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(t.x >> 16), r, oq + rb, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b16((unsigned short)t.y, r, oq + 2u * rb, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(t.y >> 16), r, oq + 3u * rb, 0, 0);
         }
     }
   };
 
   if constexpr (EPI == EPI_SIGN_ACT) {   // the rotated rows themselves, as EPI_ACT writes them
+    stage_begin();
     store_act(g.Yact, g.ldy, g.batchY);
   }
   if constexpr (EPI == EPI_SIGN || EPI == EPI_SIGN_ACT || EPI == EPI_SIGN_XT) {
@@ -382,11 +547,14 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
     // through its own slice of the (now idle) stage memory and stores whole 16-byte chunks, 8 or 16 lanes per row.
     bf16_bits* St = reinterpret_cast<bf16_bits*>(g.C) + (int64_t)bz * g.batchC;
     const uint32_t one = g.sign_f16 ? 0x3C00u : 0x3F80u;
-    constexpr int SROW = WM * 2;                      // bytes per staged row (one output column n, WM tokens)
-    constexpr int CPR = WM / 8;                       // 16-byte chunks per staged row, XOR swizzled by the row
-    static_assert(NW * WN * SROW <= NSTAGE * STAGE && (CPR & (CPR - 1)) == 0, "sign staging fits the stage memory");
-    unsigned char* stg = smem + wave * (WN * SROW);
+    constexpr int CPR = WM / 8;                       // 16-byte chunks per staged row (one output column n, WM tokens)
+    constexpr bool POW2 = (CPR & (CPR - 1)) == 0;     // ... XOR swizzled by the row, or rows padded by one chunk (WM = 96)
+    constexpr int SROW = WM * 2 + (POW2 ? 0 : 16);
+    static_assert(WN * SROW <= SLICE, "sign staging fits the wavefront's slice");
+    auto sign_chunk = [](int r, int c) { return POW2 ? c ^ (r & (CPR - 1)) : c; };
+    unsigned char* const stg = slice;
     // EPI_SIGN_XT: the block of A this wavefront transposes below, loaded now so that the sign staging covers the latency
+    // (loaded ahead of the main loop instead, the prologue grows by what the epilogue saves)
     constexpr int XT_ITEMS = EPI == EPI_SIGN_XT ? (WM / 2) * (WN / 8) / 64 : 1;
     [[maybe_unused]] uint4 xt_a[XT_ITEMS], xt_b[XT_ITEMS];
     [[maybe_unused]] float xt_w0[XT_ITEMS], xt_w1[XT_ITEMS];
@@ -408,24 +576,24 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
     }
     __syncthreads();                                  // every wavefront has finished reading operand tiles
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+    for (int i = 0; i < TM; ++i) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x16& a = acc[i][j];
-          uint2 v;  // +1 with the sign bit of each accumulator (sgn(+-0) = +1, so test >= 0)
-          v.x = (a[4 * q + 0] >= 0.0f ? one : one | 0x8000u) | ((a[4 * q + 1] >= 0.0f ? one : one | 0x8000u) << 16);
-          v.y = (a[4 * q + 2] >= 0.0f ? one : one | 0x8000u) | ((a[4 * q + 3] >= 0.0f ? one : one | 0x8000u) << 16);
-          const int r = j * 32 + col, c = i * 4 + q;   // tokens 8 c + 4 half .. + 3 of row r
-          *reinterpret_cast<uint2*>(stg + r * SROW + ((c ^ (r & (CPR - 1))) << 4) + 8 * half) = v;
-        }
+      for (int j = 0; j < TN; ++j) {
+        const f32x4& a = acc[i][j];
+        uint2 v;  // +1 with the sign bit of each accumulator (sgn(+-0) = +1, so test >= 0)
+        v.x = (a[0] >= 0.0f ? one : one | 0x8000u) | ((a[1] >= 0.0f ? one : one | 0x8000u) << 16);
+        v.y = (a[2] >= 0.0f ? one : one | 0x8000u) | ((a[3] >= 0.0f ? one : one | 0x8000u) << 16);
+        const int r = j * 16 + col, c = 2 * i + (kg >> 1);   // tokens 16 i + 4 kg .. + 3 of row r
+        *reinterpret_cast<uint2*>(stg + r * SROW + (sign_chunk(r, c) << 4) + 8 * (kg & 1)) = v;
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
     // the slice is private to the wavefront: its own LDS writes are visible to it after the wait the compiler inserts
 #pragma unroll
     for (int it2 = 0; it2 < WN * CPR / 64; ++it2) {
       const int idx = it2 * 64 + lane, r = idx / CPR, c = idx % CPR;
       const int n = nw + r, m = mw + c * 8;
-      const uint4 v = *reinterpret_cast<const uint4*>(stg + r * SROW + ((c ^ (r & (CPR - 1))) << 4));
+      const uint4 v = *reinterpret_cast<const uint4*>(stg + r * SROW + (sign_chunk(r, c) << 4));
       if (n < g.N && m < g.st_rows_valid) *reinterpret_cast<uint4*>(St + (int64_t)n * g.ldc + m) = v;
     }
     if constexpr (EPI == EPI_SIGN_XT) {
@@ -439,7 +607,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
       static_assert((PAIRS * CH) % 64 == 0, "whole wavefronts of items");
       const float* wrow = g.xt_w + (int64_t)bz * g.xt_ldw;
       bf16_bits* Xt = g.Xt + (int64_t)bz * g.batchC;
-      auto phys = [](int r, int cc) { return cc ^ ((r ^ (r >> 3)) & (CPR - 1)); };
+      auto phys = [](int r, int cc) { return POW2 ? cc ^ ((r ^ (r >> 3)) & (CPR - 1)) : cc; };
 #pragma unroll
       for (int q = 0; q < PAIRS * CH / 64; ++q) {
         const int item = q * 64 + lane, c = item % CH, p = item / CH;
@@ -480,83 +648,58 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
       }
     }
   } else if constexpr (EPI == EPI_ACT) {
+    stage_begin();
     store_act(g.C, g.ldc, g.batchC);
   } else if constexpr (EPI == EPI_F32) {
     const auto rC = out_rsrc(reinterpret_cast<float*>(g.C) + (int64_t)bz * g.batchC, nat_rows * 4u);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        float v[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = g.out_scale * acc[i][j][e];
-        if (g.accumulate) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) v[e] += ld32(rC, nat4[j] + row_off(32 * i + 8 * (e >> 2) + (e & 3)) * 4u);
-        }
-#pragma unroll
-        for (int e = 0; e < 16; ++e) st32(rC, nat4[j] + row_off(32 * i + 8 * (e >> 2) + (e & 3)) * 4u, v[e]);
-      }
+    auto val = [&](int i, int j) { return g.out_scale * acc[i][j]; };
+    if (g.accumulate) store_f32(rC, std::true_type{}, rC, val);
+    else store_f32(rC, std::false_type{}, rC, val);
   } else if constexpr (EPI == EPI_GRAMW) {
     const int64_t boff = (int64_t)bz * g.batchC;
     [[maybe_unused]] const bool mirror = SYM && tm != tn;   // this tile is also the transpose of tile (tn, tm)
     double rsum = 0.0;
-    // Only a workgroup whose tile meets the diagonal has entries of the identity to add and subtract: the others run
-    // the version of the code without them (a wave-uniform choice).
-    auto tiles = [&](auto on_diagonal) {
+    // Only a workgroup whose tile meets the diagonal has entries of the identity to add and subtract: the others run the
+    // version of the code without them (a wave-uniform choice).
+    auto write = [&](auto on_diagonal) {
+      constexpr bool DIAG = decltype(on_diagonal)::value;
+      auto eye = [&](int i, int j, int r) { return (mw + 4 * kg + 16 * i + r == nw + 16 * j + col) ? 1.0f : 0.0f; };
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int i = 0; i < TM; ++i) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
           float part = 0.0f;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int ml = 32 * i + 8 * q;            // rows ml .. ml + 3 of this lane's block (M is a multiple of 4)
-            float w[4], part_q = 0.0f;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float a = acc[i][j][4 * q + r];
-              if constexpr (decltype(on_diagonal)::value) {
-                const float eye = (mw + 4 * half + ml + r == nw + 32 * j + col) ? 1.0f : 0.0f;
-                const float d = a - eye;
-                part_q += d * d;
-                w[r] = g.coef_i * eye + g.coef_g * a;
-              } else {
-                part_q += a * a;
-                w[r] = g.coef_g * a;
-              }
-            }
-            part += (n_ok[j] && ml < mlim) ? part_q : 0.0f;
-            if constexpr (!F16) {   // (fp16 operands: no planes to add)
-              for (int p = 0; p < g.np_add; ++p) {
-                const auto rA = in_rsrc(g.Padd + p * g.plane_out + boff, nat_rows * 2u);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) w[r] += bf16_to_f32(ld16(rA, nat2[j] + row_off(ml + r) * 2u));
-              }
-            }
-            for (int p = 0; p < (F16 ? 1 : g.np_out); ++p) {
-              uint2 t;
-              if constexpr (F16) {   // fp16 operands: the factor is one fp16 plane
-                t.x = f32x2_to_f16x2(w[0], w[1]);
-                t.y = f32x2_to_f16x2(w[2], w[3]);
-              } else {
-                t.x = f32x2_to_bf16x2(w[0], w[1]);
-                t.y = f32x2_to_bf16x2(w[2], w[3]);
-                w[0] -= __uint_as_float(t.x << 16); w[1] -= __uint_as_float(t.x & 0xffff0000u);
-                w[2] -= __uint_as_float(t.y << 16); w[3] -= __uint_as_float(t.y & 0xffff0000u);
-              }
-              const auto rP = out_rsrc(g.Pn + p * g.plane_out + boff, nat_rows * 2u);
-              st_rows4(rP, nat2[j] + row_off(ml) * 2u, t);
-              if constexpr (SYM) {
-                if (mirror) st64(rP, tr_off(j, ml), t);
-              }
-            }
+          for (int r = 0; r < 4; ++r) {
+            const float d = DIAG ? acc[i][j][r] - eye(i, j, r) : acc[i][j][r];
+            part += d * d;
           }
-          rsum += (double)part;
+          rsum += (double)((n_ok[j] && 16 * i < mlim) ? part : 0.0f);   // rows 16 i .. + 3 of the lane's block (M is a multiple of 4)
         }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      auto val = [&](int i, int j) {
+        f32x4 w = again(g.coef_g) * acc[i][j];
+        if constexpr (DIAG) {
+          const float ci = again(g.coef_i);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) w[r] += ci * eye(i, j, r);
+        }
+        return w;
+      };
+      auto plane = [&](auto p) {
+        const auto rP = out_rsrc(g.Pn + decltype(p)::value * g.plane_out + boff, nat_rows * 2u);
+        store_plane(p, val, rP, true, rP, mirror);
+      };
+      plane(Plane0{});
+      if constexpr (!F16) {   // fp16 operands: the factor is one fp16 plane
+        if (g.np_out > 1) plane(Plane1{});
+        if (g.np_out > 2) plane(Plane2{});
+      }
     };
-    if (m0 < n0 + BN && n0 < m0 + BM) tiles(std::true_type{});
-    else tiles(std::false_type{});
+    stage_begin();
+    if (m0 < n0 + BN && n0 < m0 + BM) write(std::true_type{});
+    else write(std::false_type{});
     if (g.resid_part) {
       rsum = wave_sum_d(rsum);
       if (lane == 0) {
@@ -570,8 +713,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
     const int64_t boff = (int64_t)bz * g.batchC;
     [[maybe_unused]] const bool mirror = SYM && tm != tn;
     const auto rA0 = in_rsrc(g.Padd + boff, nat_rows * 2u), rA1 = in_rsrc(g.Padd + g.plane_out + boff, nat_rows * 2u);
-    const auto rSq = out_rsrc(g.Pacc + boff, nat_rows * 2u);
-    const auto rW0 = out_rsrc(g.Pn + boff, nat_rows * 2u), rW1 = out_rsrc(g.Pn + g.plane_out + boff, nat_rows * 2u);
     double rsum = 0.0;   // sum of the squares of this wavefront's accumulators: ||D^2||_F^2 over the whole launch
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -579,39 +720,34 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
       for (int j = 0; j < TN; ++j) {
         float part = 0.0f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int ml = 32 * i + 8 * q;
-          const bool in = n_ok[j] && ml < mlim;
-          float a[4], w[4];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const uint32_t off = nat2[j] + row_off(ml + r) * 2u;
-            a[r] = acc[i][j][4 * q + r];
-            part += in ? a[r] * a[r] : 0.0f;
-            w[r] = g.coef_g * a[r] + bf16_to_f32(ld16(rA0, off)) + bf16_to_f32(ld16(rA1, off));
-          }
-          uint2 ta, t0, t1;
-          ta.x = f32x2_to_bf16x2(a[0], a[1]);
-          ta.y = f32x2_to_bf16x2(a[2], a[3]);
-          t0.x = f32x2_to_bf16x2(w[0], w[1]);
-          t0.y = f32x2_to_bf16x2(w[2], w[3]);
-          t1.x = f32x2_to_bf16x2(w[0] - __uint_as_float(t0.x << 16), w[1] - __uint_as_float(t0.x & 0xffff0000u));
-          t1.y = f32x2_to_bf16x2(w[2] - __uint_as_float(t0.y << 16), w[3] - __uint_as_float(t0.y & 0xffff0000u));
-          const uint32_t off = nat2[j] + row_off(ml) * 2u;
-          st_rows4(rSq, off, ta);
-          st_rows4(rW0, off, t0);
-          st_rows4(rW1, off, t1);
-          if constexpr (SYM) {
-            if (mirror) {
-              const uint32_t offt = tr_off(j, ml);
-              st64(rSq, offt, ta);
-              st64(rW0, offt, t0);
-              st64(rW1, offt, t1);
-            }
-          }
-        }
-        rsum += (double)part;
+        for (int r = 0; r < 4; ++r) part += acc[i][j][r] * acc[i][j][r];
+        rsum += (double)((n_ok[j] && 16 * i < mlim) ? part : 0.0f);
       }
+    stage_begin();
+    {   // D^2 itself
+      const auto rSq = out_rsrc(g.Pacc + boff, nat_rows * 2u);
+      store_plane(Plane0{}, acc_val, rSq, true, rSq, mirror);
+    }
+    // the accumulators become the entries of the correction; D is symmetric: its entries (m .. m + 3, n) are 4 consecutive ones
+    // of row n
+#pragma unroll
+    for (int i = 0; i < TM; ++i) {
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const uint32_t off = tr_off(j, 16 * i);
+        const uint2 d0 = ld64(rA0, off), d1 = ld64(rA1, off);
+        acc[i][j][0] = g.coef_g * acc[i][j][0] + __uint_as_float(d0.x << 16) + __uint_as_float(d1.x << 16);
+        acc[i][j][1] = g.coef_g * acc[i][j][1] + __uint_as_float(d0.x & 0xffff0000u) + __uint_as_float(d1.x & 0xffff0000u);
+        acc[i][j][2] = g.coef_g * acc[i][j][2] + __uint_as_float(d0.y << 16) + __uint_as_float(d1.y << 16);
+        acc[i][j][3] = g.coef_g * acc[i][j][3] + __uint_as_float(d0.y & 0xffff0000u) + __uint_as_float(d1.y & 0xffff0000u);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    {
+      const auto r0 = out_rsrc(g.Pn + boff, nat_rows * 2u), r1 = out_rsrc(g.Pn + g.plane_out + boff, nat_rows * 2u);
+      store_plane(Plane0{}, acc_val, r0, true, r0, mirror);
+      store_plane(Plane1{}, acc_val, r1, true, r1, mirror);
+    }
     if (g.resid_part) {
       rsum = wave_sum_d(rsum);
       if (lane == 0) {
@@ -629,8 +765,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
       for (int j = 0; j < TN; ++j) {
         float part = 0.0f;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const bool in = n_ok[j] && 32 * i + 8 * (e >> 2) + (e & 3) < mlim;
+        for (int e = 0; e < 4; ++e) {
+          const bool in = n_ok[j] && 16 * i + e < mlim;
           part += in ? acc[i][j][e] * acc[i][j][e] : 0.0f;
         }
         rsum += (double)part;
@@ -646,82 +782,66 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
     const int64_t boff = (int64_t)bz * g.batchC;
     const bool two = g.np_out == 2;
     const auto rC = out_rsrc(g.C32 + boff, nat_rows * 4u);
-    const auto rN0 = out_rsrc(g.Pn + boff, nat_rows * 2u), rN1 = out_rsrc(g.Pn + g.plane_out + boff, two ? nat_rows * 2u : 0u);
-    const auto rT0 = out_rsrc(g.Pt + boff, tr_rows * 2u), rT1 = out_rsrc(g.Pt + g.plane_out + boff, two ? tr_rows * 2u : 0u);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int ml = 32 * i + 8 * q;
-          const float v0 = acc[i][j][4 * q], v1 = acc[i][j][4 * q + 1], v2 = acc[i][j][4 * q + 2], v3 = acc[i][j][4 * q + 3];
-          uint2 hi;
-          hi.x = f32x2_to_bf16x2(v0, v1);
-          hi.y = f32x2_to_bf16x2(v2, v3);
-          float h0 = __uint_as_float(hi.x << 16), h1 = __uint_as_float(hi.x & 0xffff0000u);
-          float h2 = __uint_as_float(hi.y << 16), h3 = __uint_as_float(hi.y & 0xffff0000u);
-          const uint32_t off = nat2[j] + row_off(ml) * 2u, offt = tr_off(j, ml);
-          st_rows4(rN0, off, hi);
-          st64(rT0, offt, hi);
-          if (two) {
-            uint2 lo;
-            lo.x = f32x2_to_bf16x2(v0 - h0, v1 - h1);
-            lo.y = f32x2_to_bf16x2(v2 - h2, v3 - h3);
-            st_rows4(rN1, off, lo);
-            st64(rT1, offt, lo);
-            // hi + lo has at most 17 significant bits: the fp32 sums are exact
-            h0 += __uint_as_float(lo.x << 16); h1 += __uint_as_float(lo.x & 0xffff0000u);
-            h2 += __uint_as_float(lo.y << 16); h3 += __uint_as_float(lo.y & 0xffff0000u);
-          }
-          st32(rC, nat4[j] + row_off(ml) * 4u, h0);
-          st32(rC, nat4[j] + row_off(ml + 1) * 4u, h1);
-          st32(rC, nat4[j] + row_off(ml + 2) * 4u, h2);
-          st32(rC, nat4[j] + row_off(ml + 3) * 4u, h3);
-        }
+    // the value the planes hold: hi, or hi + lo (at most 17 significant bits: the fp32 sums are exact)
+    auto rounded = [&](int i, int j) {
+      const uint2 hi = split16(Plane0{}, acc[i][j]);
+      f32x4 v = {__uint_as_float(hi.x << 16), __uint_as_float(hi.x & 0xffff0000u), __uint_as_float(hi.y << 16), __uint_as_float(hi.y & 0xffff0000u)};
+      if (two) {
+        const uint2 lo = split16(Plane1{}, acc[i][j]);
+        v[0] += __uint_as_float(lo.x << 16); v[1] += __uint_as_float(lo.x & 0xffff0000u);
+        v[2] += __uint_as_float(lo.y << 16); v[3] += __uint_as_float(lo.y & 0xffff0000u);
       }
+      return v;
+    };
+    stage_begin();
+    store_f32(rC, std::false_type{}, rC, rounded);
+    store_plane(Plane0{}, acc_val, out_rsrc(g.Pn + boff, nat_rows * 2u), true, out_rsrc(g.Pt + boff, tr_rows * 2u), true);
+    if (two)
+      store_plane(Plane1{}, acc_val, out_rsrc(g.Pn + g.plane_out + boff, nat_rows * 2u), true,
+                  out_rsrc(g.Pt + g.plane_out + boff, tr_rows * 2u), true);
+  } else if constexpr (EPI == EPI_XADD) {
+    const int64_t boff = (int64_t)bz * g.batchC;
+    const auto rX = in_rsrc(g.Xadd + boff, nat_rows * 4u);
+    const auto rC = out_rsrc(g.C32 + boff, nat_rows * 4u);
+    store_f32(rC, std::true_type{}, rX, acc_val);
   } else {  // EPI_XOUT
     const int64_t boff = (int64_t)bz * g.batchC;
-    // an absent array gets an empty range: its loads return zero and its stores are dropped
-    const auto rX = in_rsrc(g.Xadd ? g.Xadd + boff : nullptr, g.Xadd ? nat_rows * 4u : 0u);
-    const auto rC = out_rsrc(g.C32 ? g.C32 + boff : nullptr, g.C32 ? nat_rows * 4u : 0u);
     const int np_max = F16 ? 1 : (g.np_out > g.np_out_n ? g.np_out : g.np_out_n);
+    stage_begin();
+    if constexpr (!F16) {
+      const auto rX = in_rsrc(g.Xadd ? g.Xadd + boff : nullptr, g.Xadd ? nat_rows * 4u : 0u);
+      const auto rC = out_rsrc(g.C32 ? g.C32 + boff : nullptr, g.C32 ? nat_rows * 4u : 0u);
+      if (g.Xadd) {
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+        for (int i = 0; i < TM; ++i) {
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        float v[16];
+          for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = acc[i][j][e];
-        if (g.Xadd) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) v[e] += ld32(rX, nat4[j] + row_off(32 * i + 8 * (e >> 2) + (e & 3)) * 4u);
-        }
-        if (g.C32) {
-#pragma unroll
-          for (int e = 0; e < 16; ++e) st32(rC, nat4[j] + row_off(32 * i + 8 * (e >> 2) + (e & 3)) * 4u, v[e]);
-        }
-        for (int p = 0; p < np_max; ++p) {
-          const auto rN = out_rsrc(g.Pn + p * g.plane_out + boff, p < g.np_out_n ? nat_rows * 2u : 0u);
-          const auto rT = out_rsrc(g.Pt + p * g.plane_out + boff, p < g.np_out ? tr_rows * 2u : 0u);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int ml = 32 * i + 8 * q;
-            uint2 t;   // the 4 values of rows ml .. ml + 3, packed; the remainder goes on to the next plane
-            if constexpr (F16) {   // fp16 operands: the iterate is one fp16 plane of each layout
-              t.x = f32x2_to_f16x2(v[4 * q], v[4 * q + 1]);
-              t.y = f32x2_to_f16x2(v[4 * q + 2], v[4 * q + 3]);
-            } else {
-              t.x = f32x2_to_bf16x2(v[4 * q], v[4 * q + 1]);
-              t.y = f32x2_to_bf16x2(v[4 * q + 2], v[4 * q + 3]);
-              v[4 * q] -= __uint_as_float(t.x << 16); v[4 * q + 1] -= __uint_as_float(t.x & 0xffff0000u);
-              v[4 * q + 2] -= __uint_as_float(t.y << 16); v[4 * q + 3] -= __uint_as_float(t.y & 0xffff0000u);
-            }
-            st_rows4(rN, nat2[j] + row_off(ml) * 2u, t);
-            st64(rT, tr_off(j, ml), t);
-          }
+            for (int e = 0; e < 4; ++e) acc[i][j][e] += ld32(rX, nat4[j] + row_off(16 * i + e) * 4u);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
+      if (g.C32) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) st32(rC, nat4[j] + row_off(16 * i + e) * 4u, acc[i][j][e]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    }
+    auto plane = [&](auto p) {
+      constexpr int P = decltype(p)::value;
+      const bool nat = F16 || P < g.np_out_n, tr = F16 || P < g.np_out;
+      store_plane(p, acc_val, out_rsrc(g.Pn + P * g.plane_out + boff, nat_rows * 2u), nat, out_rsrc(g.Pt + P * g.plane_out + boff, tr_rows * 2u), tr);
+    };
+    if (F16 || np_max > 0) plane(Plane0{});   // fp16 operands: the iterate is one fp16 plane of each layout
+    if constexpr (!F16) {
+      if (np_max > 1) plane(Plane1{});
+      if (np_max > 2) plane(Plane2{});
+    }
   }
   if (g.clk) {
     wait_vmcnt<0>();   // the epilogue's stores have left the wavefront
@@ -736,8 +856,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
 }
 
 struct Tile { int bm, bn, wgm, wgn; float eff; };
-constexpr Tile kTiles[] = {{256, 256, 2, 4, 1.0f}, {256, 128, 4, 2, 0.85f}, {128, 128, 2, 2, 0.7f}, {64, 64, 2, 2, 0.35f},
-                           {192, 192, 3, 2, 0.9f}};   // 192: fills the chip exactly at d = 3072
+constexpr Tile kTiles[] = {{256, 256, 2, 2, 1.0f}, {256, 128, 2, 2, 0.85f}, {128, 128, 2, 2, 0.7f}, {64, 64, 2, 2, 0.35f},
+                           {192, 192, 2, 2, 0.88f}};   // 192: fills the chip exactly at d = 3072
 constexpr int kNumTiles = 5;
 
 int pick_tile(int M, int N, int batch) {
@@ -793,9 +913,9 @@ hipError_t launch_epi(const GemmArgs& a, int batch, hipStream_t stream) {
   if constexpr (EPI == EPI_GRAMW || EPI == EPI_SQUARE || EPI == EPI_FRO2) {
     if (a.symmetric) {   // tiles on and above the diagonal only, where a square tile gives enough of them per side
       switch (pick_tile_sym(a.M, batch)) {
-        case 0: return launch_one<256, 256, 2, 4, 2, EPI, F16, true>(a, batch, stream);
+        case 0: return launch_one<256, 256, 2, 2, 2, EPI, F16, true>(a, batch, stream);
         case 2: return launch_one<128, 128, 2, 2, 3, EPI, F16, true>(a, batch, stream);
-        case 4: return launch_one<192, 192, 3, 2, 3, EPI, F16, true>(a, batch, stream);
+        case 4: return launch_one<192, 192, 2, 2, 3, EPI, F16, true>(a, batch, stream);
         case 3: return launch_one<64, 64, 2, 2, 3, EPI, F16, true>(a, batch, stream);
         default: break;
       }
@@ -804,10 +924,10 @@ hipError_t launch_epi(const GemmArgs& a, int batch, hipStream_t stream) {
   switch (pick_tile(a.M, a.N, batch)) {
     // LDS stages: as many 64-deep tiles as fit (two of 64 KiB for 256 x 256; smaller tiles take a third, which
     // puts two K steps instead of one between a load's issue and its use)
-    case 0: return launch_one<256, 256, 2, 4, 2, EPI, F16>(a, batch, stream);
-    case 1: return launch_one<256, 128, 4, 2, 3, EPI, F16>(a, batch, stream);
+    case 0: return launch_one<256, 256, 2, 2, 2, EPI, F16>(a, batch, stream);
+    case 1: return launch_one<256, 128, 2, 2, 3, EPI, F16>(a, batch, stream);
     case 2: return launch_one<128, 128, 2, 2, 3, EPI, F16>(a, batch, stream);
-    case 4: return launch_one<192, 192, 3, 2, 3, EPI, F16>(a, batch, stream);
+    case 4: return launch_one<192, 192, 2, 2, 3, EPI, F16>(a, batch, stream);
     default: return launch_one<64, 64, 2, 2, 3, EPI, F16>(a, batch, stream);
   }
 }
@@ -845,19 +965,21 @@ int gemm_num_workgroups(int M, int N, int batch) {
 hipError_t launch_gemm_nt(const GemmArgs& a, GemmEpilogue epi, int batch, hipStream_t stream) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0 || (a.K & 7) || (a.lda & 7) || (a.ldb & 7) || a.nseg < 1 || a.nseg > kMaxSegments ||
       batch < 1 || (a.ab_f16 && epi != EPI_F32 && epi != EPI_GRAMW && epi != EPI_XOUT && epi != EPI_XLAST) ||
-      (a.ab_f16 && ((epi == EPI_GRAMW && (a.np_out != 1 || a.np_add != 0)) ||
+      (a.ab_f16 && ((epi == EPI_GRAMW && a.np_out != 1) ||
                     (epi == EPI_XOUT && (a.np_out != 1 || a.np_out_n != 1 || a.Xadd || a.C32)))) || (int64_t)a.M * a.lda >= (1ll << 30) || (int64_t)a.N * a.ldb >= (1ll << 30))
     return hipErrorInvalidValue;
   if (a.symmetric && ((epi != EPI_GRAMW && epi != EPI_SQUARE && epi != EPI_FRO2) || (epi != EPI_FRO2 && a.A != a.B) ||
                       a.M != a.N || a.lda != a.ldb || (a.M & 3)))
     return hipErrorInvalidValue;
   // the matrix-writing epilogues address their arrays [M or N rows][ldc] through 32-bit byte offsets
-  if ((epi == EPI_F32 || epi == EPI_GRAMW || epi == EPI_SQUARE || epi == EPI_XLAST || epi == EPI_XOUT) &&
-      (a.ldc < a.N || (epi != EPI_F32 && a.ldc < a.M) || (int64_t)((a.M > a.N ? a.M : a.N) + 256) * a.ldc >= (1ll << 29)))
+  if ((epi == EPI_F32 || epi == EPI_GRAMW || epi == EPI_SQUARE || epi == EPI_XLAST || epi == EPI_XOUT || epi == EPI_XADD) &&
+      ((a.M & 7) || (a.N & 7) || (a.ldc & 7) || a.ldc < a.N || (epi != EPI_F32 && a.ldc < a.M) || (int64_t)((a.M > a.N ? a.M : a.N) + 256) * a.ldc >= (1ll << 29)))
     return hipErrorInvalidValue;
   // EPI_ACT / EPI_SIGN_ACT address Y relative to a tile's first row: 256 rows x pitch x 4 bytes below 2^31
   if ((epi == EPI_ACT && (a.ldc < a.N || a.ldc >= (1ll << 21))) || (epi == EPI_SIGN_ACT && (a.ldy < a.N || a.ldy >= (1ll << 21))))
     return hipErrorInvalidValue;
+  if ((epi == EPI_ACT || epi == EPI_SIGN_ACT) && (a.N & 7)) return hipErrorInvalidValue;   // the staged stores take whole chunks of columns
+  if (epi == EPI_XADD && (!a.Xadd || !a.C32)) return hipErrorInvalidValue;
   if (epi == EPI_XLAST && (!a.C32 || !a.Pn || !a.Pt || (a.M & 3) || a.np_out < 1 || a.np_out > 2)) return hipErrorInvalidValue;
   switch (epi) {
     case EPI_SIGN: return launch_epi<EPI_SIGN>(a, batch, stream);
@@ -870,6 +992,7 @@ hipError_t launch_gemm_nt(const GemmArgs& a, GemmEpilogue epi, int batch, hipStr
     case EPI_GRAMW: return a.ab_f16 ? launch_epi<EPI_GRAMW, true>(a, batch, stream) : launch_epi<EPI_GRAMW>(a, batch, stream);
     case EPI_XLAST: return a.ab_f16 ? launch_epi<EPI_XLAST, true>(a, batch, stream) : launch_epi<EPI_XLAST>(a, batch, stream);
     case EPI_XOUT: return a.ab_f16 ? launch_epi<EPI_XOUT, true>(a, batch, stream) : launch_epi<EPI_XOUT>(a, batch, stream);
+    case EPI_XADD: return launch_epi<EPI_XADD>(a, batch, stream);
     case EPI_SQUARE: return launch_epi<EPI_SQUARE>(a, batch, stream);
     case EPI_FRO2: return launch_epi<EPI_FRO2>(a, batch, stream);
   }

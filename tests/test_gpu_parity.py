@@ -996,3 +996,32 @@ def test_planted_polar_large(B, d):
         assert abs((R64 * A).sum() - sig.sum()) <= TOL_REL * sig.sum()
     finally:
         cal.close()
+
+
+@pytest.mark.parametrize("T,d,dtype", [(2048, 4096, "bf16"), (3001, 3072, "bf16"), (4104, 4096, "bf16"), (1000, 1040, "bf16"), (1500, 1664, "f32"),
+                                       (70, 208, "bf16")])
+def test_rotate_into_rows_of_any_alignment(B, T, d, dtype):
+    """Every tile of the rotate GEMM (256 x 128, 192, 256, 128, 64 wide; ragged rows and columns) into aligned rows, which the
+    large tiles store 16 bytes per lane, and into rows of an odd pitch from an odd element on, which they may not: the same
+    bits, the right rows (a plain product of the same operands), and nothing beside them."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(T + d)
+    R0 = (torch.randn((1, d, d), generator=g, device="cuda:0") / math.sqrt(d)).cpu().numpy()
+    X = torch.randn((T, d), generator=g, device="cuda:0")
+    X = X.to(torch.bfloat16) if dtype == "bf16" else X
+    cal = B.Calibrator(d, 1, dtype, R0, max_tokens=T)
+    try:
+        ref = X.double() @ torch.from_numpy(R0[0]).to("cuda:0").to(X.dtype).double()
+        Y = cal.rotate(X)
+        flat = torch.full((T * (d + 3) + 1,), 7.0, dtype=X.dtype, device=X.device)
+        odd = flat[1:].view(T, d + 3)
+        cal.rotate(X, odd)
+        torch.cuda.synchronize()
+        assert torch.equal(odd[:, :d], Y)
+        assert bool((odd[:, d:] == 7.0).all()) and float(flat[0]) == 7.0
+        # one rounding of the result (2^-9 relative) and fp32 sums of d terms; fp32: split-precision products
+        tol = 2.0 ** -8 if dtype == "bf16" else 1e-5
+        assert float((Y.double() - ref).abs().max()) <= tol * float(ref.abs().max())
+    finally:
+        cal.close()
