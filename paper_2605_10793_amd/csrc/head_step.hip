@@ -196,6 +196,9 @@ __global__ void __launch_bounds__(NTHREADS) k_head_step128(const bf16_bits* __re
     // sXt / sCt are written again only after the next tile's first barrier.
   }
 
+  // A share without tiles has met no barrier since R_h^T was written: its l1 term below would read the other wavefronts'
+  // part of it before it is there, and zero times whatever the LDS held last need not be zero.
+  if (ntiles == 0) __syncthreads();
   // ---- partial M_h of this share; and this share's l1 term without a per-token reduction:
   //   sum_t ||y_t||_1 / ||x_t|| = sum_t sum_n sgn(y_tn) y_tn / ||x_t|| = sqrt(dh) <R_op, x^^T C>   (y = x R_op, C = sgn(y)/sqrt(dh))
   // i.e. the inner product of the operand rotation with the partial M just accumulated (the l1 identity of Sec. 3.2
@@ -276,7 +279,7 @@ hipError_t launch_head_step128(const bf16_bits* X, int64_t T, int64_t stride, in
   // whole tiles per share, so that the shares' 4-token sign stores never straddle a share boundary
   const int64_t tiles = (T + TT - 1) / TT;
   const int64_t tokens_per_split = (tiles + nsplit - 1) / nsplit * TT;
-  const dim3 grid(heads, nsplit);
+  const dim3 grid(heads, nsplit);   // (a share behind the last tile is empty: it stores zeros)
   static PerDeviceOnce configured;
   hipError_t e = configured.run([] {
     hipError_t r = hipFuncSetAttribute(reinterpret_cast<const void*>(k_head_step128<true>),

@@ -1025,3 +1025,12 @@ def test_rotate_into_rows_of_any_alignment(B, T, d, dtype):
         assert float((Y.double() - ref).abs().max()) <= tol * float(ref.abs().max())
     finally:
         cal.close()
+
+
+@pytest.mark.parametrize("heads,T", [(32, 1100), (8, 1153), (16, 1025)])
+def test_head_step_with_empty_token_shares(B, heads, T):
+    """Token counts whose tiles do not divide among the shares, so that the last shares are empty (32 heads, 1100 tokens: 9
+    tiles in 8 shares of 2): the l1 term and M of every head, over several batches and updates on the same context, whose
+    LDS then holds other kernels' leftovers."""
+    w = I.small_workload(128 * heads, T, n_batches=2, heads=heads, seed=900 + heads, prox_lambda=0.1)
+    run_stream(B, w, 2, check_R=True)
