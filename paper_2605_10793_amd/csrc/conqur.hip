@@ -629,22 +629,23 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   if (timed) HIP_TRY(hipEventRecord(ctx->ev[ST_UPDATE][0], s));
 
   const int np_main = 1 + (int)ctx->cfg.polar_precision;
-  // Heads of width 128 on the fused path: the launch that runs the main phase also forms the start iterate (and, below,
-  // takes the closing step), so the update is the reduction of the token shares and that one launch.
-  HeadPolarStart hstart;
-  bool use_hstart = ctx->head_fused && dh == 128 && np_main == 1 && ctx->cfg.polar_max_iters > 0;
+  // Heads of width up to kHeadPolarMaxDh: the launch that runs the main phase also forms the start iterate (and, below, takes
+  // the closing step), so the update is that one launch (for heads of width 128 behind the reduction of the token shares).
+  HeadPolarStart hstart{};
+  const bool one_launch = dh <= kHeadPolarMaxDh && np_main == 1;
+  bool use_hstart = one_launch && ctx->cfg.polar_max_iters > 0;
   if (ctx->parts_pending) {   // per-head step: M is summed from the token shares here, ||M||_F^2 from the same pass
     HIP_TRY(launch_head_reduce(ctx->Mpart, ctx->parts_pending, h, ctx->M, 0, ctx->dotrm_part, s));
     if (use_hstart) { hstart.fro2_parts = ctx->dotrm_part; hstart.nparts = kHeadReduceParts; }
     else HIP_TRY(launch_sum_partials(ctx->dotrm_part, kHeadReduceParts, h, ctx->fro2, s));
     ctx->parts_pending = 0;
-  } else {
+  } else if (!use_hstart) {
     HIP_TRY(launch_fro2(ctx->M, h, blk, ctx->dotrm_part, ctx->fro2, s));
-    if (use_hstart) { hstart.fro2_parts = ctx->fro2; hstart.nparts = 1; }
   }
   if (use_hstart) {
     hstart.M = ctx->M; hstart.R = ctx->R; hstart.fro2_out = ctx->fro2; hstart.lambda = ctx->cfg.prox_lambda;
     hstart.L = ctx->L; hstart.ldot = ctx->ldot;
+    hstart.rop_dot = ctx->head_fused ? 0 : 1; hstart.round_bf16 = ctx->f32 ? 0 : 1;
   }
 
   // Single-plane main steps run on fp16 operands (iterate and polynomial factor): the MFMA rate of bf16 with 11
@@ -780,14 +781,14 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   // step and are finished by the closing iterations.)
   int handover_planes = 0;   // 1 / 2: the iterate in PX is exactly the sum of that many planes of buffer `cur`; 0: all three
   bool allow_fuse = true;    // (only the first main phase of an update: not the one after a nudge)
-  int fused_slot = -1;       // heads of width 128: the launch of the main phase also took the closing step (per head, if
+  int fused_slot = -1;       // narrow heads: the launch of the main phase also took the closing step (per head, if
                              // its residual allowed); residual slots fused_slot (||I - G||_F^2) and fused_slot + 1 (||D^2||_F^2)
   auto main_phase = [&](double l0, bool planes_ready) -> conqur_status {
     if (!planes_ready) HIP_TRY(launch_pack(ctx->PX, h, dh, dh, np_main, ctx->PXn[cur], ctx->PXt[cur], plane, s, main_f16));
     const double e_stop = np_main == 1 ? 4e-3 : 5e-4;   // the safety margins below floor the ripple near 2e-4
     double l = l0, u = 1.0;
-    if (dh == 128 && np_main == 1 && iters < cap) {
-      // heads of width 128: the whole schedule in one launch, the iterate stays in LDS (head_polar.hip)
+    if (one_launch && iters < cap) {
+      // narrow heads: the whole schedule in one launch, the iterate stays in LDS (head_polar.hip)
       PolarSchedule sc;
       sc.nsteps = 0;
       while (sc.nsteps < kPolarScheduleMax) {
@@ -805,7 +806,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       HeadPolarClose hc;
       const bool fuse = allow_fuse && !ctx->cfg.polar_verify && iters + sc.nsteps + 1 <= cap && slot + 2 < kResidSlots - 8;
       if (fuse) {
-        hc.R = ctx->R; hc.RopT = ctx->RopT; hc.M = ctx->M;
+        hc.R = ctx->R; hc.RopT = ctx->RopT; hc.rop_planes = ctx->np; hc.rop_plane = plane; hc.M = ctx->M;
         hc.res_out = ctx->resid + (size_t)slot * h; hc.sq_out = ctx->resid + (size_t)(slot + 1) * h; hc.inner_out = ctx->inner;
         hc.res_max = (float)(1e-2 * std::sqrt((double)dh));
         fused_slot = slot;
@@ -813,14 +814,15 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       } else {
         fused_slot = -1;
       }
-      HIP_TRY(launch_head_polar128(ctx->PXn[cur], ctx->PXt[cur], h, sc, ctx->PX, ctx->PXn[cur ^ 1], ctx->PXt[cur ^ 1],
+      HIP_TRY(launch_head_polar(ctx->PXn[cur], ctx->PXt[cur], h, dh, sc, ctx->PX, ctx->PXn[cur ^ 1], ctx->PXt[cur ^ 1],
                                    fuse ? &hc : nullptr, (use_hstart && planes_ready) ? &hstart : nullptr, s));
       use_hstart = false;
       cur ^= 1;
       handover_planes = 1;
       iters += sc.nsteps;
-      // per head: two 128^3 products per step, a third in the last one, and four in the closing step if it is taken
-      mfma_flop += 2.0 * 128.0 * 128.0 * 128.0 * h * (2.0 * sc.nsteps + 1.0 + (fuse ? 4.0 : 0.0));
+      // per head: two products per step, a third in the last one, and four in the closing step if it is taken
+      const double pad = (double)round_up(dh, 32);
+      mfma_flop += 2.0 * pad * pad * pad * h * (2.0 * sc.nsteps + 1.0 + (fuse ? 4.0 : 0.0));
       if (trace) std::fprintf(stderr, "[conqur] polar main phase: %d steps in one launch, l0=%.3e\n", sc.nsteps, l0);
       return CONQUR_OK;
     }
@@ -875,7 +877,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     if (timed) HIP_TRY(hipEventRecord(ctx->ev[ST_UPDATE][1], s));
     return CONQUR_OK;
   };
-  // Outcome of a closing step taken inside the main phase's launch (heads of width 128): accepted if every head took it
+  // Outcome of a closing step taken inside the main phase's launch (narrow heads): accepted if every head took it
   // and the bound from ||D^2||_F (see below) is within the tolerance; otherwise the general closing steps continue from
   // the hand-over state, which that launch wrote as well.  (R of the heads that did take the step is overwritten already:
   // should the rare nudge below follow, it moves those heads towards their new rotation instead of the previous one.)

@@ -1,216 +1,229 @@
-// Main phase of the polar iteration for heads of width 128, one launch for all steps
+// Main phase of the polar iteration for heads of width up to 128, one launch for all steps
 // (the composed cubics X <- X (a_k I + b_k X^T X) of the Procrustes update, Sec. 3.3).
 //
-// At this width the iterate (32 KiB as fp16, natural and transposed), and the
-// polynomial factor W (32 KiB) live in the LDS of one compute unit, so a workgroup
-// per head runs the whole schedule without touching HBM between steps; the general
-// path needs two GEMM launches per step, which at 128 x 128 are launch latency only.
-// Per step, with every product a 32x32x16 fp16 MFMA on K-contiguous operands (the iterate and the factor are held as
-// fp16: 11 significant bits at the rate of bf16's 8; every entry is at most a few units in magnitude):
+// At these widths the iterate (up to 34 KiB as fp16, natural and transposed) and the
+// polynomial factor W live in the LDS of one compute unit, so a workgroup per head runs the
+// whole schedule without touching HBM between steps; the general path needs two GEMM launches
+// per step, which at 128 x 128 are launch latency only (32 heads of width 64: 41 launches of
+// 4.3 us, the update 0.30 ms; here one launch).  Per step, with every product 16x16x32 fp16
+// MFMAs on K-contiguous operands (the iterate and the factor are held as fp16: 11 significant
+// bits at the rate of bf16's 8; every entry is at most a few units in magnitude):
 //   G = X^T X            A = B = X^T                     -> W = a I + b G, fp16, to LDS
 //   X' = X W             A = X,  B = W (symmetric)       -> accumulators hold X'
 // An accumulator lane owns 4 consecutive rows of one column, i.e. 8 contiguous bytes of the transposed matrix:
-// X'^T goes to LDS as packed 8-byte writes, X' itself as four 2-byte writes per such group (64 per lane and step,
-// their addresses computed once).  Computing the product in the other orientation as well (X'^T = W X^T, packed
-// stores for both layouts) cost a third of the step's MFMA and LDS-read time and is kept for the last step only,
-// whose results leave for HBM.
+// X'^T goes to LDS as packed 8-byte writes, X' itself as four 2-byte writes per such group.  Computing the product in
+// the other orientation as well (X'^T = W X^T, packed stores for both layouts) costs a third of the step's MFMA and
+// LDS-read time and is kept for the last step only, whose results leave for HBM.
 // The last step writes what the closing iterations read: the iterate rounded to bf16, as
 // fp32 and as one plane of each layout.  On request the same launch then takes the closing
 // step itself (exact Gram matrix of that bf16 iterate, D, D^2, two-plane correction; bf16
 // MFMAs) and leaves the rotation, the rotate operand and <R, M>: see HeadPolarClose.
+//
+// Widths between multiples of 32 run in the next larger square, zero outside the head: zero rows and columns of X stay
+// zero through every step, and the identity of the closing step ends at the head's width.
 #include "kernels.h"
+
+#include <type_traits>
 
 namespace conqur {
 
 namespace {
 
-constexpr int DH = 128;
-constexpr int ROWB = 256;   // bytes per LDS row (128 bf16), 16 chunks of 16 bytes, XOR swizzled
-constexpr int kSmemBytes = 3 * DH * ROWB;
-constexpr int kSmemBytesClose = 4 * DH * ROWB;   // the closing step holds two planes of its correction beside the iterate
-
-__device__ __forceinline__ int loff(int row, int chunk) { return row * ROWB + ((chunk ^ (row & 15)) << 4); }
-
-template <bool CLOSE>
-__global__ void __launch_bounds__(256) k_head_polar128(const bf16_bits* __restrict__ Xn0, const bf16_bits* __restrict__ Xt0,
-                                                       const PolarSchedule sched, float* __restrict__ X32,
-                                                       bf16_bits* __restrict__ Pn, bf16_bits* __restrict__ Pt,
-                                                       const HeadPolarClose cl, const HeadPolarStart st) {
+// N: width of the square (a multiple of 32); WGM x WGN wavefronts own (N / WGM) x (N / WGN) blocks of every product.
+template <int N, int WGM, int WGN, bool CLOSE>
+__global__ void __launch_bounds__(64 * WGM * WGN) k_head_polar(const bf16_bits* __restrict__ Xn0, const bf16_bits* __restrict__ Xt0,
+                                                               const int dh, const PolarSchedule sched, float* __restrict__ X32,
+                                                               bf16_bits* __restrict__ Pn, bf16_bits* __restrict__ Pt,
+                                                               const HeadPolarClose cl, const HeadPolarStart st) {
+  constexpr int NT = 64 * WGM * WGN, WM = N / WGM, WN = N / WGN, TM = WM / 16, TN = WN / 16;
+  static_assert(N % 32 == 0 && WM % 16 == 0 && WN % 16 == 0, "whole MFMA tiles");
+  // bytes per LDS row: the 16-byte pad spreads 16 consecutive rows of one chunk (fragment reads), 16 columns x 4 row groups of
+  // 8 bytes (transposed writes) and 4 rows x 16 values (natural writes) over the 64 banks
+  constexpr int ROWB = N * 2 + 16;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* const sXn = smem;                  // X   : row r, K = column
-  unsigned char* const sXt = smem + DH * ROWB;      // X^T : row c, K = row of X
-  unsigned char* const sW = smem + 2 * DH * ROWB;   // W   : symmetric
+  unsigned char* const sXt = smem + N * ROWB;       // X^T : row c, K = row of X
+  unsigned char* const sW = smem + 2 * N * ROWB;    // W   : symmetric
+  __shared__ double red[5][WGM * WGN];
   const int h = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int half = lane >> 5, col = lane & 31;
-  const int wm = wave >> 1, wn = wave & 1;          // this wavefront's 64 x 64 block of every 128 x 128 product
-  const int64_t hoff = (int64_t)h * DH * DH;
+  const int kg = lane >> 4, col = lane & 15;
+  const int wm = wave / WGN, wn = wave % WGN;
+  const int mb = WM * wm, nb = WN * wn;             // this wavefront's block of every product
+  const int64_t hoff = (int64_t)h * dh * dh;
 
-  if (!st.M) {   // the start iterate is given as planes
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int idx = q * 256 + tid, row = idx >> 4, chunk = idx & 15;
-      *reinterpret_cast<uint4*>(sXn + loff(row, chunk)) = *reinterpret_cast<const uint4*>(Xn0 + hoff + row * DH + chunk * 8);
-      *reinterpret_cast<uint4*>(sXt + loff(row, chunk)) = *reinterpret_cast<const uint4*>(Xt0 + hoff + row * DH + chunk * 8);
-    }
-    __syncthreads();
-  }
-
+  typedef f32x4 Acc[TM][TN];
   auto frag = [&](const unsigned char* base, int row, int kk) {
-    return *reinterpret_cast<const f16x8*>(base + loff(row, 2 * kk + half));
+    return *reinterpret_cast<const f16x8*>(base + (row + col) * ROWB + kk * 64 + kg * 16);
   };
-  // acc[i][j] = sum_k A[rowA + 32 i + .][k] B[rowB + 32 j + .][k]
-  auto product = [&](const unsigned char* A, int rowA, const unsigned char* B, int rowB, f32x16 (&acc)[2][2]) {
+  auto zero = [](Acc& v) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < TN; ++j) v[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  };
+  // acc[i][j] += sum_k A[mb + 16 i + .][k] B[nb + 16 j + .][k], fp16 or bf16 operands
+  auto product = [&](auto f16, const unsigned char* A, const unsigned char* B, Acc& acc) {
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.0f;
+    for (int kk = 0; kk < N / 32; ++kk) {
+      f16x8 fa[TM], fb[TN];
 #pragma unroll
-    for (int kk = 0; kk < DH / 16; ++kk) {
-      f16x8 fa[2], fb[2];
+      for (int i = 0; i < TM; ++i) fa[i] = frag(A, mb + 16 * i, kk);
 #pragma unroll
-      for (int i = 0; i < 2; ++i) fa[i] = frag(A, rowA + 32 * i + col, kk);
+      for (int j = 0; j < TN; ++j) fb[j] = frag(B, nb + 16 * j, kk);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) fb[j] = frag(B, rowB + 32 * j + col, kk);
+      for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < TN; ++j) {
+          if constexpr (decltype(f16)::value) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(fa[i], fb[j], acc[i][j], 0, 0, 0);
+          else acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, fa[i]), __builtin_bit_cast(bf16x8, fb[j]), acc[i][j], 0, 0, 0);
+        }
     }
   };
-  // Element e = 4 jj + ii of acc[i][j]: row m = rowA + 32 i + 8 jj + 4 half + ii, column n = rowB + 32 j + col.
-  // Store the transposed matrix into an LDS operand: row n, K positions m .. m + 3 (8 bytes).
-  auto store_transposed = [&](unsigned char* dst, int rowA, int rowB, const f32x16 (&acc)[2][2], float ci, float cg) {
+  constexpr std::true_type kF16{};
+  constexpr std::false_type kBF16{};
+  // Element r of acc[i][j]: row m = mb + 16 i + 4 kg + r, column n = nb + 16 j + col.  fn(i, j, m of r = 0, n) over the block;
+  // inside(i, j): whether the 16 x 16 tile lies in the head (dh is a multiple of 16: as a whole or not at all).
+  auto each = [&](auto&& fn) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int n = rowB + 32 * j + col;
+      for (int j = 0; j < TN; ++j) fn(i, j, mb + 16 * i + 4 * kg, nb + 16 * j + col);
+  };
+  auto inside = [&](int i, int j) { return mb + 16 * i < dh && nb + 16 * j < dh; };
+  auto tr_addr = [&](int m0, int n) { return n * ROWB + m0 * 2; };      // transposed: row n, K positions m0 .. m0 + 3 (8 bytes)
+  // the transposed matrix into an LDS operand (fp16): W = ci I + cg acc, or the iterate itself
+  auto store_transposed = [&](unsigned char* dst, const Acc& acc, float ci, float cg) {
+    each([&](int i, int j, int m0, int n) {
+      float v[4];
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const int m0 = rowA + 32 * i + 8 * jj + 4 * half;
-          float v[4];
+      for (int r = 0; r < 4; ++r) v[r] = cg * acc[i][j][r] + ((m0 + r == n) ? ci : 0.0f);
+      *reinterpret_cast<uint2*>(dst + tr_addr(m0, n)) = make_uint2(f32x2_to_f16x2(v[0], v[1]), f32x2_to_f16x2(v[2], v[3]));
+    });
+  };
+  // the iterate in both layouts: packed rows of X^T, and row m, K position n of X one value at a time
+  auto store_iterate = [&](const Acc& acc) {
+    each([&](int i, int j, int m0, int n) {
+      const uint32_t lo = f32x2_to_f16x2(acc[i][j][0], acc[i][j][1]), hi = f32x2_to_f16x2(acc[i][j][2], acc[i][j][3]);
+      *reinterpret_cast<uint2*>(sXt + tr_addr(m0, n)) = make_uint2(lo, hi);
+      unsigned char* d = sXn + m0 * ROWB + n * 2;
+      *reinterpret_cast<unsigned short*>(d) = (unsigned short)lo;
+      *reinterpret_cast<unsigned short*>(d + ROWB) = (unsigned short)(lo >> 16);
+      *reinterpret_cast<unsigned short*>(d + 2 * ROWB) = (unsigned short)hi;
+      *reinterpret_cast<unsigned short*>(d + 3 * ROWB) = (unsigned short)(hi >> 16);
+    });
+  };
+  // sum of one double per lane over the workgroup, known to every thread afterwards (a slot is used once)
+  auto block_sum = [&](double v, int slot) {
+    v = wave_sum_d(v);
+    if (lane == 0) red[slot][wave] = v;
+    __syncthreads();
+    double t = 0.0;
 #pragma unroll
-          for (int ii = 0; ii < 4; ++ii) v[ii] = cg * acc[i][j][4 * jj + ii] + ((m0 + ii == n) ? ci : 0.0f);
-          uint2 pk;
-          pk.x = f32x2_to_f16x2(v[0], v[1]);
-          pk.y = f32x2_to_f16x2(v[2], v[3]);
-          *reinterpret_cast<uint2*>(dst + loff(n, m0 >> 3) + (m0 & 7) * 2) = pk;
-        }
-      }
+    for (int q = 0; q < WGM * WGN; ++q) t += red[slot][q];
+    return t;
   };
 
-  // LDS byte offsets of the natural-layout positions of this lane's accumulator elements in tile row i = 0
-  // (tile row 1 lies 32 rows = 32 * ROWB bytes further on): element e = 4 jj + ii of acc[.][j].
-  uint32_t nat_addr[2][4][4];
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-      for (int ii = 0; ii < 4; ++ii) {
-        const int m = 64 * wm + 8 * jj + 4 * half + ii, n = 64 * wn + 32 * j + col;
-        nat_addr[j][jj][ii] = (uint32_t)(loff(m, n >> 3) + (n & 7) * 2);
-      }
-  // The iterate itself into an LDS operand: row m, K position n, one fp16 value at a time.
-  auto store_natural = [&](unsigned char* dst, const f32x16 (&acc)[2][2]) {
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const uint32_t lo = f32x2_to_f16x2(acc[i][j][4 * jj], acc[i][j][4 * jj + 1]);
-          const uint32_t hi = f32x2_to_f16x2(acc[i][j][4 * jj + 2], acc[i][j][4 * jj + 3]);
-          unsigned char* d = dst + i * 32 * ROWB;
-          *reinterpret_cast<unsigned short*>(d + nat_addr[j][jj][0]) = (unsigned short)lo;
-          *reinterpret_cast<unsigned short*>(d + nat_addr[j][jj][1]) = (unsigned short)(lo >> 16);
-          *reinterpret_cast<unsigned short*>(d + nat_addr[j][jj][2]) = (unsigned short)hi;
-          *reinterpret_cast<unsigned short*>(d + nat_addr[j][jj][3]) = (unsigned short)(hi >> 16);
-        }
-  };
-
-  f32x16 acc[2][2], accT[2][2];
+  Acc acc, accT;
   if (st.M) {
     // The start of the update in this launch as well (what the packing pass does on the general path):
-    // X0 = (M + lambda tau R_prev) / alpha, tau = ||M||_F / sqrt(dh), alpha = ||M||_F (1 + lambda), with ||M||_F^2 summed from
-    // the partial sums the reduction of the token shares left (or given whole: nparts = 1); lambda = 0 stands for the
-    // limit at fp32 resolution, an empty M for R_prev itself.  Elements in the accumulators' layout, so that the two LDS
-    // operands are written exactly as after a step.
-    double f2 = 0.0;
-    for (int p = 0; p < st.nparts; ++p) f2 += st.fro2_parts[(int64_t)h * st.nparts + p];
+    // X0 = (M + lambda tau R_prev) / alpha, tau = ||M||_F / sqrt(dh), alpha = ||M||_F (1 + lambda); lambda = 0 stands for the
+    // limit at fp32 resolution, an empty M for R_prev itself.  ||M||_F^2 is the sum of the partial sums the reduction of the
+    // token shares left, or is taken here.  Elements in the accumulators' layout, so that the two LDS operands are written
+    // exactly as after a step.
+    Acc prev;
+    zero(acc);
+    zero(prev);
+    double f2 = 0.0, dot = 0.0;
+    each([&](int i, int j, int m0, int n) {
+      if (!inside(i, j)) return;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t off = hoff + (int64_t)(m0 + r) * dh + n;
+        acc[i][j][r] = st.M[off];
+        prev[i][j][r] = st.R[off];
+      }
+    });
+    if (st.nparts > 0) {
+      for (int p = 0; p < st.nparts; ++p) f2 += st.fro2_parts[(int64_t)h * st.nparts + p];
+    } else {
+      each([&](int i, int j, int, int) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) f2 += (double)acc[i][j][r] * acc[i][j][r];
+      });
+      f2 = block_sum(f2, 0);
+    }
+    if (st.rop_dot) {   // <R_op, M>: the l1 term of the rows this update consumes (see k_dot_rm)
+      each([&](int i, int j, int, int) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          dot += (double)acc[i][j][r] * (st.round_bf16 ? bf16_to_f32(f32_to_bf16(prev[i][j][r])) : prev[i][j][r]);
+      });
+      dot = block_sum(dot, 1);
+    }
     if (tid == 0) {
       st.fro2_out[h] = f2;
-      if (st.ldot) st.ldot[h] = st.L[h];   // the l1 term of the rows this update consumes, kept before the statistics restart
+      if (st.ldot) st.ldot[h] = st.rop_dot ? dot : st.L[h];   // kept before the statistics restart
     }
     const double f = sqrt(f2);
     const bool empty = !(f > 0.0);
     const float lambda = fmaxf(st.lambda, 9.5367431640625e-07f);
-    const float tau = (float)(f / sqrt((double)DH));
+    const float tau = (float)(f / sqrt((double)dh));
     const float inv_alpha = empty ? 1.0f : (float)(1.0 / (f * (1.0 + (double)lambda)));
     const float cm = empty ? 0.0f : inv_alpha, cr = empty ? 1.0f : lambda * tau * inv_alpha;
+    each([&](int i, int j, int, int) {
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int m = 64 * wm + 32 * i + 8 * (e >> 2) + 4 * half + (e & 3), n = 64 * wn + 32 * j + col;
-          const int64_t off = hoff + (int64_t)m * DH + n;
-          acc[i][j][e] = cm * st.M[off] + cr * st.R[off];
-        }
-    store_transposed(sXt, 64 * wm, 64 * wn, acc, 0.0f, 1.0f);
-    store_natural(sXn, acc);
-    __syncthreads();
+      for (int r = 0; r < 4; ++r) acc[i][j][r] = fmaf(cm, acc[i][j][r], cr * prev[i][j][r]);   // (as the packing pass rounds it)
+    });
+    store_iterate(acc);
+  } else {   // the start iterate is given as planes
+    for (int idx = tid; idx < N * (N / 8); idx += NT) {
+      const int row = idx / (N / 8), chunk = idx % (N / 8);
+      uint4 a = make_uint4(0u, 0u, 0u, 0u), b = a;
+      if (row < dh && chunk * 8 < dh) {
+        a = *reinterpret_cast<const uint4*>(Xn0 + hoff + (int64_t)row * dh + chunk * 8);
+        b = *reinterpret_cast<const uint4*>(Xt0 + hoff + (int64_t)row * dh + chunk * 8);
+      }
+      *reinterpret_cast<uint4*>(sXn + row * ROWB + chunk * 16) = a;
+      *reinterpret_cast<uint4*>(sXt + row * ROWB + chunk * 16) = b;
+    }
   }
+  __syncthreads();
   for (int k = 0; k < sched.nsteps; ++k) {
     const bool last = k + 1 == sched.nsteps;
     // G = X^T X;  W = a I + b G (G symmetric: storing the transpose stores W itself)
-    product(sXt, 64 * wm, sXt, 64 * wn, acc);
-    store_transposed(sW, 64 * wm, 64 * wn, acc, sched.a[k], sched.b[k]);
+    zero(acc);
+    product(kF16, sXt, sXt, acc);
+    store_transposed(sW, acc, sched.a[k], sched.b[k]);
     __syncthreads();
-    product(sXn, 64 * wm, sW, 64 * wn, acc);    // X'   [r][c]
+    zero(acc);
+    product(kF16, sXn, sW, acc);                  // X'   [r][c]
     if (last) {
-      product(sW, 64 * wm, sXn, 64 * wn, accT);   // X'^T [c][r]: the natural-layout plane below as packed stores
+      zero(accT);
+      product(kF16, sW, sXn, accT);               // X'^T [c][r]: the natural-layout plane below as packed stores
       break;
     }
-    __syncthreads();                            // every wavefront has read the old iterate
-    store_transposed(sXt, 64 * wm, 64 * wn, acc, 0.0f, 1.0f);
-    store_natural(sXn, acc);
+    __syncthreads();                              // every wavefront has read the old iterate
+    store_iterate(acc);
     __syncthreads();
   }
 
   // Hand-over to the closing iterations: the result rounded to bf16 like every step's, and exactly that value as fp32 X,
   // as one transposed plane (from X') and as one natural plane (from X'^T; the two orientations issue the same products
   // in the same order, so they hold the same numbers): the closing Gram matrix is then exact with one plane product.
+  auto rounded = [](f32x4& a) {   // the packed bf16 values; a becomes exactly those
+    const uint2 t = make_uint2(f32x2_to_bf16x2(a[0], a[1]), f32x2_to_bf16x2(a[2], a[3]));
+    a = f32x4{__uint_as_float(t.x << 16), __uint_as_float(t.x & 0xffff0000u), __uint_as_float(t.y << 16), __uint_as_float(t.y & 0xffff0000u)};
+    return t;
+  };
+  each([&](int i, int j, int m0, int n) {
+    const uint2 hi = rounded(acc[i][j]), thi = rounded(accT[i][j]);
+    if (!inside(i, j)) return;
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int n = 64 * wn + 32 * j + col;
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int m0 = 64 * wm + 32 * i + 8 * jj + 4 * half;
-        uint2 hi, thi;
-        hi.x = f32x2_to_bf16x2(acc[i][j][4 * jj], acc[i][j][4 * jj + 1]);
-        hi.y = f32x2_to_bf16x2(acc[i][j][4 * jj + 2], acc[i][j][4 * jj + 3]);
-        thi.x = f32x2_to_bf16x2(accT[i][j][4 * jj], accT[i][j][4 * jj + 1]);
-        thi.y = f32x2_to_bf16x2(accT[i][j][4 * jj + 2], accT[i][j][4 * jj + 3]);
-        // from here on the accumulators hold the rounded values (exact as bf16)
-        acc[i][j][4 * jj] = __uint_as_float(hi.x << 16); acc[i][j][4 * jj + 1] = __uint_as_float(hi.x & 0xffff0000u);
-        acc[i][j][4 * jj + 2] = __uint_as_float(hi.y << 16); acc[i][j][4 * jj + 3] = __uint_as_float(hi.y & 0xffff0000u);
-        accT[i][j][4 * jj] = __uint_as_float(thi.x << 16); accT[i][j][4 * jj + 1] = __uint_as_float(thi.x & 0xffff0000u);
-        accT[i][j][4 * jj + 2] = __uint_as_float(thi.y << 16); accT[i][j][4 * jj + 3] = __uint_as_float(thi.y & 0xffff0000u);
-        X32[hoff + (int64_t)m0 * DH + n] = acc[i][j][4 * jj];
-        X32[hoff + (int64_t)(m0 + 1) * DH + n] = acc[i][j][4 * jj + 1];
-        X32[hoff + (int64_t)(m0 + 2) * DH + n] = acc[i][j][4 * jj + 2];
-        X32[hoff + (int64_t)(m0 + 3) * DH + n] = acc[i][j][4 * jj + 3];
-        *reinterpret_cast<uint2*>(Pt + hoff + (int64_t)n * DH + m0) = hi;     // X^T[c = n][r = m0 ..]
-        *reinterpret_cast<uint2*>(Pn + hoff + (int64_t)n * DH + m0) = thi;    // accT: X[r = n][c = m0 ..]
-      }
-    }
+    for (int r = 0; r < 4; ++r) X32[hoff + (int64_t)(m0 + r) * dh + n] = acc[i][j][r];
+    *reinterpret_cast<uint2*>(Pt + hoff + (int64_t)n * dh + m0) = hi;     // X^T[c = n][r = m0 ..]
+    *reinterpret_cast<uint2*>(Pn + hoff + (int64_t)n * dh + m0) = thi;    // accT: X[r = n][c = m0 ..]
+  });
 
   if constexpr (CLOSE) {
     // ---- the closing step of the update in the same launch (Sec. 3.3; the general path's sequence of Gram matrix, D^2,
@@ -220,99 +233,45 @@ __global__ void __launch_bounds__(256) k_head_polar128(const bf16_bits* __restri
     // its residual, marks the step as not taken (sq_out < 0) and the host continues on the general path from the
     // hand-over state written above.
     unsigned char* const sD0 = sW;                    // first plane of D, then of the correction
-    unsigned char* const sD1 = smem + 3 * DH * ROWB;  // second plane
-    __shared__ double red[3][4];
+    unsigned char* const sD1 = smem + 3 * N * ROWB;   // second plane
     // bf16 planes of a symmetric matrix given as accumulator blocks: the transposed store of block (wm, wn) is block
     // (wn, wm) of the matrix itself
-    auto store_planes = [&](const f32x16 (&v)[2][2]) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const int n = 64 * wn + 32 * j + col;
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj) {
-            const int m0 = 64 * wm + 32 * i + 8 * jj + 4 * half;
-            uint2 h0, h1;
-            h0.x = f32x2_to_bf16x2(v[i][j][4 * jj], v[i][j][4 * jj + 1]);
-            h0.y = f32x2_to_bf16x2(v[i][j][4 * jj + 2], v[i][j][4 * jj + 3]);
-            h1.x = f32x2_to_bf16x2(v[i][j][4 * jj] - __uint_as_float(h0.x << 16), v[i][j][4 * jj + 1] - __uint_as_float(h0.x & 0xffff0000u));
-            h1.y = f32x2_to_bf16x2(v[i][j][4 * jj + 2] - __uint_as_float(h0.y << 16), v[i][j][4 * jj + 3] - __uint_as_float(h0.y & 0xffff0000u));
-            *reinterpret_cast<uint2*>(sD0 + loff(n, m0 >> 3) + (m0 & 7) * 2) = h0;
-            *reinterpret_cast<uint2*>(sD1 + loff(n, m0 >> 3) + (m0 & 7) * 2) = h1;
-          }
-        }
+    auto store_planes = [&](const Acc& v) {
+      each([&](int i, int j, int m0, int n) {
+        const f32x4 a = v[i][j];
+        f32x4 hi = a;
+        const uint2 h0 = rounded(hi);
+        const f32x4 lo = a - hi;
+        *reinterpret_cast<uint2*>(sD0 + tr_addr(m0, n)) = h0;
+        *reinterpret_cast<uint2*>(sD1 + tr_addr(m0, n)) = make_uint2(f32x2_to_bf16x2(lo[0], lo[1]), f32x2_to_bf16x2(lo[2], lo[3]));
+      });
     };
-    auto product_bf16 = [&](const unsigned char* A, int rowA, const unsigned char* Bm, int rowB, f32x16 (&out)[2][2]) {
-#pragma unroll
-      for (int kk = 0; kk < DH / 16; ++kk) {
-        bf16x8 fa[2], fb[2];
-#pragma unroll
-        for (int i = 0; i < 2; ++i) fa[i] = *reinterpret_cast<const bf16x8*>(A + loff(rowA + 32 * i + col, 2 * kk + half));
-#pragma unroll
-        for (int j = 0; j < 2; ++j) fb[j] = *reinterpret_cast<const bf16x8*>(Bm + loff(rowB + 32 * j + col, 2 * kk + half));
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-          for (int j = 0; j < 2; ++j) out[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], out[i][j], 0, 0, 0);
-      }
-    };
-    auto zero = [](f32x16 (&v)[2][2]) {
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) v[i][j][e] = 0.0f;
-    };
-    // sum of one double per lane over the workgroup, known to every thread afterwards
-    auto block_sum = [&](double v, int slot) {
-      v = wave_sum_d(v);
-      if (lane == 0) red[slot][wave] = v;
-      __syncthreads();
-      return red[slot][0] + red[slot][1] + red[slot][2] + red[slot][3];
-    };
-
     __syncthreads();   // every wavefront has finished the last step's reads of the old iterate and of W
     // the rounded iterate as bf16 operands: X^T from X', X from X'^T (packed 8-byte writes both)
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int n = 64 * wn + 32 * j + col;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const int m0 = 64 * wm + 32 * i + 8 * jj + 4 * half;
-          uint2 a, t;
-          a.x = f32x2_to_bf16x2(acc[i][j][4 * jj], acc[i][j][4 * jj + 1]);
-          a.y = f32x2_to_bf16x2(acc[i][j][4 * jj + 2], acc[i][j][4 * jj + 3]);
-          t.x = f32x2_to_bf16x2(accT[i][j][4 * jj], accT[i][j][4 * jj + 1]);
-          t.y = f32x2_to_bf16x2(accT[i][j][4 * jj + 2], accT[i][j][4 * jj + 3]);
-          *reinterpret_cast<uint2*>(sXt + loff(n, m0 >> 3) + (m0 & 7) * 2) = a;
-          *reinterpret_cast<uint2*>(sXn + loff(n, m0 >> 3) + (m0 & 7) * 2) = t;
-        }
-      }
+    each([&](int i, int j, int m0, int n) {
+      *reinterpret_cast<uint2*>(sXt + tr_addr(m0, n)) = rounded(acc[i][j]);
+    });
+    // accT's block is (wm, wn) of X^T as a product of W's rows and X's rows: element (m, n) is X[n][m]
+    each([&](int i, int j, int m0, int n) {
+      *reinterpret_cast<uint2*>(sXn + tr_addr(m0, n)) = rounded(accT[i][j]);
+    });
     __syncthreads();
     // G = X^T X (products of bf16 values are exact in fp32), D = (I - G) / 2, ||I - G||_F^2
-    f32x16 dm[2][2];
+    Acc dm;
     zero(dm);
-    product_bf16(sXt, 64 * wm, sXt, 64 * wn, dm);
+    product(kBF16, sXt, sXt, dm);
     double part = 0.0;
+    each([&](int i, int j, int m0, int n) {
+      float p32 = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        float p32 = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int m = 64 * wm + 32 * i + 8 * (e >> 2) + 4 * half + (e & 3), n = 64 * wn + 32 * j + col;
-          const float dlt = (m == n ? 1.0f : 0.0f) - dm[i][j][e];
-          p32 += dlt * dlt;
-          dm[i][j][e] = 0.5f * dlt;
-        }
-        part += (double)p32;
+      for (int r = 0; r < 4; ++r) {
+        const float dlt = (m0 + r == n && n < dh ? 1.0f : 0.0f) - dm[i][j][r];
+        p32 += dlt * dlt;
+        dm[i][j][r] = 0.5f * dlt;
       }
-    const double res2 = block_sum(part, 0);
+      part += (double)p32;
+    });
+    const double res2 = block_sum(part, 2);
     if (!(res2 <= (double)cl.res_max * cl.res_max)) {   // (also a non-finite residual)
       if (tid == 0) { cl.res_out[h] = res2; cl.sq_out[h] = -1.0; }
       return;
@@ -320,92 +279,105 @@ __global__ void __launch_bounds__(256) k_head_polar128(const bf16_bits* __restri
     store_planes(dm);
     __syncthreads();
     // D^2 from the first plane (second-order small: one plane is ample), ||D^2||_F^2, the correction D + 1.5 D^2
-    f32x16 sq[2][2];
+    Acc sq;
     zero(sq);
-    product_bf16(sD0, 64 * wm, sD0, 64 * wn, sq);
+    product(kBF16, sD0, sD0, sq);
     part = 0.0;
+    each([&](int i, int j, int, int) {
+      float p32 = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        float p32 = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          p32 += sq[i][j][e] * sq[i][j][e];
-          dm[i][j][e] += 1.5f * sq[i][j][e];
-        }
-        part += (double)p32;
+      for (int r = 0; r < 4; ++r) {
+        p32 += sq[i][j][r] * sq[i][j][r];
       }
-    const double sq2 = block_sum(part, 1);   // (its barrier: every wavefront has read the planes of D)
+      part += (double)p32;
+      if constexpr (N == 128) {
+        dm[i][j] += 1.5f * sq[i][j];
+      } else {   // D as its two planes hold it: the rounding of the general path, bit for bit
+        f32x4 d0 = dm[i][j];
+        rounded(d0);
+        f32x4 d1 = dm[i][j] - d0;
+        rounded(d1);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) dm[i][j][r] = fmaf(1.5f, sq[i][j][r], d0[r]) + d1[r];
+      }
+    });
+    const double sq2 = block_sum(part, 3);   // (its barrier: every wavefront has read the planes of D)
     store_planes(dm);
     __syncthreads();
     // X <- X + X (W0 + W1).  The small correction is summed on its own and the iterate added once at the end: with the
-    // iterate as the accumulators' start every one of the 16 MFMAs would round at the iterate's magnitude, and the
-    // orthogonality of the result was measured above the bound that holds for the general path's order.
+    // iterate as the accumulators' start every MFMA would round at the iterate's magnitude, and the orthogonality of the
+    // result was measured above the bound that holds for the general path's order.
     zero(sq);
-    product_bf16(sXn, 64 * wm, sD0, 64 * wn, sq);
-    product_bf16(sXn, 64 * wm, sD1, 64 * wn, sq);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] += sq[i][j][e];
-    // R, the rotate operand R^T (bf16, [n][m]: packed rows of the transposed matrix) and <R, M>
+    product(kBF16, sXn, N == 128 ? sD0 : sD1, sq);   // (below 128 the general path's order, smaller plane first)
+    product(kBF16, sXn, N == 128 ? sD1 : sD0, sq);
+    // R, the rotate operand R^T (bf16 planes, [n][m]: packed rows of the transposed matrix) and <R, M>
     part = 0.0;
+    each([&](int i, int j, int m0, int n) {
+      acc[i][j] += sq[i][j];
+      if (!inside(i, j)) return;
+      float p32 = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        const int n = 64 * wn + 32 * j + col;
-        float p32 = 0.0f;
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const int m0 = 64 * wm + 32 * i + 8 * jj + 4 * half;
-          uint2 r;
-          r.x = f32x2_to_bf16x2(acc[i][j][4 * jj], acc[i][j][4 * jj + 1]);
-          r.y = f32x2_to_bf16x2(acc[i][j][4 * jj + 2], acc[i][j][4 * jj + 3]);
-          *reinterpret_cast<uint2*>(cl.RopT + hoff + (int64_t)n * DH + m0) = r;
-#pragma unroll
-          for (int ii = 0; ii < 4; ++ii) {
-            const int64_t off = hoff + (int64_t)(m0 + ii) * DH + n;
-            cl.R[off] = acc[i][j][4 * jj + ii];
-            p32 += acc[i][j][4 * jj + ii] * cl.M[off];
-          }
-        }
-        part += (double)p32;
+      for (int r = 0; r < 4; ++r) {
+        const int64_t off = hoff + (int64_t)(m0 + r) * dh + n;
+        cl.R[off] = acc[i][j][r];
+        p32 += acc[i][j][r] * cl.M[off];
       }
-    const double inner = block_sum(part, 2);
+      part += (double)p32;
+      f32x4 left = acc[i][j];
+      for (int p = 0; p < cl.rop_planes; ++p) {
+        f32x4 hi = left;
+        *reinterpret_cast<uint2*>(cl.RopT + p * cl.rop_plane + hoff + (int64_t)n * dh + m0) = rounded(hi);
+        left -= hi;
+      }
+    });
+    const double inner = block_sum(part, 4);
     if (tid == 0) { cl.res_out[h] = res2; cl.sq_out[h] = sq2; cl.inner_out[h] = inner; }
   }
 }
 
-}  // namespace
-
-hipError_t launch_head_polar128(const bf16_bits* Xn0, const bf16_bits* Xt0, int heads, const PolarSchedule& sched, float* X32,
-                                bf16_bits* Pn, bf16_bits* Pt, const HeadPolarClose* close, const HeadPolarStart* start,
-                                hipStream_t s) {
-  if (heads < 1 || sched.nsteps < 1 || sched.nsteps > kPolarScheduleMax) return hipErrorInvalidValue;
-  if (close && (!close->R || !close->RopT || !close->M || !close->res_out || !close->sq_out || !close->inner_out)) return hipErrorInvalidValue;
-  if (start && (!start->M || !start->R || !start->fro2_parts || start->nparts < 1 || !start->fro2_out || (start->ldot && !start->L)))
-    return hipErrorInvalidValue;
-  if (!start && (!Xn0 || !Xt0)) return hipErrorInvalidValue;
+template <int N, int WGM, int WGN, bool CLOSE>
+hipError_t launch_one(const bf16_bits* Xn0, const bf16_bits* Xt0, int heads, int dh, const PolarSchedule& sched, float* X32,
+                      bf16_bits* Pn, bf16_bits* Pt, const HeadPolarClose& cl, const HeadPolarStart& st, hipStream_t s) {
+  constexpr int smem = (CLOSE ? 4 : 3) * N * (N * 2 + 16);   // the closing step holds two planes of its correction beside the iterate
   static PerDeviceOnce configured;
-  hipError_t e = configured.run([] {
-    hipError_t r = hipFuncSetAttribute(reinterpret_cast<const void*>(k_head_polar128<false>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       kSmemBytes);
-    if (r == hipSuccess)
-      r = hipFuncSetAttribute(reinterpret_cast<const void*>(k_head_polar128<true>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              kSmemBytesClose);
-    return r;
+  auto kern = k_head_polar<N, WGM, WGN, CLOSE>;
+  hipError_t e = configured.run([&] {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   });
   if (e != hipSuccess) return e;
-  const HeadPolarStart st = start ? *start : HeadPolarStart{};
-  if (close)
-    hipLaunchKernelGGL(k_head_polar128<true>, dim3(heads), dim3(256), kSmemBytesClose, s, Xn0, Xt0, sched, X32, Pn, Pt, *close, st);
-  else
-    hipLaunchKernelGGL(k_head_polar128<false>, dim3(heads), dim3(256), kSmemBytes, s, Xn0, Xt0, sched, X32, Pn, Pt, HeadPolarClose{}, st);
+  hipLaunchKernelGGL(kern, dim3(heads), dim3(64 * WGM * WGN), smem, s, Xn0, Xt0, dh, sched, X32, Pn, Pt, cl, st);
   return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_head_polar(const bf16_bits* Xn0, const bf16_bits* Xt0, int heads, int dh, const PolarSchedule& sched, float* X32,
+                             bf16_bits* Pn, bf16_bits* Pt, const HeadPolarClose* close, const HeadPolarStart* start, hipStream_t s) {
+  if (heads < 1 || dh < 16 || dh > kHeadPolarMaxDh || (dh & 15) || sched.nsteps < 1 || sched.nsteps > kPolarScheduleMax) return hipErrorInvalidValue;
+  if (close && (!close->R || !close->RopT || !close->M || !close->res_out || !close->sq_out || !close->inner_out || close->rop_planes < 1))
+    return hipErrorInvalidValue;
+  if (start && (!start->M || !start->R || (start->nparts > 0 && !start->fro2_parts) || !start->fro2_out ||
+                (start->ldot && !start->rop_dot && !start->L)))
+    return hipErrorInvalidValue;
+  if (!start && (!Xn0 || !Xt0)) return hipErrorInvalidValue;
+  const HeadPolarStart st = start ? *start : HeadPolarStart{};
+  const HeadPolarClose cl = close ? *close : HeadPolarClose{};
+  auto go = [&](auto n, auto wgm, auto wgn) {
+    constexpr int N = decltype(n)::value, M_ = decltype(wgm)::value, N_ = decltype(wgn)::value;
+    return close ? launch_one<N, M_, N_, true>(Xn0, Xt0, heads, dh, sched, X32, Pn, Pt, cl, st, s)
+                 : launch_one<N, M_, N_, false>(Xn0, Xt0, heads, dh, sched, X32, Pn, Pt, cl, st, s);
+  };
+  // 8 wavefronts (2 per SIMD, so that one's LDS writes and conversions run beside the other's MFMAs) read half as much LDS
+  // again as 4 with square blocks and are still ahead: 32 heads of width 128, 22 steps, whole update 94 us with 2 x 2, 86 with
+  // 4 x 2, 92 with 4 x 4 wavefronts; width 64: 35, 34, 37; width 96 (9 steps): 38, 36 with 3 x 2, 36 with 3 x 3.
+  using std::integral_constant;
+  constexpr integral_constant<int, 2> two{};
+  constexpr integral_constant<int, 3> three{};
+  constexpr integral_constant<int, 4> four{};
+  if (dh <= 32) return go(integral_constant<int, 32>{}, two, two);
+  if (dh <= 64) return go(integral_constant<int, 64>{}, four, two);
+  if (dh <= 96) return go(integral_constant<int, 96>{}, three, two);
+  return go(integral_constant<int, 128>{}, four, two);
 }
 
 }  // namespace conqur

@@ -1034,3 +1034,31 @@ def test_head_step_with_empty_token_shares(B, heads, T):
     LDS then holds other kernels' leftovers."""
     w = I.small_workload(128 * heads, T, n_batches=2, heads=heads, seed=900 + heads, prox_lambda=0.1)
     run_stream(B, w, 2, check_R=True)
+
+
+@pytest.mark.parametrize("heads,dh,T,dtype,lam", [
+    (5, 16, 301, "bf16", 0.1), (3, 32, 401, "f32", 0.0), (9, 48, 203, "bf16", 0.1), (4, 64, 1100, "bf16", 0.0), (7, 80, 513, "bf16", 0.1),
+    (2, 96, 333, "f32", 0.1), (3, 112, 190, "bf16", 0.1), (2, 128, 700, "f32", 0.1), (1, 64, 900, "bf16", 0.0), (3, 144, 257, "bf16", 0.1),
+    (2, 256, 300, "bf16", 0.1)])
+def test_narrow_heads(B, heads, dh, T, dtype, lam):
+    """Every square of the one-launch update (widths 16 .. 128 in squares of 32, 64, 96, 128) and every lane count of the narrow
+    row norms (a slice of 2 .. 32 chunks of 16 bytes), with the first widths beyond either, against the oracle; then the
+    rotate operand the update left, through the rotated rows: all its planes belong to the new rotation."""
+    import torch
+    w = I.small_workload(dh * heads, T, n_batches=2, heads=heads, dtype=dtype, seed=40 + dh, prox_lambda=lam, massive_frac=0.01)
+    run_stream(B, w, 2, check_R=lam > 0)
+    cal = B.Calibrator(w.d, heads, dtype, I.initial_rotation(w), max_tokens=T, prox_lambda=lam)
+    try:
+        X = B.to_device(I.batch(w, 0, T), dtype)
+        cal.step_batch(X)
+        cal.update_rotation()
+        R, _, _ = cal.get_state(want_M=False)
+        Y = cal.rotate(X).double().cpu()
+        Rop = torch.from_numpy(R).to(X.dtype).double()
+        x = X.double().cpu().reshape(T, heads, dh)
+        ref = torch.stack([x[:, h] @ Rop[h] for h in range(heads)], dim=1).reshape(T, w.d)
+        # per row: bf16 rounds once; fp32 products from 24-bit splits (sums of dh terms of up to the row's norm)
+        tol = (2.0 ** -8 if dtype == "bf16" else 2e-6) * x.reshape(T, -1).norm(dim=1, keepdim=True)
+        assert bool(((Y - ref).abs() <= tol).all())
+    finally:
+        cal.close()
