@@ -71,6 +71,7 @@ struct conqur_ctx {
   float *row_sse = nullptr, *row_en = nullptr;
   double* qsum = nullptr;      // [2]
   // polar workspaces
+  float* Rprev = nullptr;                            // heads narrower than 128: the rotation the running update started from
   float* PX = nullptr;                               // polar iterate, fp32 [heads][dh][dh]
   bf16_bits *PXn[2] = {nullptr, nullptr};            // iterate as bf16 split planes [3][heads][dh][dh], ping-pong
   bf16_bits *PXt[2] = {nullptr, nullptr};            // ... transposed
@@ -268,6 +269,7 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   ctx->row_en = ctx->row_sse + tmax;
   A(dev_alloc(ctx, &ctx->qsum, (size_t)2));
   A(dev_alloc(ctx, &ctx->PX, blk));
+  if (dh < 128 && cfg->polar_precision == 0) A(dev_alloc(ctx, &ctx->Rprev, blk));   // (read only by updates that take the one-launch path)
   for (int b = 0; b < 2; ++b) {
     A(dev_alloc(ctx, &ctx->PXn[b], 3 * blk));
     A(dev_alloc(ctx, &ctx->PXt[b], 3 * blk));
@@ -645,6 +647,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   if (use_hstart) {
     hstart.M = ctx->M; hstart.R = ctx->R; hstart.fro2_out = ctx->fro2; hstart.lambda = ctx->cfg.prox_lambda;
     hstart.L = ctx->L; hstart.ldot = ctx->ldot;
+    hstart.R_keep = ctx->Rprev;
     hstart.rop_dot = ctx->head_fused ? 0 : 1; hstart.round_bf16 = ctx->f32 ? 0 : 1;
   }
 
@@ -879,8 +882,9 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   };
   // Outcome of a closing step taken inside the main phase's launch (narrow heads): accepted if every head took it
   // and the bound from ||D^2||_F (see below) is within the tolerance; otherwise the general closing steps continue from
-  // the hand-over state, which that launch wrote as well.  (R of the heads that did take the step is overwritten already:
-  // should the rare nudge below follow, it moves those heads towards their new rotation instead of the previous one.)
+  // the hand-over state, which that launch wrote as well.  (R of the heads that did take the step is overwritten already; for
+  // the rare nudge below the previous rotation is kept aside, except with heads of width 128: there the nudge moves the heads
+  // that took the step towards their new rotation.)
   auto fused_outcome = [&]() -> conqur_status {
     HIP_TRY(hipMemcpyAsync(hist + (size_t)fused_slot * h, ctx->resid + (size_t)fused_slot * h, 2 * h * sizeof(double),
                            hipMemcpyDeviceToHost, s));
@@ -942,7 +946,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       // directions every completion is optimal and this one is nearest to R_prev --
       // and run the main phase again from the nudge's scale.
       const double kappa = np_main == 1 ? 1.0 / 64.0 : 1.0 / 256.0;
-      HIP_TRY(launch_axpy(ctx->PX, ctx->R, plane, (float)kappa, s));
+      HIP_TRY(launch_axpy(ctx->PX, ctx->Rprev ? ctx->Rprev : ctx->R, plane, (float)kappa, s));
       ++kicks;
       st = main_phase(0.25 * kappa / std::sqrt((double)dh), false);
       if (st != CONQUR_OK) return st;

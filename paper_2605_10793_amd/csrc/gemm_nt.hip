@@ -427,6 +427,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   // holds a quarter of the block at a time, the 4096^2 M of the accumulate GEMM took 10 us instead of 6).  add: the array at
   // radd (same addressing) is added first, its loads one row of accumulators ahead of their use.
   [[maybe_unused]] auto store_f32 = [&](__amdgpu_buffer_rsrc_t r, auto add, __amdgpu_buffer_rsrc_t radd, auto&& val) {
+#pragma clang fp contract(off)   // the scaled product is rounded before the sum, as a further batch always was
     constexpr bool ADD = decltype(add)::value;
     [[maybe_unused]] f32x4 more[2][ADD ? TN : 1];
     auto fetch = [&](int i) {
@@ -679,12 +680,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
         __builtin_amdgcn_sched_barrier(0);
       }
       auto val = [&](int i, int j) {
-        f32x4 w = again(g.coef_g) * acc[i][j];
-        if constexpr (DIAG) {
-          const float ci = again(g.coef_i);
+        const float cg = again(g.coef_g), ci = again(g.coef_i);
+        f32x4 w;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) w[r] += ci * eye(i, j, r);
-        }
+        for (int r = 0; r < 4; ++r) w[r] = DIAG ? fmaf(ci, eye(i, j, r), cg * acc[i][j][r]) : cg * acc[i][j][r];
         return w;
       };
       auto plane = [&](auto p) {
@@ -736,10 +735,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
       for (int j = 0; j < TN; ++j) {
         const uint32_t off = tr_off(j, 16 * i);
         const uint2 d0 = ld64(rA0, off), d1 = ld64(rA1, off);
-        acc[i][j][0] = g.coef_g * acc[i][j][0] + __uint_as_float(d0.x << 16) + __uint_as_float(d1.x << 16);
-        acc[i][j][1] = g.coef_g * acc[i][j][1] + __uint_as_float(d0.x & 0xffff0000u) + __uint_as_float(d1.x & 0xffff0000u);
-        acc[i][j][2] = g.coef_g * acc[i][j][2] + __uint_as_float(d0.y << 16) + __uint_as_float(d1.y << 16);
-        acc[i][j][3] = g.coef_g * acc[i][j][3] + __uint_as_float(d0.y & 0xffff0000u) + __uint_as_float(d1.y & 0xffff0000u);
+        acc[i][j][0] = fmaf(g.coef_g, acc[i][j][0], __uint_as_float(d0.x << 16)) + __uint_as_float(d1.x << 16);
+        acc[i][j][1] = fmaf(g.coef_g, acc[i][j][1], __uint_as_float(d0.x & 0xffff0000u)) + __uint_as_float(d1.x & 0xffff0000u);
+        acc[i][j][2] = fmaf(g.coef_g, acc[i][j][2], __uint_as_float(d0.y << 16)) + __uint_as_float(d1.y << 16);
+        acc[i][j][3] = fmaf(g.coef_g, acc[i][j][3], __uint_as_float(d0.y & 0xffff0000u)) + __uint_as_float(d1.y & 0xffff0000u);
       }
       __builtin_amdgcn_sched_barrier(0);
     }

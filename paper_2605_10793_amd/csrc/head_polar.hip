@@ -97,7 +97,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN) k_head_polar(const bf16_bits* 
     each([&](int i, int j, int m0, int n) {
       float v[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = cg * acc[i][j][r] + ((m0 + r == n) ? ci : 0.0f);
+      for (int r = 0; r < 4; ++r) {
+        // (below 128 rounded as the general path's epilogue rounds it, the product first)
+        const float eye = m0 + r == n ? 1.0f : 0.0f;
+        v[r] = N == 128 ? fmaf(cg, acc[i][j][r], eye * ci) : fmaf(ci, eye, cg * acc[i][j][r]);
+      }
       *reinterpret_cast<uint2*>(dst + tr_addr(m0, n)) = make_uint2(f32x2_to_f16x2(v[0], v[1]), f32x2_to_f16x2(v[2], v[3]));
     });
   };
@@ -142,6 +146,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) k_head_polar(const bf16_bits* 
         const int64_t off = hoff + (int64_t)(m0 + r) * dh + n;
         acc[i][j][r] = st.M[off];
         prev[i][j][r] = st.R[off];
+        if (st.R_keep) st.R_keep[off] = prev[i][j][r];
       }
     });
     if (st.nparts > 0) {

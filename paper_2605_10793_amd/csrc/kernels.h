@@ -115,6 +115,7 @@ struct HeadPolarStart {
   double* ldot;
   int rop_dot;
   int round_bf16;
+  float* R_keep;       // non-null: a copy of R, which the closing step may replace in the same launch
 };
 hipError_t launch_head_polar(const bf16_bits* Xn0, const bf16_bits* Xt0, int heads, int dh, const PolarSchedule& sched, float* X32,
                              bf16_bits* Pn, bf16_bits* Pt, const HeadPolarClose* close, const HeadPolarStart* start, hipStream_t s);
