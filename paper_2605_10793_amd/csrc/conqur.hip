@@ -172,6 +172,20 @@ void rotate_args(conqur_ctx* c, const void* X, int64_t T, int64_t stride, GemmAr
   }
 }
 
+// Y = X R_op into rows of pitch ldy (activation dtype): a few rows in a kernel of their own, more through the tiled GEMM.
+hipError_t rotate_into(conqur_ctx* c, const void* X, int64_t T, int64_t stride, void* Y, int64_t ldy) {
+  if (rotate_rows_fits(c->f32, T, c->dh))
+    return launch_rotate_rows(X, c->f32, T, stride, c->RopT, (int64_t)c->heads * c->dh * c->dh, c->heads, c->dh, Y, ldy, c->stream);
+  if (c->f32) {
+    hipError_t e = launch_split_rows(reinterpret_cast<const float*>(X), T, stride, c->d, c->Xs, c->tmax * c->d, c->stream);
+    if (e != hipSuccess) return e;
+  }
+  GemmArgs g;
+  rotate_args(c, X, T, stride, &g);
+  g.C = Y; g.ldc = ldy; g.batchC = c->dh; g.c_is_f32 = c->f32;
+  return launch_gemm_nt(g, EPI_ACT, c->heads, c->stream);
+}
+
 conqur_status refresh_operand(conqur_ctx* ctx) {
   const int64_t plane = (int64_t)ctx->heads * ctx->dh * ctx->dh;
   HIP_TRY(launch_pack(ctx->R, ctx->heads, ctx->dh, ctx->dh, ctx->np, nullptr, ctx->RopT, plane, ctx->stream));
@@ -532,14 +546,12 @@ conqur_status conqur_step_batch_quant(conqur_ctx* ctx, const void* X, uint64_t T
   hipStream_t s = ctx->stream;
   {
     StageTimer whole(ctx, ST_STEP, 1);
-    if (ctx->head_fused) {
-      // heads of width 128: the fused step kernel keeps Y on the compute unit; the rows are rotated once more for the quantiser
-      st = step_fused(ctx, X, T, stride, 0, ctx->heads);
+    if (ctx->head_fused || rotate_rows_fits(ctx->f32, T, ctx->dh)) {
+      // heads of width 128: the fused step kernel keeps Y on the compute unit; the rows are rotated once more for the quantiser.
+      // A few rows: likewise, so that they are summed in the order conqur_rotate_quant sums them in.
+      st = ctx->head_fused ? step_fused(ctx, X, T, stride, 0, ctx->heads) : step_general(ctx, X, T, stride, false);
       if (st != CONQUR_OK) return st;
-      GemmArgs g;
-      rotate_args(ctx, X, T, stride, &g);
-      g.C = ctx->Y; g.ldc = ctx->d; g.batchC = ctx->dh; g.c_is_f32 = ctx->f32;
-      HIP_TRY(launch_gemm_nt(g, EPI_ACT, ctx->heads, s));
+      HIP_TRY(rotate_into(ctx, X, T, stride, ctx->Y, ctx->d));
     } else {
       st = step_general(ctx, X, T, stride, true);   // one rotate GEMM: corner signs and Y
       if (st != CONQUR_OK) return st;
@@ -1074,12 +1086,7 @@ static conqur_status quant_error_impl(conqur_ctx* ctx, const void* X, uint64_t T
   StageTimer whole(ctx, ST_QUANT, 1);
   {
     StageTimer tm(ctx, ST_QROT);
-    if (ctx->f32)
-      HIP_TRY(launch_split_rows(reinterpret_cast<const float*>(X), T, stride, ctx->d, ctx->Xs, ctx->tmax * ctx->d, s));
-    GemmArgs g;
-    rotate_args(ctx, X, T, stride, &g);
-    g.C = ctx->Y; g.ldc = ctx->d; g.batchC = ctx->dh; g.c_is_f32 = ctx->f32;
-    HIP_TRY(launch_gemm_nt(g, EPI_ACT, ctx->heads, s));
+    HIP_TRY(rotate_into(ctx, X, T, stride, ctx->Y, ctx->d));
   }
   {
     StageTimer tm(ctx, ST_QERR);
@@ -1124,12 +1131,7 @@ conqur_status conqur_rotate(conqur_ctx* ctx, const void* X, uint64_t T64, uint64
   HIP_TRY(hipSetDevice(ctx->cfg.device));
   const int64_t T = (int64_t)T64, stride = (int64_t)stride64;
   hipStream_t s = ctx->stream;
-  if (ctx->f32)
-    HIP_TRY(launch_split_rows(reinterpret_cast<const float*>(X), T, stride, ctx->d, ctx->Xs, ctx->tmax * ctx->d, s));
-  GemmArgs g;
-  rotate_args(ctx, X, T, stride, &g);
-  g.C = Y; g.ldc = (int64_t)y_stride64; g.batchC = ctx->dh; g.c_is_f32 = ctx->f32;
-  HIP_TRY(launch_gemm_nt(g, EPI_ACT, ctx->heads, s));
+  HIP_TRY(rotate_into(ctx, X, T, stride, Y, (int64_t)y_stride64));
   return CONQUR_OK;
 }
 
@@ -1151,12 +1153,7 @@ conqur_status conqur_rotate_quant(conqur_ctx* ctx, const void* X, uint64_t T64, 
   StageTimer whole(ctx, ST_QUANT, 1);   // the stages are timed in the slots of conqur_quant_error
   {
     StageTimer tm(ctx, ST_QROT);
-    if (ctx->f32)
-      HIP_TRY(launch_split_rows(reinterpret_cast<const float*>(X), T, stride, ctx->d, ctx->Xs, ctx->tmax * ctx->d, s));
-    GemmArgs g;
-    rotate_args(ctx, X, T, stride, &g);
-    g.C = ctx->Y; g.ldc = ctx->d; g.batchC = ctx->dh; g.c_is_f32 = ctx->f32;
-    HIP_TRY(launch_gemm_nt(g, EPI_ACT, ctx->heads, s));
+    HIP_TRY(rotate_into(ctx, X, T, stride, ctx->Y, ctx->d));
   }
   {
     StageTimer tm(ctx, ST_QERR);
@@ -1173,12 +1170,7 @@ conqur_status conqur_row_diagnostics(conqur_ctx* ctx, const void* X, uint64_t T6
   HIP_TRY(hipSetDevice(ctx->cfg.device));
   const int64_t T = (int64_t)T64, stride = (int64_t)stride64;
   hipStream_t s = ctx->stream;
-  if (ctx->f32)
-    HIP_TRY(launch_split_rows(reinterpret_cast<const float*>(X), T, stride, ctx->d, ctx->Xs, ctx->tmax * ctx->d, s));
-  GemmArgs g;
-  rotate_args(ctx, X, T, stride, &g);
-  g.C = ctx->Y; g.ldc = ctx->d; g.batchC = ctx->dh; g.c_is_f32 = ctx->f32;
-  HIP_TRY(launch_gemm_nt(g, EPI_ACT, ctx->heads, s));
+  HIP_TRY(rotate_into(ctx, X, T, stride, ctx->Y, ctx->d));
   HIP_TRY(launch_row_diag(ctx->Y, ctx->f32, T, ctx->d, ctx->d, ctx->row_sse, ctx->row_en, s));
   if (pr_host) HIP_TRY(hipMemcpyAsync(pr_host, ctx->row_sse, T * sizeof(float), hipMemcpyDeviceToHost, s));
   if (rho_host) HIP_TRY(hipMemcpyAsync(rho_host, ctx->row_en, T * sizeof(float), hipMemcpyDeviceToHost, s));

@@ -25,6 +25,12 @@ hipError_t launch_transpose_scale(const void* X, int x_is_f32, int64_t T, int64_
 hipError_t launch_split_rows(const float* X, int64_t T, int64_t stride, int d, bf16_bits* Xs, int64_t plane,
                              hipStream_t s);
 
+// Y = X R_op per head for the few rows rotate_rows_fits() admits (rotate_rows.hip): X [T][stride] and Y [T][ldy] in bf16 or fp32,
+// RopT the rotate operand [heads][dh][dh] (R^T; three split planes, `plane` elements apart, for fp32).
+bool rotate_rows_fits(int x_is_f32, int64_t T, int dh);
+hipError_t launch_rotate_rows(const void* X, int x_is_f32, int64_t T, int64_t stride, const bf16_bits* RopT, int64_t plane, int heads,
+                              int dh, void* Y, int64_t ldy, hipStream_t s);
+
 // Split an fp32 matrix batch [batch][rows][cols] into np bf16 planes, in natural
 // layout (outN[p][b][r][c]) and/or transposed (outT[p][b][c][r]); either may be null.
 // out_f16 (np = 1 only): the plane holds the values rounded to fp16 instead of bf16.

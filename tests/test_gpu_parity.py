@@ -1062,3 +1062,41 @@ def test_narrow_heads(B, heads, dh, T, dtype, lam):
         assert bool(((Y - ref).abs() <= tol).all())
     finally:
         cal.close()
+
+
+@pytest.mark.parametrize("d,heads,dtype", [(4096, 1, "bf16"), (1104, 1, "bf16"), (16, 1, "f32"), (48 * 5, 5, "bf16"), (128 * 4, 4, "bf16"), (1040, 1, "f32"),
+                                           (8192, 1, "bf16")])
+def test_rotate_few_rows(B, d, heads, dtype):
+    """The kernel for a few rows at the ends of its range (1, 16, 17, 32 rows and the first count beyond; a width that is half
+    a K chunk, several heads, rows of a pitch of their own), against a plain product; and the three calls that rotate the same
+    rows (rotate, rotate_quant, step_batch_quant) agree to the bit with one another."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d)
+    dh = d // heads
+    R0 = (torch.randn((heads, dh, dh), generator=g, device="cuda:0") / math.sqrt(dh)).cpu().numpy()
+    cal = B.Calibrator(d, heads, dtype, R0, max_tokens=64)
+    try:
+        for T in (1, 5, 16, 17, 32, 33):
+            wide = torch.randn((T, d + 8), generator=g, device="cuda:0")
+            wide = wide.to(torch.bfloat16) if dtype == "bf16" else wide
+            X = wide[:, :d]
+            Rop = torch.from_numpy(R0).to("cuda:0").to(X.dtype).double()
+            ref = torch.stack([X[:, h * dh:(h + 1) * dh].double() @ Rop[h] for h in range(heads)], dim=1).reshape(T, d)
+            Yw = torch.full((T, d + 3), 7.0, dtype=X.dtype, device=X.device)
+            cal.rotate(X, Yw)
+            torch.cuda.synchronize()
+            # one rounding (2^-9 relative) resp. fp32 sums of dh products of 24-bit splits
+            tol = 2.0 ** -8 if dtype == "bf16" else 2e-6
+            assert bool(((Yw[:, :d].double() - ref).abs() <= tol * ref.abs().max()).all()), T
+            assert bool((Yw[:, d:] == 7.0).all())
+            q1 = cal.rotate_quant(X, 4, True, 0.9)
+            q2 = cal.step_batch_quant(X, 4, True, 0.9)
+            out = torch.empty(2, dtype=torch.float64, device=X.device)
+            B.score_rows_static(cal.rotate(X), out, 4, False)
+            sse, en = cal.quant_error(X, 4)
+            torch.cuda.synchronize()
+            assert torch.equal(q1, q2), T
+            assert abs(float(out[0]) - sse) <= 1e-12 * sse and abs(float(out[1]) - en) <= 1e-12 * en
+    finally:
+        cal.close()
