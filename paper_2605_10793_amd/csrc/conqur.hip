@@ -291,7 +291,7 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   A(dev_alloc(ctx, &ctx->PW, 3 * blk));
   A(dev_alloc(ctx, &ctx->PW2, 3 * blk));
   A(dev_alloc(ctx, &ctx->resid, (size_t)kResidSlots * ctx->heads));
-  ctx->resid_parts = gemm_num_partials((int)dh, (int)dh, ctx->heads, 1);   // every launch that leaves residual partials is a symmetric one
+  ctx->resid_parts = gemm_num_partials((int)dh, ctx->heads, 1);   // every launch that leaves residual partials is a symmetric one
   A(dev_alloc(ctx, &ctx->resid_part, (size_t)ctx->resid_parts * ctx->heads));
   ctx->head_fused = ctx->dh == 128 && !ctx->f32;
   if (ctx->head_fused) {
@@ -301,8 +301,8 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   // One rotation of a width whose dh x dh output gives the accumulate GEMM only a few tiles (dh <= 512: at most 64 of the
   // chip's 256 compute units, each with the whole token range to itself): the token range is split into shares instead.
   if (!ctx->head_fused && ctx->heads == 1 && dh <= 512 && (blk & 1023) == 0) {
-    const int tiles = gemm_num_workgroups((int)dh, (int)dh, 1);
-    ctx->ksplit_max = std::max(1, std::min(16, 256 / std::max(tiles, 1)));
+    const int tiles = (int)((dh + 63) / 64 * ((dh + 63) / 64));   // of 64 x 64
+    ctx->ksplit_max = std::max(1, std::min(16, 256 / tiles));
     if (ctx->ksplit_max > 1) A(dev_alloc(ctx, &ctx->Mpart, (size_t)ctx->ksplit_max * blk));
     else ctx->ksplit_max = 0;
   }
@@ -471,7 +471,7 @@ static conqur_status step_general(conqur_ctx* ctx, const void* X, int64_t T, int
     g.C = ctx->St; g.ldc = ctx->pitch; g.batchC = (int64_t)ctx->dh * ctx->pitch;
     g.st_rows_valid = ctx->pitch;
     g.sign_f16 = ctx->f32 ? 0 : 1;   // the accumulate GEMM runs in fp16 for bf16 activations
-    const int wg = gemm_num_workgroups(g.M, g.N, ctx->heads);
+    const int wg = gemm_num_workgroups(g.M, g.N, g.K, ctx->heads);
     ctx->clk_wg[0] = (ctx->timing >= 2 && wg <= kClkMaxWorkgroups) ? wg : 0;
     g.clk = ctx->clk_wg[0] ? ctx->clk[0] : nullptr;
     if (keep_y) { g.Yact = ctx->Y; g.ldy = ctx->d; g.batchY = ctx->dh; g.c_is_f32 = ctx->f32; }
@@ -507,7 +507,7 @@ static conqur_status step_general(conqur_ctx* ctx, const void* X, int64_t T, int
       HIP_TRY(launch_gemm_nt(g, EPI_F32, shares, s));
       HIP_TRY(launch_sum_shares(ctx->Mpart, shares, (int64_t)ctx->dh * ctx->dh, ctx->M, ctx->m_empty ? 0 : 1, s));
     } else {
-      const int wg = gemm_num_workgroups(g.M, g.N, ctx->heads);
+      const int wg = gemm_num_workgroups(g.M, g.N, g.K, ctx->heads);
       ctx->clk_wg[1] = (ctx->timing >= 2 && wg <= kClkMaxWorkgroups) ? wg : 0;
       g.clk = ctx->clk_wg[1] ? ctx->clk[1] : nullptr;
       HIP_TRY(launch_gemm_nt(g, EPI_F32, ctx->heads, s));

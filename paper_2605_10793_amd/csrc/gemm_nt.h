@@ -93,12 +93,12 @@ hipError_t launch_gemm_nt(const GemmArgs& args, GemmEpilogue epi, int batch, hip
 // x 2 (a symmetric launch runs the tiles on and above the diagonal only).
 double gemm_issued_flop(const GemmArgs& args, GemmEpilogue epi, int batch);
 
-// Number of workgroups launch_gemm_nt uses for an M x N problem with `batch` entries (size of the clock probe / 4).
-int gemm_num_workgroups(int M, int N, int batch);
+// Number of workgroups launch_gemm_nt uses for an M x N x K problem with `batch` entries (size of the clock probe / 4).
+int gemm_num_workgroups(int M, int N, int K, int batch);
 
-// Per-batch-entry count of the partial sums the EPI_GRAMW / EPI_FRO2 epilogues write for an M x N problem launched
-// with the given `symmetric` flag (the flag can select another tile).
-int gemm_num_partials(int M, int N, int batch, int symmetric);
+// Per-batch-entry count of the partial sums the EPI_GRAMW / EPI_SQUARE / EPI_FRO2 epilogues write for an M x M x M problem (any
+// number of segments) launched with the given `symmetric` flag (the flag can select another tile).
+int gemm_num_partials(int M, int batch, int symmetric);
 
 
 }  // namespace conqur

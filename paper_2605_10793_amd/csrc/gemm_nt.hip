@@ -854,39 +854,50 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   }
 }
 
-struct Tile { int bm, bn, wgm, wgn; float eff; };
-constexpr Tile kTiles[] = {{256, 256, 2, 2, 1.0f}, {256, 128, 2, 2, 0.85f}, {128, 128, 2, 2, 0.7f}, {64, 64, 2, 2, 0.35f},
-                           {192, 192, 2, 2, 0.88f}};   // 192: fills the chip exactly at d = 3072
+// Tiles, with what a workgroup that has its CU to itself takes: t0 us outside the main loop and ts per K step of 64 (fits to
+// rotate, accumulate and polar launches at 16 .. 10500 tokens and widths 64 .. 8192).  192: fills the chip exactly at 3072.
+struct Tile { int bm, bn, wgm, wgn; float t0, ts; };
+constexpr Tile kTiles[] = {{256, 256, 2, 2, 10.0f, 1.30f}, {256, 128, 2, 2, 8.5f, 0.72f}, {128, 128, 2, 2, 6.5f, 0.42f}, {64, 64, 2, 2, 4.5f, 0.26f},
+                           {192, 192, 2, 2, 8.5f, 0.75f}};
 constexpr int kNumTiles = 5;
 
-int pick_tile(int M, int N, int batch) {
+// Expected time of `tiles` workgroups of tile t with K elements each.  The large tiles fill a CU's LDS: whole rounds of 256.
+// Three 64 x 64 workgroups share one: up to 768 start at once, and a step of n sharing a CU takes 0.26 + 0.22 (n - 1) us.
+// Against the rule before (rounds x area / efficiency, without K): accumulate of 1024 tokens at d = 3072 36.6 -> 29.6 us
+// (192 instead of 256 wide), of 512 at d = 2048 18.0 -> 14.4; 1500 tokens of d = 1104 rotated for the statistics 19.1 -> 17.1
+// and the update there 352 -> 330 (64 instead of 128 wide); 32 heads of width 64, 2048 tokens 20.5 -> 16.6.
+double tile_time(int t, int64_t tiles, int K) {
+  const double steps = (K + BK - 1) / BK;
+  const int64_t rounds = (tiles + 255) / 256;
+  if (t == 3) return kTiles[t].t0 * (tiles > 768 ? tiles / 768.0 : 1.0) + steps * (kTiles[t].ts + 0.22 * (double)(rounds - 1));
+  return (double)rounds * (kTiles[t].t0 + steps * kTiles[t].ts);
+}
+
+int pick_tile(int M, int N, int K, int batch) {
   int best = 0;
-  double best_cost = 1e300;
+  double best_time = 1e300;
   for (int t = 0; t < kNumTiles; ++t) {
     const int64_t tiles = (int64_t)((M + kTiles[t].bm - 1) / kTiles[t].bm) * ((N + kTiles[t].bn - 1) / kTiles[t].bn) * batch;
-    const int64_t waves = (tiles + 255) / 256;
-    const double cost = (double)waves * kTiles[t].bm * kTiles[t].bn / kTiles[t].eff;
-    if (cost < best_cost) { best_cost = cost; best = t; }
+    const double time = tile_time(t, tiles, K);
+    if (time < best_time) { best_time = time; best = t; }
   }
   return best;
 }
 
 constexpr int kSymMinTiles = 8;   // tiles per side from which the mirrored form is used
 
-// Tile for a symmetric product (only the t (t + 1) / 2 tiles on and above the diagonal run): the square tile with the
-// least rounds x tile area / efficiency, or -1 if no square tile gives at least kSymMinTiles per side.  Counting the
-// tiles that really run matters: at 4096 the 256 x 256 tile leaves 136 workgroups on 256 compute units, the 192 x 192
-// tile 253 (measured 80 against 96 us for a Gram matrix); at 8192 it is 946 tiles in 4 rounds against 528 in 3.
+// Tile for a symmetric product (M x M x M; only the t (t + 1) / 2 tiles on and above the diagonal run), or -1 if no square
+// tile gives at least kSymMinTiles per side.  Counting the tiles that really run matters: at 4096 the 256 x 256 tile leaves 136
+// workgroups on 256 compute units, the 192 x 192 tile 253.
 int pick_tile_sym(int M, int batch) {
   int best = -1;
-  double best_cost = 1e300;
+  double best_time = 1e300;
   for (int t = 0; t < kNumTiles; ++t) {
     if (kTiles[t].bm != kTiles[t].bn) continue;
     const int64_t side = (M + kTiles[t].bm - 1) / kTiles[t].bm;
     if (side < kSymMinTiles) continue;
-    const int64_t rounds = (side * (side + 1) / 2 * batch + 255) / 256;
-    const double cost = (double)rounds * kTiles[t].bm * kTiles[t].bn / kTiles[t].eff;
-    if (cost < best_cost) { best_cost = cost; best = t; }
+    const double time = tile_time(t, side * (side + 1) / 2 * batch, M);
+    if (time < best_time) { best_time = time; best = t; }
   }
   return best;
 }
@@ -920,7 +931,7 @@ hipError_t launch_epi(const GemmArgs& a, int batch, hipStream_t stream) {
       }
     }
   }
-  switch (pick_tile(a.M, a.N, batch)) {
+  switch (pick_tile(a.M, a.N, a.K, batch)) {
     // LDS stages: as many 64-deep tiles as fit (two of 64 KiB for 256 x 256; smaller tiles take a third, which
     // puts two K steps instead of one between a load's issue and its use)
     case 0: return launch_one<256, 256, 2, 2, 2, EPI, F16>(a, batch, stream);
@@ -933,9 +944,10 @@ hipError_t launch_epi(const GemmArgs& a, int batch, hipStream_t stream) {
 
 }  // namespace
 
-int gemm_num_partials(int M, int N, int batch, int symmetric) {
-  int t = pick_tile(M, N, batch);
-  if (symmetric && M == N) {
+int gemm_num_partials(int M, int batch, int symmetric) {
+  const int N = M;
+  int t = pick_tile(M, N, M, batch);
+  if (symmetric) {
     const int ts = pick_tile_sym(M, batch);
     if (ts >= 0) t = ts;
   }
@@ -944,7 +956,7 @@ int gemm_num_partials(int M, int N, int batch, int symmetric) {
 }
 
 double gemm_issued_flop(const GemmArgs& a, GemmEpilogue epi, int batch) {
-  int t = pick_tile(a.M, a.N, batch);
+  int t = pick_tile(a.M, a.N, a.K, batch);
   bool sym = false;
   if (a.symmetric && (epi == EPI_GRAMW || epi == EPI_SQUARE || epi == EPI_FRO2)) {
     const int ts = pick_tile_sym(a.M, batch);
@@ -956,8 +968,8 @@ double gemm_issued_flop(const GemmArgs& a, GemmEpilogue epi, int batch) {
   return 2.0 * (double)tiles * u.bm * u.bn * (double)a.K * a.nseg * batch;
 }
 
-int gemm_num_workgroups(int M, int N, int batch) {
-  const Tile& t = kTiles[pick_tile(M, N, batch)];
+int gemm_num_workgroups(int M, int N, int K, int batch) {
+  const Tile& t = kTiles[pick_tile(M, N, K, batch)];
   return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * batch;
 }
 
