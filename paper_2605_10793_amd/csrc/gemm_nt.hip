@@ -42,11 +42,17 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | (N & 15) | ((N >> 4) << 14));
 }
 
+// The same, and every LDS read this wavefront has issued has returned (lgkmcnt(0)).
+template <int N>
+__device__ __forceinline__ void wait_vmcnt_and_lds() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt(0x0070 | (N & 15) | ((N >> 4) << 14));
+}
+
 // Workgroup barrier without the release/acquire fence of __syncthreads(): the fence
 // would drain every outstanding LDS-direct load (vmcnt(0)) and serialise the
-// pipeline.  Ordering here is explicit: each wave waits (vmcnt) for its own loads of
-// the tile that is consumed next, and its LDS reads of the current tile have
-// returned before its last MFMA of the step could issue.  The "memory" clobber keeps
+// pipeline.  Ordering here is explicit: each wave waits for its own loads of the tile that
+// is consumed next (vmcnt) and for its LDS reads of the current one (lgkmcnt).  The "memory" clobber keeps
 // the compiler from moving LDS accesses across the barrier.
 __device__ __forceinline__ void pipeline_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
@@ -276,8 +282,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
 #pragma unroll
     for (int m = 0; m < HALF; ++m) mfma(1, m);
     __builtin_amdgcn_sched_barrier(0);
-    // tiles up to it+NSTAGE-1 have been issued; all but the newest NSTAGE-2 have landed => tile it+1 is in LDS
-    wait_vmcnt<(NSTAGE - 2) * LPT>();
+    // tiles up to it+NSTAGE-1 have been issued; all but the newest NSTAGE-2 have landed => tile it+1 is in LDS.  And this
+    // wavefront's last fragment reads of the current tile have returned: behind the barrier the other wavefronts refill its
+    // stage, and a load that fetches nothing (padding steps, the K tail) writes its zeros within the time a read takes.  (The
+    // small tiles issue their last read 2 MFMAs ahead of this point; the large ones wait for nothing here.)
+    wait_vmcnt_and_lds<(NSTAGE - 2) * LPT>();
     pipeline_barrier();
     const unsigned char* sn = smem + next_stage * STAGE;
 #pragma unroll
