@@ -1100,3 +1100,63 @@ def test_rotate_few_rows(B, d, heads, dtype):
             assert abs(float(out[0]) - sse) <= 1e-12 * sse and abs(float(out[1]) - en) <= 1e-12 * en
     finally:
         cal.close()
+
+
+@pytest.mark.parametrize("d,dtype", [(16, "f32"), (400, "bf16"), (4096, "bf16"), (9008, "f32")])
+def test_quantiser_rows_at_the_edges(B, d, dtype):
+    """Rows on which the quantisers' clamps and zero points could go wrong, one per call: far from zero in steps (both sides of
+    the line where the zero-point kernel keeps its shifted form), one-sided, constant, zero, tiny, with a NaN; symmetric and
+    zero-point, against the definition in fp32 codes.  Then the emitted rows where a row's scale is infinite."""
+    import torch
+    g = torch.Generator(device="cpu")
+    g.manual_seed(d)
+    z = torch.randn((d,), generator=g)
+    rows = [z, z + 4.0, 1000.0 + z, 1e6 + z, 1e6 + 1e-1 * z, 3000.0 + 1e-3 * z, -1e5 + 1e-2 * z, z.abs(), torch.full((d,), 2.5), torch.zeros(d), z * 1e-30]   # (1 / scale stays finite in fp32)
+    bad = z.clone()
+    bad[d // 2] = float("nan")
+    rows.append(bad)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    out = torch.empty(2, dtype=torch.float64, device="cuda:0")
+    f32 = np.float32
+    for k, r in enumerate(rows):
+        y = r.to(tdt)
+        f = y.float().numpy()
+        for zp, clip, bits in ((False, 1.0, 4), (True, 1.0, 4), (True, 0.9, 4), (True, 0.5, 8), (False, 1.0, 8)):
+            B.score_rows_static(y.to("cuda:0")[None, :].contiguous(), out, bits, zp, clip)
+            sse = float(out[0])
+            if k == len(rows) - 1:
+                assert math.isnan(sse)
+                continue
+            with np.errstate(all="ignore"):
+                if zp:
+                    # the range hi - lo in one rounding (the kernel's fused multiply-add): far from zero the scale depends on it
+                    qmax, lo = f32(2 ** bits - 1), f32(clip) * f.min()
+                    delta = f32(float(f32(clip)) * float(f.max()) - float(lo)) / qmax
+                    if delta > 0:
+                        zeta = -np.rint(lo / delta)
+                        code = np.clip(np.rint(f * (f32(1.0) / delta)) + zeta, f32(0), qmax) - zeta
+                        err = f.astype(np.float64) - float(delta) * code.astype(np.float64)
+                    else:
+                        err = f.astype(np.float64) - float(lo)
+                else:
+                    qmax = f32(2 ** (bits - 1) - 1)
+                    delta = f32(np.abs(f).max() / qmax)
+                    code = np.clip(np.rint(f * (f32(1.0) / delta)), -qmax, qmax) if delta > 0 else np.zeros_like(f)
+                    err = f.astype(np.float64) - float(delta) * code.astype(np.float64)
+            want = float((err.astype(f32).astype(np.float64) ** 2).sum())
+            # fp32 sums of d squares per row; the codes themselves agree (same fp32 steps)
+            assert abs(sse - want) <= 2e-5 * want + 1e-70, (k, zp, clip, bits, sse, want)
+    if d <= 4096:
+        w = I.small_workload(128, 4, dtype=dtype, seed=3)
+        cal = B.Calibrator(128, 1, dtype, np.eye(128, dtype=np.float32)[None], max_tokens=4)
+        try:
+            X = B.to_device(I.batch(w, 0, 4), dtype)
+            # An infinite value: the rotated row is infinite or NaN throughout (fp32, whose split planes turn it into NaN: all NaN,
+            # which leaves the scale 0), and every symmetric code is the clamp's lower end: -infinity, or -0 with scale 0.
+            X[1, 7] = float("inf")
+            q = cal.rotate_quant(X, 4, False, 1.0)
+            torch.cuda.synchronize()
+            assert bool((q[1] == (float("-inf") if dtype == "bf16" else 0.0)).all()) and bool(torch.signbit(q[1]).all())
+            assert bool(q[[0, 2, 3]].isfinite().all())
+        finally:
+            cal.close()
