@@ -216,7 +216,8 @@ conqur_status conqur_rotate_quant(conqur_ctx* ctx, const void* X_dev, uint64_t T
  * conqur_step_batch does, and Yq_dev receives Q(X R_op) exactly as conqur_rotate_quant writes it --
  * the quantised input of the layer behind the site.  Arguments and errors as for those two calls.
  * (Heads of width 128 with bf16 activations rotate twice internally: their fused step keeps the
- * rotated rows on the compute unit.)  Asynchronous on the context's stream.
+ * rotated rows on the compute unit.  So do calls of up to 32 rows, which conqur_rotate_quant sums in
+ * an order of its own.)  Asynchronous on the context's stream.
  */
 conqur_status conqur_step_batch_quant(conqur_ctx* ctx, const void* X_dev, uint64_t T, uint64_t row_stride_elems, uint32_t bits,
                                       uint32_t zero_point, float clip_ratio, void* Yq_dev, uint64_t yq_row_stride_elems);

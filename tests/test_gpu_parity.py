@@ -1144,8 +1144,9 @@ def test_quantiser_rows_at_the_edges(B, d, dtype):
                     code = np.clip(np.rint(f * (f32(1.0) / delta)), -qmax, qmax) if delta > 0 else np.zeros_like(f)
                     err = f.astype(np.float64) - float(delta) * code.astype(np.float64)
             want = float((err.astype(f32).astype(np.float64) ** 2).sum())
-            # fp32 sums of d squares per row; the codes themselves agree (same fp32 steps)
-            assert abs(sse - want) <= 2e-5 * want + 1e-70, (k, zp, clip, bits, sse, want)
+            # fp32 sums of d squares per row; the codes themselves agree (same fp32 steps).  Squares below fp32's smallest normal
+            # number may vanish: at most d of them.
+            assert abs(sse - want) <= 2e-5 * want + d * 1.2e-38, (k, zp, clip, bits, sse, want)
     if d <= 4096:
         w = I.small_workload(128, 4, dtype=dtype, seed=3)
         cal = B.Calibrator(128, 1, dtype, np.eye(128, dtype=np.float32)[None], max_tokens=4)
