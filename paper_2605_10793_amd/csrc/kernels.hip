@@ -501,7 +501,9 @@ __global__ void __launch_bounds__(256) k_quant_error(const void* __restrict__ Y,
         // (v_med3: the clamp in one instruction; a NaN takes the lower end, as max then min gives it)
         const float code = __builtin_amdgcn_fmed3f(rintf(f[e] * inv_delta), code_lo, code_hi);
         err = fmaf(-delta, code, f[e]);
-        qv[e] = delta * code;
+        // (level 0 of the zero-point quantiser is +0, as a code minus the zero point gives it: the sum with +0 takes the sign
+        // off the -0 that rounding a small negative value leaves)
+        qv[e] = ZP ? fmaf(delta, code, 0.0f) : delta * code;
       } else {
         const float code = fminf(fmaxf(rintf(f[e] * inv_delta) + zeta, 0.0f), qmax);
         err = delta > 0.0f ? fmaf(-delta, code - zeta, f[e]) : f[e] - lo;

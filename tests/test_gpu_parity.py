@@ -1161,3 +1161,30 @@ def test_quantiser_rows_at_the_edges(B, d, dtype):
             assert bool(q[[0, 2, 3]].isfinite().all())
         finally:
             cal.close()
+
+
+@pytest.mark.parametrize("d,T,dtype", [(64, 8, "bf16"), (336, 40, "f32"), (4096, 33, "bf16")])
+def test_zero_level_of_the_zero_point_quantiser_is_plus_zero(B, d, T, dtype):
+    """A level is the step times (code - zero point): an emitted value carries a minus sign where it is below zero and nowhere
+    else, also where a small negative value is rounded to level 0.  (The symmetric quantiser rounds such a value to -0.)"""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d)
+    X = torch.randn((T, d), generator=g, device="cuda:0").to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    X[1] = X[1].abs()          # zero point 0
+    X[2] = -X[2].abs()
+    X[0, :3] = -1e-3           # below half a step of every row's quantiser here
+    cal = B.Calibrator(d, 1, dtype, np.eye(d, dtype=np.float32)[None], max_tokens=T)
+    try:
+        for clip, bits in ((1.0, 4), (0.9, 4), (0.9, 8)):
+            for q in (cal.rotate_quant(X, bits, True, clip), cal.step_batch_quant(X, bits, True, clip)):
+                torch.cuda.synchronize()
+                zero = q == 0
+                assert bool((zero & (X < 0)).any())
+                assert not bool(torch.signbit(q[zero]).any())
+        q = cal.rotate_quant(X, 4, False, 1.0)
+        torch.cuda.synchronize()
+        zero = q == 0
+        assert torch.equal(torch.signbit(q[zero]), torch.signbit(X[zero]))
+    finally:
+        cal.close()
