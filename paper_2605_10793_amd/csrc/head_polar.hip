@@ -30,7 +30,9 @@ namespace conqur {
 namespace {
 
 // N: width of the square (a multiple of 32); WGM x WGN wavefronts own (N / WGM) x (N / WGN) blocks of every product.
-template <int N, int WGM, int WGN, bool CLOSE>
+// DH128: heads of width 128 themselves.  Their results keep the order of roundings they have always had; narrower heads, 112
+// in the square of 128 among them, have the general path's, bit for bit.
+template <int N, int WGM, int WGN, bool CLOSE, bool DH128>
 __global__ void __launch_bounds__(64 * WGM * WGN) k_head_polar(const bf16_bits* __restrict__ Xn0, const bf16_bits* __restrict__ Xt0,
                                                                const int dh, const PolarSchedule sched, float* __restrict__ X32,
                                                                bf16_bits* __restrict__ Pn, bf16_bits* __restrict__ Pt,
@@ -98,9 +100,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) k_head_polar(const bf16_bits* 
       float v[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        // (below 128 rounded as the general path's epilogue rounds it, the product first)
+        // (as the general path's epilogue rounds it, the product first; heads of width 128: the identity's part first)
         const float eye = m0 + r == n ? 1.0f : 0.0f;
-        v[r] = N == 128 ? fmaf(cg, acc[i][j][r], eye * ci) : fmaf(ci, eye, cg * acc[i][j][r]);
+        v[r] = DH128 ? fmaf(cg, acc[i][j][r], eye * ci) : fmaf(ci, eye, cg * acc[i][j][r]);
       }
       *reinterpret_cast<uint2*>(dst + tr_addr(m0, n)) = make_uint2(f32x2_to_f16x2(v[0], v[1]), f32x2_to_f16x2(v[2], v[3]));
     });
@@ -295,7 +297,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) k_head_polar(const bf16_bits* 
         p32 += sq[i][j][r] * sq[i][j][r];
       }
       part += (double)p32;
-      if constexpr (N == 128) {
+      if constexpr (DH128) {
         dm[i][j] += 1.5f * sq[i][j];
       } else {   // D as its two planes hold it: the rounding of the general path, bit for bit
         f32x4 d0 = dm[i][j];
@@ -313,8 +315,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) k_head_polar(const bf16_bits* 
     // iterate as the accumulators' start every MFMA would round at the iterate's magnitude, and the orthogonality of the
     // result was measured above the bound that holds for the general path's order.
     zero(sq);
-    product(kBF16, sXn, N == 128 ? sD0 : sD1, sq);   // (below 128 the general path's order, smaller plane first)
-    product(kBF16, sXn, N == 128 ? sD1 : sD0, sq);
+    product(kBF16, sXn, DH128 ? sD0 : sD1, sq);   // (the general path's order: smaller plane first)
+    product(kBF16, sXn, DH128 ? sD1 : sD0, sq);
     // R, the rotate operand R^T (bf16 planes, [n][m]: packed rows of the transposed matrix) and <R, M>
     part = 0.0;
     each([&](int i, int j, int m0, int n) {
@@ -340,12 +342,12 @@ __global__ void __launch_bounds__(64 * WGM * WGN) k_head_polar(const bf16_bits* 
   }
 }
 
-template <int N, int WGM, int WGN, bool CLOSE>
+template <int N, int WGM, int WGN, bool CLOSE, bool DH128>
 hipError_t launch_one(const bf16_bits* Xn0, const bf16_bits* Xt0, int heads, int dh, const PolarSchedule& sched, float* X32,
                       bf16_bits* Pn, bf16_bits* Pt, const HeadPolarClose& cl, const HeadPolarStart& st, hipStream_t s) {
   constexpr int smem = (CLOSE ? 4 : 3) * N * (N * 2 + 16);   // the closing step holds two planes of its correction beside the iterate
   static PerDeviceOnce configured;
-  auto kern = k_head_polar<N, WGM, WGN, CLOSE>;
+  auto kern = k_head_polar<N, WGM, WGN, CLOSE, DH128>;
   hipError_t e = configured.run([&] {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   });
@@ -367,10 +369,11 @@ hipError_t launch_head_polar(const bf16_bits* Xn0, const bf16_bits* Xt0, int hea
   if (!start && (!Xn0 || !Xt0)) return hipErrorInvalidValue;
   const HeadPolarStart st = start ? *start : HeadPolarStart{};
   const HeadPolarClose cl = close ? *close : HeadPolarClose{};
-  auto go = [&](auto n, auto wgm, auto wgn) {
+  auto go = [&](auto n, auto wgm, auto wgn, auto own) {
     constexpr int N = decltype(n)::value, M_ = decltype(wgm)::value, N_ = decltype(wgn)::value;
-    return close ? launch_one<N, M_, N_, true>(Xn0, Xt0, heads, dh, sched, X32, Pn, Pt, cl, st, s)
-                 : launch_one<N, M_, N_, false>(Xn0, Xt0, heads, dh, sched, X32, Pn, Pt, cl, st, s);
+    constexpr bool OWN = decltype(own)::value;
+    return close ? launch_one<N, M_, N_, true, OWN>(Xn0, Xt0, heads, dh, sched, X32, Pn, Pt, cl, st, s)
+                 : launch_one<N, M_, N_, false, OWN>(Xn0, Xt0, heads, dh, sched, X32, Pn, Pt, cl, st, s);
   };
   // 8 wavefronts (2 per SIMD, so that one's LDS writes and conversions run beside the other's MFMAs) read half as much LDS
   // again as 4 with square blocks and are still ahead: 32 heads of width 128, 22 steps, whole update 94 us with 2 x 2, 86 with
@@ -379,10 +382,12 @@ hipError_t launch_head_polar(const bf16_bits* Xn0, const bf16_bits* Xt0, int hea
   constexpr integral_constant<int, 2> two{};
   constexpr integral_constant<int, 3> three{};
   constexpr integral_constant<int, 4> four{};
-  if (dh <= 32) return go(integral_constant<int, 32>{}, two, two);
-  if (dh <= 64) return go(integral_constant<int, 64>{}, four, two);
-  if (dh <= 96) return go(integral_constant<int, 96>{}, three, two);
-  return go(integral_constant<int, 128>{}, four, two);
+  constexpr std::false_type general{};
+  if (dh <= 32) return go(integral_constant<int, 32>{}, two, two, general);
+  if (dh <= 64) return go(integral_constant<int, 64>{}, four, two, general);
+  if (dh <= 96) return go(integral_constant<int, 96>{}, three, two, general);
+  if (dh < 128) return go(integral_constant<int, 128>{}, four, two, general);
+  return go(integral_constant<int, 128>{}, four, two, std::true_type{});
 }
 
 }  // namespace conqur

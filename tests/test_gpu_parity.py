@@ -1188,3 +1188,23 @@ def test_zero_level_of_the_zero_point_quantiser_is_plus_zero(B, d, T, dtype):
         assert torch.equal(torch.signbit(q[zero]), torch.signbit(X[zero]))
     finally:
         cal.close()
+
+
+@pytest.mark.parametrize("dh,dtype", [(16, "bf16"), (48, "f32"), (80, "bf16"), (96, "bf16"), (112, "bf16"), (112, "f32")])
+def test_closing_step_of_narrow_heads_rounds_as_the_general_path(B, dh, dtype):
+    """Below width 128 the closing step taken in the update's one launch leaves the rotation the general path's closing step
+    leaves, bit for bit: polar_verify keeps the closing step out of that launch."""
+    heads, T = 3, 40 * dh
+    w = I.small_workload(dh * heads, T, n_batches=1, heads=heads, dtype=dtype, seed=70 + dh, prox_lambda=0.1)
+    X = B.to_device(I.batch(w, 0), dtype)
+    out = []
+    for verify in (0, 1):
+        cal = B.Calibrator(w.d, heads, dtype, I.initial_rotation(w), max_tokens=T, prox_lambda=0.1, polar_verify=verify)
+        try:
+            cal.step_batch(X)
+            _, st = cal.update_rotation()
+            assert st[0]["accurate"] == 1 and st[0]["orth_measured"] == verify
+            out.append(cal.get_state(want_M=False)[0])
+        finally:
+            cal.close()
+    assert np.array_equal(out[0], out[1])
