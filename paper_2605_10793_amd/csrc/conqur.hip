@@ -71,7 +71,7 @@ struct conqur_ctx {
   float *row_sse = nullptr, *row_en = nullptr;
   double* qsum = nullptr;      // [2]
   // polar workspaces
-  float* Rprev = nullptr;                            // heads narrower than 128: the rotation the running update started from
+  float* Rprev = nullptr;                            // narrow heads: the rotation the running update started from
   float* PX = nullptr;                               // polar iterate, fp32 [heads][dh][dh]
   bf16_bits *PXn[2] = {nullptr, nullptr};            // iterate as bf16 split planes [3][heads][dh][dh], ping-pong
   bf16_bits *PXt[2] = {nullptr, nullptr};            // ... transposed
@@ -264,13 +264,13 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   // L, rows, skipped (fused per-head step) and the slot counters (general path) share one allocation so that one
   // fill clears the batch statistics
   ctx->stat_words = (size_t)3 * ctx->heads + (size_t)2 * kCountSlots * ctx->heads;
-  A(dev_alloc(ctx, &ctx->L, ctx->stat_words));
+  // The update's scalar results lie in front of them (one copy brings them to the host):
+  // <R_op, M> | <R, M> | ||M||_F^2 per head, then the non-finite flag, which is cleared with the statistics
+  A(dev_alloc(ctx, &ctx->ldot, (size_t)3 * ctx->heads + 1 + ctx->stat_words));
+  ctx->L = ctx->ldot + 3 * ctx->heads + 1;
   ctx->rows = reinterpret_cast<unsigned long long*>(ctx->L + ctx->heads);
   ctx->skipped = ctx->rows + ctx->heads;
   ctx->cnt = ctx->skipped + ctx->heads;
-  // the update's scalar results share one allocation (one copy brings them to the host):
-  // <R_op, M> | <R, M> | ||M||_F^2 per head, then the non-finite flag
-  A(dev_alloc(ctx, &ctx->ldot, (size_t)3 * ctx->heads + 1));
   ctx->inner = ctx->ldot + ctx->heads;
   ctx->fro2 = ctx->inner + ctx->heads;
   ctx->nonfinite = reinterpret_cast<int*>(ctx->fro2 + ctx->heads);
@@ -283,7 +283,7 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   ctx->row_en = ctx->row_sse + tmax;
   A(dev_alloc(ctx, &ctx->qsum, (size_t)2));
   A(dev_alloc(ctx, &ctx->PX, blk));
-  if (dh < 128 && cfg->polar_precision == 0) A(dev_alloc(ctx, &ctx->Rprev, blk));   // (read only by updates that take the one-launch path)
+  if (dh <= (uint32_t)kHeadPolarMaxDh && cfg->polar_precision == 0) A(dev_alloc(ctx, &ctx->Rprev, blk));   // (read only by updates that take the one-launch path)
   for (int b = 0; b < 2; ++b) {
     A(dev_alloc(ctx, &ctx->PXn[b], 3 * blk));
     A(dev_alloc(ctx, &ctx->PXt[b], 3 * blk));
@@ -894,28 +894,40 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   };
   // Outcome of a closing step taken inside the main phase's launch (narrow heads): accepted if every head took it
   // and the bound from ||D^2||_F (see below) is within the tolerance; otherwise the general closing steps continue from
-  // the hand-over state, which that launch wrote as well.  (R of the heads that did take the step is overwritten already; for
-  // the rare nudge below the previous rotation is kept aside, except with heads of width 128: there the nudge moves the heads
-  // that took the step towards their new rotation.)
+  // the hand-over state, which that launch wrote as well.  R and the operand of the heads that did take the step are replaced
+  // by then; the launch has kept the previous rotation aside, for the nudge below and for an update that fails.  The
+  // statistics are cleared behind the outcome, in one launch with the non-finite flag.
+  double* const resblk = ctx->host_res + (size_t)kResidSlots * h;   // <R_op, M> | <R, M> | ||M||_F^2 | non-finite flag
+  const size_t resblk_bytes = ((size_t)3 * h + 1) * sizeof(double);
+  bool r_replaced = false, fused_done = false;
+  auto fail_nonfinite = [&]() -> conqur_status {   // the context is left as the update found it
+    if (r_replaced) {
+      HIP_TRY(hipMemcpyAsync(ctx->R, ctx->Rprev, (size_t)plane * sizeof(float), hipMemcpyDeviceToDevice, s));
+      const conqur_status st_op = refresh_operand(ctx);
+      if (st_op != CONQUR_OK) return st_op;
+    }
+    return fail(ctx, CONQUR_ENONFINITE, "update_rotation: non-finite polar iterate");
+  };
   auto fused_outcome = [&]() -> conqur_status {
+    if (timed) HIP_TRY(hipEventRecord(ctx->ev[ST_UPDATE][1], s));
     HIP_TRY(hipMemcpyAsync(hist + (size_t)fused_slot * h, ctx->resid + (size_t)fused_slot * h, 2 * h * sizeof(double),
                            hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipMemcpyAsync(resblk, ctx->ldot, resblk_bytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipEventRecord(ctx->ev_resid, s));
-    // expected to be the end: what follows the last step goes in before the host waits
-    HIP_TRY(launch_fill_zero(ctx->L, ctx->stat_words * sizeof(double), s));
-    if (timed) HIP_TRY(hipEventRecord(ctx->ev[ST_UPDATE][1], s));
     HIP_TRY(hipEventSynchronize(ctx->ev_resid));
-    bool ok = true;
+    bool ok = true, finite = true;
     double worst_res = 0.0, worst_pred = 0.0;
     for (int q = 0; q < h; ++q) {
       const double r2 = hist[(size_t)fused_slot * h + q], s2 = hist[(size_t)(fused_slot + 1) * h + q];
-      if (!std::isfinite(r2)) return fail(ctx, CONQUR_ENONFINITE, "update_rotation: non-finite polar iterate");
+      if (!std::isfinite(r2)) finite = false;
       worst_res = std::max(worst_res, std::sqrt(r2));
       if (!(s2 >= 0.0)) { ok = false; continue; }
+      r_replaced = true;
       const double b = kCubeFactor * std::pow(std::sqrt(s2), 1.5) + kOrthFloorPerDim * dh;
       worst_pred = std::max(worst_pred, b);
       if (!(std::isfinite(b) && b <= tol)) ok = false;
     }
+    if (!finite) return fail_nonfinite();
     if (trace) std::fprintf(stderr, "[conqur] polar closing in the main phase's launch: resid_F=%.6e bound on resid_F=%.4e accepted=%d\n",
                             worst_res, worst_pred, (int)ok);
     if (!ok) { fused_slot = -1; return CONQUR_OK; }
@@ -926,6 +938,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     last_slot = fused_slot + 1;
     ++iters; ++closing;
     converged = predicted = finished = true;
+    fused_done = true;
     final_x = ctx->R;
     return CONQUR_OK;
   };
@@ -947,7 +960,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     st = wait_resid(last_slot, &res);
     if (st != CONQUR_OK) return st;
     if (trace) std::fprintf(stderr, "[conqur] polar closing check: resid_F=%.6e (iters %u)\n", res, iters);
-    if (!std::isfinite(res)) return fail(ctx, CONQUR_ENONFINITE, "update_rotation: non-finite polar iterate");
+    if (!std::isfinite(res)) return fail_nonfinite();
     if (res <= tol) { converged = true; break; }
     if (iters >= cap || slot >= kResidSlots - 8) break;
     if (res > 0.7 && kicks < 2 && iters + 8 < cap && final_x == ctx->PX) {
@@ -958,7 +971,9 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       // directions every completion is optimal and this one is nearest to R_prev --
       // and run the main phase again from the nudge's scale.
       const double kappa = np_main == 1 ? 1.0 / 64.0 : 1.0 / 256.0;
-      HIP_TRY(launch_axpy(ctx->PX, ctx->Rprev ? ctx->Rprev : ctx->R, plane, (float)kappa, s));
+      // (Heads that took the closing step inside the main phase's launch have their new rotation in R.  Width 128 nudges them
+      // towards that one, which leaves them where they are; narrower heads are nudged as the general path would.)
+      HIP_TRY(launch_axpy(ctx->PX, ctx->Rprev && dh < 128 ? ctx->Rprev : ctx->R, plane, (float)kappa, s));
       ++kicks;
       st = main_phase(0.25 * kappa / std::sqrt((double)dh), false);
       if (st != CONQUR_OK) return st;
@@ -1043,10 +1058,12 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     if (st != CONQUR_OK) return st;
   }
   ctx->ev_valid[ST_UPDATE] = timed;
-  // <R_op, M> | <R, M> | ||M||_F^2 | non-finite flag: one copy of the result block
-  double* const resblk = ctx->host_res + (size_t)kResidSlots * h;
-  HIP_TRY(hipMemcpyAsync(resblk, ctx->ldot, ((size_t)3 * h + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
-  HIP_TRY(launch_fill_zero(ctx->nonfinite, sizeof(int), s));
+  if (fused_done) {   // (the result block came with the outcome)
+    HIP_TRY(launch_fill_zero(ctx->nonfinite, (1 + ctx->stat_words) * sizeof(double), s));
+  } else {
+    HIP_TRY(hipMemcpyAsync(resblk, ctx->ldot, resblk_bytes, hipMemcpyDeviceToHost, s));
+    HIP_TRY(launch_fill_zero(ctx->nonfinite, sizeof(int), s));
+  }
   HIP_TRY(hipStreamSynchronize(s));
   const double *ldot = resblk, *inner = resblk + h, *fro2 = resblk + 2 * h;
   int nonfinite = 0;

@@ -1208,3 +1208,74 @@ def test_closing_step_of_narrow_heads_rounds_as_the_general_path(B, dh, dtype):
         finally:
             cal.close()
     assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("dh,dtype", [(32, "bf16"), (64, "bf16"), (80, "bf16"), (112, "f32")])
+def test_narrow_heads_whose_neighbour_declines_the_closing_step(B, dh, dtype):
+    """The cancelled start of the test above with heads narrower than 128: two heads take the closing step inside the update's one
+    launch, whose R is then the new one, the third declines it and is nudged towards its previous rotation.  The nudge
+    reaches all heads and goes towards the rotation the update started from, as on the general path: bit for bit the
+    result of an update that keeps the closing step out of the launch (polar_verify)."""
+    heads, d, T = 3, 3 * dh, 40 * dh
+    w = I.small_workload(d, T, n_batches=1, heads=heads, dtype=dtype, seed=77 + dh, prox_lambda=1.0)
+    R0 = I.initial_rotation(w).astype(np.float32)
+    X = B.to_device(I.batch(w, 0), dtype)
+    out = []
+    for verify in (0, 1):
+        cal = B.Calibrator(d, heads, dtype, R0, max_tokens=T, prox_lambda=1.0, polar_verify=verify)
+        try:
+            cal.step_batch(X)
+            _, M, _ = cal.get_state(want_R=False)
+            M[2] = -0.125 * R0[2]
+            cal.set_state(M=M)
+            _, st = cal.update_rotation()
+            R, _, _ = cal.get_state(want_M=False)
+            assert st[0]["iters"] >= 12              # two main phases: the schedule's 6 steps, the nudge, and its 10 or more
+            out.append(R)
+        finally:
+            cal.close()
+    R64 = out[0].astype(np.float64)
+    for h in range(heads):
+        assert np.linalg.norm(R64[h].T @ R64[h] - np.eye(dh)) <= TOL_ORTH
+    assert np.abs(R64[2] - R0[2]).max() <= 1e-2 and np.abs(R64[0] - R0[0]).max() > 1e-2
+    assert np.array_equal(out[0], out[1])
+
+
+@pytest.mark.parametrize("dh,dtype", [(64, "bf16"), (112, "bf16"), (96, "f32"), (128, "bf16"), (128, "f32")])
+def test_failed_update_leaves_the_context_as_it_was(B, dh, dtype):
+    """M of one head non-finite: the update fails.  The other heads, whose closing step may ride in the same launch, keep their
+    rotation and its operand, and the statistics are still there; with a finite M the next update is the one a fresh context
+    gives."""
+    import torch
+    heads, d, T = 3, 3 * dh, 500
+    w = I.small_workload(d, T, n_batches=1, heads=heads, dtype=dtype, seed=31 + dh, prox_lambda=0.1)
+    R0 = I.initial_rotation(w)
+    X = B.to_device(I.batch(w, 0), dtype)
+    cal, ref = (B.Calibrator(d, heads, dtype, R0, max_tokens=T, prox_lambda=0.1) for _ in range(2))
+    try:
+        for c in (cal, ref):
+            c.step_batch(X)
+        before, Y = cal.batch_stats(), cal.rotate(X).clone()
+        R, M, n = cal.get_state()
+        for value in (np.nan, np.inf):
+            bad = M.copy()
+            bad[1, 3, 5] = value
+            cal.set_state(M=bad)
+            rc, _ = cal.update_rotation(allow=(B.ENONFINITE,))
+            assert rc == B.ENONFINITE
+            R1, _, n1 = cal.get_state(want_M=False)
+            assert np.array_equal(R, R1) and np.array_equal(n, n1)
+            assert torch.equal(cal.rotate(X), Y)
+        cal.set_state(M=M)
+        after = cal.batch_stats()
+        assert [(s["rows"], s["skipped"]) for s in after] == [(s["rows"], s["skipped"]) for s in before]
+        for a, b in zip(after, before):
+            assert abs(a["l1"] - b["l1"]) <= 1e-12 * abs(b["l1"])
+        rc, st = cal.update_rotation()
+        _, st_ref = ref.update_rotation()
+        assert np.array_equal(cal.get_state(want_M=False)[0], ref.get_state(want_M=False)[0])
+        assert [s["inner"] for s in st] == [s["inner"] for s in st_ref]
+        assert [s["rows"] for s in cal.batch_stats()] == [0] * heads    # and the statistics restart
+    finally:
+        cal.close()
+        ref.close()
