@@ -785,7 +785,11 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   auto wait_resid = [&](int sl_idx, double* worst) -> conqur_status {
     HIP_TRY(hipEventSynchronize(ctx->ev_resid));
     double w = 0.0;
-    for (int q = 0; q < h; ++q) w = std::max(w, std::sqrt(hist[(size_t)sl_idx * h + q]));
+    for (int q = 0; q < h; ++q) {
+      const double r = std::sqrt(hist[(size_t)sl_idx * h + q]);
+      if (!(r <= w)) w = r;   // (a NaN stays: std::max would drop it)
+      if (std::isnan(w)) break;
+    }
     *worst = w;
     return CONQUR_OK;
   };

@@ -1241,7 +1241,7 @@ def test_narrow_heads_whose_neighbour_declines_the_closing_step(B, dh, dtype):
     assert np.array_equal(out[0], out[1])
 
 
-@pytest.mark.parametrize("dh,dtype", [(64, "bf16"), (112, "bf16"), (96, "f32"), (128, "bf16"), (128, "f32")])
+@pytest.mark.parametrize("dh,dtype", [(64, "bf16"), (112, "bf16"), (96, "f32"), (128, "bf16"), (128, "f32"), (160, "bf16"), (256, "f32")])
 def test_failed_update_leaves_the_context_as_it_was(B, dh, dtype):
     """M of one head non-finite: the update fails.  The other heads, whose closing step may ride in the same launch, keep their
     rotation and its operand, and the statistics are still there; with a finite M the next update is the one a fresh context
