@@ -186,7 +186,12 @@ conqur_status conqur_quant_error_zp(conqur_ctx* ctx, const void* X_dev, uint64_t
  * call).  Y_dev: DEVICE, T rows of y_row_stride_elems elements of act_dtype
  * (d <= y_row_stride_elems < 2^21, else CONQUR_EINVAL), owned by the caller, must not
  * overlap X.  Asynchronous on the context's stream; does not change the calibration
- * state.
+ * state.  Every call that rotates rows (this one, the scores, the diagnostics, the
+ * quantised rows, the statistics steps of the general path) gives the same rows the same
+ * sums in calls of the same size.  Calls of up to 16 rows (32 with fp32 activations or dh <= 4096)
+ * add up the dh products of an entry in another order than larger calls: a row rotated in
+ * either may differ in the last bit of its fp32 sums, hence in the rounding of an entry
+ * or in the corner sign of one that is zero to rounding.
  */
 conqur_status conqur_rotate(conqur_ctx* ctx, const void* X_dev, uint64_t T, uint64_t row_stride_elems, void* Y_dev,
                             uint64_t y_row_stride_elems);
@@ -216,8 +221,7 @@ conqur_status conqur_rotate_quant(conqur_ctx* ctx, const void* X_dev, uint64_t T
  * conqur_step_batch does, and Yq_dev receives Q(X R_op) exactly as conqur_rotate_quant writes it --
  * the quantised input of the layer behind the site.  Arguments and errors as for those two calls.
  * (Heads of width 128 with bf16 activations rotate twice internally: their fused step keeps the
- * rotated rows on the compute unit.  So do calls of up to 32 rows, which conqur_rotate_quant sums in
- * an order of its own.)  Asynchronous on the context's stream.
+ * rotated rows on the compute unit.)  Asynchronous on the context's stream.
  */
 conqur_status conqur_step_batch_quant(conqur_ctx* ctx, const void* X_dev, uint64_t T, uint64_t row_stride_elems, uint32_t bits,
                                       uint32_t zero_point, float clip_ratio, void* Yq_dev, uint64_t yq_row_stride_elems);

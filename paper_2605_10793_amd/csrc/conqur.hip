@@ -175,7 +175,7 @@ void rotate_args(conqur_ctx* c, const void* X, int64_t T, int64_t stride, GemmAr
 // Y = X R_op into rows of pitch ldy (activation dtype): a few rows in a kernel of their own, more through the tiled GEMM.
 hipError_t rotate_into(conqur_ctx* c, const void* X, int64_t T, int64_t stride, void* Y, int64_t ldy) {
   if (rotate_rows_fits(c->f32, T, c->dh))
-    return launch_rotate_rows(X, c->f32, T, stride, c->RopT, (int64_t)c->heads * c->dh * c->dh, c->heads, c->dh, Y, ldy, c->stream);
+    return launch_rotate_rows(X, c->f32, T, stride, c->RopT, (int64_t)c->heads * c->dh * c->dh, c->heads, c->dh, Y, ldy, nullptr, c->stream);
   if (c->f32) {
     hipError_t e = launch_split_rows(reinterpret_cast<const float*>(X), T, stride, c->d, c->Xs, c->tmax * c->d, c->stream);
     if (e != hipSuccess) return e;
@@ -451,20 +451,29 @@ static conqur_status step_general(conqur_ctx* ctx, const void* X, int64_t T, int
   const int64_t Tk = round_up(T, 64);
   hipStream_t s = ctx->stream;
   ctx->last_signs_valid = true;
+  // A few rows are rotated by the kernel that rotates them for every other call (rotate_into), signs and rows from the same sums.
+  const bool few = rotate_rows_fits(ctx->f32, T, ctx->dh);
   // bf16 activations: the scaled transposed operand of the accumulate GEMM is produced by the rotate GEMM's epilogue
-  // (every workgroup transposes the block of X under its output block through the LDS staging of the signs), which
-  // saves the transposing launch; fp32 activations (split planes) and the variant that also emits Y keep that launch.
-  const bool xt_in_gemm = !ctx->f32 && !keep_y;
+  // (every workgroup transposes the block of X under its output block through the LDS staging of the signs) or by the
+  // kernel for a few rows, which saves the transposing launch; fp32 activations (split planes) and the GEMM variant that
+  // also emits Y keep that launch.
+  const bool xt_in_rotate = !ctx->f32 && (few || !keep_y);
   {
     StageTimer tm(ctx, ST_PREP);
     HIP_TRY(launch_row_norms(X, ctx->f32, T, stride, ctx->heads, ctx->dh, ctx->nrm, ctx->w, ctx->tmax, ctx->nonfinite, s));
-    if (!xt_in_gemm)
+    if (!xt_in_rotate)
       HIP_TRY(launch_transpose_scale(X, ctx->f32, T, Tk, stride, ctx->d, ctx->dh, ctx->w, ctx->tmax, ctx->Xt, ctx->pitch,
                                      (int64_t)ctx->d * ctx->pitch, ctx->np, ctx->cnt, s));
-    if (ctx->f32)
+    if (ctx->f32 && !few)
       HIP_TRY(launch_split_rows(reinterpret_cast<const float*>(X), T, stride, ctx->d, ctx->Xs, ctx->tmax * ctx->d, s));
   }
-  {
+  if (few) {
+    StageTimer tm(ctx, ST_ROTATE);
+    ctx->clk_wg[0] = 0;
+    const RotateRowsStats rs{ctx->St, ctx->Xt, ctx->pitch, ctx->w, ctx->tmax, ctx->cnt, kCountSlots};
+    HIP_TRY(launch_rotate_rows(X, ctx->f32, T, stride, ctx->RopT, (int64_t)ctx->heads * ctx->dh * ctx->dh, ctx->heads, ctx->dh,
+                               keep_y ? ctx->Y : nullptr, ctx->d, &rs, s));
+  } else {
     StageTimer tm(ctx, ST_ROTATE);
     GemmArgs g;
     rotate_args(ctx, X, T, stride, &g);
@@ -475,10 +484,10 @@ static conqur_status step_general(conqur_ctx* ctx, const void* X, int64_t T, int
     ctx->clk_wg[0] = (ctx->timing >= 2 && wg <= kClkMaxWorkgroups) ? wg : 0;
     g.clk = ctx->clk_wg[0] ? ctx->clk[0] : nullptr;
     if (keep_y) { g.Yact = ctx->Y; g.ldy = ctx->d; g.batchY = ctx->dh; g.c_is_f32 = ctx->f32; }
-    if (xt_in_gemm) {
+    if (xt_in_rotate) {
       g.xt_w = ctx->w; g.xt_ldw = ctx->tmax; g.Xt = ctx->Xt; g.cnt = ctx->cnt; g.cnt_slots = kCountSlots;
     }
-    HIP_TRY(launch_gemm_nt(g, keep_y ? EPI_SIGN_ACT : (xt_in_gemm ? EPI_SIGN_XT : EPI_SIGN), ctx->heads, s));
+    HIP_TRY(launch_gemm_nt(g, keep_y ? EPI_SIGN_ACT : (xt_in_rotate ? EPI_SIGN_XT : EPI_SIGN), ctx->heads, s));
   }
   {
     StageTimer tm(ctx, ST_ACCUM);
@@ -546,14 +555,13 @@ conqur_status conqur_step_batch_quant(conqur_ctx* ctx, const void* X, uint64_t T
   hipStream_t s = ctx->stream;
   {
     StageTimer whole(ctx, ST_STEP, 1);
-    if (ctx->head_fused || rotate_rows_fits(ctx->f32, T, ctx->dh)) {
-      // heads of width 128: the fused step kernel keeps Y on the compute unit; the rows are rotated once more for the quantiser.
-      // A few rows: likewise, so that they are summed in the order conqur_rotate_quant sums them in.
-      st = ctx->head_fused ? step_fused(ctx, X, T, stride, 0, ctx->heads) : step_general(ctx, X, T, stride, false);
+    if (ctx->head_fused) {
+      // heads of width 128: the fused step kernel keeps Y on the compute unit; the rows are rotated once more for the quantiser
+      st = step_fused(ctx, X, T, stride, 0, ctx->heads);
       if (st != CONQUR_OK) return st;
       HIP_TRY(rotate_into(ctx, X, T, stride, ctx->Y, ctx->d));
     } else {
-      st = step_general(ctx, X, T, stride, true);   // one rotate GEMM: corner signs and Y
+      st = step_general(ctx, X, T, stride, true);   // one rotation: corner signs and Y
       if (st != CONQUR_OK) return st;
     }
   }

@@ -26,10 +26,23 @@ hipError_t launch_split_rows(const float* X, int64_t T, int64_t stride, int d, b
                              hipStream_t s);
 
 // Y = X R_op per head for the few rows rotate_rows_fits() admits (rotate_rows.hip): X [T][stride] and Y [T][ldy] in bf16 or fp32,
-// RopT the rotate operand [heads][dh][dh] (R^T; three split planes, `plane` elements apart, for fp32).
+// RopT the rotate operand [heads][dh][dh] (R^T; three split planes, `plane` elements apart, for fp32).  stats non-null: a
+// statistics step, whose operands the launch leaves in the first kRotateRowsTokens tokens of St and (bf16) Xt, both
+// [heads * dh][pitch]: the corner signs (+1 beyond T; fp16 for bf16 activations, bf16 for fp32) and the rows of X times w
+// ([heads][ldw]), fp16 (0 beyond T); the rows entered and skipped are added to cnt (bf16).  Y may be null then.
+constexpr int kRotateRowsTokens = 64;
+struct RotateRowsStats {
+  bf16_bits* St;
+  bf16_bits* Xt;
+  int64_t pitch;
+  const float* w;
+  int64_t ldw;
+  unsigned long long* cnt;   // [heads][cnt_slots][2]
+  int cnt_slots;
+};
 bool rotate_rows_fits(int x_is_f32, int64_t T, int dh);
 hipError_t launch_rotate_rows(const void* X, int x_is_f32, int64_t T, int64_t stride, const bf16_bits* RopT, int64_t plane, int heads,
-                              int dh, void* Y, int64_t ldy, hipStream_t s);
+                              int dh, void* Y, int64_t ldy, const RotateRowsStats* stats, hipStream_t s);
 
 // Split an fp32 matrix batch [batch][rows][cols] into np bf16 planes, in natural
 // layout (outN[p][b][r][c]) and/or transposed (outT[p][b][c][r]); either may be null.

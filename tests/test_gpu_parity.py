@@ -1279,3 +1279,59 @@ def test_failed_update_leaves_the_context_as_it_was(B, dh, dtype):
     finally:
         cal.close()
         ref.close()
+
+
+@pytest.mark.parametrize("d,heads,dtype", [(4096, 1, "bf16"), (1104, 1, "bf16"), (16, 1, "f32"), (16, 1, "bf16"), (48 * 5, 5, "bf16"), (96 * 3, 3, "f32"),
+                                           (1040, 1, "f32"), (8192, 1, "bf16")])
+def test_statistics_step_of_few_rows(B, d, heads, dtype):
+    """Steps of 1 .. 33 rows (both ends of the range of the kernel for a few rows, which also leaves the accumulate GEMM's operands):
+    with and without the quantised rows the same statistics to the bit, corner signs that are those of the rows
+    conqur_rotate gives, and M as these corners make it; a zero row, a non-finite row and a second batch on top."""
+    import torch
+    dh = d // heads
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d + heads)
+    R0 = (torch.randn((heads, dh, dh), generator=g, device="cuda:0") / math.sqrt(dh)).cpu().numpy()
+    one, both = (B.Calibrator(d, heads, dtype, R0, max_tokens=64) for _ in range(2))
+    try:
+        M_ref, rows = np.zeros((heads, dh, dh)), 0
+        entered = skipped = 0
+        for T in (1, 5, 16, 17, 32, 33):
+            wide = torch.randn((T, d + 8), generator=g, device="cuda:0")
+            wide = wide.to(torch.bfloat16) if dtype == "bf16" else wide
+            X = wide[:, :d]
+            if T > 3:
+                X[1] = 0
+                X[3, d - 1] = float("inf")       # the last head's slice of row 3
+            one.step_batch(X)
+            Yq = both.step_batch_quant(X, 4, True, 0.9)
+            signs, norms = one.last_corners(T)
+            signs2, _ = both.last_corners(T)
+            Y = one.rotate(X)
+            torch.cuda.synchronize()
+            assert np.array_equal(signs, signs2), T
+            assert torch.equal(torch.nan_to_num(Yq.float()), torch.nan_to_num(both.rotate_quant(X, 4, True, 0.9).float())), T
+            want = torch.where(Y >= 0, 1, -1).to(torch.int8).cpu().numpy().reshape(T, heads, dh)
+            x = X.double().cpu().numpy().reshape(T, heads, dh)
+            for h in range(heads):
+                n = np.linalg.norm(x[:, h], axis=1)
+                ok = np.isfinite(n) & (n > 0)
+                want[~ok, h] = 0                 # (how the tap reports a skipped row)
+                M_ref[h] += (x[ok, h] / n[ok, None]).T @ (want[ok, h].astype(np.float64) / math.sqrt(dh))
+                if h == 0:
+                    entered += int(ok.sum())
+                    skipped += int((~ok).sum())
+            assert np.array_equal(signs.reshape(T, heads, dh), want), T
+            rows += T
+            Ma, Mb = one.get_state(want_R=False)[1], both.get_state(want_R=False)[1]
+            assert np.array_equal(Ma, Mb), T
+            # every entry is a sum of `rows` terms of up to 1 / sqrt(dh); x^ in fp16 (bf16 activations: 2^-11) or three bf16 planes,
+            # the norm and the scale in fp32
+            tol = (2.0 ** -10 if dtype == "bf16" else 2e-6) * rows / math.sqrt(dh)
+            assert np.abs(Ma - M_ref).max() <= tol, T
+            for c in (one, both):
+                s = c.batch_stats()[0]
+                assert (s["rows"], s["skipped"]) == (entered, skipped), T
+    finally:
+        one.close()
+        both.close()
