@@ -20,6 +20,9 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-u
          "-Rpass-analysis=kernel-resource-usage"]
 
 
+MAX_SCRATCH = 64   # bytes per lane; every kernel has 0
+
+
 def hipcc() -> str:
     for c in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", "hipcc"):
         if c and (os.path.isabs(c) and os.path.exists(c) or not os.path.isabs(c)):
@@ -57,6 +60,9 @@ def build_lib(verbose: bool = False) -> str:
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l and "kernel-resource-usage" not in l)
         if p.returncode != 0:
             raise RuntimeError(f"hipcc failed on {src}:\n{out}")
+        worst = max((n for _, n in spills), default=0)
+        if worst > MAX_SCRATCH:
+            raise RuntimeError(f"{src}: a kernel uses {worst} bytes/lane of scratch: {spills}")
         for name, nbytes in spills:
             print(f"build.py: WARNING {src}: kernel {name} uses {nbytes} bytes/lane of scratch (register spill)",
                   file=sys.stderr, flush=True)

@@ -78,7 +78,6 @@ struct conqur_ctx {
   bf16_bits *PW = nullptr, *PW2 = nullptr;           // polynomial factor planes [3][heads][dh][dh]
   double* resid = nullptr;                           // [kResidSlots][heads] residual history of one update
   double* resid_part = nullptr;                      // [heads][parts] per-wavefront partials of one Gram GEMM
-  int resid_parts = 0;
   double *fro2 = nullptr, *inner = nullptr;          // [heads]
   double* dot_part = nullptr;                        // [heads][(dh/64)^2] per-tile partials of <R, M>
   int64_t last_T = 0;
@@ -291,8 +290,7 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   A(dev_alloc(ctx, &ctx->PW, 3 * blk));
   A(dev_alloc(ctx, &ctx->PW2, 3 * blk));
   A(dev_alloc(ctx, &ctx->resid, (size_t)kResidSlots * ctx->heads));
-  ctx->resid_parts = gemm_num_partials((int)dh, ctx->heads, 1);   // every launch that leaves residual partials is a symmetric one
-  A(dev_alloc(ctx, &ctx->resid_part, (size_t)ctx->resid_parts * ctx->heads));
+  A(dev_alloc(ctx, &ctx->resid_part, (size_t)gemm_max_partials((int)dh) * ctx->heads));
   ctx->head_fused = ctx->dh == 128 && !ctx->f32;
   if (ctx->head_fused) {
     ctx->head_splits = head_step_splits(ctx->heads, ctx->tmax);
@@ -480,14 +478,15 @@ static conqur_status step_general(conqur_ctx* ctx, const void* X, int64_t T, int
     g.C = ctx->St; g.ldc = ctx->pitch; g.batchC = (int64_t)ctx->dh * ctx->pitch;
     g.st_rows_valid = ctx->pitch;
     g.sign_f16 = ctx->f32 ? 0 : 1;   // the accumulate GEMM runs in fp16 for bf16 activations
-    const int wg = gemm_num_workgroups(g.M, g.N, g.K, ctx->heads);
+    const GemmEpilogue epi = keep_y ? EPI_SIGN_ACT : (xt_in_rotate ? EPI_SIGN_XT : EPI_SIGN);
+    const int wg = gemm_num_workgroups(g, epi, ctx->heads);
     ctx->clk_wg[0] = (ctx->timing >= 2 && wg <= kClkMaxWorkgroups) ? wg : 0;
     g.clk = ctx->clk_wg[0] ? ctx->clk[0] : nullptr;
     if (keep_y) { g.Yact = ctx->Y; g.ldy = ctx->d; g.batchY = ctx->dh; g.c_is_f32 = ctx->f32; }
     if (xt_in_rotate) {
       g.xt_w = ctx->w; g.xt_ldw = ctx->tmax; g.Xt = ctx->Xt; g.cnt = ctx->cnt; g.cnt_slots = kCountSlots;
     }
-    HIP_TRY(launch_gemm_nt(g, keep_y ? EPI_SIGN_ACT : (xt_in_rotate ? EPI_SIGN_XT : EPI_SIGN), ctx->heads, s));
+    HIP_TRY(launch_gemm_nt(g, epi, ctx->heads, s));
   }
   {
     StageTimer tm(ctx, ST_ACCUM);
@@ -516,7 +515,7 @@ static conqur_status step_general(conqur_ctx* ctx, const void* X, int64_t T, int
       HIP_TRY(launch_gemm_nt(g, EPI_F32, shares, s));
       HIP_TRY(launch_sum_shares(ctx->Mpart, shares, (int64_t)ctx->dh * ctx->dh, ctx->M, ctx->m_empty ? 0 : 1, s));
     } else {
-      const int wg = gemm_num_workgroups(g.M, g.N, g.K, ctx->heads);
+      const int wg = gemm_num_workgroups(g, EPI_F32, ctx->heads);
       ctx->clk_wg[1] = (ctx->timing >= 2 && wg <= kClkMaxWorkgroups) ? wg : 0;
       g.clk = ctx->clk_wg[1] ? ctx->clk[1] : nullptr;
       HIP_TRY(launch_gemm_nt(g, EPI_F32, ctx->heads, s));
@@ -708,7 +707,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     hipError_t e = launch_gemm_nt(g, EPI_GRAMW, h, s);
     mfma_flop += gemm_issued_flop(g, EPI_GRAMW, h);
     if (e == hipSuccess && want_resid)
-      e = launch_sum_partials(ctx->resid_part, ctx->resid_parts, h, ctx->resid + (size_t)slot * h, s);
+      e = launch_sum_partials(ctx->resid_part, gemm_num_partials(g, EPI_GRAMW, h), h, ctx->resid + (size_t)slot * h, s);
     return e;
   };
   // X' = X W (+ X): reads the planes in buffer `cur`, writes np_x planes (both layouts)
@@ -760,7 +759,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     mfma_flop += gemm_issued_flop(g, EPI_SQUARE, h);
     hipError_t e = launch_gemm_nt(g, EPI_SQUARE, h, s);
     if (!keep_square) return e;
-    if (e == hipSuccess) e = launch_sum_partials(ctx->resid_part, ctx->resid_parts, h, ctx->resid + (size_t)slot * h, s);
+    if (e == hipSuccess) e = launch_sum_partials(ctx->resid_part, gemm_num_partials(g, EPI_SQUARE, h), h, ctx->resid + (size_t)slot * h, s);
     if (e == hipSuccess)
       e = hipMemcpyAsync(ctx->host_res + (size_t)slot * h, ctx->resid + (size_t)slot * h, h * sizeof(double), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipEventRecord(ctx->ev_sq, s);
@@ -780,7 +779,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     g.resid_part = ctx->resid_part;
     hipError_t e = launch_gemm_nt(g, EPI_FRO2, h, s);
     mfma_flop += gemm_issued_flop(g, EPI_FRO2, h);
-    if (e == hipSuccess) e = launch_sum_partials(ctx->resid_part, ctx->resid_parts, h, ctx->resid + (size_t)slot * h, s);
+    if (e == hipSuccess) e = launch_sum_partials(ctx->resid_part, gemm_num_partials(g, EPI_FRO2, h), h, ctx->resid + (size_t)slot * h, s);
     return e;
   };
   double* const hist = ctx->host_res;   // pinned, so that the copies below are asynchronous
@@ -857,7 +856,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       double a, b;
       const double E = step_cubic(l, u, &a, &b);
       const bool last = E <= e_stop || iters + 1 >= cap;
-      HIP_TRY(gram(seg_main, (float)a, (float)b, np_main, trace, main_f16));
+      HIP_TRY(gram(seg_main, (float)a, (float)b, np_main, false, main_f16));
       ++slot;
       // The last main step hands over to the closing iterations.  Its result is rounded to the planes this phase
       // works with anyway (one: 8 bits, two: 16 bits -- a perturbation of the size every step of this phase

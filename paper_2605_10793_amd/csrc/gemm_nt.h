@@ -63,7 +63,7 @@ struct GemmArgs {
   int cnt_slots;
   void* Yact;              // EPI_SIGN_ACT: bf16/f32 Y (element type by c_is_f32), pitch ldy, batch offset batchY
   int64_t ldy, batchY;
-  double* resid_part;      // EPI_GRAMW: [batch][gemm_num_partials()] per-wavefront sums of (acc - I)^2, or null.
+  double* resid_part;      // EPI_GRAMW: [batch][gemm_num_partials()] per-wavefront sums of (acc - I)^2, or null (fp16 operands: null).
                            // (No atomics: same-address atomics from all XCDs serialise at the memory side.)
   float coef_i, coef_g;    // EPI_GRAMW
   int np_out;              // EPI_GRAMW: planes of W written; EPI_XOUT: transposed planes (Pt) written (1..3);
@@ -93,12 +93,12 @@ hipError_t launch_gemm_nt(const GemmArgs& args, GemmEpilogue epi, int batch, hip
 // x 2 (a symmetric launch runs the tiles on and above the diagonal only).
 double gemm_issued_flop(const GemmArgs& args, GemmEpilogue epi, int batch);
 
-// Number of workgroups launch_gemm_nt uses for an M x N x K problem with `batch` entries (size of the clock probe / 4).
-int gemm_num_workgroups(int M, int N, int K, int batch);
+// Number of workgroups launch_gemm_nt uses for this problem with `batch` entries (size of the clock probe / 4).
+int gemm_num_workgroups(const GemmArgs& args, GemmEpilogue epi, int batch);
 
-// Per-batch-entry count of the partial sums the EPI_GRAMW / EPI_SQUARE / EPI_FRO2 epilogues write for an M x M x M problem (any
-// number of segments) launched with the given `symmetric` flag (the flag can select another tile).
-int gemm_num_partials(int M, int batch, int symmetric);
-
+// Per-batch-entry count of the partial sums the EPI_GRAMW / EPI_SQUARE / EPI_FRO2 epilogues leave in resid_part, and the
+// largest such count of any M x M problem.
+int gemm_num_partials(const GemmArgs& args, GemmEpilogue epi, int batch);
+int gemm_max_partials(int M);
 
 }  // namespace conqur

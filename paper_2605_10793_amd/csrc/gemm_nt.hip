@@ -155,6 +155,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   const uint32_t recB = (uint32_t)((((int64_t)g.N - 1) * g.ldb + BK) * 2);
   const int nkb = (g.K + BK - 1) / BK;
   const int nit = nkb * g.nseg;
+  // Epilogues of the largest tile whose registers need help (see where the accumulators are pinned): a guard around the loop
+  // costs them a second set of accumulators at its exit.  The others spill nothing either way, and the two that rotate or
+  // accumulate lose up to 5 % without it (11008 x 4096 x 4096: 297 us instead of 282).
+  constexpr bool TIGHT = (BM / WGM) * (BN / WGN) >= 128 * 128 && EPI != EPI_ACT && EPI != EPI_F32;
+  if constexpr (TIGHT) __builtin_assume(nit > 0);
   const bool ktail = (g.K % BK) != 0;
   // offsets for the last, partial K step of a segment: chunks past K read zeros
   uint32_t offAt[QA], offBt[QB];
@@ -303,6 +308,16 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   }
   const unsigned long long pr_w2 = g.clk ? wall_clock64() : 0, pr_c2 = g.clk ? clock64() : 0;
   wait_vmcnt<0>();   // drain the padding loads before the epilogue reuses nothing of LDS (keeps exit clean)
+  // The 256 accumulators of the largest tile fill one half of the registers.  Left to itself the compiler moves them over to
+  // the other half for the epilogue's arithmetic, all at once, and spills what that half held.  Pinned to their half here,
+  // they are read from it where they are used.  (The two sign epilogues that store a second array spill with the pin and
+  // not without.)
+  if constexpr (TIGHT && EPI != EPI_SIGN_XT && EPI != EPI_SIGN_ACT) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+  }
 
   // Accumulator element r of tile (i, j) is output row
   //   m = m0 + wm*WM + 16*i + 4*kg + r,   column n = n0 + wn*WN + 16*j + col.
@@ -547,10 +562,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
     }
   };
 
-  if constexpr (EPI == EPI_SIGN_ACT) {   // the rotated rows themselves, as EPI_ACT writes them
-    stage_begin();
-    store_act(g.Yact, g.ldy, g.batchY);
-  }
   if constexpr (EPI == EPI_SIGN || EPI == EPI_SIGN_ACT || EPI == EPI_SIGN_XT) {
     // St is the transpose of the accumulator tile.  Storing it straight from the registers gives every lane 8 bytes of
     // a different row (64 cache lines per store instruction); instead each wavefront transposes its WM x WN block
@@ -605,7 +616,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
       const int n = nw + r, m = mw + c * 8;
       const uint4 v = *reinterpret_cast<const uint4*>(stg + r * SROW + (sign_chunk(r, c) << 4));
       if (n < g.N && m < g.st_rows_valid) *reinterpret_cast<uint4*>(St + (int64_t)n * g.ldc + m) = v;
+      if (it2 % 8 == 7) __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (EPI == EPI_SIGN_ACT) store_act(g.Yact, g.ldy, g.batchY);   // the rotated rows themselves, as EPI_ACT writes them
     if constexpr (EPI == EPI_SIGN_XT) {
       // The scaled, transposed fp16 copy of A's block under this wavefront's output block: tokens [mw, mw + WM) x
       // channels [nw, nw + WN).  A lane takes items (token pair p, 16-byte chunk c of 8 channels), chunk fastest so
@@ -668,47 +681,48 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   } else if constexpr (EPI == EPI_GRAMW) {
     const int64_t boff = (int64_t)bz * g.batchC;
     [[maybe_unused]] const bool mirror = SYM && tm != tn;   // this tile is also the transpose of tile (tn, tm)
-    double rsum = 0.0;
-    // Only a workgroup whose tile meets the diagonal has entries of the identity to add and subtract: the others run the
-    // version of the code without them (a wave-uniform choice).
-    auto write = [&](auto on_diagonal) {
-      constexpr bool DIAG = decltype(on_diagonal)::value;
-      auto eye = [&](int i, int j, int r) { return (mw + 4 * kg + 16 * i + r == nw + 16 * j + col) ? 1.0f : 0.0f; };
+    // The identity: of a 16 x 16 tile on the diagonal (a wave-uniform choice, `on`) the entries 4 kg + r == col.  One
+    // multiply-add per entry whether the tile meets the diagonal or not: two versions of the walks cost more registers than
+    // the largest tile has.
+    auto on = [&](int i, int j) { return mw + 16 * i == nw + 16 * j ? 1.0f : 0.0f; };
+    f32x4 eye;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) eye[r] = 4 * kg + r == col ? 1.0f : 0.0f;
+    auto val = [&](int i, int j) {
+      const float cg = again(g.coef_g), ci = again(g.coef_i * on(i, j));
+      f32x4 w;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w[r] = fmaf(ci, eye[r], cg * acc[i][j][r]);
+      return w;
+    };
+    auto plane = [&](auto p) {
+      const auto rP = out_rsrc(g.Pn + decltype(p)::value * g.plane_out + boff, nat_rows * 2u);
+      const auto rM = out_rsrc(g.Pn + decltype(p)::value * g.plane_out + boff, mirror ? nat_rows * 2u : 0u);   // (a diagonal tile's mirror image: dropped)
+      store_plane(p, val, rP, true, rM, SYM);
+    };
+    stage_begin();
+    plane(Plane0{});
+    if constexpr (!F16) {   // fp16 operands: the factor is one fp16 plane, and nobody asks for the residual
+      if (g.np_out > 1) plane(Plane1{});
+      if (g.np_out > 2) plane(Plane2{});
+    }
+    if (!F16 && g.resid_part) {
+      double rsum = 0.0;
 #pragma unroll
       for (int i = 0; i < TM; ++i) {
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
+          const float o = on(i, j);
           float part = 0.0f;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            const float d = DIAG ? acc[i][j][r] - eye(i, j, r) : acc[i][j][r];
+            const float d = fmaf(-o, eye[r], acc[i][j][r]);
             part += d * d;
           }
           rsum += (double)((n_ok[j] && 16 * i < mlim) ? part : 0.0f);   // rows 16 i .. + 3 of the lane's block (M is a multiple of 4)
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      auto val = [&](int i, int j) {
-        const float cg = again(g.coef_g), ci = again(g.coef_i);
-        f32x4 w;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) w[r] = DIAG ? fmaf(ci, eye(i, j, r), cg * acc[i][j][r]) : cg * acc[i][j][r];
-        return w;
-      };
-      auto plane = [&](auto p) {
-        const auto rP = out_rsrc(g.Pn + decltype(p)::value * g.plane_out + boff, nat_rows * 2u);
-        store_plane(p, val, rP, true, rP, mirror);
-      };
-      plane(Plane0{});
-      if constexpr (!F16) {   // fp16 operands: the factor is one fp16 plane
-        if (g.np_out > 1) plane(Plane1{});
-        if (g.np_out > 2) plane(Plane2{});
-      }
-    };
-    stage_begin();
-    if (m0 < n0 + BN && n0 < m0 + BM) write(std::true_type{});
-    else write(std::false_type{});
-    if (g.resid_part) {
       rsum = wave_sum_d(rsum);
       if (lane == 0) {
         g.resid_part[((int64_t)bz * ntiles + tn * tiles_m + tm) * NW + wave] = rsum;
@@ -870,43 +884,45 @@ constexpr Tile kTiles[] = {{256, 256, 2, 2, 10.0f, 1.30f}, {256, 128, 2, 2, 8.5f
                            {192, 192, 2, 2, 8.5f, 0.75f}};
 constexpr int kNumTiles = 5;
 
-// Expected time of `tiles` workgroups of tile t with K elements each.  The large tiles fill a CU's LDS: whole rounds of 256.
+// Whether an epilogue's registers fit beside the 256 accumulators per lane of the 256 x 256 tile.  Those that change the
+// accumulators in place or walk over them for a varying number of planes do not (64 .. 970 bytes per lane of scratch): they
+// take the next best tile, in most cases 192 x 192.  None of them runs more than twice in an update.
+constexpr bool fits_largest(int epi, bool f16) {
+  return !(epi == EPI_SQUARE || (!f16 && (epi == EPI_GRAMW || epi == EPI_XOUT)));
+}
+
+// Expected time of `tiles` workgroups of tile t with `steps` K steps each.  The large tiles fill a CU's LDS: whole rounds of 256.
 // Three 64 x 64 workgroups share one: up to 768 start at once, and a step of n sharing a CU takes 0.26 + 0.22 (n - 1) us.
 // Against the rule before (rounds x area / efficiency, without K): accumulate of 1024 tokens at d = 3072 36.6 -> 29.6 us
 // (192 instead of 256 wide), of 512 at d = 2048 18.0 -> 14.4; 1500 tokens of d = 1104 rotated for the statistics 19.1 -> 17.1
 // and the update there 352 -> 330 (64 instead of 128 wide); 32 heads of width 64, 2048 tokens 20.5 -> 16.6.
-double tile_time(int t, int64_t tiles, int K) {
-  const double steps = (K + BK - 1) / BK;
+double tile_time(int t, int64_t tiles, double steps) {
   const int64_t rounds = (tiles + 255) / 256;
   if (t == 3) return kTiles[t].t0 * (tiles > 768 ? tiles / 768.0 : 1.0) + steps * (kTiles[t].ts + 0.22 * (double)(rounds - 1));
   return (double)rounds * (kTiles[t].t0 + steps * kTiles[t].ts);
 }
 
-int pick_tile(int M, int N, int K, int batch) {
-  int best = 0;
-  double best_time = 1e300;
-  for (int t = 0; t < kNumTiles; ++t) {
-    const int64_t tiles = (int64_t)((M + kTiles[t].bm - 1) / kTiles[t].bm) * ((N + kTiles[t].bn - 1) / kTiles[t].bn) * batch;
-    const double time = tile_time(t, tiles, K);
-    if (time < best_time) { best_time = time; best = t; }
-  }
-  return best;
-}
+constexpr int kSymMinTiles = 8;   // tiles per side from which the mirrored form of a symmetric product is used
 
-constexpr int kSymMinTiles = 8;   // tiles per side from which the mirrored form is used
+struct Choice { int tile; bool sym; int64_t tiles; };   // tiles: workgroups per batch entry
 
-// Tile for a symmetric product (M x M x M; only the t (t + 1) / 2 tiles on and above the diagonal run), or -1 if no square
-// tile gives at least kSymMinTiles per side.  Counting the tiles that really run matters: at 4096 the 256 x 256 tile leaves 136
-// workgroups on 256 compute units, the 192 x 192 tile 253.
-int pick_tile_sym(int M, int batch) {
-  int best = -1;
-  double best_time = 1e300;
-  for (int t = 0; t < kNumTiles; ++t) {
-    if (kTiles[t].bm != kTiles[t].bn) continue;
-    const int64_t side = (M + kTiles[t].bm - 1) / kTiles[t].bm;
-    if (side < kSymMinTiles) continue;
-    const double time = tile_time(t, side * (side + 1) / 2 * batch, M);
-    if (time < best_time) { best_time = time; best = t; }
+// The tile of the least expected time.  A symmetric product whose square tiles give at least kSymMinTiles per side runs the
+// t (t + 1) / 2 of them on and above the diagonal only, and is compared by the count that really runs: at 4096 the
+// 256 x 256 tile leaves 136 workgroups on 256 compute units, the 192 x 192 tile 253.
+Choice choose(const GemmArgs& a, GemmEpilogue epi, int batch) {
+  const double steps = (a.K + BK - 1) / BK;
+  const bool sym_epi = a.symmetric && (epi == EPI_GRAMW || epi == EPI_SQUARE || epi == EPI_FRO2);
+  Choice best{-1, false, 0};
+  for (int sym = sym_epi ? 1 : 0; sym >= 0 && best.tile < 0; --sym) {
+    double best_time = 1e300;
+    for (int t = 0; t < kNumTiles; ++t) {
+      if (t == 0 && !fits_largest(epi, a.ab_f16)) continue;
+      const int64_t tm = (a.M + kTiles[t].bm - 1) / kTiles[t].bm, tn = (a.N + kTiles[t].bn - 1) / kTiles[t].bn;
+      if (sym && (kTiles[t].bm != kTiles[t].bn || tm < kSymMinTiles)) continue;
+      const int64_t tiles = sym ? tm * (tm + 1) / 2 : tm * tn;
+      const double time = tile_time(t, tiles * batch, steps);
+      if (time < best_time) { best_time = time; best = Choice{t, sym != 0, tiles}; }
+    }
   }
   return best;
 }
@@ -929,63 +945,64 @@ hipError_t launch_one(const GemmArgs& a, int batch, hipStream_t stream) {
 
 template <int EPI, bool F16 = false>
 hipError_t launch_epi(const GemmArgs& a, int batch, hipStream_t stream) {
+  const Choice c = choose(a, (GemmEpilogue)EPI, batch);
+  constexpr bool LARGEST = fits_largest(EPI, F16);
   if constexpr (EPI == EPI_GRAMW || EPI == EPI_SQUARE || EPI == EPI_FRO2) {
-    if (a.symmetric) {   // tiles on and above the diagonal only, where a square tile gives enough of them per side
-      switch (pick_tile_sym(a.M, batch)) {
-        case 0: return launch_one<256, 256, 2, 2, 2, EPI, F16, true>(a, batch, stream);
+    if (c.sym) {   // tiles on and above the diagonal only
+      switch (c.tile) {
+        case 0: if constexpr (LARGEST) return launch_one<256, 256, 2, 2, 2, EPI, F16, true>(a, batch, stream); break;
         case 2: return launch_one<128, 128, 2, 2, 3, EPI, F16, true>(a, batch, stream);
         case 4: return launch_one<192, 192, 2, 2, 3, EPI, F16, true>(a, batch, stream);
-        case 3: return launch_one<64, 64, 2, 2, 3, EPI, F16, true>(a, batch, stream);
-        default: break;
+        default: return launch_one<64, 64, 2, 2, 3, EPI, F16, true>(a, batch, stream);
       }
     }
   }
-  switch (pick_tile(a.M, a.N, a.K, batch)) {
+  switch (c.tile) {
     // LDS stages: as many 64-deep tiles as fit (two of 64 KiB for 256 x 256; smaller tiles take a third, which
     // puts two K steps instead of one between a load's issue and its use)
-    case 0: return launch_one<256, 256, 2, 2, 2, EPI, F16>(a, batch, stream);
+    case 0: if constexpr (LARGEST) return launch_one<256, 256, 2, 2, 2, EPI, F16>(a, batch, stream); break;
     case 1: return launch_one<256, 128, 2, 2, 3, EPI, F16>(a, batch, stream);
     case 2: return launch_one<128, 128, 2, 2, 3, EPI, F16>(a, batch, stream);
     case 4: return launch_one<192, 192, 2, 2, 3, EPI, F16>(a, batch, stream);
     default: return launch_one<64, 64, 2, 2, 3, EPI, F16>(a, batch, stream);
   }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
 
-int gemm_num_partials(int M, int batch, int symmetric) {
-  const int N = M;
-  int t = pick_tile(M, N, M, batch);
-  if (symmetric) {
-    const int ts = pick_tile_sym(M, batch);
-    if (ts >= 0) t = ts;
-  }
-  const Tile& u = kTiles[t];
-  return ((M + u.bm - 1) / u.bm) * ((N + u.bn - 1) / u.bn) * u.wgm * u.wgn;
+// For tests (host code only): the tile launch_gemm_nt takes for such a launch, as { rows, columns, wavefronts, workgroups per
+// batch entry, 1 if mirrored }.
+extern "C" __attribute__((visibility("default"))) void conqur_gemm_tile_for_tests(int epi, int f16, int symmetric, int M, int N, int K, int nseg,
+                                                                                  int batch, int* out) {
+  GemmArgs a{};
+  a.M = M; a.N = N; a.K = K; a.nseg = nseg; a.ab_f16 = f16; a.symmetric = symmetric;
+  const Choice c = choose(a, (GemmEpilogue)epi, batch);
+  const Tile& u = kTiles[c.tile];
+  out[0] = u.bm; out[1] = u.bn; out[2] = u.wgm * u.wgn; out[3] = (int)c.tiles; out[4] = c.sym;
+}
+
+int gemm_num_workgroups(const GemmArgs& a, GemmEpilogue epi, int batch) { return (int)(choose(a, epi, batch).tiles * batch); }
+
+int gemm_num_partials(const GemmArgs& a, GemmEpilogue epi, int batch) {
+  const Tile& u = kTiles[choose(a, epi, batch).tile];   // (a mirrored tile has slots of its own)
+  return ((a.M + u.bm - 1) / u.bm) * ((a.N + u.bn - 1) / u.bn) * u.wgm * u.wgn;
+}
+
+int gemm_max_partials(int M) {
+  const Tile& u = kTiles[3];
+  return ((M + u.bm - 1) / u.bm) * ((M + u.bn - 1) / u.bn) * u.wgm * u.wgn;
 }
 
 double gemm_issued_flop(const GemmArgs& a, GemmEpilogue epi, int batch) {
-  int t = pick_tile(a.M, a.N, a.K, batch);
-  bool sym = false;
-  if (a.symmetric && (epi == EPI_GRAMW || epi == EPI_SQUARE || epi == EPI_FRO2)) {
-    const int ts = pick_tile_sym(a.M, batch);
-    if (ts >= 0) { t = ts; sym = true; }
-  }
-  const Tile& u = kTiles[t];
-  const int64_t tm = (a.M + u.bm - 1) / u.bm, tn = (a.N + u.bn - 1) / u.bn;
-  const int64_t tiles = sym ? tm * (tm + 1) / 2 : tm * tn;
-  return 2.0 * (double)tiles * u.bm * u.bn * (double)a.K * a.nseg * batch;
-}
-
-int gemm_num_workgroups(int M, int N, int K, int batch) {
-  const Tile& t = kTiles[pick_tile(M, N, K, batch)];
-  return ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * batch;
+  const Choice c = choose(a, epi, batch);
+  return 2.0 * (double)c.tiles * kTiles[c.tile].bm * kTiles[c.tile].bn * (double)a.K * a.nseg * batch;
 }
 
 hipError_t launch_gemm_nt(const GemmArgs& a, GemmEpilogue epi, int batch, hipStream_t stream) {
   if (a.M <= 0 || a.N <= 0 || a.K <= 0 || (a.K & 7) || (a.lda & 7) || (a.ldb & 7) || a.nseg < 1 || a.nseg > kMaxSegments ||
       batch < 1 || (a.ab_f16 && epi != EPI_F32 && epi != EPI_GRAMW && epi != EPI_XOUT && epi != EPI_XLAST) ||
-      (a.ab_f16 && ((epi == EPI_GRAMW && a.np_out != 1) ||
+      (a.ab_f16 && ((epi == EPI_GRAMW && (a.np_out != 1 || a.resid_part)) ||
                     (epi == EPI_XOUT && (a.np_out != 1 || a.np_out_n != 1 || a.Xadd || a.C32)))) || (int64_t)a.M * a.lda >= (1ll << 30) || (int64_t)a.N * a.ldb >= (1ll << 30))
     return hipErrorInvalidValue;
   if (a.symmetric && ((epi != EPI_GRAMW && epi != EPI_SQUARE && epi != EPI_FRO2) || (epi != EPI_FRO2 && a.A != a.B) ||

@@ -1335,3 +1335,43 @@ def test_statistics_step_of_few_rows(B, d, heads, dtype):
     finally:
         one.close()
         both.close()
+
+
+EPI_GRAMW, EPI_SQUARE = 3, 5
+
+
+def gemm_tile(B, epi, f16, symmetric, M, N, K, nseg=1, batch=1):
+    """(rows, columns, wavefronts, workgroups per batch entry, mirrored) of the tile the GEMM launcher takes."""
+    import ctypes
+    out = (ctypes.c_int * 5)()
+    B.load().conqur_gemm_tile_for_tests(epi, f16, symmetric, M, N, K, nseg, batch, out)
+    return tuple(out)
+
+
+@pytest.mark.parametrize("precision,verify", [(0, 0), (0, 1), (1, 1), (2, 0)])
+def test_planted_polar_on_mirrored_256_tiles(B, precision, verify):
+    """A = U diag(s) V^T (U, V orthogonal, s from 1 to 1e-3), polar(A) = U V^T, at a width whose symmetric fp16 products take the
+    mirrored 256 x 256 tile, ragged at the last tile row and column, and whose closing products (two and three planes, D^2)
+    take smaller tiles, with another count of partial sums."""
+    import torch
+    d = 4256
+    assert gemm_tile(B, EPI_GRAMW, 1, 1, d, d, d)[:3] == (256, 256, 4) and gemm_tile(B, EPI_GRAMW, 1, 1, d, d, d)[4] == 1
+    assert all(gemm_tile(B, e, 0, 1, d, d, d)[0] < 256 and gemm_tile(B, e, 0, 1, d, d, d)[4] == 1 for e in (EPI_GRAMW, EPI_SQUARE))
+    U, V = (torch.from_numpy(np.kron(I.random_orthogonal(56, k), I.random_orthogonal(76, k + 1))).to("cuda:0").double() for k in (5, 15))
+    s = torch.logspace(0, -3, d, dtype=torch.float64, device="cuda:0")
+    A = ((U * s) @ V.T.contiguous()).float().cpu().numpy()
+    cal = B.Calibrator(d, 1, "bf16", np.eye(d, dtype=np.float32), max_tokens=64, polar_precision=precision, polar_verify=verify)
+    try:
+        cal.set_state(M=A)
+        _, st = cal.update_rotation()
+        R = torch.from_numpy(cal.get_state(want_M=False)[0][0]).to("cuda:0").double()
+        orth = float(torch.linalg.matrix_norm(R.T.contiguous() @ R - torch.eye(d, dtype=torch.float64, device="cuda:0")))
+        best = float(s.sum())
+        got = float((R * torch.from_numpy(A).to("cuda:0").double()).sum())
+        say(f"  planted polar d={d} precision {precision} verify {verify}: iters={st[0]['iters']} orth={orth:.2e} "
+            f"objective {got / best - 1:+.1e} ms={st[0]['ms']:.2f}")
+        # reported: an upper estimate, or measured on the device, whose fp32 sums of d products add up to 1e-8 d over the matrix
+        assert orth <= TOL_ORTH and orth <= st[0]["orth_err"] + (1e-8 * d if verify else 0.0)
+        assert abs(got - best) <= TOL_REL * best
+    finally:
+        cal.close()
