@@ -2,8 +2,11 @@
 //
 // Tiling: a workgroup of WGM x WGN wavefronts owns a BM x BN tile of the output; each
 // 64-lane wavefront owns (BM/WGM) x (BN/WGN) as a grid of 16x16 MFMA tiles
-// (v_mfma_f32_16x16x32_bf16 / _f16, fp32 accumulators), 4 wavefronts (1 per SIMD) in
-// every tile.
+// (v_mfma_f32_16x16x32_bf16 / _f16, fp32 accumulators).  4 wavefronts (1 per SIMD) in the
+// tiles that run the polar products, 8 in 256 x 128, which mostly rotates: its launches are
+// one round of short K loops, and the sign and row epilogues wait on memory and LDS as much
+// as they work (2048 x 3072 x 3072 rotated 42.0 us with 4 wavefronts, 40.0 with 8; with corner
+// signs and the transposed operand 45.7 and 40.8).
 //
 // These kernels are limited by power and by LDS reads, so both choices are about what a
 // multiply-add costs besides the MFMA itself.  A 128 x 128 wavefront tile reads 128 KiB of
@@ -308,6 +311,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   }
   const unsigned long long pr_w2 = g.clk ? wall_clock64() : 0, pr_c2 = g.clk ? clock64() : 0;
   wait_vmcnt<0>();   // drain the padding loads before the epilogue reuses nothing of LDS (keeps exit clean)
+  // The epilogues read accumulators in inline asm (cvt_bf16x2_again), for which the compiler keeps no distance from the MFMA
+  // that writes them: 20 wait states, more than any MFMA needs, stand here once.
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
   // The 256 accumulators of the largest tile fill one half of the registers.  Left to itself the compiler moves them over to
   // the other half for the epilogue's arithmetic, all at once, and spills what that half held.  Pinned to their half here,
   // they are read from it where they are used.  (The two sign epilogues that store a second array spill with the pin and
@@ -880,15 +888,23 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
 // Tiles, with what a workgroup that has its CU to itself takes: t0 us outside the main loop and ts per K step of 64 (fits to
 // rotate, accumulate and polar launches at 16 .. 10500 tokens and widths 64 .. 8192).  192: fills the chip exactly at 3072.
 struct Tile { int bm, bn, wgm, wgn; float t0, ts; };
-constexpr Tile kTiles[] = {{256, 256, 2, 2, 10.0f, 1.30f}, {256, 128, 2, 2, 8.5f, 0.72f}, {128, 128, 2, 2, 6.5f, 0.42f}, {64, 64, 2, 2, 4.5f, 0.26f},
-                           {192, 192, 2, 2, 8.5f, 0.75f}};
-constexpr int kNumTiles = 5;
+constexpr Tile kTiles[] = {{256, 256, 2, 2, 10.0f, 1.30f}, {256, 128, 4, 2, 6.5f, 0.72f}, {128, 128, 2, 2, 6.5f, 0.42f}, {64, 64, 2, 2, 4.5f, 0.26f},
+                           {192, 192, 2, 2, 8.5f, 0.75f}, {256, 256, 2, 4, 8.5f, 1.34f}};
+constexpr int kNumTiles = 6;
 
 // Whether an epilogue's registers fit beside the 256 accumulators per lane of the 256 x 256 tile.  Those that change the
 // accumulators in place or walk over them for a varying number of planes do not (64 .. 970 bytes per lane of scratch): they
 // take the next best tile, in most cases 192 x 192.  None of them runs more than twice in an update.
 constexpr bool fits_largest(int epi, bool f16) {
   return !(epi == EPI_SQUARE || (!f16 && (epi == EPI_GRAMW || epi == EPI_XOUT)));
+}
+
+// The largest tile in 8 wavefronts: a dearer K step (half as much LDS again is read), but less time outside the main loop,
+// where 4 wavefronts have little to cover a latency with.  For the launches whose epilogue weighs against a short K: 6713 x
+// 1584 rotated for the statistics 57.5 us in 4, 53.1 in 8; 432 tokens accumulated at d = 3280 30.8 and 28.6; but 8192 x 8192
+// rotated 354 and 374.  The polar products have K = width.
+constexpr bool fits_largest_8(int epi) {
+  return epi == EPI_ACT || epi == EPI_SIGN || epi == EPI_SIGN_ACT || epi == EPI_SIGN_XT || epi == EPI_F32;
 }
 
 // Expected time of `tiles` workgroups of tile t with `steps` K steps each.  The large tiles fill a CU's LDS: whole rounds of 256.
@@ -916,7 +932,7 @@ Choice choose(const GemmArgs& a, GemmEpilogue epi, int batch) {
   for (int sym = sym_epi ? 1 : 0; sym >= 0 && best.tile < 0; --sym) {
     double best_time = 1e300;
     for (int t = 0; t < kNumTiles; ++t) {
-      if (t == 0 && !fits_largest(epi, a.ab_f16)) continue;
+      if ((t == 0 && !fits_largest(epi, a.ab_f16)) || (t == 5 && !fits_largest_8(epi))) continue;
       const int64_t tm = (a.M + kTiles[t].bm - 1) / kTiles[t].bm, tn = (a.N + kTiles[t].bn - 1) / kTiles[t].bn;
       if (sym && (kTiles[t].bm != kTiles[t].bn || tm < kSymMinTiles)) continue;
       const int64_t tiles = sym ? tm * (tm + 1) / 2 : tm * tn;
@@ -961,9 +977,10 @@ hipError_t launch_epi(const GemmArgs& a, int batch, hipStream_t stream) {
     // LDS stages: as many 64-deep tiles as fit (two of 64 KiB for 256 x 256; smaller tiles take a third, which
     // puts two K steps instead of one between a load's issue and its use)
     case 0: if constexpr (LARGEST) return launch_one<256, 256, 2, 2, 2, EPI, F16>(a, batch, stream); break;
-    case 1: return launch_one<256, 128, 2, 2, 3, EPI, F16>(a, batch, stream);
+    case 1: return launch_one<256, 128, 4, 2, 3, EPI, F16>(a, batch, stream);
     case 2: return launch_one<128, 128, 2, 2, 3, EPI, F16>(a, batch, stream);
     case 4: return launch_one<192, 192, 2, 2, 3, EPI, F16>(a, batch, stream);
+    case 5: if constexpr (fits_largest_8(EPI)) return launch_one<256, 256, 2, 4, 2, EPI, F16>(a, batch, stream); break;
     default: return launch_one<64, 64, 2, 2, 3, EPI, F16>(a, batch, stream);
   }
   return hipErrorInvalidValue;

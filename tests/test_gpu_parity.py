@@ -1375,3 +1375,45 @@ def test_planted_polar_on_mirrored_256_tiles(B, precision, verify):
         assert abs(got - best) <= TOL_REL * best
     finally:
         cal.close()
+
+
+EPI_ACT, EPI_F32, EPI_SIGN_ACT, EPI_SIGN_XT = 1, 2, 8, 9
+
+
+@pytest.mark.parametrize("T,d,rotate,accumulate", [
+    (6713, 1584, (256, 256, 8), (128, 128, 4)), (2003, 3152, (256, 128, 8), (256, 256, 8)), (8185, 4096, (256, 256, 4), (256, 256, 4)),
+    (3001, 3072, (192, 192, 4), (192, 192, 4)), (2041, 2048, (128, 128, 4), (128, 128, 4))])
+def test_step_on_every_large_tile(B, T, d, rotate, accumulate):
+    """The statistics steps on the tiles of 4 and of 8 wavefronts, ragged in rows and columns: with and without the rotated rows the
+    same signs and the same M, signs that are those of the rows conqur_rotate gives, and M as these signs make it."""
+    import torch
+    K = (T + 63) // 64 * 64
+    assert all(gemm_tile(B, e, 0, 0, T, d, d)[:3] == rotate for e in (EPI_ACT, EPI_SIGN_ACT, EPI_SIGN_XT))
+    assert gemm_tile(B, EPI_F32, 1, 0, d, d, K)[:3] == accumulate
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(T)
+    R0 = (torch.randn((1, d, d), generator=g, device="cuda:0") / math.sqrt(d)).cpu().numpy()
+    X = torch.randn((T, d), generator=g, device="cuda:0").to(torch.bfloat16)
+    X[T // 2] = 0
+    cal = B.Calibrator(d, 1, "bf16", R0, max_tokens=T)
+    try:
+        cal.step_batch(X)
+        signs = torch.from_numpy(cal.last_corners(T)[0]).to("cuda:0")
+        M = cal.get_state(want_R=False)[1][0]
+        Y = cal.rotate(X)
+        want = torch.where(Y >= 0, 1, -1).to(torch.int8)
+        want[T // 2] = 0
+        assert torch.equal(signs, want)
+        x = X.float()
+        x /= x.norm(dim=1, keepdim=True).clamp_min(1e-30)
+        ref = (x.T.contiguous().double() @ (want.double() / math.sqrt(d))).cpu().numpy()
+        # sums of T terms x^ c: x^ in fp16 (2^-11 of it), a random walk of T such errors of 1 / d each; fp32 sums of T terms
+        assert np.abs(M - ref).max() <= 2.0 ** -10 * math.sqrt(T) * 6 / d, np.abs(M - ref).max()
+        for _ in range(2):                       # a second batch on top of the first: the accumulating form, in both steps
+            cal.step_batch_quant(X, 4, True, 0.9)
+        assert torch.equal(torch.from_numpy(cal.last_corners(T)[0]).to("cuda:0"), want)
+        M3 = cal.get_state(want_R=False)[1][0]
+        assert np.abs(M3 - 3 * M.astype(np.float64)).max() <= 2.0 ** -22 * np.abs(M).max() * 3
+        assert cal.batch_stats()[0]["rows"] == 3 * (T - 1) and cal.batch_stats()[0]["skipped"] == 3
+    finally:
+        cal.close()
