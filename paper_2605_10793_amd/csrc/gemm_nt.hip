@@ -907,14 +907,16 @@ constexpr bool fits_largest_8(int epi) {
   return epi == EPI_ACT || epi == EPI_SIGN || epi == EPI_SIGN_ACT || epi == EPI_SIGN_XT || epi == EPI_F32;
 }
 
-// Expected time of `tiles` workgroups of tile t with `steps` K steps each.  The large tiles fill a CU's LDS: whole rounds of 256.
-// Three 64 x 64 workgroups share one: up to 768 start at once, and a step of n sharing a CU takes 0.26 + 0.22 (n - 1) us.
-// Against the rule before (rounds x area / efficiency, without K): accumulate of 1024 tokens at d = 3072 36.6 -> 29.6 us
-// (192 instead of 256 wide), of 512 at d = 2048 18.0 -> 14.4; 1500 tokens of d = 1104 rotated for the statistics 19.1 -> 17.1
-// and the update there 352 -> 330 (64 instead of 128 wide); 32 heads of width 64, 2048 tokens 20.5 -> 16.6.
+// Expected time of `tiles` workgroups of tile t with `steps` K steps each, all segments counted.  The large tiles fill a CU's
+// LDS: whole rounds of 256.  Three 64 x 64 workgroups share one: up to 768 start at once, and a step of two or three sharing a
+// CU takes 0.48 or 0.75 us, three also 1 us more outside the loop.  (Constants chosen over 170 random shapes, rotate, accumulate and update launches of both dtypes,
+// every tile timed.)
 double tile_time(int t, int64_t tiles, double steps) {
   const int64_t rounds = (tiles + 255) / 256;
-  if (t == 3) return kTiles[t].t0 * (tiles > 768 ? tiles / 768.0 : 1.0) + steps * (kTiles[t].ts + 0.22 * (double)(rounds - 1));
+  if (t == 3) {
+    const double step = rounds <= 1 ? kTiles[t].ts : (rounds == 2 ? 0.48 : 0.75);
+    return (kTiles[t].t0 + (rounds > 2 ? 1.0 : 0.0) + steps * step) * (tiles > 768 ? tiles / 768.0 : 1.0);
+  }
   return (double)rounds * (kTiles[t].t0 + steps * kTiles[t].ts);
 }
 
@@ -926,7 +928,7 @@ struct Choice { int tile; bool sym; int64_t tiles; };   // tiles: workgroups per
 // t (t + 1) / 2 of them on and above the diagonal only, and is compared by the count that really runs: at 4096 the
 // 256 x 256 tile leaves 136 workgroups on 256 compute units, the 192 x 192 tile 253.
 Choice choose(const GemmArgs& a, GemmEpilogue epi, int batch) {
-  const double steps = (a.K + BK - 1) / BK;
+  const double steps = (double)((a.K + BK - 1) / BK) * a.nseg;
   const bool sym_epi = a.symmetric && (epi == EPI_GRAMW || epi == EPI_SQUARE || epi == EPI_FRO2);
   Choice best{-1, false, 0};
   for (int sym = sym_epi ? 1 : 0; sym >= 0 && best.tile < 0; --sym) {
