@@ -82,6 +82,7 @@ struct conqur_ctx {
   double* dot_part = nullptr;                        // [heads][(dh/64)^2] per-tile partials of <R, M>
   int64_t last_T = 0;
   size_t stat_words = 0;
+  double* fused_res = nullptr;                       // start of the result block: [2][heads] residuals of the one-launch update
   // heads of width 128 with bf16 activations take the fused step kernel (head_step.hip)
   bool head_fused = false;
   float* Mpart = nullptr;                            // [head_splits][heads][128][128] partial M of the token shares
@@ -101,7 +102,7 @@ struct conqur_ctx {
   bool ev_valid[ST_COUNT]{};
   hipEvent_t ev_resid = nullptr;   // behind the copy of a closing residual: the host waits for this, not for the stream
   hipEvent_t ev_sq = nullptr;      // behind the copy of ||D^2||_F^2 of the closing step's D^2 product
-  double* host_res = nullptr;      // pinned: [kResidSlots][heads] residual history, then the update's result block
+  double* host_res = nullptr;      // pinned: [kResidSlots][heads] residual history, then the update's result block (from fused_res on)
   float* host_rows = nullptr;      // pinned: per-row errors and energies of one score call (up to kHostSumRows rows)
   std::vector<void*> allocs;
 };
@@ -263,9 +264,11 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   // L, rows, skipped (fused per-head step) and the slot counters (general path) share one allocation so that one
   // fill clears the batch statistics
   ctx->stat_words = (size_t)3 * ctx->heads + (size_t)2 * kCountSlots * ctx->heads;
-  // The update's scalar results lie in front of them (one copy brings them to the host):
-  // <R_op, M> | <R, M> | ||M||_F^2 per head, then the non-finite flag, which is cleared with the statistics
-  A(dev_alloc(ctx, &ctx->ldot, (size_t)3 * ctx->heads + 1 + ctx->stat_words));
+  // The update's scalar results lie in front of them (one copy brings them to the host): ||I - G||_F^2 | ||D^2||_F^2 of a
+  // closing step in the main phase's launch, <R_op, M> | <R, M> | ||M||_F^2, all per head, then the non-finite flag, which is
+  // cleared with the statistics
+  A(dev_alloc(ctx, &ctx->fused_res, (size_t)5 * ctx->heads + 1 + ctx->stat_words));
+  ctx->ldot = ctx->fused_res + 2 * ctx->heads;
   ctx->L = ctx->ldot + 3 * ctx->heads + 1;
   ctx->rows = reinterpret_cast<unsigned long long*>(ctx->L + ctx->heads);
   ctx->skipped = ctx->rows + ctx->heads;
@@ -311,7 +314,7 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_resid, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_sq, hipEventDisableTiming);
   if (e == hipSuccess)
-    e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host_res), ((size_t)kResidSlots * ctx->heads + 3 * ctx->heads + 1) * sizeof(double),
+    e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host_res), ((size_t)kResidSlots * ctx->heads + 5 * ctx->heads + 1) * sizeof(double),
                       hipHostMallocDefault);
   if (e == hipSuccess)
     e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host_rows), (size_t)2 * std::min<size_t>(tmax, kHostSumRows) * sizeof(float),
@@ -809,6 +812,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   bool allow_fuse = true;    // (only the first main phase of an update: not the one after a nudge)
   int fused_slot = -1;       // narrow heads: the launch of the main phase also took the closing step (per head, if
                              // its residual allowed); residual slots fused_slot (||I - G||_F^2) and fused_slot + 1 (||D^2||_F^2)
+                             // of the history on the host (fused_res on the device)
   auto main_phase = [&](double l0, bool planes_ready) -> conqur_status {
     if (!planes_ready) HIP_TRY(launch_pack(ctx->PX, h, dh, dh, np_main, ctx->PXn[cur], ctx->PXt[cur], plane, s, main_f16));
     const double e_stop = np_main == 1 ? 4e-3 : 5e-4;   // the safety margins below floor the ripple near 2e-4
@@ -833,7 +837,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       const bool fuse = allow_fuse && !ctx->cfg.polar_verify && iters + sc.nsteps + 1 <= cap && slot + 2 < kResidSlots - 8;
       if (fuse) {
         hc.R = ctx->R; hc.RopT = ctx->RopT; hc.rop_planes = ctx->np; hc.rop_plane = plane; hc.M = ctx->M;
-        hc.res_out = ctx->resid + (size_t)slot * h; hc.sq_out = ctx->resid + (size_t)(slot + 1) * h; hc.inner_out = ctx->inner;
+        hc.res_out = ctx->fused_res; hc.sq_out = ctx->fused_res + h; hc.inner_out = ctx->inner;
         hc.res_max = (float)(1e-2 * std::sqrt((double)dh));
         fused_slot = slot;
         slot += 2;
@@ -907,10 +911,12 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   // and the bound from ||D^2||_F (see below) is within the tolerance; otherwise the general closing steps continue from
   // the hand-over state, which that launch wrote as well.  R and the operand of the heads that did take the step are replaced
   // by then; the launch has kept the previous rotation aside, for the nudge below and for an update that fails.  The
-  // statistics are cleared behind the outcome, in one launch with the non-finite flag.
-  double* const resblk = ctx->host_res + (size_t)kResidSlots * h;   // <R_op, M> | <R, M> | ||M||_F^2 | non-finite flag
+  // statistics and the non-finite flag are cleared on the device, unless a residual is not finite: the outcome and the result
+  // block come in one copy, and the host waits once, with nothing left to enqueue behind the outcome it expects.
+  double* const resblk = ctx->host_res + (size_t)(kResidSlots + 2) * h;   // <R_op, M> | <R, M> | ||M||_F^2 | non-finite flag
   const size_t resblk_bytes = ((size_t)3 * h + 1) * sizeof(double);
   bool r_replaced = false, fused_done = false;
+  int nonfinite = 0;
   auto fail_nonfinite = [&]() -> conqur_status {   // the context is left as the update found it
     if (r_replaced) {
       HIP_TRY(hipMemcpyAsync(ctx->R, ctx->Rprev, (size_t)plane * sizeof(float), hipMemcpyDeviceToDevice, s));
@@ -920,12 +926,14 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     return fail(ctx, CONQUR_ENONFINITE, "update_rotation: non-finite polar iterate");
   };
   auto fused_outcome = [&]() -> conqur_status {
-    if (timed) HIP_TRY(hipEventRecord(ctx->ev[ST_UPDATE][1], s));
-    HIP_TRY(hipMemcpyAsync(hist + (size_t)fused_slot * h, ctx->resid + (size_t)fused_slot * h, 2 * h * sizeof(double),
-                           hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(resblk, ctx->ldot, resblk_bytes, hipMemcpyDeviceToHost, s));
+    double* const outcome = resblk - 2 * h;
+    HIP_TRY(hipMemcpyAsync(outcome, ctx->fused_res, 2 * h * sizeof(double) + resblk_bytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(hipEventRecord(ctx->ev_resid, s));
+    HIP_TRY(launch_fill_zero_if_finite(ctx->fused_res, h, ctx->nonfinite, (1 + ctx->stat_words) * sizeof(double), s));
+    if (timed) HIP_TRY(hipEventRecord(ctx->ev[ST_UPDATE][1], s));
     HIP_TRY(hipEventSynchronize(ctx->ev_resid));
+    std::memcpy(hist + (size_t)fused_slot * h, outcome, 2 * h * sizeof(double));
+    std::memcpy(&nonfinite, resblk + 3 * h, sizeof(int));
     bool ok = true, finite = true;
     double worst_res = 0.0, worst_pred = 0.0;
     for (int q = 0; q < h; ++q) {
@@ -1069,16 +1077,17 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     if (st != CONQUR_OK) return st;
   }
   ctx->ev_valid[ST_UPDATE] = timed;
-  if (fused_done) {   // (the result block came with the outcome)
-    HIP_TRY(launch_fill_zero(ctx->nonfinite, (1 + ctx->stat_words) * sizeof(double), s));
-  } else {
+  if (!fused_done) {   // (else the result block came with the outcome)
     HIP_TRY(hipMemcpyAsync(resblk, ctx->ldot, resblk_bytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(launch_fill_zero(ctx->nonfinite, sizeof(int), s));
   }
   HIP_TRY(hipStreamSynchronize(s));
   const double *ldot = resblk, *inner = resblk + h, *fro2 = resblk + 2 * h;
-  int nonfinite = 0;
-  std::memcpy(&nonfinite, resblk + 3 * h, sizeof(int));
+  if (!fused_done) {
+    int flag = 0;
+    std::memcpy(&flag, resblk + 3 * h, sizeof(int));
+    nonfinite |= flag;   // (an outcome that was not accepted has brought the flag, and cleared it, already)
+  }
   ctx->m_empty = true;
   ctx->have_rows = false;
   ctx->h_empty.assign(h, 1);

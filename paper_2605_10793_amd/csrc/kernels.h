@@ -153,6 +153,8 @@ hipError_t launch_row_diag(const void* Y, int y_is_f32, int64_t T, int64_t ld, i
 // out[h] = sum of part[h][0..n) for h < heads, fixed order.
 hipError_t launch_sum_partials(const double* part, int n, int heads, double* out, hipStream_t s);
 
+// p (bytes a multiple of 4) cleared if the n values at v are all finite.
+hipError_t launch_fill_zero_if_finite(const double* v, int n, void* p, size_t bytes, hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 
 // Device address, on the current device, of the static array conqur_score_rows_static keeps its per-row results in

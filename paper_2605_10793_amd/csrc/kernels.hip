@@ -659,6 +659,14 @@ __global__ void __launch_bounds__(256) k_fill_zero(uint32_t* p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = 0u;
 }
 
+// p cleared if all n values are finite; every workgroup looks at all of them (a few hundred doubles at most).
+__global__ void __launch_bounds__(256) k_fill_zero_if_finite(const double* __restrict__ v, int n, uint32_t* __restrict__ p, size_t words) {
+  int bad = 0;
+  for (int i = threadIdx.x; i < n; i += 256) bad |= isfinite(v[i]) ? 0 : 1;
+  if (__syncthreads_or(bad)) return;
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (size_t)gridDim.x * 256) p[i] = 0u;
+}
+
 inline int grid_for(int64_t items, int cap = 4096) {
   int64_t g = (items + 255) / 256;
   if (g < 1) g = 1;
@@ -823,6 +831,12 @@ hipError_t launch_row_diag(const void* Y, int y_is_f32, int64_t T, int64_t ld, i
 
 hipError_t launch_sum_partials(const double* part, int n, int heads, double* out, hipStream_t s) {
   hipLaunchKernelGGL(k_sum_partials, dim3(heads), dim3(256), 0, s, part, n, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_fill_zero_if_finite(const double* v, int n, void* p, size_t bytes, hipStream_t s) {
+  const size_t words = bytes / 4;
+  hipLaunchKernelGGL(k_fill_zero_if_finite, dim3(grid_for((int64_t)words, 64)), dim3(256), 0, s, v, n, reinterpret_cast<uint32_t*>(p), words);
   return hipGetLastError();
 }
 
