@@ -152,6 +152,8 @@ conqur_status conqur_get_batch_stats(conqur_ctx* ctx, conqur_batch_stats* stats_
  * Returns CONQUR_ESTATE if no row was accumulated, CONQUR_ENOCONV if the cap was
  * hit (R is still replaced; stats->orth_err tells how good it is), and
  * CONQUR_ENONFINITE (after a successful update) if rows were skipped as non-finite.
+ * CONQUR_ENONFINITE is also returned when M itself is not finite; rotation, operand and
+ * statistics are then left as they were (conqur_last_error tells which of the two it is).
  */
 conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* stats_host);
 

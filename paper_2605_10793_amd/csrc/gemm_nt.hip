@@ -22,8 +22,9 @@
 //
 // LDS layout: a tile row is 64 bf16 = 128 bytes = 8 chunks of 16 bytes; chunk c of row r
 // sits at physical chunk c ^ ((r >> 1) & 7), which spreads any 16 consecutive rows of
-// one logical chunk (what a ds_read_b128 quarter-wave touches) over all 64 banks;
-// measured SQ_LDS_BANK_CONFLICT = 0.
+// one logical chunk (what a ds_read_b128 quarter-wave touches) over all 64 banks:
+// SQ_LDS_BANK_CONFLICT = 0 in the accumulate launch, whose epilogue leaves LDS alone (1.5 %
+// of the LDS-active cycles where the staged sign epilogue is in the launch).
 #include "gemm_nt.h"
 
 #include <algorithm>
@@ -899,6 +900,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
 
 // Tiles, with what a workgroup that has its CU to itself takes: t0 us outside the main loop and ts per K step of 64 (fits to
 // rotate, accumulate and polar launches at 16 .. 10500 tokens and widths 64 .. 8192).  192: fills the chip exactly at 3072.
+// The last form of the largest tile is the one in 8 wavefronts, for the launches fits_largest_8 names.
 struct Tile { int bm, bn, wgm, wgn; float t0, ts; };
 constexpr Tile kTiles[] = {{256, 256, 2, 2, 10.0f, 1.30f}, {256, 128, 4, 2, 6.5f, 0.72f}, {128, 128, 2, 2, 6.5f, 0.42f}, {64, 64, 2, 2, 4.5f, 0.26f},
                            {192, 192, 2, 2, 8.5f, 0.75f}, {256, 256, 2, 4, 8.5f, 1.34f}};
@@ -922,7 +924,9 @@ constexpr bool fits_largest_8(int epi) {
 // Expected time of `tiles` workgroups of tile t with `steps` K steps each, all segments counted.  The large tiles fill a CU's
 // LDS: whole rounds of 256.  Three 64 x 64 workgroups share one: up to 768 start at once, and a step of two or three sharing a
 // CU takes 0.48 or 0.75 us, three also 1 us more outside the loop.  (Constants chosen over 170 random shapes, rotate, accumulate and update launches of both dtypes,
-// every tile timed.)
+// every tile timed.)  The lines between 64 and 128 wide, us: 393 rows of 16 heads of width 384 rotated 13.2 (672 small tiles) and
+// 8.6; fp32, six segments, 815 rows of 8 x 384 50.7 (624) and 36.2, 663 x 1488 59.9 (264) and 76.5; 1500 x 1104 with signs 17.3 (432)
+// and 19.4; 2316 tokens of 32 heads of width 256 accumulated 38.0 (512, 37 steps) and 29.5.
 double tile_time(int t, int64_t tiles, double steps) {
   const int64_t rounds = (tiles + 255) / 256;
   if (t == 3) {

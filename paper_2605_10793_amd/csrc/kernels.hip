@@ -97,7 +97,7 @@ __global__ void __launch_bounds__(256) k_row_norms(const void* __restrict__ X, i
 
 // The same for narrow heads: LPS lanes per head slice, one 16-byte load each (slices of at most LPS chunks), so that a wavefront
 // takes 64 / LPS consecutive slices, which lie next to each other in memory.  A wavefront per slice leaves most lanes and
-// all but one load in flight unused: 32 heads of width 64, 2048 tokens 24.8 us, here 4.2 (8 MiB, 2 TB/s).  The lanes of a slice
+// all but one load in flight unused: 32 heads of width 64, 2048 tokens 24.8 us, here 4.7 (8 MiB, 1.8 TB/s).  The lanes of a slice
 // are added in the order of the whole wavefront's sum, the lanes beyond it being zero there: the same bits.
 template <bool F32, int LPS>
 __global__ void __launch_bounds__(256) k_row_norms_narrow(const void* __restrict__ X, int64_t T, int64_t stride, int heads, int dh,
