@@ -844,7 +844,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       } else {
         fused_slot = -1;
       }
-      HIP_TRY(launch_head_polar(ctx->PXn[cur], ctx->PXt[cur], h, dh, sc, ctx->PX, ctx->PXn[cur ^ 1], ctx->PXt[cur ^ 1],
+      HIP_TRY(launch_head_polar(ctx->PXt[cur], h, dh, sc, ctx->PX, ctx->PXn[cur ^ 1], ctx->PXt[cur ^ 1],
                                    fuse ? &hc : nullptr, (use_hstart && planes_ready) ? &hstart : nullptr, s));
       use_hstart = false;
       cur ^= 1;

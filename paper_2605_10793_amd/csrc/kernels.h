@@ -95,7 +95,7 @@ hipError_t launch_head_reduce(const float* Mpart, int nsplit, int heads, float* 
 
 // Main phase of the polar iteration for heads of width up to kHeadPolarMaxDh (a multiple of 16) in one launch
 // (head_polar.hip): runs the composed cubics X <- X (a_k I + b_k X^T X), k < nsteps, on single fp16 operand planes held in
-// LDS (11 significant bits).  Xn0 / Xt0: the start iterate as one natural and one transposed fp16 plane [heads][dh][dh].
+// LDS (11 significant bits).  Xt0: the start iterate as one transposed fp16 plane [heads][dh][dh].
 // Outputs, as the last step of the general path writes them: the result rounded to bf16, as X32 (fp32), Pt (one transposed
 // bf16 plane) and Pn (one natural bf16 plane).
 constexpr int kHeadPolarMaxDh = 128;
@@ -119,8 +119,8 @@ struct HeadPolarClose {
   double* inner_out;
   float res_max;
 };
-// start non-null: the launch forms the start iterate itself, X0 = (M + lambda tau R) / alpha per head (Xn0 / Xt0 unused,
-// may be null), from M and R (fp32 [heads][dh][dh]).  ||M_h||_F^2 is the sum of nparts partial sums per head
+// start non-null: the launch forms the start iterate itself, X0 = (M + lambda tau R) / alpha per head (Xt0 unused, may
+// be null), from M and R (fp32 [heads][dh][dh]).  ||M_h||_F^2 is the sum of nparts partial sums per head
 // (fro2_parts[h * nparts + p]), or taken from M in the launch (nparts = 0); it also goes to fro2_out[h].  ldot non-null:
 // ldot[h] = <R_op, M_h> (rop_dot; R_op = R rounded to bf16 if round_bf16, else R), or a copy of L[h].
 struct HeadPolarStart {
@@ -136,8 +136,8 @@ struct HeadPolarStart {
   int round_bf16;
   float* R_keep;       // non-null: a copy of R, which the closing step may replace in the same launch
 };
-hipError_t launch_head_polar(const bf16_bits* Xn0, const bf16_bits* Xt0, int heads, int dh, const PolarSchedule& sched, float* X32,
-                             bf16_bits* Pn, bf16_bits* Pt, const HeadPolarClose* close, const HeadPolarStart* start, hipStream_t s);
+hipError_t launch_head_polar(const bf16_bits* Xt0, int heads, int dh, const PolarSchedule& sched, float* X32, bf16_bits* Pn, bf16_bits* Pt,
+                             const HeadPolarClose* close, const HeadPolarStart* start, hipStream_t s);
 
 // Per-row fake-quantisation error of Y [T][ld] (bf16 or fp32) into row_sse / row_en, then their sums over rows:
 // out[0] = SSE, out[1] = energy (skipped if out is null).  zero_point = 0: symmetric quantiser; 1: zero-point quantiser on [clip*min, clip*max].

@@ -1420,3 +1420,34 @@ def test_step_on_every_large_tile(B, T, d, rotate, accumulate):
         assert cal.batch_stats()[0]["rows"] == 3 * (T - 1) and cal.batch_stats()[0]["skipped"] == 3
     finally:
         cal.close()
+
+
+@pytest.mark.parametrize("dh,dtype", [(16, "bf16"), (32, "f32"), (48, "bf16"), (64, "bf16"), (80, "f32"), (96, "bf16"), (112, "bf16"), (128, "bf16"), (128, "f32")])
+def test_one_launch_update_after_even_and_odd_step_counts(B, dh, dtype):
+    """Every square of the one-launch update (32, 64, 96, 128; filled and with a margin), with schedules of an even and an odd
+    number of steps, which start in different buffers, against polar(M + lambda tau R) in 64 bits.  The main phase holds the
+    iterate as fp16 (2^-11 a step) and hands it over rounded to bf16 (2^-9 of every entry); M's singular values lie in
+    [0.5, 1.5], so a step's rounding is not amplified: 2^-8 in the Frobenius norm."""
+    heads, rng = 3, np.random.default_rng(dh)
+    R0 = np.stack([np.linalg.qr(rng.standard_normal((dh, dh)))[0] for _ in range(heads)]).astype(np.float32)
+    M = np.stack([(np.linalg.qr(rng.standard_normal((dh, dh)))[0] * rng.uniform(0.5, 1.5, dh)) @ np.linalg.qr(rng.standard_normal((dh, dh)))[0]
+                  for _ in range(heads)]).astype(np.float32)
+    parities = set()
+    for lam in (0.03, 0.1, 0.3, 1.0, 3.0):
+        cal = B.Calibrator(dh * heads, heads, dtype, R0, max_tokens=64, prox_lambda=lam)
+        try:
+            cal.set_state(M=M)
+            _, st = cal.update_rotation()
+            R = cal.get_state(want_M=False)[0].astype(np.float64)
+        finally:
+            cal.close()
+        parities.add(st[0]["iters"] % 2)
+        for h in range(heads):
+            A = M[h].astype(np.float64) + lam * np.linalg.norm(M[h]) / math.sqrt(dh) * R0[h]
+            U, s, Vt = np.linalg.svd(A)
+            err = np.linalg.norm(R[h] - U @ Vt) / math.sqrt(dh)
+            say(f"  dh={dh} lam={lam} iters={st[0]['iters']} head {h}: err {err:.2e}, smallest sigma {s[-1] / s[0]:.2f}")
+            if s[-1] > 0.1 * s[0]:          # (the two terms may cancel in a direction)
+                assert err <= 2.0 ** -8
+            assert np.linalg.norm(R[h].T @ R[h] - np.eye(dh)) <= TOL_ORTH
+    assert parities == {0, 1}
