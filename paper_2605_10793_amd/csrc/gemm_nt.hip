@@ -419,7 +419,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   // values of accumulator (i, j).  (Column counts are multiples of 8: a chunk of 8 is inside or outside as a whole.)
   [[maybe_unused]] auto store_nat16 = [&](__amdgpu_buffer_rsrc_t r, uint32_t origin, uint32_t pitch, auto&& quad) {
     constexpr int ROWB = WN * 2 + 16, ROWS = pass_rows(WM, ROWB), CPR = WN / 8;
-    static_assert(ROWS % 16 == 0 && (ROWS * CPR) % 64 == 0, "whole accumulator rows and wavefronts per pass");
+    static_assert(ROWS % 16 == 0, "whole accumulator rows per pass");
 #pragma unroll
     for (int h = 0; h < WM / ROWS; ++h) {
 #pragma unroll
@@ -436,10 +436,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
         __builtin_amdgcn_sched_barrier(0);   // (bounds what the scheduler keeps live: without these the kernels spill)
       }
 #pragma unroll
-      for (int q = 0; q < ROWS * CPR / 64; ++q) {
+      for (int q = 0; q < (ROWS * CPR + 63) / 64; ++q) {
         const int idx = q * 64 + lane, row = idx / CPR, c = idx % CPR;
-        const uint4 v = *reinterpret_cast<const uint4*>(slice + row * ROWB + c * 16);
-        st128(r, nw + 8 * c < g.N ? origin + ((uint32_t)(h * ROWS + row) * pitch + 8u * c) * 2u : kOobOffset, v);
+        const uint4 v = *reinterpret_cast<const uint4*>(slice + row * ROWB + c * 16);   // (lanes past the last row read LDS nobody stores)
+        st128(r, nw + 8 * c < g.N && ((ROWS * CPR) % 64 == 0 || row < ROWS) ? origin + ((uint32_t)(h * ROWS + row) * pitch + 8u * c) * 2u : kOobOffset, v);
         if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -448,7 +448,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   // the same plane transposed, row n of the block at origin + n * 2 pitch
   [[maybe_unused]] auto store_tr16 = [&](__amdgpu_buffer_rsrc_t r, uint32_t origin, uint32_t pitch, auto&& quad) {
     constexpr int ROWB = WM * 2 + 16, ROWS = pass_rows(WN, ROWB), CPR = WM / 8;
-    static_assert(ROWS % 16 == 0 && (ROWS * CPR) % 64 == 0, "whole accumulator columns and wavefronts per pass");
+    static_assert(ROWS % 16 == 0, "whole accumulator columns per pass");
 #pragma unroll
     for (int h = 0; h < WN / ROWS; ++h) {
 #pragma unroll
@@ -459,10 +459,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
         __builtin_amdgcn_sched_barrier(0);
       }
 #pragma unroll
-      for (int q = 0; q < ROWS * CPR / 64; ++q) {
+      for (int q = 0; q < (ROWS * CPR + 63) / 64; ++q) {
         const int idx = q * 64 + lane, row = idx / CPR, c = idx % CPR;
         const uint4 v = *reinterpret_cast<const uint4*>(slice + row * ROWB + c * 16);
-        st128(r, mw + 8 * c < g.M ? origin + ((uint32_t)(h * ROWS + row) * pitch + 8u * c) * 2u : kOobOffset, v);
+        st128(r, mw + 8 * c < g.M && ((ROWS * CPR) % 64 == 0 || row < ROWS) ? origin + ((uint32_t)(h * ROWS + row) * pitch + 8u * c) * 2u : kOobOffset, v);
         if (q % 8 == 7) __builtin_amdgcn_sched_barrier(0);
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -900,11 +900,13 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
 
 // Tiles, with what a workgroup that has its CU to itself takes: t0 us outside the main loop and ts per K step of 64 (fits to
 // rotate, accumulate and polar launches at 16 .. 10500 tokens and widths 64 .. 8192).  192: fills the chip exactly at 3072.
-// The last form of the largest tile is the one in 8 wavefronts, for the launches fits_largest_8 names.
+// The second form of the largest tile is the one in 8 wavefronts, for the launches fits_largest_8 names; the last four are for
+// the launches special_tile names.
 struct Tile { int bm, bn, wgm, wgn; float t0, ts; };
 constexpr Tile kTiles[] = {{256, 256, 2, 2, 10.0f, 1.30f}, {256, 128, 4, 2, 6.5f, 0.72f}, {128, 128, 2, 2, 6.5f, 0.42f}, {64, 64, 2, 2, 4.5f, 0.26f},
-                           {192, 192, 2, 2, 8.5f, 0.75f}, {256, 256, 2, 4, 8.5f, 1.34f}};
-constexpr int kNumTiles = 6;
+                           {192, 192, 2, 2, 8.5f, 0.75f}, {256, 256, 2, 4, 8.5f, 1.34f},
+                           {96, 96, 2, 2, 4.5f, 0.38f}, {160, 160, 2, 2, 5.5f, 0.69f}, {96, 64, 2, 2, 4.7f, 0.29f}, {128, 64, 2, 2, 6.2f, 0.45f}};
+constexpr int kNumTiles = 10;
 
 // Whether an epilogue's registers fit beside the 256 accumulators per lane of the 256 x 256 tile.  Those that change the
 // accumulators in place or walk over them for a varying number of planes do not (64 .. 970 bytes per lane of scratch): they
@@ -921,6 +923,22 @@ constexpr bool fits_largest_8(int epi) {
   return epi == EPI_ACT || epi == EPI_SIGN || epi == EPI_SIGN_ACT || epi == EPI_SIGN_XT || epi == EPI_F32;
 }
 
+// Tiles between the others' sizes, each for launches whose count of the others' tiles just misses the 256 compute units:
+//  96 x 96, 160 x 160   mirrored symmetric products: X^T X at 2048 253 tiles, 15.9 us (128 x 128 20.0), at 1792 14.2 (18.1); at
+//                       3072 210 tiles, 35.2 us (192 x 192 42.2), at 2832 33.2 (39.5), at 3328 38.9 (45.3)
+//  96 x 64              polar and accumulate products: 1104^3 216 tiles, 9.2 us (64 x 64, some sharing a compute unit, 10.0); among an
+//                       update's other launches 11.3 and 13.2, the correction 18.3 (128 x 128 24.0)
+//  128 x 64             signs and operand of heads up to 64 wide: 32 x 2048 x 64 8.4 us (256 x 128, half of it empty, 10.6); in a
+//                       step 13.3 and 15.3
+// (One launch after another on the same operands; the constants above are dearer, as operands just written by other units are.)
+constexpr bool special_tile(int t, int epi, bool sym) {
+  switch (t) {
+    case 6: case 7: return sym;
+    case 8: return epi == EPI_F32 || epi == EPI_XOUT || epi == EPI_XLAST || epi == EPI_XADD;
+    default: return epi == EPI_SIGN_XT;
+  }
+}
+
 // Expected time of `tiles` workgroups of tile t with `steps` K steps each, all segments counted.  The large tiles fill a CU's
 // LDS: whole rounds of 256.  Three 64 x 64 workgroups share one: up to 768 start at once, and a step of two or three sharing a
 // CU takes 0.48 or 0.75 us, three also 1 us more outside the loop.  (Constants chosen over 170 random shapes, rotate, accumulate and update launches of both dtypes,
@@ -933,6 +951,7 @@ double tile_time(int t, int64_t tiles, double steps) {
     const double step = rounds <= 1 ? kTiles[t].ts : (rounds == 2 ? 0.48 : 0.75);
     return (kTiles[t].t0 + (rounds > 2 ? 1.0 : 0.0) + steps * step) * (tiles > 768 ? tiles / 768.0 : 1.0);
   }
+  if (t == 9 && rounds > 1) return (double)((tiles + 511) / 512) * (kTiles[t].t0 + steps * 0.60);   // two share a compute unit
   return (double)rounds * (kTiles[t].t0 + steps * kTiles[t].ts);
 }
 
@@ -950,7 +969,7 @@ Choice choose(const GemmArgs& a, GemmEpilogue epi, int batch) {
   for (int sym = sym_epi ? 1 : 0; sym >= 0 && best.tile < 0; --sym) {
     double best_time = 1e300;
     for (int t = 0; t < kNumTiles; ++t) {
-      if ((t == 0 && !fits_largest(epi, a.ab_f16)) || (t == 5 && !fits_largest_8(epi))) continue;
+      if ((t == 0 && !fits_largest(epi, a.ab_f16)) || (t == 5 && !fits_largest_8(epi)) || (t > 5 && !special_tile(t, epi, sym))) continue;
       const int64_t tm = (a.M + kTiles[t].bm - 1) / kTiles[t].bm, tn = (a.N + kTiles[t].bn - 1) / kTiles[t].bn;
       if (sym && (kTiles[t].bm != kTiles[t].bn || tm < kSymMinTiles)) continue;
       const int64_t tiles = sym ? tm * (tm + 1) / 2 : tm * tn;
@@ -990,6 +1009,8 @@ hipError_t launch_epi(const GemmArgs& a, int batch, hipStream_t stream) {
         case 0: if constexpr (LARGEST) return launch_one<256, 256, 2, 2, 2, EPI, F16, true>(a, batch, stream); break;
         case 2: return launch_one<128, 128, 2, 2, 3, EPI, F16, true>(a, batch, stream);
         case 4: return launch_one<192, 192, 2, 2, 3, EPI, F16, true>(a, batch, stream);
+        case 6: return launch_one<96, 96, 2, 2, 3, EPI, F16, true>(a, batch, stream);
+        case 7: return launch_one<160, 160, 2, 2, 3, EPI, F16, true>(a, batch, stream);
         default: return launch_one<64, 64, 2, 2, 3, EPI, F16, true>(a, batch, stream);
       }
     }
@@ -1002,6 +1023,8 @@ hipError_t launch_epi(const GemmArgs& a, int batch, hipStream_t stream) {
     case 2: return launch_one<128, 128, 2, 2, 3, EPI, F16>(a, batch, stream);
     case 4: return launch_one<192, 192, 2, 2, 3, EPI, F16>(a, batch, stream);
     case 5: if constexpr (fits_largest_8(EPI)) return launch_one<256, 256, 2, 4, 2, EPI, F16>(a, batch, stream); break;
+    case 8: if constexpr (special_tile(8, EPI, false)) return launch_one<96, 64, 2, 2, 3, EPI, F16>(a, batch, stream); break;
+    case 9: if constexpr (special_tile(9, EPI, false)) return launch_one<128, 64, 2, 2, 3, EPI, F16>(a, batch, stream); break;
     default: return launch_one<64, 64, 2, 2, 3, EPI, F16>(a, batch, stream);
   }
   return hipErrorInvalidValue;

@@ -1380,7 +1380,7 @@ def test_planted_polar_on_mirrored_256_tiles(B, precision, verify):
         cal.close()
 
 
-EPI_ACT, EPI_F32, EPI_SIGN_ACT, EPI_SIGN_XT = 1, 2, 8, 9
+EPI_ACT, EPI_F32, EPI_SIGN_ACT, EPI_SIGN_XT, EPI_XOUT, EPI_XLAST = 1, 2, 8, 9, 4, 7
 
 
 @pytest.mark.parametrize("T,d,rotate,accumulate", [
@@ -1451,3 +1451,38 @@ def test_one_launch_update_after_even_and_odd_step_counts(B, dh, dtype):
                 assert err <= 2.0 ** -8
             assert np.linalg.norm(R[h].T @ R[h] - np.eye(dh)) <= TOL_ORTH
     assert parities == {0, 1}
+
+
+@pytest.mark.parametrize("a,b,gram,apply", [(31, 64, (96, 96), (128, 128)), (47, 64, (160, 160), (192, 192)), (23, 48, (64, 64), (96, 64))])
+def test_planted_polar_on_tiles_between_the_others(B, a, b, gram, apply):
+    """A = U diag(s) V^T (U, V orthogonal, s from 1 to 1e-3), polar(A) = U V^T, at widths whose symmetric products, or whose other
+    products, take the tiles between the others' sizes, ragged at the last tile row and column."""
+    import torch
+    d = a * b
+    assert gemm_tile(B, EPI_GRAMW, 1, 1, d, d, d)[:2] == gram and gemm_tile(B, EPI_GRAMW, 1, 1, d, d, d)[4] == 1 and d % gram[0]
+    assert gemm_tile(B, EPI_XOUT, 1, 0, d, d, d)[:2] == apply and gemm_tile(B, EPI_XLAST, 1, 0, d, d, d)[:2] == apply and d % apply[1]
+    U, V = (torch.from_numpy(np.kron(I.random_orthogonal(a, k), I.random_orthogonal(b, k + 1))).to("cuda:0").double() for k in (3, 13))
+    s = torch.logspace(0, -3, d, dtype=torch.float64, device="cuda:0")
+    A = ((U * s) @ V.T.contiguous()).float().cpu().numpy()
+    best = float(s.sum())
+    for verify in (0, 1):
+        cal = B.Calibrator(d, 1, "bf16", np.eye(d, dtype=np.float32), max_tokens=64, polar_verify=verify)
+        try:
+            cal.set_state(M=A)
+            _, st = cal.update_rotation()
+            R = torch.from_numpy(cal.get_state(want_M=False)[0][0]).to("cuda:0").double()
+            orth = float(torch.linalg.matrix_norm(R.T.contiguous() @ R - torch.eye(d, dtype=torch.float64, device="cuda:0")))
+            got = float((R * torch.from_numpy(A).to("cuda:0").double()).sum())
+            say(f"  planted polar d={d} verify {verify}: iters={st[0]['iters']} orth={orth:.2e} objective {got / best - 1:+.1e}")
+            assert orth <= TOL_ORTH and orth <= st[0]["orth_err"] + (1e-8 * d if verify else 0.0)
+            assert abs(got - best) <= TOL_REL * best
+        finally:
+            cal.close()
+
+
+@pytest.mark.parametrize("T", [2041, 1985])
+def test_step_of_heads_up_to_64_wide_on_their_tile(B, T):
+    """Signs, transposed operand and M of 32 heads of width 64 on the 128 x 64 tile, ragged in the rows, against the oracle."""
+    assert gemm_tile(B, EPI_SIGN_XT, 0, 0, T, 64, 64, 1, 32)[:2] == (128, 64)
+    w = I.small_workload(64 * 32, T, n_batches=1, heads=32, seed=64 + T, prox_lambda=0.1, massive_frac=0.01)
+    run_stream(B, w, 1, check_R=True)
