@@ -4,7 +4,8 @@
 // calibration path (rotate, accumulate, Gram, polynomial apply) is this kernel:
 // operands that are K-strided in their natural layout are produced transposed by
 // the kernel that writes them, and fp32-accurate products are obtained by feeding
-// bf16 split planes as several K-segments (hi*hi, hi*mid, mid*hi, ...).
+// bf16 split planes as several K-segments (hi*hi, hi*mid, mid*hi, ...), or, where six
+// of them rotate fp32 rows, from all planes of a K step in LDS together.
 #pragma once
 #include "common.h"
 

@@ -78,7 +78,7 @@ __device__ __forceinline__ float again(float x) {
 // the hardware returns zeros (also for loads whose destination is LDS).
 constexpr uint32_t kOobOffset = 0x80000000u;
 
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool F16, bool SYM>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool F16, bool SYM, int PLANES>
 __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int by_rows) {
   static_assert(!SYM || (BM == BN && (EPI == EPI_GRAMW || EPI == EPI_SQUARE || EPI == EPI_FRO2)),
                 "mirrored tiles: square tiles, symmetric results");
@@ -87,7 +87,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   constexpr int NLA = BM / 8, NLB = BN / 8;     // wave-wide 1 KiB loads per stage (8 tile rows each)
   constexpr int QA = NLA / NW, QB = NLB / NW;   // ... per wavefront
   static_assert(NLA % NW == 0 && NLB % NW == 0 && WM % 16 == 0 && WN % 16 == 0, "tile shape");
-  constexpr int STAGE = (BM + BN) * 128;
+  static_assert(PLANES == 1 || (PLANES == 3 && !F16 && !SYM), "split planes: the products of fp32 rows");
+  constexpr int PSTAGE = (BM + BN) * 128, STAGE = PLANES * PSTAGE;   // bytes of one plane of both operands, and of a stage
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // Optional clock probe (g.clk != null): wall-clock ticks (100 MHz) of the prologue, main loop and epilogue
   // of this workgroup and the shader-clock cycles of the main loop, from which the host derives the clock
@@ -170,7 +171,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   const uint32_t recA = (uint32_t)((((int64_t)g.M - 1) * g.lda + BK) * 2);
   const uint32_t recB = (uint32_t)((((int64_t)g.N - 1) * g.ldb + BK) * 2);
   const int nkb = (g.K + BK - 1) / BK;
-  const int nit = nkb * g.nseg;
+  const int nit = PLANES == 1 ? nkb * g.nseg : nkb;
   // Epilogues of the largest tile whose registers need help (see where the accumulators are pinned): a guard around the loop
   // costs them a second set of accumulators at its exit.  The others spill nothing either way, and the two that rotate or
   // accumulate lose up to 5 % without it (11008 x 4096 x 4096: 297 us instead of 282).
@@ -190,19 +191,29 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   // Issue state: the next tile to fetch is K step is_kb of segment is_s; its operand
   // pointers advance incrementally (wave-uniform, scalar registers).
   int is_s = 0, is_kb = 0;
-  const bf16_bits* pa = Ab + g.a_seg[0];
-  const bf16_bits* pb = Bb + g.b_seg[0];
+  const bf16_bits* pa = Ab + (PLANES == 1 ? g.a_seg[0] : 0);
+  const bf16_bits* pb = Bb + (PLANES == 1 ? g.b_seg[0] : 0);
   __amdgpu_buffer_rsrc_t ra, rb;
+  const bf16_bits *ga = pa, *gb = pb;   // split planes: the prepared tile, and the ranges of its descriptors
+  uint32_t rangeA = recA, rangeB = recB;
   bool tail = false;
   auto issue_prep = [&]() {
     // Past the last tile the pipeline keeps issuing (so that every step has the same
     // number of loads in flight and needs no branches); those loads get an empty
     // descriptor range, fetch nothing and write zeros to a stage nobody reads again.
-    const bool real = is_s < g.nseg;
-    ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_bits*>(pa), 0, real ? recA : 0u, 0x00020000);
-    rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_bits*>(pb), 0, real ? recB : 0u, 0x00020000);
+    const bool real = PLANES == 1 ? is_s < g.nseg : is_kb < nkb;
+    if constexpr (PLANES == 1) {
+      ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_bits*>(pa), 0, real ? recA : 0u, 0x00020000);
+      rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_bits*>(pb), 0, real ? recB : 0u, 0x00020000);
+    } else {
+      ga = pa; gb = pb;
+      rangeA = real ? recA : 0u; rangeB = real ? recB : 0u;
+    }
     tail = ktail && is_kb == nkb - 1;
-    if (++is_kb == nkb) {
+    if (PLANES > 1) {
+      ++is_kb;
+      pa += BK; pb += BK;
+    } else if (++is_kb == nkb) {
       is_kb = 0;
       ++is_s;
       const int sc = is_s < g.nseg ? is_s : g.nseg - 1;
@@ -212,8 +223,13 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
       pa += BK; pb += BK;
     }
   };
-  auto issue_one = [&](int q, int stage) {   // load q of LPT of the prepared tile
-    unsigned char* sa = smem + stage * STAGE;
+  auto issue_one = [&](int n, int stage) {   // load n of LPT of the prepared tile
+    const int p = PLANES == 1 ? 0 : n / (QA + QB), q = PLANES == 1 ? n : n % (QA + QB);
+    unsigned char* sa = smem + stage * STAGE + p * PSTAGE;
+    if constexpr (PLANES > 1) {   // (plane p of A is segment 2 - p of the six, of B segment p)
+      if (q < QA) ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_bits*>(ga) + g.a_seg[2 - p], 0, rangeA, 0x00020000);
+      else rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_bits*>(gb) + g.b_seg[p], 0, rangeB, 0x00020000);
+    }
     if (q < QA) {
       const uint32_t off = tail ? offAt[q] : offA[q];
       __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)(sa + (q * NW + wave) * 1024), 16,
@@ -227,12 +243,17 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   };
 
   f32x4 acc[TM][TN];
+  // split planes: hi * hi of a K step's second half, and all other products, summed apart
+  [[maybe_unused]] f32x4 acc2[PLANES > 1 ? TM : 1][TN], low[PLANES > 1 ? TM : 1][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.0f;
+      for (int e = 0; e < 4; ++e) {
+        acc[i][j][e] = 0.0f;
+        if constexpr (PLANES > 1) acc2[i][j][e] = low[i][j][e] = 0.0f;
+      }
 
   // Software pipeline.  LDS holds NSTAGE tiles; tile t lives in stage t % NSTAGE.
   // Operand fragments are double buffered in registers: while the MFMAs of K-substep
@@ -244,9 +265,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   // reading the current stage), refill the current stage with tile it+NSTAGE, read the
   // first fragments of the next tile, and cover that latency with the second half of the
   // substep's MFMAs.
-  constexpr int LPT = QA + QB;   // loads per thread per tile
+  constexpr int LPT = PLANES * (QA + QB);   // loads per thread per tile
   constexpr int KS = BK / 32;    // MFMA K-substeps per tile
-  constexpr int NMF = TM * TN, HALF = NMF / 2, NR = TM + TN;
+  constexpr int NMF = TM * TN * (PLANES == 1 ? 1 : 6), HALF = NMF / 2, NR = PLANES * (TM + TN);
   constexpr int RS = NMF / NR > 1 ? NMF / NR : 1;       // MFMAs between two fragment reads of a full substep
   constexpr int RH = HALF / NR > 1 ? HALF / NR : 1;     // ... of the half substep behind the barrier
   constexpr int R0 = NR > HALF ? NR - HALF : 0;         // reads issued ahead of that half (small tiles: more reads than MFMAs)
@@ -255,22 +276,33 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   constexpr int S1 = NMF / LQ1 > 4 ? 4 : (NMF / LQ1 > 1 ? NMF / LQ1 : 1);   // has less time to land before the next barrier)
   static_assert(KS == 2, "fragment double buffering: the two substeps of a step take one buffer each");
   static_assert(LQ2 * S2 <= HALF + S2 - 1 && LQ1 * S1 <= NMF + S1 - 1 && NR <= NMF, "every load and read has its MFMA");
-  bf16x8 fa[2][TM], fb[2][TN];
+  bf16x8 fa[2][PLANES][TM], fb[2][PLANES][TN];
 
-  auto read_frag = [&](int buf, int r, const unsigned char* sa, int kk) {
-    // read number r of a substep, in the order the MFMAs need them: a0, b0..b(TN-1), a1..a(TM-1)
-    const unsigned char* sb = sa + BM * 128;
-    if (r == 0) fa[buf][0] = *reinterpret_cast<const bf16x8*>(sa + lds_off(wm * WM + col, kk * 4 + kg));
-    else if (r <= TN) fb[buf][r - 1] = *reinterpret_cast<const bf16x8*>(sb + lds_off(wn * WN + (r - 1) * 16 + col, kk * 4 + kg));
-    else fa[buf][r - TN] = *reinterpret_cast<const bf16x8*>(sa + lds_off(wm * WM + (r - TN) * 16 + col, kk * 4 + kg));
+  // Products of split planes, smallest first: kSeg6 of the general form, but every K step takes all six from planes that are in
+  // LDS together (see kSplitTiles).
+  constexpr int kPA[6] = {2, 1, 0, 1, 0, 0}, kPB[6] = {0, 1, 2, 0, 1, 0};
+  auto read_frag = [&](int buf, int n, const unsigned char* stage_at, int kk) {
+    // read number n of a substep, in the order the MFMAs need them: a0, b0..b(TN-1), a1..a(TM-1); planes: A's in falling, B's in
+    // rising order
+    const int k = PLANES == 1 ? 0 : n / (TM + TN), r = PLANES == 1 ? n : n % (TM + TN), pA = PLANES - 1 - k, pB = k;
+    const unsigned char* sa = stage_at + pA * PSTAGE;
+    const unsigned char* sb = stage_at + pB * PSTAGE + BM * 128;
+    if (r == 0) fa[buf][pA][0] = *reinterpret_cast<const bf16x8*>(sa + lds_off(wm * WM + col, kk * 4 + kg));
+    else if (r <= TN) fb[buf][pB][r - 1] = *reinterpret_cast<const bf16x8*>(sb + lds_off(wn * WN + (r - 1) * 16 + col, kk * 4 + kg));
+    else fa[buf][pA][r - TN] = *reinterpret_cast<const bf16x8*>(sa + lds_off(wm * WM + (r - TN) * 16 + col, kk * 4 + kg));
   };
   auto mfma = [&](int buf, int m) {
-    const int i = m / TN, j = m % TN;
+    const int i = PLANES == 1 ? m / TN : m % (TM * TN) / TN, j = m % TN;
     if constexpr (F16)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, fa[buf][i]), __builtin_bit_cast(f16x8, fb[buf][j]),
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, fa[buf][0][i]), __builtin_bit_cast(f16x8, fb[buf][0][j]),
                                                          acc[i][j], 0, 0, 0);
-    else
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[buf][i], fb[buf][j], acc[i][j], 0, 0, 0);
+    else if constexpr (PLANES == 1)
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[buf][0][i], fb[buf][0][j], acc[i][j], 0, 0, 0);
+    else {
+      const int seg = m / (TM * TN);
+      f32x4& c = seg < 5 ? low[i][j] : (buf ? acc2[i][j] : acc[i][j]);   // (buf: the half of the K step)
+      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[buf][kPA[seg]][i], fb[buf][kPB[seg]][j], c, 0, 0, 0);
+    }
   };
 
 #pragma unroll
@@ -329,6 +361,12 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
+  if constexpr (PLANES > 1) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = (acc[i][j] + acc2[i][j]) + low[i][j];
+  }
   // The 256 accumulators of the largest tile fill one half of the registers.  Left to itself the compiler moves them over to
   // the other half for the epilogue's arithmetic, all at once, and spills what that half held.  Pinned to their half here,
   // they are read from it where they are used.  (The two sign epilogues that store a second array spill with the pin and
@@ -980,12 +1018,41 @@ Choice choose(const GemmArgs& a, GemmEpilogue epi, int batch) {
   return best;
 }
 
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool F16, bool SYM = false>
+// Rotations of fp32 rows: six products of three bf16 planes a side.  As six segments of the general form every plane is fetched
+// three times, and the rate at which the compute units fetch operands (13 to 14 TB/s over the chip) is what the launch waits for.
+// In split form a K step has all planes of both operands in LDS and takes the six products from there: half the bytes.  The five
+// small products are summed apart, so that they are not rounded at the result's magnitude in every step, and hi * hi in two
+// halves, which end at 0.7 of the result's magnitude: the error against 64 bits, 1.9e-7 as segments at 777 x 1040, is 1.4e-7 (0.72 to 0.81 of it for widths
+// 192 to 1040).  us, six segments on their best tile and split: 777 x 1040 x 1040 28.2 and 15.2; 2048 x 256 9.1 and 5.5; 400 x 784
+// 20.3 and 8.3; 4096 x 1024 61.7 and 46.1; 12000 x 304 25.3 and 18.8; 9000 x 1024 114 and 104.  From about that size on the
+// 256 x 256 segments fetch less for each product than 128 x 64 split ones: 12000 x 1024 125 and 131, 8192 x 1536 184 and 187.
+// Constants as in kTiles, whole rounds of 256 workgroups (a stage is 36, 48 or 72 KiB).  What is chosen depends on the problem's
+// sizes alone, so that rows and corner signs of a batch come from the same sums.
+constexpr Tile kSplitTiles[] = {{64, 64, 2, 2, 4.1f, 0.65f}, {32, 64, 2, 2, 3.1f, 0.42f}, {128, 64, 2, 2, 3.2f, 1.24f}};
+constexpr bool split_epilogue(int epi) { return epi == EPI_ACT || epi == EPI_SIGN || epi == EPI_SIGN_ACT; }
+
+// The tile of the split form, or -1: not such a product, or the segments are expected to be faster.
+int choose_split(const GemmArgs& a, GemmEpilogue epi, int batch) {
+  if (!split_epilogue(epi) || a.nseg != 6 || a.ab_f16) return -1;
+  const Choice seg = choose(a, epi, batch);
+  const int64_t steps = (a.K + BK - 1) / BK;
+  double best = tile_time(seg.tile, seg.tiles * batch, 6.0 * steps);
+  int t = -1;
+  for (int i = 0; i < 3; ++i) {
+    const Tile& u = kSplitTiles[i];
+    const int64_t tiles = (int64_t)((a.M + u.bm - 1) / u.bm) * ((a.N + u.bn - 1) / u.bn) * batch;
+    const double time = (double)((tiles + 255) / 256) * (u.t0 + steps * u.ts);
+    if (time < best) { best = time; t = i; }
+  }
+  return t;
+}
+
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool F16, bool SYM = false, int PLANES = 1>
 hipError_t launch_one(const GemmArgs& a, int batch, hipStream_t stream) {
-  constexpr int smem = NSTAGE * (BM + BN) * BK * 2;
+  constexpr int smem = NSTAGE * PLANES * (BM + BN) * BK * 2;
   static_assert(smem <= 160 * 1024, "LDS of one CU");
   static PerDeviceOnce configured;
-  auto kern = gemm_nt_kernel<BM, BN, WGM, WGN, NSTAGE, EPI, F16, SYM>;
+  auto kern = gemm_nt_kernel<BM, BN, WGM, WGN, NSTAGE, EPI, F16, SYM, PLANES>;
   hipError_t e = configured.run([&] {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   });
@@ -1001,6 +1068,13 @@ hipError_t launch_one(const GemmArgs& a, int batch, hipStream_t stream) {
 
 template <int EPI, bool F16 = false>
 hipError_t launch_epi(const GemmArgs& a, int batch, hipStream_t stream) {
+  if constexpr (split_epilogue(EPI)) {
+    switch (choose_split(a, (GemmEpilogue)EPI, batch)) {
+      case 0: return launch_one<64, 64, 2, 2, 3, EPI, false, false, 3>(a, batch, stream);
+      case 1: return launch_one<32, 64, 2, 2, 3, EPI, false, false, 3>(a, batch, stream);
+      case 2: return launch_one<128, 64, 2, 2, 2, EPI, false, false, 3>(a, batch, stream);
+    }
+  }
   const Choice c = choose(a, (GemmEpilogue)EPI, batch);
   constexpr bool LARGEST = fits_largest(EPI, F16);
   if constexpr (EPI == EPI_GRAMW || EPI == EPI_SQUARE || EPI == EPI_FRO2) {
@@ -1043,7 +1117,19 @@ extern "C" __attribute__((visibility("default"))) void conqur_gemm_tile_for_test
   out[0] = u.bm; out[1] = u.bn; out[2] = u.wgm * u.wgn; out[3] = (int)c.tiles; out[4] = c.sym;
 }
 
-int gemm_num_workgroups(const GemmArgs& a, GemmEpilogue epi, int batch) { return (int)(choose(a, epi, batch).tiles * batch); }
+// The same for the split form of six products: { rows, columns, workgroups per batch entry }, or 0 rows if segments run.
+extern "C" __attribute__((visibility("default"))) void conqur_gemm_split_for_tests(int epi, int M, int N, int K, int batch, int* out) {
+  GemmArgs a{};
+  a.M = M; a.N = N; a.K = K; a.nseg = 6;
+  const int t = choose_split(a, (GemmEpilogue)epi, batch);
+  out[0] = t < 0 ? 0 : kSplitTiles[t].bm; out[1] = t < 0 ? 0 : kSplitTiles[t].bn; out[2] = t < 0 ? 0 : gemm_num_workgroups(a, (GemmEpilogue)epi, batch) / batch;
+}
+
+int gemm_num_workgroups(const GemmArgs& a, GemmEpilogue epi, int batch) {
+  const int t = choose_split(a, epi, batch);
+  if (t < 0) return (int)(choose(a, epi, batch).tiles * batch);
+  return ((a.M + kSplitTiles[t].bm - 1) / kSplitTiles[t].bm) * ((a.N + kSplitTiles[t].bn - 1) / kSplitTiles[t].bn) * batch;
+}
 
 int gemm_num_partials(const GemmArgs& a, GemmEpilogue epi, int batch) {
   const Tile& u = kTiles[choose(a, epi, batch).tile];   // (a mirrored tile has slots of its own)
@@ -1077,6 +1163,9 @@ hipError_t launch_gemm_nt(const GemmArgs& a, GemmEpilogue epi, int batch, hipStr
   if ((epi == EPI_ACT && (a.ldc < a.N || a.ldc >= (1ll << 21))) || (epi == EPI_SIGN_ACT && (a.ldy < a.N || a.ldy >= (1ll << 21))))
     return hipErrorInvalidValue;
   if ((epi == EPI_ACT || epi == EPI_SIGN_ACT) && (a.N & 7)) return hipErrorInvalidValue;   // the staged stores take whole chunks of columns
+  if (split_epilogue(epi) && a.nseg == 6 &&   // the split form takes plane p of A from segment 2 - p, of B from segment p
+      (a.a_seg[2] || a.a_seg[3] != a.a_seg[1] || a.a_seg[4] || a.a_seg[5] || a.b_seg[0] || a.b_seg[3] || a.b_seg[4] != a.b_seg[1] || a.b_seg[5]))
+    return hipErrorInvalidValue;
   if (epi == EPI_XADD && (!a.Xadd || !a.C32)) return hipErrorInvalidValue;
   if (epi == EPI_XLAST && (!a.C32 || !a.Pn || !a.Pt || (a.M & 3) || a.np_out < 1 || a.np_out > 2)) return hipErrorInvalidValue;
   switch (epi) {

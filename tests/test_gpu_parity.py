@@ -1486,3 +1486,40 @@ def test_step_of_heads_up_to_64_wide_on_their_tile(B, T):
     assert gemm_tile(B, EPI_SIGN_XT, 0, 0, T, 64, 64, 1, 32)[:2] == (128, 64)
     w = I.small_workload(64 * 32, T, n_batches=1, heads=32, seed=64 + T, prox_lambda=0.1, massive_frac=0.01)
     run_stream(B, w, 1, check_R=True)
+
+
+@pytest.mark.parametrize("T,d,heads,tile", [(33, 16, 1, (32, 64)), (130, 5 * 48, 5, (32, 64)), (401, 784, 1, (32, 64)), (777, 1040, 1, (64, 64)), (1025, 3 * 272, 3, (64, 64)),
+                                            (5999, 304, 1, (128, 64)), (4093, 1008, 1, (128, 64)), (12000, 1024, 1, (0, 0))])
+def test_rotation_of_fp32_rows_from_planes_in_lds(B, T, d, heads, tile):
+    """Every tile of the split form, and the largest problems, which keep the segments: rows against 64 bits, into rows of any
+    alignment; the statistics steps with and without the rotated rows take their corner signs from the same sums."""
+    import ctypes
+    import torch
+    out = (ctypes.c_int * 3)()
+    for epi in (EPI_ACT, 0, EPI_SIGN_ACT):
+        B.load().conqur_gemm_split_for_tests(epi, T, d // heads, d // heads, heads, out)
+        assert tuple(out)[:2] == tile
+    dh = d // heads
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(T + d)
+    R0 = (torch.randn((heads, dh, dh), generator=g, device="cuda:0") / math.sqrt(dh)).cpu().numpy()
+    X = torch.randn((T, d), generator=g, device="cuda:0") * torch.exp(2 * torch.randn((T, d), generator=g, device="cuda:0"))
+    cal = B.Calibrator(d, heads, "f32", R0, max_tokens=T)
+    try:
+        x, R = X.double(), torch.from_numpy(R0).to("cuda:0").double()
+        ref = torch.cat([x[:, h * dh:(h + 1) * dh] @ R[h] for h in range(heads)], dim=1)
+        Y = cal.rotate(X)
+        flat = torch.full((T * (d + 3) + 1,), 7.0, dtype=X.dtype, device=X.device)
+        odd = flat[1:].view(T, d + 3)
+        cal.rotate(X, odd)
+        torch.cuda.synchronize()
+        assert torch.equal(odd[:, :d], Y) and bool((odd[:, d:] == 7.0).all()) and float(flat[0]) == 7.0
+        # three planes of 8 bits hold all 24 of an fp32 value, the products dropped are below 2^-24 of |x| |r|, and the fp32 sums
+        # round once per 32 terms at their own magnitude: 2^-21 of the row's norm leaves a factor of four and more
+        assert bool(((Y.double() - ref).abs() <= 2.0 ** -21 * x.reshape(T, heads, dh).norm(dim=2).amax(dim=1)[:, None] * R.norm(dim=1).max()).all())
+        cal.step_batch(X)
+        assert torch.equal(torch.from_numpy(cal.last_corners(T)[0]).to("cuda:0"), torch.where(Y >= 0, 1, -1).to(torch.int8))
+        cal.step_batch_quant(X, 4, True, 0.9)
+        assert torch.equal(torch.from_numpy(cal.last_corners(T)[0]).to("cuda:0"), torch.where(Y >= 0, 1, -1).to(torch.int8))
+    finally:
+        cal.close()
