@@ -657,6 +657,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   // the closing step), so the update is that one launch (for heads of width 128 behind the reduction of the token shares).
   HeadPolarStart hstart{};
   const bool one_launch = dh <= kHeadPolarMaxDh && np_main == 1;
+  const bool one_launch_step = !one_launch && dh <= kPolarStepMaxDh && np_main == 1;   // (a launch a step: polar_step.hip)
   bool use_hstart = one_launch && ctx->cfg.polar_max_iters > 0;
   if (ctx->parts_pending) {   // per-head step: M is summed from the token shares here, ||M||_F^2 from the same pass
     HIP_TRY(launch_head_reduce(ctx->Mpart, ctx->parts_pending, h, ctx->M, 0, ctx->dotrm_part, s));
@@ -860,7 +861,13 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       double a, b;
       const double E = step_cubic(l, u, &a, &b);
       const bool last = E <= e_stop || iters + 1 >= cap;
-      HIP_TRY(gram(seg_main, (float)a, (float)b, np_main, false, main_f16));
+      if (one_launch_step) {   // (as the two launches below, bit for bit)
+        HIP_TRY(launch_polar_step(ctx->PXt[cur], h, dh, (float)a, (float)b, ctx->PXt[cur ^ 1], last, ctx->PX, ctx->PXn[cur ^ 1], s));
+        mfma_flop += polar_step_flop(h, dh);
+        cur ^= 1;
+      } else {
+        HIP_TRY(gram(seg_main, (float)a, (float)b, np_main, false, main_f16));
+      }
       ++slot;
       // The last main step hands over to the closing iterations.  Its result is rounded to the planes this phase
       // works with anyway (one: 8 bits, two: 16 bits -- a perturbation of the size every step of this phase
@@ -870,7 +877,8 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       if (last && np_main == 3) {
         HIP_TRY(apply(seg_main, ctx->PW, 3, 2, false, ctx->PX));
       } else {
-        HIP_TRY(apply(seg_main, ctx->PW, last ? -np_main : np_main, last ? -np_main : np_main, false, nullptr, main_f16));
+        if (!one_launch_step)
+          HIP_TRY(apply(seg_main, ctx->PW, last ? -np_main : np_main, last ? -np_main : np_main, false, nullptr, main_f16));
         if (last) handover_planes = np_main;
       }
       ++iters;

@@ -139,6 +139,14 @@ struct HeadPolarStart {
 hipError_t launch_head_polar(const bf16_bits* Xt0, int heads, int dh, const PolarSchedule& sched, float* X32, bf16_bits* Pn, bf16_bits* Pt,
                              const HeadPolarClose* close, const HeadPolarStart* start, hipStream_t s);
 
+// One step X <- X (a I + b X^T X) of that phase for wider heads, up to kPolarStepMaxDh (a multiple of 16), in one launch
+// (polar_step.hip): reads the iterate as one transposed fp16 plane [heads][dh][dh] and writes the next one the same way into another.
+// last: the hand-over outputs of launch_head_polar instead (Xt_out the transposed bf16 plane).
+constexpr int kPolarStepMaxDh = 256;
+hipError_t launch_polar_step(const bf16_bits* Xt, int heads, int dh, float a, float b, bf16_bits* Xt_out, int last, float* X32, bf16_bits* Pn,
+                             hipStream_t s);
+double polar_step_flop(int heads, int dh);   // multiply-add work of such a launch
+
 // Per-row fake-quantisation error of Y [T][ld] (bf16 or fp32) into row_sse / row_en, then their sums over rows:
 // out[0] = SSE, out[1] = energy (skipped if out is null).  zero_point = 0: symmetric quantiser; 1: zero-point quantiser on [clip*min, clip*max].
 // Q non-null: the quantised rows are also written to Q [T][ldq] in Y's element type (Q must not overlap Y).

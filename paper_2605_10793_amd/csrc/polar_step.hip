@@ -1,0 +1,202 @@
+// One step of the polar iteration's main phase, X <- X (a I + b X^T X) (Sec. 3.3), in one launch: heads of width
+// kHeadPolarMaxDh + 16 .. kPolarStepMaxDh.
+//
+// Up to 128 the iterate and the products of a whole update fit one compute unit (head_polar.hip); here a step's products take
+// one 5 us and more, so a head is spread over workgroups.  Column block p of the step needs, besides X, only columns p of
+// W = a I + b G: a workgroup forms G[:, p] = X^T X[:, p], turns it into W[:, p] and takes X'[:, p] = X W[:, p].  Nothing passes
+// between workgroups within a step, so Gram matrix and apply are one launch instead of two, W never leaves the compute unit, and
+// one layout of the iterate, X^T, is all that is stored between steps: LDS holds all of it, read as rows (the Gram product) and
+// by transposing reads (the apply).  Beyond kPolarStepMaxDh it does not fit and would be fetched twice.
+//
+// What bounds it: launch, one fetch of X^T (up to 128 KiB per workgroup, from memory: the step before wrote it on other XCDs)
+// and a short chain of MFMAs behind it.  16 columns per workgroup while that gives at most one workgroup per compute unit,
+// else 32.  A whole update by events, two launches a step and one, us: width 256, 23 iterations, one head 276 and 179, 32 heads
+// 434 and 226; 24 x 208 422 and 200; 10 iterations of 3 x 192 143 and 99, 8 x 176 146 and 95; 40 x 160, 9 iterations 182 and 104.
+//
+// Roundings are those of the two GEMM launches it stands for (K in ascending blocks of 32, W and X' once to fp16), bit for bit.
+#include "kernels.h"
+
+#include <type_traits>
+
+namespace conqur {
+
+namespace {
+
+constexpr int kRowB = 512;   // bytes of an LDS row, whatever the width: the rows' bank pattern is head_polar.hip's
+constexpr int kNW = 4;
+
+// N: width of the square the head is taken as (zero beyond the head); P: columns of a workgroup.
+template <int N, int P>
+__global__ void __launch_bounds__(64 * kNW, 2) k_polar_step(const bf16_bits* __restrict__ Xt, const int dh, const int panels, const float ci,
+                                                           const float cg, bf16_bits* __restrict__ Xt_out, const int last,
+                                                           float* __restrict__ X32, bf16_bits* __restrict__ Pn) {
+  static_assert(N % (16 * kNW) == 0 && N <= kPolarStepMaxDh && P % 16 == 0, "whole row tiles per wavefront");
+  constexpr int TM = N / (16 * kNW), TN = P / 16, KB = N / 32;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  unsigned char* const sX = smem;                  // X^T: row c, K = row of X
+  unsigned char* const sW = smem + N * kRowB;      // columns p of W: row = column, K = row of W
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = lane >> 4, col = lane & 15;
+  // a head's workgroups on one XCD (bid % 8), where its L2 fetches X^T once
+  const int total = gridDim.x, xcd = blockIdx.x & 7, rest = total & 7;
+  const int at = xcd * (total >> 3) + (xcd < rest ? xcd : rest) + (blockIdx.x >> 3);
+  const int h = at / panels, n0 = (at % panels) * P;
+  const int64_t hoff = (int64_t)h * dh * dh;
+  constexpr uint32_t kOob = 0x80000000u;           // an offset past every descriptor's range: loads give zero, stores nothing
+  auto rsrc = [&](const void* p, int elem) {
+    return __builtin_amdgcn_make_buffer_rsrc((char*)const_cast<void*>(p) + hoff * elem, 0, dh * dh * elem, 0x00020000);
+  };
+
+  // 16-byte chunk c of row r lies at chunk c ^ swz(r): see head_polar.hip
+  auto swz = [](int r) { return ((r >> 2) & 1) | ((r & 1) << 1) | ((r & 2) << 1) | ((r ^ (r << 1)) & 8); };
+  const int s = swz(col), t = 8 * kg + (col >> 2);
+  const uint32_t l_row = col * kRowB + ((kg ^ s) << 4);                                              // row col, chunk kg
+  const uint32_t l_tr = t * kRowB + ((((col >> 1) & 1) ^ swz(t)) << 4) + 8 * (col & 1);              // row 8 kg + col / 4, element 4 (col % 4)
+  const uint32_t l_put = col * kRowB + (((kg >> 1) ^ s) << 4) + 8 * (kg & 1);                        // row col, element 4 kg
+
+  auto fetch = [&](__amdgpu_buffer_rsrc_t r, int row0, uint32_t off) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(sX + row0 * kRowB), 16, off, 0, 0, 0);
+  };
+  {   // X^T to LDS, 2 rows per instruction; what lies beyond the head reads zero
+    const auto rx = rsrc(Xt, 2);
+    const int half = lane >> 5, pc = lane & 31;
+#pragma unroll
+    for (int q = 0; q < N / 2 / kNW; ++q) {
+      const int row0 = 2 * (q * kNW + wave), row = row0 + half, chunk = pc ^ swz(row);
+      const uint32_t off = row < dh && 8 * chunk < dh ? (uint32_t)(row * dh + 8 * chunk) * 2u : kOob;
+      fetch(rx, row0, off);
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): they have landed
+  }
+  __syncthreads();
+
+  // rows row .. row + 15 of an LDS matrix, K elements 32 kk + 8 kg .. + 7
+  auto frag = [&](const unsigned char* base, int row, int kk) {
+    return *reinterpret_cast<const f16x8*>(base + row * kRowB + (l_row ^ (kk << 6)));
+  };
+  // rows 16 i + col of the matrix's transpose
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) s16x4* lds_s16x4;
+  auto frag_tr = [&](int i, int kk) {
+    unsigned char* const p = sX + 32 * kk * kRowB;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(p + (l_tr ^ (i << 5))));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4)(p + 4 * kRowB + (l_tr ^ (i << 5) ^ 144)));   // swz(r + 4) = swz(r) ^ 9
+    return __builtin_bit_cast(f16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  auto pack_f16 = [](const f32x4& a) { return make_uint2(f32x2_to_f16x2(a[0], a[1]), f32x2_to_f16x2(a[2], a[3])); };
+
+  // Element r of acc[i][j]: row 16 (TM wave + i) + 4 kg + r, column n0 + 16 j + col.
+  const int i0 = TM * wave;
+  f32x4 acc[TM][TN];
+  auto zero = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  };
+  auto product = [&](auto&& fa, auto&& fb) {
+    zero();
+#pragma unroll
+    for (int kk = 0; kk < KB; ++kk) {
+      f16x8 a[TM], b[TN];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) b[j] = fb(j, kk);
+#pragma unroll
+      for (int i = 0; i < TM; ++i) a[i] = fa(i0 + i, kk);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+  };
+
+  // G[:, p], then W[:, p] (as the general path's epilogue rounds it)
+  product([&](int i, int kk) { return frag(sX, 16 * i, kk); }, [&](int j, int kk) { return frag(sX, n0 + 16 * j < N ? n0 + 16 * j : 0, kk); });
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const float on = 16 * (i0 + i) == n0 + 16 * j ? ci : 0.0f;
+      f32x4 v;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) v[r] = fmaf(on, 4 * kg + r == col ? 1.0f : 0.0f, cg * acc[i][j][r]);
+      *reinterpret_cast<uint2*>(sW + 16 * j * kRowB + (l_put ^ ((i0 + i) << 5))) = pack_f16(v);
+    }
+  __syncthreads();
+  // X'[:, p]
+  product([&](int i, int kk) { return frag_tr(i, kk); }, [&](int j, int kk) { return frag(sW, 16 * j, kk); });
+
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  const auto rt = rsrc(Xt_out, 2);
+  auto put_tr = [&](int i, int j, const uint2& v) {   // rows n past the head lie past the range
+    const uint32_t off = (uint32_t)((n0 + 16 * j + col) * dh + 16 * (i0 + i) + 4 * kg) * 2u;
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2{v.x, v.y}, rt, 16 * (i0 + i) < dh ? off : kOob, 0, 0);
+  };
+  if (!last) {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) put_tr(i, j, pack_f16(acc[i][j]));
+    return;
+  }
+  // The hand-over to the closing iterations: rounded to bf16, that value as fp32, transposed and natural plane.
+  const auto r32 = rsrc(X32, 4), rn = rsrc(Pn, 2);
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const uint2 v = make_uint2(f32x2_to_bf16x2(acc[i][j][0], acc[i][j][1]), f32x2_to_bf16x2(acc[i][j][2], acc[i][j][3]));
+      put_tr(i, j, v);
+      const int n = n0 + 16 * j + col;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const uint32_t bits = (r & 2 ? v.y : v.x) >> (16 * (r & 1)) & 0xffffu;
+        const uint32_t el = (uint32_t)((16 * (i0 + i) + 4 * kg + r) * dh + n);   // rows past the head: past the range
+        __builtin_amdgcn_raw_buffer_store_b32(bits << 16, r32, n < dh ? el * 4u : kOob, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)bits, rn, n < dh ? el * 2u : kOob, 0, 0);
+      }
+    }
+}
+
+template <int N, int P>
+hipError_t launch_one(const bf16_bits* Xt, int heads, int dh, float a, float b, bf16_bits* Xt_out, int last, float* X32, bf16_bits* Pn,
+                      hipStream_t s) {
+  constexpr int smem = (N + P) * kRowB;
+  static PerDeviceOnce configured;
+  auto kern = k_polar_step<N, P>;
+  hipError_t e = configured.run([&] {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+  });
+  if (e != hipSuccess) return e;
+  const int panels = (dh + P - 1) / P;
+  hipLaunchKernelGGL(kern, dim3(panels * heads), dim3(64 * kNW), smem, s, Xt, dh, panels, a, b, Xt_out, last, X32, Pn);
+  return hipGetLastError();
+}
+
+// 32 columns per workgroup from more than one workgroup per compute unit on.
+int panel_width(int heads, int dh) { return (int64_t)heads * (dh / 16) <= 256 ? 16 : 32; }
+
+int square_width(int dh) { return dh <= 192 ? 192 : 256; }
+
+}  // namespace
+
+double polar_step_flop(int heads, int dh) {
+  const double n = square_width(dh), p = panel_width(heads, dh);
+  return 4.0 * n * n * (double)round_up(dh, (int64_t)p) * heads;
+}
+
+hipError_t launch_polar_step(const bf16_bits* Xt, int heads, int dh, float a, float b, bf16_bits* Xt_out, int last, float* X32, bf16_bits* Pn,
+                             hipStream_t s) {
+  if (heads < 1 || dh < 16 || dh > kPolarStepMaxDh || (dh & 15) || !Xt || !Xt_out || Xt == Xt_out || (last && (!X32 || !Pn)))
+    return hipErrorInvalidValue;
+  using std::integral_constant;
+  auto go = [&](auto n, auto p) {
+    return launch_one<decltype(n)::value, decltype(p)::value>(Xt, heads, dh, a, b, Xt_out, last, X32, Pn, s);
+  };
+  const bool narrow = panel_width(heads, dh) == 16;
+  if (square_width(dh) == 192)
+    return narrow ? go(integral_constant<int, 192>{}, integral_constant<int, 16>{}) : go(integral_constant<int, 192>{}, integral_constant<int, 32>{});
+  return narrow ? go(integral_constant<int, 256>{}, integral_constant<int, 16>{}) : go(integral_constant<int, 256>{}, integral_constant<int, 32>{});
+}
+
+}  // namespace conqur

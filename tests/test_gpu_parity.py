@@ -1523,3 +1523,30 @@ def test_rotation_of_fp32_rows_from_planes_in_lds(B, T, d, heads, tile):
         assert torch.equal(torch.from_numpy(cal.last_corners(T)[0]).to("cuda:0"), torch.where(Y >= 0, 1, -1).to(torch.int8))
     finally:
         cal.close()
+
+
+@pytest.mark.parametrize("dh,heads", [(144, 1), (144, 29), (176, 2), (192, 1), (192, 22), (208, 3), (224, 19), (240, 1), (256, 1), (256, 16), (256, 17)])
+def test_update_with_one_launch_per_step(B, dh, heads):
+    """Heads of 144 .. 256: both squares (192, 256; filled and with a margin), 16 and 32 columns a workgroup on either side of
+    256 workgroups (32 also with half a column block at the edge), head counts that leave the XCDs unequal shares, against
+    polar(M + lambda tau R) in 64 bits.  Bound as in the test above: fp16 iterates, a hand-over rounded to bf16, 2^-8."""
+    rng = np.random.default_rng(dh + heads)
+    q = lambda: np.linalg.qr(rng.standard_normal((dh, dh)))[0]
+    R0 = np.stack([q() for _ in range(heads)]).astype(np.float32)
+    M = np.stack([(q() * rng.uniform(0.5, 1.5, dh)) @ q() for _ in range(heads)]).astype(np.float32)
+    for lam in (0.0, 0.1):
+        cal = B.Calibrator(dh * heads, heads, "bf16", R0, max_tokens=64, prox_lambda=lam)
+        try:
+            cal.set_state(M=M)
+            _, st = cal.update_rotation()
+            R = cal.get_state(want_M=False)[0].astype(np.float64)
+        finally:
+            cal.close()
+        worst = 0.0
+        for h in range(heads):
+            U, s, Vt = np.linalg.svd(M[h].astype(np.float64) + lam * np.linalg.norm(M[h]) / math.sqrt(dh) * R0[h])
+            assert s[-1] > 0.1 * s[0]
+            worst = max(worst, np.linalg.norm(R[h] - U @ Vt) / math.sqrt(dh))
+            assert np.linalg.norm(R[h].T @ R[h] - np.eye(dh)) <= TOL_ORTH
+        say(f"  dh={dh} heads={heads} lam={lam} iters={st[0]['iters']}: err {worst:.2e}")
+        assert worst <= 2.0 ** -8
