@@ -938,13 +938,14 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
 
 // Tiles, with what a workgroup that has its CU to itself takes: t0 us outside the main loop and ts per K step of 64 (fits to
 // rotate, accumulate and polar launches at 16 .. 10500 tokens and widths 64 .. 8192).  192: fills the chip exactly at 3072.
-// The second form of the largest tile is the one in 8 wavefronts, for the launches fits_largest_8 names; the last four are for
+// The second form of the largest tile is the one in 8 wavefronts, for the launches fits_largest_8 names; the last five are for
 // the launches special_tile names.
 struct Tile { int bm, bn, wgm, wgn; float t0, ts; };
 constexpr Tile kTiles[] = {{256, 256, 2, 2, 10.0f, 1.30f}, {256, 128, 4, 2, 6.5f, 0.72f}, {128, 128, 2, 2, 6.5f, 0.42f}, {64, 64, 2, 2, 4.5f, 0.26f},
                            {192, 192, 2, 2, 8.5f, 0.75f}, {256, 256, 2, 4, 8.5f, 1.34f},
-                           {96, 96, 2, 2, 4.5f, 0.38f}, {160, 160, 2, 2, 5.5f, 0.69f}, {96, 64, 2, 2, 4.7f, 0.29f}, {128, 64, 2, 2, 6.2f, 0.45f}};
-constexpr int kNumTiles = 10;
+                           {96, 96, 2, 2, 4.5f, 0.38f}, {160, 160, 2, 2, 5.5f, 0.69f}, {96, 64, 2, 2, 4.7f, 0.29f}, {128, 64, 2, 2, 6.2f, 0.45f},
+                           {128, 192, 2, 2, 6.5f, 0.62f}};
+constexpr int kNumTiles = 11;
 
 // Whether an epilogue's registers fit beside the 256 accumulators per lane of the 256 x 256 tile.  Those that change the
 // accumulators in place or walk over them for a varying number of planes do not (64 .. 970 bytes per lane of scratch): they
@@ -968,12 +969,17 @@ constexpr bool fits_largest_8(int epi) {
 //                       update's other launches 11.3 and 13.2, the correction 18.3 (128 x 128 24.0)
 //  128 x 64             signs and operand of heads up to 64 wide: 32 x 2048 x 64 8.4 us (256 x 128, half of it empty, 10.6); in a
 //                       step 13.3 and 15.3
+//  128 x 192            rotations of at most 256 such tiles (4 wavefronts of 64 x 96 read 80 KiB of LDS a K step, 8 of 64 x 48 would 112)
+//                       and applies: 2048 x 3072 rotated 36.0 us (192 tiles of 256 x 128 39.3), 1842 x 2576 34.8 (40.0), 978 x 4464
+//                       50.4 (59.5), with signs and operand 2.5 to 10 us less a step; update at 2304 727 (746).  Two rounds lose:
+//                       2165 x 4240 104 and 92.  Accumulating at 2304 it was no faster than 192 x 192.
 // (One launch after another on the same operands; the constants above are dearer, as operands just written by other units are.)
 constexpr bool special_tile(int t, int epi, bool sym) {
   switch (t) {
     case 6: case 7: return sym;
     case 8: return epi == EPI_F32 || epi == EPI_XOUT || epi == EPI_XLAST || epi == EPI_XADD;
-    default: return epi == EPI_SIGN_XT;
+    case 9: return epi == EPI_SIGN_XT;
+    default: return epi == EPI_ACT || epi == EPI_SIGN || epi == EPI_SIGN_ACT || epi == EPI_SIGN_XT || epi == EPI_XOUT || epi == EPI_XLAST;
   }
 }
 
@@ -989,6 +995,7 @@ double tile_time(int t, int64_t tiles, double steps) {
     const double step = rounds <= 1 ? kTiles[t].ts : (rounds == 2 ? 0.48 : 0.75);
     return (kTiles[t].t0 + (rounds > 2 ? 1.0 : 0.0) + steps * step) * (tiles > 768 ? tiles / 768.0 : 1.0);
   }
+  if (t == 10 && rounds > 1) return 1e300;   // (see special_tile)
   if (t == 9 && rounds > 1) return (double)((tiles + 511) / 512) * (kTiles[t].t0 + steps * 0.60);   // two share a compute unit
   return (double)rounds * (kTiles[t].t0 + steps * kTiles[t].ts);
 }
@@ -1099,6 +1106,7 @@ hipError_t launch_epi(const GemmArgs& a, int batch, hipStream_t stream) {
     case 5: if constexpr (fits_largest_8(EPI)) return launch_one<256, 256, 2, 4, 2, EPI, F16>(a, batch, stream); break;
     case 8: if constexpr (special_tile(8, EPI, false)) return launch_one<96, 64, 2, 2, 3, EPI, F16>(a, batch, stream); break;
     case 9: if constexpr (special_tile(9, EPI, false)) return launch_one<128, 64, 2, 2, 3, EPI, F16>(a, batch, stream); break;
+    case 10: if constexpr (special_tile(10, EPI, false)) return launch_one<128, 192, 2, 2, 3, EPI, F16>(a, batch, stream); break;
     default: return launch_one<64, 64, 2, 2, 3, EPI, F16>(a, batch, stream);
   }
   return hipErrorInvalidValue;

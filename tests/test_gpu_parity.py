@@ -1550,3 +1550,12 @@ def test_update_with_one_launch_per_step(B, dh, heads):
             assert np.linalg.norm(R[h].T @ R[h] - np.eye(dh)) <= TOL_ORTH
         say(f"  dh={dh} heads={heads} lam={lam} iters={st[0]['iters']}: err {worst:.2e}")
         assert worst <= 2.0 ** -8
+
+
+@pytest.mark.parametrize("T,d,accumulate", [(2041, 3056, (192, 192, 4)), (1301, 3472, (256, 256, 8))])
+def test_step_on_tiles_of_128_by_192(B, T, d, accumulate):
+    test_step_on_every_large_tile(B, T, d, (128, 192, 4), accumulate)
+
+
+def test_planted_polar_on_tiles_of_128_by_192(B):
+    test_planted_polar_on_tiles_between_the_others(B, 49, 48, gemm_tile(B, EPI_GRAMW, 1, 1, 2352, 2352, 2352)[:2], (128, 192))
