@@ -650,7 +650,14 @@ __global__ void __launch_bounds__(256) k_sum_partials(const double* __restrict__
   __shared__ double sh[4];
   const double* p = part + (int64_t)blockIdx.x * n;
   double s = 0.0;
-  for (int i = threadIdx.x; i < n; i += 256) s += p[i];
+  // sixteen loads in flight per lane, summed in the order of one at a time
+  for (int i0 = threadIdx.x; i0 < n; i0 += 16 * 256) {
+    double v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = p[i0 + u * 256 < n ? i0 + u * 256 : n - 1];   // (no branch around a load)
+#pragma unroll
+    for (int u = 0; u < 16; ++u) s = i0 + u * 256 < n ? s + v[u] : s;
+  }
   s = block_sum_d(s, sh);
   if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
