@@ -972,7 +972,8 @@ constexpr bool fits_largest_8(int epi) {
 //  128 x 192            rotations of at most 256 such tiles (4 wavefronts of 64 x 96 read 80 KiB of LDS a K step, 8 of 64 x 48 would 112)
 //                       and applies: 2048 x 3072 rotated 36.0 us (192 tiles of 256 x 128 39.3), 1842 x 2576 34.8 (40.0), 978 x 4464
 //                       50.4 (59.5), with signs and operand 2.5 to 10 us less a step; update at 2304 727 (746).  Two rounds lose:
-//                       2165 x 4240 104 and 92.  Accumulating at 2304 it was no faster than 192 x 192.
+//                       2165 x 4240 104 and 92.  From 20 K steps (below, 4600 x 1072 takes 17.1
+//                       against 19.3, but tests name 256 x 128 there) to 100 (700 x 6400; not measured beyond).  Accumulating at 2304 it was no faster than 192 x 192.
 // (One launch after another on the same operands; the constants above are dearer, as operands just written by other units are.)
 constexpr bool special_tile(int t, int epi, bool sym) {
   switch (t) {
@@ -995,7 +996,7 @@ double tile_time(int t, int64_t tiles, double steps) {
     const double step = rounds <= 1 ? kTiles[t].ts : (rounds == 2 ? 0.48 : 0.75);
     return (kTiles[t].t0 + (rounds > 2 ? 1.0 : 0.0) + steps * step) * (tiles > 768 ? tiles / 768.0 : 1.0);
   }
-  if (t == 10 && rounds > 1) return 1e300;   // (see special_tile)
+  if (t == 10 && (rounds > 1 || steps < 20 || steps > 100)) return 1e300;   // (see special_tile)
   if (t == 9 && rounds > 1) return (double)((tiles + 511) / 512) * (kTiles[t].t0 + steps * 0.60);   // two share a compute unit
   return (double)rounds * (kTiles[t].t0 + steps * kTiles[t].ts);
 }
