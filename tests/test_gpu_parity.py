@@ -1559,3 +1559,31 @@ def test_step_on_tiles_of_128_by_192(B, T, d, accumulate):
 
 def test_planted_polar_on_tiles_of_128_by_192(B):
     test_planted_polar_on_tiles_between_the_others(B, 49, 48, gemm_tile(B, EPI_GRAMW, 1, 1, 2352, 2352, 2352)[:2], (128, 192))
+
+
+@pytest.mark.parametrize("T,d,heads", [(777, 1040, 1), (401, 784, 1), (5999, 304, 1), (130, 240, 5)])
+def test_fp32_rows_split_in_registers_or_by_a_launch_in_front(B, T, d, heads):
+    """Rows of a pitch that is no multiple of 8 values, which the GEMM reads itself, and rows that reach beyond 32-bit byte offsets,
+    whose planes a launch writes first: the bits of dense rows, NaN and infinite values among them, and the same corner signs."""
+    import torch
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(T)
+    dh = d // heads
+    R0 = (torch.randn((heads, dh, dh), generator=g, device="cuda:0") / math.sqrt(dh)).cpu().numpy()
+    X = torch.randn((T, d), generator=g, device="cuda:0") * torch.exp(2 * torch.randn((T, d), generator=g, device="cuda:0"))
+    X[3, 5], X[7, d - 1], X[T - 1, 0] = float("nan"), float("inf"), 1e38
+    cal = B.Calibrator(d, heads, "f32", R0, max_tokens=T)
+    try:
+        Y = cal.rotate(X).view(torch.int32).clone()
+        cal.step_batch(X)
+        signs = cal.last_corners(T)[0]
+        assert bool(torch.isnan(cal.rotate(X)[3, :dh]).all())
+        for pitch in (d + 4, ((1 << 29) // T + 4) // 4 * 4):
+            flat = torch.full((T * pitch,), 7.0, device="cuda:0")
+            x = flat.view(T, pitch)[:, :d]
+            x.copy_(X)
+            assert torch.equal(cal.rotate(x).view(torch.int32), Y)
+            cal.step_batch(x)
+            assert np.array_equal(cal.last_corners(T)[0], signs)
+    finally:
+        cal.close()
