@@ -163,8 +163,7 @@ void rotate_args(conqur_ctx* c, const void* X, int64_t T, int64_t stride, GemmAr
   g->M = (int)T; g->N = c->dh; g->K = c->dh;
   g->batchA = c->dh;
   if (c->f32) {
-    g->A = c->Xs; g->lda = c->d;                                               // (the planes: launch_split_rows, where
-    g->A32 = reinterpret_cast<const float*>(X); g->lda32 = stride;             // the launch does not read the rows themselves)
+    g->A = c->Xs; g->lda = c->d;
     g->nseg = kSeg6.n;
     for (int s = 0; s < kSeg6.n; ++s) { g->a_seg[s] = kSeg6.a[s] * c->tmax * c->d; g->b_seg[s] = kSeg6.b[s] * rplane; }
   } else {
@@ -177,13 +176,13 @@ void rotate_args(conqur_ctx* c, const void* X, int64_t T, int64_t stride, GemmAr
 hipError_t rotate_into(conqur_ctx* c, const void* X, int64_t T, int64_t stride, void* Y, int64_t ldy) {
   if (rotate_rows_fits(c->f32, T, c->dh))
     return launch_rotate_rows(X, c->f32, T, stride, c->RopT, (int64_t)c->heads * c->dh * c->dh, c->heads, c->dh, Y, ldy, nullptr, c->stream);
-  GemmArgs g;
-  rotate_args(c, X, T, stride, &g);
-  g.C = Y; g.ldc = ldy; g.batchC = c->dh; g.c_is_f32 = c->f32;
-  if (c->f32 && !gemm_takes_fp32_rows(g, EPI_ACT, c->heads)) {
+  if (c->f32) {
     hipError_t e = launch_split_rows(reinterpret_cast<const float*>(X), T, stride, c->d, c->Xs, c->tmax * c->d, c->stream);
     if (e != hipSuccess) return e;
   }
+  GemmArgs g;
+  rotate_args(c, X, T, stride, &g);
+  g.C = Y; g.ldc = ldy; g.batchC = c->dh; g.c_is_f32 = c->f32;
   return launch_gemm_nt(g, EPI_ACT, c->heads, c->stream);
 }
 
@@ -460,16 +459,13 @@ static conqur_status step_general(conqur_ctx* ctx, const void* X, int64_t T, int
   // kernel for a few rows, which saves the transposing launch; fp32 activations (split planes) and the GEMM variant that
   // also emits Y keep that launch.
   const bool xt_in_rotate = !ctx->f32 && (few || !keep_y);
-  const GemmEpilogue epi = keep_y ? EPI_SIGN_ACT : (xt_in_rotate ? EPI_SIGN_XT : EPI_SIGN);
-  GemmArgs rot;
-  rotate_args(ctx, X, T, stride, &rot);
   {
     StageTimer tm(ctx, ST_PREP);
     HIP_TRY(launch_row_norms(X, ctx->f32, T, stride, ctx->heads, ctx->dh, ctx->nrm, ctx->w, ctx->tmax, ctx->nonfinite, s));
     if (!xt_in_rotate)
       HIP_TRY(launch_transpose_scale(X, ctx->f32, T, Tk, stride, ctx->d, ctx->dh, ctx->w, ctx->tmax, ctx->Xt, ctx->pitch,
                                      (int64_t)ctx->d * ctx->pitch, ctx->np, ctx->cnt, s));
-    if (ctx->f32 && !few && !gemm_takes_fp32_rows(rot, epi, ctx->heads))
+    if (ctx->f32 && !few)
       HIP_TRY(launch_split_rows(reinterpret_cast<const float*>(X), T, stride, ctx->d, ctx->Xs, ctx->tmax * ctx->d, s));
   }
   if (few) {
@@ -480,10 +476,12 @@ static conqur_status step_general(conqur_ctx* ctx, const void* X, int64_t T, int
                                keep_y ? ctx->Y : nullptr, ctx->d, &rs, s));
   } else {
     StageTimer tm(ctx, ST_ROTATE);
-    GemmArgs& g = rot;
+    GemmArgs g;
+    rotate_args(ctx, X, T, stride, &g);
     g.C = ctx->St; g.ldc = ctx->pitch; g.batchC = (int64_t)ctx->dh * ctx->pitch;
     g.st_rows_valid = ctx->pitch;
     g.sign_f16 = ctx->f32 ? 0 : 1;   // the accumulate GEMM runs in fp16 for bf16 activations
+    const GemmEpilogue epi = keep_y ? EPI_SIGN_ACT : (xt_in_rotate ? EPI_SIGN_XT : EPI_SIGN);
     const int wg = gemm_num_workgroups(g, epi, ctx->heads);
     ctx->clk_wg[0] = (ctx->timing >= 2 && wg <= kClkMaxWorkgroups) ? wg : 0;
     g.clk = ctx->clk_wg[0] ? ctx->clk[0] : nullptr;

@@ -4,8 +4,7 @@
 // calibration path (rotate, accumulate, Gram, polynomial apply) is this kernel:
 // operands that are K-strided in their natural layout are produced transposed by
 // the kernel that writes them, and fp32-accurate products are obtained by feeding
-// bf16 split planes as several K-segments (hi*hi, hi*mid, mid*hi, ...), or, where six
-// of them rotate fp32 rows, from all planes (or the rows themselves) of a K step in LDS together.
+// bf16 split planes as several K-segments (hi*hi, hi*mid, mid*hi, ...).
 #pragma once
 #include "common.h"
 
@@ -43,8 +42,6 @@ struct GemmArgs {
   const bf16_bits* B;
   int64_t lda, ldb;        // row pitch in elements (multiples of 8)
   int64_t batchA, batchB;  // element offset between batch entries (grid.z)
-  const float* A32;        // the rows A's planes split, fp32, in 6 segments that rotate (may be null): the launch may read these
-  int64_t lda32;           // instead, see gemm_takes_fp32_rows; pitch in elements (a multiple of 4), batch offset batchA
   int M, N, K;             // K per segment, a multiple of 8
   int ab_f16;              // operands hold fp16 instead of bf16 (EPI_F32; EPI_GRAMW / EPI_XOUT with one output plane,
                            // which is then fp16 as well: the single-plane polar steps; EPI_XLAST, whose outputs stay bf16)
@@ -95,9 +92,6 @@ hipError_t launch_gemm_nt(const GemmArgs& args, GemmEpilogue epi, int batch, hip
 // Multiply-add work launch_gemm_nt issues for these arguments, in FLOP: workgroups that run x tile area x K x segments
 // x 2 (a symmetric launch runs the tiles on and above the diagonal only).
 double gemm_issued_flop(const GemmArgs& args, GemmEpilogue epi, int batch);
-
-// Whether launch_gemm_nt reads the rows A32 themselves for these arguments; A then need not hold their planes.
-bool gemm_takes_fp32_rows(const GemmArgs& args, GemmEpilogue epi, int batch);
 
 // Number of workgroups launch_gemm_nt uses for this problem with `batch` entries (size of the clock probe / 4).
 int gemm_num_workgroups(const GemmArgs& args, GemmEpilogue epi, int batch);

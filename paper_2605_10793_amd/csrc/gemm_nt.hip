@@ -40,12 +40,6 @@ __device__ __forceinline__ int lds_off(int row, int chunk) {
   return row * 128 + ((chunk ^ ((row >> 1) & 7)) << 4);
 }
 
-// Rows of 64 fp32 values in LDS: 16 chunks of 16 bytes.  A fragment's lane group kg takes values 8 kg .. + 7 of 32, two chunks; place
-// 8 kk + 4 half + kg holds chunk 8 kk + 2 kg + half, so that one read takes 4 neighbouring places of 16 rows, and place c of row r
-// lies at c ^ swz32(r): no bank conflicts (see head_polar.hip, whose rows are as long).
-__device__ __forceinline__ int chunk32(int place) { return (place & 8) | (place & 3) << 1 | ((place >> 2) & 1); }
-__device__ __forceinline__ int swz32(int r) { return ((r >> 2) & 1) | ((r & 1) << 1) | ((r & 2) << 1) | ((r ^ (r << 1)) & 8); }
-
 // s_waitcnt vmcnt(N) only (gfx9 encoding: vmcnt = simm16[15:14]:[3:0], expcnt and lgkmcnt left at max).
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -84,20 +78,16 @@ __device__ __forceinline__ float again(float x) {
 // the hardware returns zeros (also for loads whose destination is LDS).
 constexpr uint32_t kOobOffset = 0x80000000u;
 
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool F16, bool SYM, int PLANES, bool FP32A>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool F16, bool SYM>
 __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int by_rows) {
   static_assert(!SYM || (BM == BN && (EPI == EPI_GRAMW || EPI == EPI_SQUARE || EPI == EPI_FRO2)),
                 "mirrored tiles: square tiles, symmetric results");
   constexpr int NW = WGM * WGN;                 // wavefronts per workgroup
   constexpr int WM = BM / WGM, WN = BN / WGN, TM = WM / 16, TN = WN / 16;
-  constexpr int RPLA = FP32A ? 4 : 8;     // tile rows of A in a wave-wide 1 KiB load (fp32 rows: 256 bytes each)
-  constexpr int NLA = BM / RPLA, NLB = BN / 8;  // such loads per stage, of B per plane
+  constexpr int NLA = BM / 8, NLB = BN / 8;     // wave-wide 1 KiB loads per stage (8 tile rows each)
   constexpr int QA = NLA / NW, QB = NLB / NW;   // ... per wavefront
   static_assert(NLA % NW == 0 && NLB % NW == 0 && WM % 16 == 0 && WN % 16 == 0, "tile shape");
-  static_assert(PLANES == 1 || (PLANES == 3 && !F16 && !SYM), "fp32 rows times split planes");
-  static_assert(!FP32A || PLANES == 3, "the rows themselves, or three planes of them");
-  constexpr int PA = FP32A ? 1 : PLANES;         // planes of A in a stage
-  constexpr int APLANE = BM * 1024 / RPLA, BPLANE = BN * 128, ABYTES = PA * APLANE, STAGE = ABYTES + PLANES * BPLANE;   // bytes
+  constexpr int STAGE = (BM + BN) * 128;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   // Optional clock probe (g.clk != null): wall-clock ticks (100 MHz) of the prologue, main loop and epilogue
   // of this workgroup and the shader-clock cycles of the main loop, from which the host derives the clock
@@ -155,8 +145,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   }
   const int m0 = tm * BM, n0 = tn * BN;
   const int bz = blockIdx.z;
-  // (fp32 rows: a pointer to halves of them)
-  const bf16_bits* Ab = !FP32A ? g.A + (int64_t)bz * g.batchA : reinterpret_cast<const bf16_bits*>(g.A32 + (int64_t)bz * g.batchA);
+  const bf16_bits* Ab = g.A + (int64_t)bz * g.batchA;
   const bf16_bits* Bb = g.B + (int64_t)bz * g.batchB;
 
   // Global -> LDS without passing through registers: each buffer_load ... lds moves
@@ -168,15 +157,9 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   int chunkA[QA], chunkB[QB];
 #pragma unroll
   for (int q = 0; q < QA; ++q) {
-    if constexpr (!FP32A) {
-      const int row = (q * NW + wave) * 8 + lrow;
-      chunkA[q] = lpc ^ ((row >> 1) & 7);
-      offA[q] = (m0 + row < g.M) ? (uint32_t)(((int64_t)(m0 + row) * g.lda + chunkA[q] * 8) * 2) : kOobOffset;
-    } else {
-      const int row = (q * NW + wave) * 4 + (lane >> 4);
-      chunkA[q] = chunk32((lane & 15) ^ swz32(row));
-      offA[q] = (m0 + row < g.M) ? (uint32_t)(((int64_t)(m0 + row) * g.lda32 + chunkA[q] * 4) * 4) : kOobOffset;
-    }
+    const int row = (q * NW + wave) * 8 + lrow;
+    chunkA[q] = lpc ^ ((row >> 1) & 7);
+    offA[q] = (m0 + row < g.M) ? (uint32_t)(((int64_t)(m0 + row) * g.lda + chunkA[q] * 8) * 2) : kOobOffset;
   }
 #pragma unroll
   for (int q = 0; q < QB; ++q) {
@@ -184,10 +167,10 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
     chunkB[q] = lpc ^ ((row >> 1) & 7);
     offB[q] = (n0 + row < g.N) ? (uint32_t)(((int64_t)(n0 + row) * g.ldb + chunkB[q] * 8) * 2) : kOobOffset;
   }
-  const uint32_t recA = !FP32A ? (uint32_t)((((int64_t)g.M - 1) * g.lda + BK) * 2) : (uint32_t)((((int64_t)g.M - 1) * g.lda32 + BK) * 4);
+  const uint32_t recA = (uint32_t)((((int64_t)g.M - 1) * g.lda + BK) * 2);
   const uint32_t recB = (uint32_t)((((int64_t)g.N - 1) * g.ldb + BK) * 2);
   const int nkb = (g.K + BK - 1) / BK;
-  const int nit = PLANES == 1 ? nkb * g.nseg : nkb;
+  const int nit = nkb * g.nseg;
   // Epilogues of the largest tile whose registers need help (see where the accumulators are pinned): a guard around the loop
   // costs them a second set of accumulators at its exit.  The others spill nothing either way, and the two that rotate or
   // accumulate lose up to 5 % without it (11008 x 4096 x 4096: 297 us instead of 282).
@@ -199,7 +182,7 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   {
     const int kleft = g.K - (nkb - 1) * BK;
 #pragma unroll
-    for (int q = 0; q < QA; ++q) offAt[q] = (chunkA[q] * (FP32A ? 4 : 8) < kleft) ? offA[q] : kOobOffset;
+    for (int q = 0; q < QA; ++q) offAt[q] = (chunkA[q] * 8 < kleft) ? offA[q] : kOobOffset;
 #pragma unroll
     for (int q = 0; q < QB; ++q) offBt[q] = (chunkB[q] * 8 < kleft) ? offB[q] : kOobOffset;
   }
@@ -207,29 +190,19 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   // Issue state: the next tile to fetch is K step is_kb of segment is_s; its operand
   // pointers advance incrementally (wave-uniform, scalar registers).
   int is_s = 0, is_kb = 0;
-  const bf16_bits* pa = Ab + (PLANES == 1 ? g.a_seg[0] : 0);
-  const bf16_bits* pb = Bb + (PLANES == 1 ? g.b_seg[0] : 0);
+  const bf16_bits* pa = Ab + g.a_seg[0];
+  const bf16_bits* pb = Bb + g.b_seg[0];
   __amdgpu_buffer_rsrc_t ra, rb;
-  [[maybe_unused]] const bf16_bits *ga = pa, *gb = pb;   // split planes: the prepared tile, and the ranges of its descriptors
-  [[maybe_unused]] uint32_t rangeA = recA, rangeB = recB;
   bool tail = false;
   auto issue_prep = [&]() {
     // Past the last tile the pipeline keeps issuing (so that every step has the same
     // number of loads in flight and needs no branches); those loads get an empty
     // descriptor range, fetch nothing and write zeros to a stage nobody reads again.
-    const bool real = PLANES == 1 ? is_s < g.nseg : is_kb < nkb;
+    const bool real = is_s < g.nseg;
     ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_bits*>(pa), 0, real ? recA : 0u, 0x00020000);
-    if constexpr (PLANES == 1) {
-      rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_bits*>(pb), 0, real ? recB : 0u, 0x00020000);
-    } else {
-      ga = pa; gb = pb;
-      rangeA = real ? recA : 0u; rangeB = real ? recB : 0u;
-    }
+    rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_bits*>(pb), 0, real ? recB : 0u, 0x00020000);
     tail = ktail && is_kb == nkb - 1;
-    if (PLANES > 1) {
-      ++is_kb;
-      pa += FP32A ? 2 * BK : BK; pb += BK;
-    } else if (++is_kb == nkb) {
+    if (++is_kb == nkb) {
       is_kb = 0;
       ++is_s;
       const int sc = is_s < g.nseg ? is_s : g.nseg - 1;
@@ -239,38 +212,27 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
       pa += BK; pb += BK;
     }
   };
-  auto issue_one = [&](int n, int stage) {   // load n of LPT of the prepared tile
+  auto issue_one = [&](int q, int stage) {   // load q of LPT of the prepared tile
     unsigned char* sa = smem + stage * STAGE;
-    // plane by plane, A's part first; (rows: A's one part, then B's planes)
-    const int p = FP32A ? (n < QA ? 0 : (n - QA) / QB) : n / (QA + QB), q = FP32A ? (n < QA ? n : QA + (n - QA) % QB) : n % (QA + QB);
-    if constexpr (PLANES > 1) {   // (plane p of A is segment 2 - p of the six, of B segment p)
-      if (q < QA && !FP32A) ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_bits*>(ga) + g.a_seg[2 - p], 0, rangeA, 0x00020000);
-      if (q >= QA) rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_bits*>(gb) + g.b_seg[p], 0, rangeB, 0x00020000);
-    }
     if (q < QA) {
       const uint32_t off = tail ? offAt[q] : offA[q];
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)(sa + p * APLANE + (q * NW + wave) * 1024), 16,
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (__attribute__((address_space(3))) void*)(sa + (q * NW + wave) * 1024), 16,
                                                off, 0, 0, 0);
     } else {
       const int qb = q - QA;
       const uint32_t off = tail ? offBt[qb] : offB[qb];
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (__attribute__((address_space(3))) void*)(sa + ABYTES + p * BPLANE + (qb * NW + wave) * 1024),
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (__attribute__((address_space(3))) void*)(sa + BM * 128 + (qb * NW + wave) * 1024),
                                                16, off, 0, 0, 0);
     }
   };
 
   f32x4 acc[TM][TN];
-  // split planes: hi * hi of a K step's second half, and all other products, summed apart
-  [[maybe_unused]] f32x4 acc2[PLANES > 1 ? TM : 1][TN], low[PLANES > 1 ? TM : 1][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc[i][j][e] = 0.0f;
-        if constexpr (PLANES > 1) acc2[i][j][e] = low[i][j][e] = 0.0f;
-      }
+      for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.0f;
 
   // Software pipeline.  LDS holds NSTAGE tiles; tile t lives in stage t % NSTAGE.
   // Operand fragments are double buffered in registers: while the MFMAs of K-substep
@@ -282,82 +244,33 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   // reading the current stage), refill the current stage with tile it+NSTAGE, read the
   // first fragments of the next tile, and cover that latency with the second half of the
   // substep's MFMAs.
-  constexpr int LPT = PA * QA + PLANES * QB;   // loads per thread per tile
+  constexpr int LPT = QA + QB;   // loads per thread per tile
   constexpr int KS = BK / 32;    // MFMA K-substeps per tile
-  constexpr int NMF = TM * TN * (PLANES == 1 ? 1 : 6), NR = FP32A ? 2 * TM + 3 * TN : PLANES * (TM + TN);
-  // (MFMAs of a last substep ahead of the barrier; fp32 rows: fewer, so that the first fragments of the next tile arrive early
-  // enough to be split behind the others)
-  constexpr int HALF = FP32A ? NMF / 4 : NMF / 2, REST = NMF - HALF;
-  constexpr int RS = !FP32A && NMF / NR > 1 ? NMF / NR : 1;       // MFMAs between two fragment reads of a full substep
-  constexpr int RH = !FP32A && REST / NR > 1 ? REST / NR : 1;     // ... of the half substep behind the barrier
-  constexpr int R0 = NR > REST ? NR - REST : 0;         // reads issued ahead of that half (small tiles: more reads than MFMAs)
+  constexpr int NMF = TM * TN, HALF = NMF / 2, NR = TM + TN;
+  constexpr int RS = NMF / NR > 1 ? NMF / NR : 1;       // MFMAs between two fragment reads of a full substep
+  constexpr int RH = HALF / NR > 1 ? HALF / NR : 1;     // ... of the half substep behind the barrier
+  constexpr int R0 = NR > HALF ? NR - HALF : 0;         // reads issued ahead of that half (small tiles: more reads than MFMAs)
   constexpr int LQ2 = LPT / 2, LQ1 = LPT - LQ2;         // a tile's loads: LQ2 behind the barrier, LQ1 in the next step's first substep
-  constexpr int S2 = REST / LQ2 > 1 ? REST / LQ2 : 1;   // ... S2 and S1 MFMAs apart (early in the step: what is issued late
+  constexpr int S2 = HALF / LQ2 > 1 ? HALF / LQ2 : 1;   // ... S2 and S1 MFMAs apart (early in the step: what is issued late
   constexpr int S1 = NMF / LQ1 > 4 ? 4 : (NMF / LQ1 > 1 ? NMF / LQ1 : 1);   // has less time to land before the next barrier)
-  // fp32 rows: the first MFMA behind which a fragment is split, a few behind its read
-  [[maybe_unused]] constexpr int SPLIT_FROM1 = 2 * TM + 2 < NMF ? 2 * TM + 2 : NMF - 1, SPLIT_FROM0 = HALF + SPLIT_FROM1 - R0 < NMF ? HALF + SPLIT_FROM1 - R0 : NMF - 1;
-  static_assert(!FP32A || NMF - SPLIT_FROM0 >= 3 * TM, "every piece of a split has an MFMA of its own");
   static_assert(KS == 2, "fragment double buffering: the two substeps of a step take one buffer each");
-  static_assert(LQ2 * S2 <= REST + S2 - 1 && LQ1 * S1 <= NMF + S1 - 1 && NR <= NMF, "every load and read has its MFMA");
-  bf16x8 fa[2][PLANES][TM], fb[2][PLANES][TN];
-  [[maybe_unused]] uint4 raw[FP32A ? TM : 1][2];   // fp32 rows: the next substep's fragments, 8 values each, before they are split
+  static_assert(LQ2 * S2 <= HALF + S2 - 1 && LQ1 * S1 <= NMF + S1 - 1 && NR <= NMF, "every load and read has its MFMA");
+  bf16x8 fa[2][TM], fb[2][TN];
 
-  // Products of split planes, smallest first: kSeg6 of the general form, but every K step takes all six from planes that are in LDS
-  // together, or from planes of B and A's values, split in registers (see kSplitTiles).
-  constexpr int kPA[6] = {2, 1, 0, 1, 0, 0}, kPB[6] = {0, 1, 2, 0, 1, 0};
-  auto read_frag = [&](int buf, int n, const unsigned char* sa, int kk) {
-    const unsigned char* sb = sa + ABYTES;
-    if constexpr (!FP32A) {
-      // read number n of a substep, in the order the MFMAs need them: a0, b0..b(TN-1), a1..a(TM-1); planes: A's in falling, B's in
-      // rising order
-      const int k = PLANES == 1 ? 0 : n / (TM + TN), r = PLANES == 1 ? n : n % (TM + TN), pA = PLANES - 1 - k, pB = k;
-      if (r == 0) fa[buf][pA][0] = *reinterpret_cast<const bf16x8*>(sa + pA * APLANE + lds_off(wm * WM + col, kk * 4 + kg));
-      else if (r <= TN) fb[buf][pB][r - 1] = *reinterpret_cast<const bf16x8*>(sb + pB * BPLANE + lds_off(wn * WN + (r - 1) * 16 + col, kk * 4 + kg));
-      else fa[buf][pA][r - TN] = *reinterpret_cast<const bf16x8*>(sa + pA * APLANE + lds_off(wm * WM + (r - TN) * 16 + col, kk * 4 + kg));
-    } else if (n < 2 * TM) {   // what has to be split first
-      const int i = n / 2, half = n % 2;
-      raw[i][half] = *reinterpret_cast<const uint4*>(sa + (wm * WM + i * 16 + col) * 256 + (((4 * (2 * kk + half) + kg) ^ swz32(col)) << 4));
-    } else {
-      const int p = (n - 2 * TM) / TN, j = (n - 2 * TM) % TN;
-      fb[buf][p][j] = *reinterpret_cast<const bf16x8*>(sb + p * BPLANE + lds_off(wn * WN + j * 16 + col, kk * 4 + kg));
-    }
-  };
-  // Piece n of 3 TM: one of the three bf16 parts of a fragment's eight values, which become what it leaves (eight at a time: a
-  // wavefront has its SIMD to itself, and nothing else covers the latency of a chain of two).
-  constexpr int NPIECES = FP32A ? 3 * TM : 0;
-  [[maybe_unused]] auto split_piece = [&](int buf, int n) {
-    if constexpr (FP32A) {
-      const int i = n / 3, p = n % 3;
-      uint4 &u = raw[i][0], &v = raw[i][1];
-      const uint4 t = make_uint4(f32x2_to_bf16x2(__uint_as_float(u.x), __uint_as_float(u.y)), f32x2_to_bf16x2(__uint_as_float(u.z), __uint_as_float(u.w)),
-                                 f32x2_to_bf16x2(__uint_as_float(v.x), __uint_as_float(v.y)), f32x2_to_bf16x2(__uint_as_float(v.z), __uint_as_float(v.w)));
-      fa[buf][p][i] = __builtin_bit_cast(bf16x8, t);
-      if (p < 2) {
-        auto less = [](uint32_t x, uint32_t part) { return __float_as_uint(__uint_as_float(x) - __uint_as_float(part)); };
-        u = make_uint4(less(u.x, t.x << 16), less(u.y, t.x & 0xffff0000u), less(u.z, t.y << 16), less(u.w, t.y & 0xffff0000u));
-        v = make_uint4(less(v.x, t.z << 16), less(v.y, t.z & 0xffff0000u), less(v.z, t.w << 16), less(v.w, t.w & 0xffff0000u));
-      }
-    }
-  };
-  // ... the pieces dealt out over the MFMAs m in [from, NMF)
-  [[maybe_unused]] auto split_over = [&](int buf, int m, int from) {
-    if constexpr (FP32A) {
-      const int span = NMF - from, n = m < from ? NPIECES : ((m - from) * NPIECES + span - 1) / span;   // (span >= NPIECES)
-      if (n < NPIECES && from + n * span / NPIECES == m) split_piece(buf, n);
-    }
+  auto read_frag = [&](int buf, int r, const unsigned char* sa, int kk) {
+    // read number r of a substep, in the order the MFMAs need them: a0, b0..b(TN-1), a1..a(TM-1)
+    const unsigned char* sb = sa + BM * 128;
+    if (r == 0) fa[buf][0] = *reinterpret_cast<const bf16x8*>(sa + lds_off(wm * WM + col, kk * 4 + kg));
+    else if (r <= TN) fb[buf][r - 1] = *reinterpret_cast<const bf16x8*>(sb + lds_off(wn * WN + (r - 1) * 16 + col, kk * 4 + kg));
+    else fa[buf][r - TN] = *reinterpret_cast<const bf16x8*>(sa + lds_off(wm * WM + (r - TN) * 16 + col, kk * 4 + kg));
   };
   auto mfma = [&](int buf, int m) {
-    const int i = PLANES == 1 ? m / TN : m % (TM * TN) / TN, j = m % TN;
+    const int i = m / TN, j = m % TN;
     if constexpr (F16)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, fa[buf][0][i]), __builtin_bit_cast(f16x8, fb[buf][0][j]),
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, fa[buf][i]), __builtin_bit_cast(f16x8, fb[buf][j]),
                                                          acc[i][j], 0, 0, 0);
-    else if constexpr (PLANES == 1)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[buf][0][i], fb[buf][0][j], acc[i][j], 0, 0, 0);
-    else {
-      const int seg = m / (TM * TN);
-      f32x4& c = seg < 5 ? low[i][j] : (buf ? acc2[i][j] : acc[i][j]);   // (buf: the half of the K step)
-      c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[buf][kPA[seg]][i], fb[buf][kPB[seg]][j], c, 0, 0, 0);
-    }
+    else
+      acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[buf][i], fb[buf][j], acc[i][j], 0, 0, 0);
   };
 
 #pragma unroll
@@ -370,8 +283,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   pipeline_barrier();
 #pragma unroll
   for (int r = 0; r < NR; ++r) read_frag(0, r, smem, 0);
-#pragma unroll
-  for (int n = 0; n < NPIECES; ++n) split_piece(0, n);
 
   const unsigned long long pr_w1 = g.clk ? wall_clock64() : 0, pr_c1 = g.clk ? clock64() : 0;
   int stage = 0;   // it % NSTAGE
@@ -383,7 +294,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
     for (int m = 0; m < NMF; ++m) {
       mfma(0, m);
       if (m % RS == 0 && m / RS < NR) read_frag(1, m / RS, sa, 1);
-      split_over(1, m, SPLIT_FROM1);
       // the loads of tile it-1+NSTAGE that were left over behind the previous step's barrier
       if (it > 0 && m % S1 == S1 / 2 && m / S1 < LQ1) issue_one(LQ2 + m / S1, prev_stage);
       __builtin_amdgcn_sched_barrier(0);
@@ -407,7 +317,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
     for (int m = HALF; m < NMF; ++m) {
       mfma(1, m);
       if ((m - HALF) % RH == 0 && R0 + (m - HALF) / RH < NR) read_frag(0, R0 + (m - HALF) / RH, sn, 0);
-      split_over(0, m, SPLIT_FROM0);
       if ((m - HALF) % S2 == S2 / 2 && (m - HALF) / S2 < LQ2) issue_one((m - HALF) / S2, stage);
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -420,12 +329,6 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   __builtin_amdgcn_sched_barrier(0);
   asm volatile("s_nop 15\n\ts_nop 3" ::: "memory");
   __builtin_amdgcn_sched_barrier(0);
-  if constexpr (PLANES > 1) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = (acc[i][j] + acc2[i][j]) + low[i][j];
-  }
   // The 256 accumulators of the largest tile fill one half of the registers.  Left to itself the compiler moves them over to
   // the other half for the epilogue's arithmetic, all at once, and spills what that half held.  Pinned to their half here,
   // they are read from it where they are used.  (The two sign epilogues that store a second array spill with the pin and
@@ -1085,60 +988,12 @@ Choice choose(const GemmArgs& a, GemmEpilogue epi, int batch) {
   return best;
 }
 
-// Rotations of fp32 rows: six products of three bf16 planes a side.  As six segments of the general form every plane is fetched
-// three times, and the rate at which the compute units fetch operands (13 to 14 TB/s over the chip) is what the launch waits for.
-// In split form a K step has all planes of both operands in LDS and takes the six products from there: half the bytes.  The five
-// small products are summed apart, so that they are not rounded at the result's magnitude in every step, and hi * hi in two
-// halves, which end at 0.7 of the result's magnitude: the error against 64 bits, 1.9e-7 as segments at 777 x 1040, is 1.4e-7 (0.72 to 0.81 of it for widths
-// 192 to 1040).  us, six segments on their best tile and split: 777 x 1040 x 1040 28.2 and 15.2; 2048 x 256 9.1 and 5.5; 400 x 784
-// 20.3 and 8.3; 4096 x 1024 61.7 and 46.1; 12000 x 304 25.3 and 18.8; 9000 x 1024 114 and 104.  From about that size on the
-// 256 x 256 segments fetch less for each product than 128 x 64 split ones: 12000 x 1024 125 and 131, 8192 x 1536 184 and 187.
-//
-// The last three read the fp32 rows themselves, and a wavefront splits its fragments of them in registers: no launch that writes the
-// planes of X first, which at these sizes is a fourth of the time and more.  The split costs as many cycles as a fourth of the
-// fragment's products, in every wavefront that holds the fragment, and lies on the chain from a fragment's read to its products: a
-// K step takes longer, and the planes keep the sizes with many steps and rounds.  So 128 x 64 gives a wavefront 16 whole rows (9000 x
-// 1024 122 us, in 4 x 2 wavefronts 149), and 64 x 64 runs in 8, two a SIMD to cover each other's chains (777 x 1040 19.7; 4 of 16 x 64
-// 21.9; 4 of 32 x 32 27.7).  Same bits.  Whole rotations by events, us, with planes and with rows: 777 x 1040 24.3 and 19.7; 2048 x 256 8.8
-// and 6.1; 400 x 784 14.7 and 11.3; 1025 rows of 3 x 272 13.0 and 7.8; 12000 x 304 32.5 and 18.4; but 2500 x 1024 41.3 and 48.6, 9000 x
-// 1024 112 and 122.
-//
-// Constants as in kTiles, whole rounds of 256 workgroups (a stage is 32 to 72 KiB).  The planes' launch, beyond what it shares with
-// the launch in front: 3 us and 0.4 a million values in front of a rotation; 1.8 in a statistics step, where the launches ahead have
-// just read X (700 x 1024, step: rows 39.7, planes 38.5; rotation 14.8 and 19.0).  Whether the split form or segments run depends on the
-// problem's sizes alone, so that rows and corner signs of a batch come from the same sums; its two kinds differ in no bit.
-constexpr Tile kSplitTiles[] = {{64, 64, 2, 2, 4.1f, 0.65f}, {32, 64, 2, 2, 3.1f, 0.42f}, {128, 64, 2, 2, 3.2f, 1.24f},
-                                {64, 64, 4, 2, 3.8f, 0.80f}, {32, 64, 2, 2, 3.8f, 0.54f}, {128, 64, 8, 1, 1.9f, 1.45f}};
-constexpr bool split_epilogue(int epi) { return epi == EPI_ACT || epi == EPI_SIGN || epi == EPI_SIGN_ACT; }
-
-// The tile of the split form, or -1: not such a product, or the segments are expected to be faster.
-int choose_split(const GemmArgs& a, GemmEpilogue epi, int batch) {
-  if (!split_epilogue(epi) || a.nseg != 6 || a.ab_f16) return -1;
-  const Choice seg = choose(a, epi, batch);
-  const int64_t steps = (a.K + BK - 1) / BK;
-  double best = tile_time(seg.tile, seg.tiles * batch, 6.0 * steps);
-  int t = -1;
-  auto look = [&](int i) {
-    const Tile& u = kSplitTiles[i];
-    const int64_t tiles = (int64_t)((a.M + u.bm - 1) / u.bm) * ((a.N + u.bn - 1) / u.bn) * batch;
-    const double time = (double)((tiles + 255) / 256) * (u.t0 + steps * u.ts);
-    if (time < best) { best = time; t = i; }
-  };
-  for (int i = 0; i < 3; ++i) look(i);
-  if (t < 0) return t;
-  if (a.A32 && !(a.lda32 & 3) && (int64_t)a.M * a.lda32 < (1ll << 29)) {   // the rows are given, and 32-bit offsets reach them
-    best += epi == EPI_ACT ? 3.0 + 0.4e-6 * a.M * a.K * batch : 1.8;
-    for (int i = 3; i < 6; ++i) look(i);
-  }
-  return t;
-}
-
-template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool F16, bool SYM = false, int PLANES = 1, bool ROWS = false>
+template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool F16, bool SYM = false>
 hipError_t launch_one(const GemmArgs& a, int batch, hipStream_t stream) {
-  constexpr int smem = NSTAGE * ((ROWS ? 2 : PLANES) * BM + PLANES * BN) * BK * 2;
+  constexpr int smem = NSTAGE * (BM + BN) * BK * 2;
   static_assert(smem <= 160 * 1024, "LDS of one CU");
   static PerDeviceOnce configured;
-  auto kern = gemm_nt_kernel<BM, BN, WGM, WGN, NSTAGE, EPI, F16, SYM, PLANES, ROWS>;
+  auto kern = gemm_nt_kernel<BM, BN, WGM, WGN, NSTAGE, EPI, F16, SYM>;
   hipError_t e = configured.run([&] {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   });
@@ -1154,16 +1009,6 @@ hipError_t launch_one(const GemmArgs& a, int batch, hipStream_t stream) {
 
 template <int EPI, bool F16 = false>
 hipError_t launch_epi(const GemmArgs& a, int batch, hipStream_t stream) {
-  if constexpr (split_epilogue(EPI)) {
-    switch (choose_split(a, (GemmEpilogue)EPI, batch)) {
-      case 0: return launch_one<64, 64, 2, 2, 3, EPI, false, false, 3>(a, batch, stream);
-      case 1: return launch_one<32, 64, 2, 2, 3, EPI, false, false, 3>(a, batch, stream);
-      case 2: return launch_one<128, 64, 2, 2, 2, EPI, false, false, 3>(a, batch, stream);
-      case 3: return launch_one<64, 64, 4, 2, 3, EPI, false, false, 3, true>(a, batch, stream);
-      case 4: return launch_one<32, 64, 2, 2, 3, EPI, false, false, 3, true>(a, batch, stream);
-      case 5: return launch_one<128, 64, 8, 1, 2, EPI, false, false, 3, true>(a, batch, stream);
-    }
-  }
   const Choice c = choose(a, (GemmEpilogue)EPI, batch);
   constexpr bool LARGEST = fits_largest(EPI, F16);
   if constexpr (EPI == EPI_GRAMW || EPI == EPI_SQUARE || EPI == EPI_FRO2) {
@@ -1207,21 +1052,7 @@ extern "C" __attribute__((visibility("default"))) void conqur_gemm_tile_for_test
   out[0] = u.bm; out[1] = u.bn; out[2] = u.wgm * u.wgn; out[3] = (int)c.tiles; out[4] = c.sym;
 }
 
-// The same for the split form of six products: { rows, columns, workgroups per batch entry }, or 0 rows if segments run.
-extern "C" __attribute__((visibility("default"))) void conqur_gemm_split_for_tests(int epi, int M, int N, int K, int batch, int* out) {
-  GemmArgs a{};
-  a.M = M; a.N = N; a.K = K; a.nseg = 6;
-  const int t = choose_split(a, (GemmEpilogue)epi, batch);
-  out[0] = t < 0 ? 0 : kSplitTiles[t].bm; out[1] = t < 0 ? 0 : kSplitTiles[t].bn; out[2] = t < 0 ? 0 : gemm_num_workgroups(a, (GemmEpilogue)epi, batch) / batch;
-}
-
-bool gemm_takes_fp32_rows(const GemmArgs& a, GemmEpilogue epi, int batch) { return choose_split(a, epi, batch) >= 3; }
-
-int gemm_num_workgroups(const GemmArgs& a, GemmEpilogue epi, int batch) {
-  const int t = choose_split(a, epi, batch);
-  if (t < 0) return (int)(choose(a, epi, batch).tiles * batch);
-  return ((a.M + kSplitTiles[t].bm - 1) / kSplitTiles[t].bm) * ((a.N + kSplitTiles[t].bn - 1) / kSplitTiles[t].bn) * batch;
-}
+int gemm_num_workgroups(const GemmArgs& a, GemmEpilogue epi, int batch) { return (int)(choose(a, epi, batch).tiles * batch); }
 
 int gemm_num_partials(const GemmArgs& a, GemmEpilogue epi, int batch) {
   const Tile& u = kTiles[choose(a, epi, batch).tile];   // (a mirrored tile has slots of its own)
@@ -1255,9 +1086,6 @@ hipError_t launch_gemm_nt(const GemmArgs& a, GemmEpilogue epi, int batch, hipStr
   if ((epi == EPI_ACT && (a.ldc < a.N || a.ldc >= (1ll << 21))) || (epi == EPI_SIGN_ACT && (a.ldy < a.N || a.ldy >= (1ll << 21))))
     return hipErrorInvalidValue;
   if ((epi == EPI_ACT || epi == EPI_SIGN_ACT) && (a.N & 7)) return hipErrorInvalidValue;   // the staged stores take whole chunks of columns
-  if (split_epilogue(epi) && a.nseg == 6 &&   // the split form takes plane p of A from segment 2 - p, of B from segment p
-      (a.a_seg[2] || a.a_seg[3] != a.a_seg[1] || a.a_seg[4] || a.a_seg[5] || a.b_seg[0] || a.b_seg[3] || a.b_seg[4] != a.b_seg[1] || a.b_seg[5]))
-    return hipErrorInvalidValue;
   if (epi == EPI_XADD && (!a.Xadd || !a.C32)) return hipErrorInvalidValue;
   if (epi == EPI_XLAST && (!a.C32 || !a.Pn || !a.Pt || (a.M & 3) || a.np_out < 1 || a.np_out > 2)) return hipErrorInvalidValue;
   switch (epi) {

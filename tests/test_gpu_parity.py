@@ -1488,43 +1488,6 @@ def test_step_of_heads_up_to_64_wide_on_their_tile(B, T):
     run_stream(B, w, 1, check_R=True)
 
 
-@pytest.mark.parametrize("T,d,heads,tile", [(33, 16, 1, (32, 64)), (130, 5 * 48, 5, (32, 64)), (401, 784, 1, (32, 64)), (777, 1040, 1, (64, 64)), (1025, 3 * 272, 3, (64, 64)),
-                                            (5999, 304, 1, (128, 64)), (4093, 1008, 1, (128, 64)), (12000, 1024, 1, (0, 0))])
-def test_rotation_of_fp32_rows_from_planes_in_lds(B, T, d, heads, tile):
-    """Every tile of the split form, and the largest problems, which keep the segments: rows against 64 bits, into rows of any
-    alignment; the statistics steps with and without the rotated rows take their corner signs from the same sums."""
-    import ctypes
-    import torch
-    out = (ctypes.c_int * 3)()
-    for epi in (EPI_ACT, 0, EPI_SIGN_ACT):
-        B.load().conqur_gemm_split_for_tests(epi, T, d // heads, d // heads, heads, out)
-        assert tuple(out)[:2] == tile
-    dh = d // heads
-    g = torch.Generator(device="cuda:0")
-    g.manual_seed(T + d)
-    R0 = (torch.randn((heads, dh, dh), generator=g, device="cuda:0") / math.sqrt(dh)).cpu().numpy()
-    X = torch.randn((T, d), generator=g, device="cuda:0") * torch.exp(2 * torch.randn((T, d), generator=g, device="cuda:0"))
-    cal = B.Calibrator(d, heads, "f32", R0, max_tokens=T)
-    try:
-        x, R = X.double(), torch.from_numpy(R0).to("cuda:0").double()
-        ref = torch.cat([x[:, h * dh:(h + 1) * dh] @ R[h] for h in range(heads)], dim=1)
-        Y = cal.rotate(X)
-        flat = torch.full((T * (d + 3) + 1,), 7.0, dtype=X.dtype, device=X.device)
-        odd = flat[1:].view(T, d + 3)
-        cal.rotate(X, odd)
-        torch.cuda.synchronize()
-        assert torch.equal(odd[:, :d], Y) and bool((odd[:, d:] == 7.0).all()) and float(flat[0]) == 7.0
-        # three planes of 8 bits hold all 24 of an fp32 value, the products dropped are below 2^-24 of |x| |r|, and the fp32 sums
-        # round once per 32 terms at their own magnitude: 2^-21 of the row's norm leaves a factor of four and more
-        assert bool(((Y.double() - ref).abs() <= 2.0 ** -21 * x.reshape(T, heads, dh).norm(dim=2).amax(dim=1)[:, None] * R.norm(dim=1).max()).all())
-        cal.step_batch(X)
-        assert torch.equal(torch.from_numpy(cal.last_corners(T)[0]).to("cuda:0"), torch.where(Y >= 0, 1, -1).to(torch.int8))
-        cal.step_batch_quant(X, 4, True, 0.9)
-        assert torch.equal(torch.from_numpy(cal.last_corners(T)[0]).to("cuda:0"), torch.where(Y >= 0, 1, -1).to(torch.int8))
-    finally:
-        cal.close()
-
-
 @pytest.mark.parametrize("dh,heads", [(144, 1), (144, 29), (176, 2), (192, 1), (192, 22), (208, 3), (224, 19), (240, 1), (256, 1), (256, 16), (256, 17)])
 def test_update_with_one_launch_per_step(B, dh, heads):
     """Heads of 144 .. 256: both squares (192, 256; filled and with a margin), 16 and 32 columns a workgroup on either side of
@@ -1561,10 +1524,72 @@ def test_planted_polar_on_tiles_of_128_by_192(B):
     test_planted_polar_on_tiles_between_the_others(B, 49, 48, gemm_tile(B, EPI_GRAMW, 1, 1, 2352, 2352, 2352)[:2], (128, 192))
 
 
+@pytest.mark.parametrize("T,d,heads,tile", [
+    (33, 16, 1, (64, 64, 4)), (130, 5 * 48, 5, (64, 64, 4)), (777, 1040, 1, (64, 64, 4)), (8335, 2 * 80, 2, (128, 128, 4)),
+    (11044, 3 * 80, 3, (256, 128, 8)), (10823, 3 * 144, 3, (192, 192, 4)), (3596, 3 * 272, 3, (128, 192, 4)), (1239, 4 * 928, 4, (128, 192, 4)),
+    (10908, 3 * 208, 3, (256, 256, 8)), (8282, 2 * 400, 2, (256, 256, 4))])
+def test_rotation_of_fp32_rows(B, T, d, heads, tile):
+    """Every tile a rotation of fp32 rows takes, ragged rows and columns: rows against 64 bits, into rows of any alignment; the
+    statistics steps with and without the rotated rows take their corner signs from the same sums."""
+    import torch
+    dh = d // heads
+    for epi in (EPI_ACT, 0, EPI_SIGN_ACT):
+        assert gemm_tile(B, epi, 0, 0, T, dh, dh, 6, heads)[:3] == tile
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(T + d)
+    R0 = (torch.randn((heads, dh, dh), generator=g, device="cuda:0") / math.sqrt(dh)).cpu().numpy()
+    X = torch.randn((T, d), generator=g, device="cuda:0") * torch.exp(2 * torch.randn((T, d), generator=g, device="cuda:0"))
+    cal = B.Calibrator(d, heads, "f32", R0, max_tokens=T)
+    try:
+        x, R = X.double(), torch.from_numpy(R0).to("cuda:0").double()
+        ref = torch.cat([x[:, h * dh:(h + 1) * dh] @ R[h] for h in range(heads)], dim=1)
+        Y = cal.rotate(X)
+        flat = torch.full((T * (d + 3) + 1,), 7.0, dtype=X.dtype, device=X.device)
+        odd = flat[1:].view(T, d + 3)
+        cal.rotate(X, odd)
+        torch.cuda.synchronize()
+        assert torch.equal(odd[:, :d], Y) and bool((odd[:, d:] == 7.0).all()) and float(flat[0]) == 7.0
+        # three planes of 8 bits hold all 24 of an fp32 value, the products dropped are below 2^-24 of |x| |r|, and the fp32 sums
+        # round once per 32 terms at their own magnitude: 2^-21 of the row's norm leaves a factor of four and more
+        assert bool(((Y.double() - ref).abs() <= 2.0 ** -21 * x.reshape(T, heads, dh).norm(dim=2).amax(dim=1)[:, None] * R.norm(dim=1).max()).all())
+        cal.step_batch(X)
+        assert torch.equal(torch.from_numpy(cal.last_corners(T)[0]).to("cuda:0"), torch.where(Y >= 0, 1, -1).to(torch.int8))
+        cal.step_batch_quant(X, 4, True, 0.9)
+        assert torch.equal(torch.from_numpy(cal.last_corners(T)[0]).to("cuda:0"), torch.where(Y >= 0, 1, -1).to(torch.int8))
+    finally:
+        cal.close()
+
+
+@pytest.mark.parametrize("dtype,d,heads,calls", [("f32", 1024, 1, (12000, 9000, 8192, 777, 33)), ("f32", 3 * 208, 3, (10908, 2048, 130)),
+                                                 ("f32", 256, 1, (12000, 2048, 40)), ("bf16", 1040, 1, (6000, 2041, 500, 33))])
+def test_a_rows_sums_do_not_depend_on_the_size_of_the_call(B, dtype, d, heads, calls):
+    """Calls of more rows than the kernel for a few takes, whatever tile they run on: a row's entries come bit for bit from one order
+    of summation, and its corner signs from the same sums."""
+    import torch
+    dh, T = d // heads, calls[0]
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d)
+    R0 = (torch.randn((heads, dh, dh), generator=g, device="cuda:0") / math.sqrt(dh)).cpu().numpy()
+    X = torch.randn((T, d), generator=g, device="cuda:0").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    cal = B.Calibrator(d, heads, dtype, R0, max_tokens=T)
+    try:
+        Y = cal.rotate(X)
+        cal.step_batch(X)
+        signs = cal.last_corners(T)[0]
+        for n in calls[1:]:
+            Yn = cal.rotate(X[T - n:])
+            say(f"  {n} of {T} rows: {int((Yn != Y[T - n:]).sum())} entries differ")
+            assert torch.equal(Yn, Y[T - n:])
+            cal.step_batch(X[T - n:])
+            assert np.array_equal(cal.last_corners(n)[0], signs[T - n:])
+    finally:
+        cal.close()
+
+
 @pytest.mark.parametrize("T,d,heads", [(777, 1040, 1), (401, 784, 1), (5999, 304, 1), (130, 240, 5)])
-def test_fp32_rows_split_in_registers_or_by_a_launch_in_front(B, T, d, heads):
-    """Rows of a pitch that is no multiple of 8 values, which the GEMM reads itself, and rows that reach beyond 32-bit byte offsets,
-    whose planes a launch writes first: the bits of dense rows, NaN and infinite values among them, and the same corner signs."""
+def test_fp32_rows_of_any_pitch(B, T, d, heads):
+    """Rows of a pitch that is no multiple of 8 values, and rows that reach beyond 32-bit byte offsets: the bits of dense rows, NaN
+    and infinite values among them, and the same corner signs."""
     import torch
     g = torch.Generator(device="cuda:0")
     g.manual_seed(T)
