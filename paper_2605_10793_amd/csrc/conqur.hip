@@ -696,6 +696,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   int slot = 0;           // next residual-history slot
   uint32_t iters = 0, closing = 0;
   double mfma_flop = 0.0; // multiply-add work the products of this update issue (reported in the statistics)
+  const double pad_product = 2.0 * std::pow((double)round_up(dh, 32), 3.0);   // ... one product of a narrow head in its square
 
   auto gram = [&](const SegList& sl, float ci, float cg, int np_w, bool want_resid, int f16 = 0) -> hipError_t {
     GemmArgs g;
@@ -851,9 +852,8 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       cur ^= 1;
       handover_planes = 1;
       iters += sc.nsteps;
-      // per head: two products per step, a third in the last one, and four in the closing step if it is taken
-      const double pad = (double)round_up(dh, 32);
-      mfma_flop += 2.0 * pad * pad * pad * h * (2.0 * sc.nsteps + 1.0 + (fuse ? 4.0 : 0.0));
+      // per head: two products per step and the closing step's Gram matrix (its other three: where the step was taken)
+      mfma_flop += pad_product * h * (2.0 * sc.nsteps + (fuse ? 1.0 : 0.0));
       if (trace) std::fprintf(stderr, "[conqur] polar main phase: %d steps in one launch, l0=%.3e\n", sc.nsteps, l0);
       return CONQUR_OK;
     }
@@ -950,6 +950,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       worst_res = std::max(worst_res, std::sqrt(r2));
       if (!(s2 >= 0.0)) { ok = false; continue; }
       r_replaced = true;
+      mfma_flop += 3.0 * pad_product;
       const double b = kCubeFactor * std::pow(std::sqrt(s2), 1.5) + kOrthFloorPerDim * dh;
       worst_pred = std::max(worst_pred, b);
       if (!(std::isfinite(b) && b <= tol)) ok = false;

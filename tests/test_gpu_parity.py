@@ -1612,3 +1612,22 @@ def test_fp32_rows_of_any_pitch(B, T, d, heads):
             assert np.array_equal(cal.last_corners(T)[0], signs)
     finally:
         cal.close()
+
+
+@pytest.mark.parametrize("dh,heads,dtype", [(16, 5, "bf16"), (64, 32, "bf16"), (80, 3, "f32"), (112, 4, "bf16"), (128, 8, "bf16")])
+def test_multiply_adds_of_the_one_launch_update(B, dh, heads, dtype):
+    """mfma_flop of an update that is one launch: in the head's square (the width up to a multiple of 32) two products per step and four
+    of the closing step, which every head takes here."""
+    rng = np.random.default_rng(dh)
+    q = lambda: np.linalg.qr(rng.standard_normal((dh, dh)))[0]
+    R0 = np.stack([q() for _ in range(heads)]).astype(np.float32)
+    M = np.stack([(q() * rng.uniform(0.5, 1.5, dh)) @ q() for _ in range(heads)]).astype(np.float32)
+    cal = B.Calibrator(dh * heads, heads, dtype, R0, max_tokens=64, prox_lambda=0.1)
+    try:
+        cal.set_state(M=M)
+        _, st = cal.update_rotation()
+        assert st[0]["accurate"] == 1 and not st[0]["orth_measured"]
+        product = 2.0 * (-(-dh // 32) * 32) ** 3 * heads
+        assert st[0]["mfma_flop"] == product * (2 * (st[0]["iters"] - 1) + 4)
+    finally:
+        cal.close()
