@@ -14,6 +14,7 @@
 // 434 and 226; 24 x 208 422 and 200; 10 iterations of 3 x 192 143 and 99, 8 x 176 146 and 95; 40 x 160, 9 iterations 182 and 104.
 //
 // Roundings are those of the two GEMM launches it stands for (K in ascending blocks of 32, W and X' once to fp16), bit for bit.
+#include "gemm_nt.h"
 #include "kernels.h"
 
 #include <type_traits>
@@ -197,6 +198,29 @@ hipError_t launch_polar_step(const bf16_bits* Xt, int heads, int dh, float a, fl
   if (square_width(dh) == 192)
     return narrow ? go(integral_constant<int, 192>{}, integral_constant<int, 16>{}) : go(integral_constant<int, 192>{}, integral_constant<int, 32>{});
   return narrow ? go(integral_constant<int, 256>{}, integral_constant<int, 16>{}) : go(integral_constant<int, 256>{}, integral_constant<int, 32>{});
+}
+
+// One step from the same start planes either way, for tests: launch_polar_step, or (two_launches) the two products it stands for,
+// which also need the natural plane Xn and room for W and write the natural plane after every step.  DEVICE pointers, default
+// stream.  Returns the hipError_t.
+extern "C" __attribute__((visibility("default"))) int conqur_polar_step_for_tests(int two_launches, const bf16_bits* Xn, const bf16_bits* Xt, int heads,
+                                                                                  int dh, float a, float b, int last, bf16_bits* Xt_out, float* X32,
+                                                                                  bf16_bits* Xn_out, bf16_bits* W) {
+  if (!two_launches) return launch_polar_step(Xt, heads, dh, a, b, Xt_out, last, X32, Xn_out, nullptr);
+  GemmArgs g{};
+  g.ab_f16 = 1;
+  g.A = g.B = Xt; g.lda = g.ldb = g.ldc = dh; g.batchA = g.batchB = g.batchC = (int64_t)dh * dh;
+  g.M = g.N = g.K = dh;
+  g.nseg = 1;
+  g.np_out = 1; g.plane_out = heads * g.batchC;
+  GemmArgs x = g;
+  g.Pn = W; g.symmetric = 1; g.coef_i = a; g.coef_g = b;
+  const hipError_t e = launch_gemm_nt(g, EPI_GRAMW, heads, nullptr);
+  if (e != hipSuccess) return e;
+  x.A = Xn; x.B = W; x.Pn = Xn_out; x.Pt = Xt_out;
+  if (last) x.C32 = X32;
+  else x.np_out_n = 1;
+  return launch_gemm_nt(x, last ? EPI_XLAST : EPI_XOUT, heads, nullptr);
 }
 
 }  // namespace conqur

@@ -1631,3 +1631,34 @@ def test_multiply_adds_of_the_one_launch_update(B, dh, heads, dtype):
         assert st[0]["mfma_flop"] == product * (2 * (st[0]["iters"] - 1) + 4)
     finally:
         cal.close()
+
+
+@pytest.mark.parametrize("dh,heads", [(144, 1), (144, 29), (176, 2), (192, 1), (192, 22), (208, 3), (240, 1), (256, 1), (256, 17)])
+def test_one_launch_step_is_the_two_products_bit_for_bit(B, dh, heads):
+    """One step of the update's main phase in one launch and as Gram matrix and apply, from the same planes: the next iterate, and
+    the hand-over's three results of a last step."""
+    import ctypes
+    import torch
+    fn = B.load().conqur_polar_step_for_tests
+    p = lambda t: ctypes.c_void_p(t.data_ptr() if t is not None else None)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(dh + heads)
+    q = torch.linalg.qr(torch.randn((heads, dh, dh), generator=g, device="cuda:0"))[0]
+    X = (q * torch.rand((heads, 1, dh), generator=g, device="cuda:0")).half().contiguous()   # (qr gives columns)
+    Xt = X.transpose(1, 2).contiguous()
+    for a, b in ((2.6, -1.7), (1.5, -0.5)):
+        for last in (0, 1):
+            got = []
+            for two in (0, 1):
+                out = [torch.full((heads, dh, dh), 7.0, dtype=t, device="cuda:0") for t in (torch.float16, torch.float32, torch.float16, torch.float16)]
+                torch.cuda.synchronize()
+                assert fn(two, p(X), p(Xt), heads, dh, ctypes.c_float(a), ctypes.c_float(b), last, *(p(t) for t in out)) == 0
+                torch.cuda.synchronize()
+                got.append([t.view(torch.int16) for t in out[:3 if last else 1]])
+            for one, pair in zip(*got):
+                assert torch.equal(one, pair)
+            nxt = got[0][0].view(torch.bfloat16 if last else torch.float16).double().transpose(1, 2)
+            x = X.double()
+            ref = a * x + b * torch.bmm(x, torch.bmm(x.transpose(1, 2).contiguous(), x))
+            # W and the result each rounded once to 11 bits (the hand-over to 8): 2^-10 (2^-8) of the matrix's norm
+            assert float((nxt - ref).norm()) <= 2.0 ** (-8 if last else -10) * float(ref.norm())
