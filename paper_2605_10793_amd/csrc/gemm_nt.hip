@@ -584,6 +584,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   };
 
   if constexpr (EPI == EPI_SIGN || EPI == EPI_SIGN_ACT || EPI == EPI_SIGN_XT) {
+    // (the accumulate product contracts over whole steps of BK tokens: every call writes them, none is left from another)
+    static_assert(BM % BK == 0, "the tiles' rows cover St up to the next multiple of BK tokens");
     // St is the transpose of the accumulator tile.  Storing it straight from the registers gives every lane 8 bytes of
     // a different row (64 cache lines per store instruction); instead each wavefront transposes its WM x WN block
     // through its own slice of the (now idle) stage memory and stores whole 16-byte chunks, 8 or 16 lanes per row.
