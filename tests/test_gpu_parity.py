@@ -1001,7 +1001,8 @@ def test_planted_polar_large(B, d):
 @pytest.mark.parametrize("T,d,dtype,tile", [
     (2048, 4096, "bf16", (256, 128, 8)), (3001, 3072, "bf16", (192, 192, 4)), (4104, 4096, "bf16", (192, 192, 4)), (1000, 1040, "bf16", (64, 64, 4)),
     (1500, 1664, "f32", (128, 128, 4)), (70, 208, "bf16", (64, 64, 4)), (2041, 2048, "bf16", (128, 128, 4)), (8185, 4096, "bf16", (256, 256, 4)),
-    (6713, 1584, "bf16", (256, 256, 8)), (4510, 1136, "bf16", (256, 128, 8)), (2798, 1424, "f32", (256, 128, 8))])
+    (6713, 1584, "bf16", (256, 256, 8)), (4510, 1136, "bf16", (256, 128, 8)), (2798, 1424, "f32", (256, 128, 8)),
+    (2041, 3056, "bf16", (128, 192, 4))])
 def test_rotate_into_rows_of_any_alignment(B, T, d, dtype, tile):
     """Every tile of the rotate GEMM (each shape's is checked; ragged rows and columns) into aligned rows, which the
     large tiles store 16 bytes per lane, and into rows of an odd pitch from an odd element on, which they may not: the same
