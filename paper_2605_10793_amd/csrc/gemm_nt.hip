@@ -936,8 +936,8 @@ constexpr bool fits_largest_8(int epi) {
 //  128 x 192            rotations of at most 256 such tiles (4 wavefronts of 64 x 96 read 80 KiB of LDS a K step, 8 of 64 x 48 would 112)
 //                       and applies: 2048 x 3072 rotated 36.0 us (192 tiles of 256 x 128 39.3), 1842 x 2576 34.8 (40.0), 978 x 4464
 //                       50.4 (59.5), with signs and operand 2.5 to 10 us less a step; update at 2304 727 (746).  Two rounds lose:
-//                       2165 x 4240 104 and 92.  From 20 K steps (below, 4600 x 1072 takes 17.1
-//                       against 19.3, but tests name 256 x 128 there) to 100 (700 x 6400; not measured beyond).  Accumulating at 2304 it was no faster than 192 x 192.
+//                       2165 x 4240 104 and 92.  From 20 K steps to 100 (700 x 6400), the range it was measured over; the lower line is no
+//                       crossing (4600 x 1072, 17 steps: 17.1 us, 256 x 128 19.3).  Accumulating at 2304 it was no faster than 192 x 192.
 // (One launch after another on the same operands; the constants above are dearer, as operands just written by other units are.)
 constexpr bool special_tile(int t, int epi, bool sym) {
   switch (t) {
