@@ -78,8 +78,65 @@ __device__ __forceinline__ float again(float x) {
 // the hardware returns zeros (also for loads whose destination is LDS).
 constexpr uint32_t kOobOffset = 0x80000000u;
 
+// a / b for 0 <= a, 0 < b.  Below 2^21 by the fp32 reciprocal: (a + 1/2) / b lies at least 1 / 2b from a whole number, its
+// relative error is below 2^-22.  (The division ahead of a kernel's first loads is the latency of the launch: an integer one takes
+// several times as long.)
+__host__ __device__ inline int quotient(int a, int b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  if (a < (1 << 21)) return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
+#else
+  if (a < (1 << 21)) return (int)(((float)a + 0.5f) * (1.0f / (float)b));
+#endif
+  return a / b;
+}
+
+// Which tile workgroup bid computes.  Workgroups are dealt round-robin to the 8 XCDs (bid % 8), each with its own L2; every XCD
+// takes a run of consecutive tiles (the first n % 8 of them one tile more) in the order of the grid:
+//   bands > 0   whole grids: `bands` bands of tile rows of equal height (+- 1), down the columns of one band after another;
+//               mirrored grids (the tiles on and above the diagonal, tiles_m == tiles_n): the same in bands of `bands` rows
+//   0           along the rows; mirrored grids: tile rows r and T-1-r, which hold T + 1 tiles between them, after one another
+// What the tiles that an XCD runs at a time read together is one panel per tile row and column they span: see order_of.
+__host__ __device__ inline void tile_of(int bid, int tiles_m, int tiles_n, bool sym, int bands, int* tm, int* tn) {
+  const int n = sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
+  const int x = bid & 7, rest = n & 7;
+  int at = x * (n >> 3) + (x < rest ? x : rest) + (bid >> 3);
+  if (sym && bands == 0) {
+    const int pair = quotient(at, tiles_m + 1), within = at - pair * (tiles_m + 1);
+    const bool first = within < tiles_m - pair;
+    *tm = first ? pair : tiles_m - 1 - pair;
+    *tn = first ? pair + within : within - 1;
+  } else if (sym) {
+    int r0 = 0, h;
+    for (;; r0 += h) {
+      h = bands < tiles_m - r0 ? bands : tiles_m - r0;
+      const int in_band = h * (tiles_m - r0) - h * (h - 1) / 2;
+      if (at < in_band) break;
+      at -= in_band;
+    }
+    int c = 0;   // the band's columns: 1, 2 .. h tiles (its triangle), then h each
+    while (c < h && at > c) { at -= c + 1; ++c; }
+    const int right = c < h ? 0 : quotient(at, h);
+    *tm = r0 + at - right * h;
+    *tn = r0 + c + right;
+  } else if (bands == 0) {
+    *tm = quotient(at, tiles_n);
+    *tn = at - *tm * tiles_n;
+  } else if (bands == 1) {
+    *tn = quotient(at, tiles_m);
+    *tm = at - *tn * tiles_m;
+  } else {
+    const int q = quotient(tiles_m, bands), r = tiles_m - q * bands;   // the first r bands have q + 1 rows
+    const int tall = r * (q + 1) * tiles_n;
+    const bool in_tall = at < tall;
+    const int h = in_tall ? q + 1 : q, local = in_tall ? at : at - tall;
+    const int band = quotient(local, h * tiles_n), in_band = local - band * (h * tiles_n);
+    *tn = quotient(in_band, h);
+    *tm = (in_tall ? 0 : r * (q + 1)) + band * h + in_band - *tn * h;
+  }
+}
+
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool F16, bool SYM>
-__global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int by_rows) {
+__global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int bands) {
   static_assert(!SYM || (BM == BN && (EPI == EPI_GRAMW || EPI == EPI_SQUARE || EPI == EPI_FRO2)),
                 "mirrored tiles: square tiles, symmetric results");
   constexpr int NW = WGM * WGN;                 // wavefronts per workgroup
@@ -99,50 +156,11 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   const int wm = wave / WGN, wn = wave % WGN;
   const int kg = lane >> 4, col = lane & 15;    // operand fragments: row (or column) col, K elements 8 kg .. 8 kg + 7 of 32
 
-  // Workgroups are dealt round-robin to the 8 XCDs (bid % 8), each with its own L2, and
-  // an XCD runs 32 of them at a time.  Map the 32 workgroups that are co-resident on an
-  // XCD to a compact 4 x 8 block of output tiles, so that per K step the XCD pulls
-  // (4 + 8) operand panels through its L2 instead of up to (32 + 1).
-  // Any other count: every XCD takes a run of consecutive tiles (the first n % 8 of them one tile more), along the rows
-  // or the columns of the tile grid, whichever the launcher found to need fewer panels.  Dealt out one by one instead, an
-  // XCD meets nearly every panel of both operands: fp32 777 x 1040 rotated (13 x 17 tiles) 36.5 us that way, 32.3 so; the
-  // update at d = 1104 (171 mirrored tiles) 331 and 311.
-  [[maybe_unused]] auto xcd_run = [](int b, int n) {
-    const int x = b & 7, r = n & 7;
-    return x * (n >> 3) + (x < r ? x : r) + (b >> 3);
-  };
-  int bid = blockIdx.x;
-  const int ntiles = tiles_m * tiles_n;
   int tm, tn;
-  if constexpr (SYM) {
-    // Tiles on and above the diagonal only: tile rows r and T-1-r together hold T+1 of them, and such a pair of rows
-    // needs few operand panels (2 of A, T-r of B).  With T a multiple of 16 every XCD (bid % 8) gets whole pairs, else a run
-    // of consecutive tiles.
-    const int T = tiles_m;
-    int pair, within;
-    if ((T & 15) == 0) {
-      const int xcd = bid & 7, local = bid >> 3;
-      pair = xcd + 8 * (local / (T + 1));
-      within = local % (T + 1);
-    } else {
-      bid = xcd_run(bid, T * (T + 1) / 2);
-      pair = bid / (T + 1);
-      within = bid % (T + 1);
-    }
-    if (within < T - pair) { tm = pair; tn = pair + within; }
-    else { tm = T - 1 - pair; tn = tm + (within - (T - pair)); }
-  } else if ((tiles_m & 3) == 0 && (tiles_n & 7) == 0 && (((tiles_m >> 2) * (tiles_n >> 3)) & 7) == 0) {
-    const int xcd = bid & 7, local = bid >> 3;
-    const int group = (local >> 5) * 8 + xcd, within = local & 31;
-    const int gm = tiles_m >> 2;
-    tm = (group % gm) * 4 + (within & 3);
-    tn = (group / gm) * 8 + (within >> 2);
-  } else {
-    bid = xcd_run(bid, ntiles);
-    const int len = by_rows ? tiles_n : tiles_m, line = bid / len, at = bid - line * len;
-    tm = by_rows ? line : at;
-    tn = by_rows ? at : line;
-  }
+  tile_of(blockIdx.x, tiles_m, tiles_n, SYM, bands, &tm, &tn);
+  tm = __builtin_amdgcn_readfirstlane(tm);   // (the reciprocal is a vector instruction)
+  tn = __builtin_amdgcn_readfirstlane(tn);
+  [[maybe_unused]] const int ntiles = tiles_m * tiles_n;
   const int m0 = tm * BM, n0 = tn * BN;
   const int bz = blockIdx.z;
   const bf16_bits* Ab = g.A + (int64_t)bz * g.batchA;
@@ -990,6 +1008,36 @@ Choice choose(const GemmArgs& a, GemmEpilogue epi, int batch) {
   return best;
 }
 
+// The order of the tiles (`bands` of tile_of).  32 tiles at a time per XCD, or its whole share: in bands for which they read the
+// fewest operand rows, that is blocks that are about square.  Where a launch has several rounds the XCDs' reads otherwise cost
+// power, if not time: 11008 x 4096 rotated (688 tiles, 33 panels at a time down the columns, 12 so) 313 -> 291 us at the clock the
+// chip sustains, fp32 777 x 1040 (one round, six segments) 31.9 -> 30.9.  A polar product of one round reads what the same XCD
+// has just written, and whole lines keep more of that in its L2: update at d = 1104 360 us along the columns, 371 in bands.
+int order_of(int tiles_m, int tiles_n, int bm, int bn, bool sym, int epi, int batch, int steps) {
+  const int n = sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
+  const int share = (n + 7) / 8, run = std::min(share, 32);
+  const bool square = (tiles_m & 3) == 0 && (tiles_n & 7) == 0 && (((tiles_m >> 2) * (tiles_n >> 3)) & 7) == 0;   // whole 4 x 8 blocks
+  const bool rotates = epi == EPI_ACT || epi == EPI_SIGN || epi == EPI_SIGN_ACT || epi == EPI_SIGN_XT;
+  const bool lines = (int64_t)n * batch <= 256 && !(rotates && steps >= 32);
+  if (sym) {
+    int h = 0;
+    if (!lines)
+      for (h = 1; (h + 1) * (h + 1) <= run;) ++h;
+    return h;
+  }
+  if (lines && !square) {   // along the columns or the rows, whichever reads fewer operand rows
+    const int down = std::min(share, tiles_m) * bm + (share / tiles_m + 1) * bn, across = std::min(share, tiles_n) * bn + (share / tiles_n + 1) * bm;
+    return across < down ? 0 : 1;
+  }
+  int best = 1;
+  int64_t best_rows = INT64_MAX;
+  for (int h = std::min(tiles_m, run); h >= 1; --h) {
+    const int64_t rows = (int64_t)h * bm + (int64_t)((run + h - 1) / h) * bn;
+    if (rows < best_rows) { best_rows = rows; best = (tiles_m + h - 1) / h; }
+  }
+  return best;
+}
+
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool F16, bool SYM = false>
 hipError_t launch_one(const GemmArgs& a, int batch, hipStream_t stream) {
   constexpr int smem = NSTAGE * (BM + BN) * BK * 2;
@@ -1002,10 +1050,8 @@ hipError_t launch_one(const GemmArgs& a, int batch, hipStream_t stream) {
   if (e != hipSuccess) return e;
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
   dim3 grid(SYM ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n, 1, batch);
-  // operand rows the run of tiles of one XCD reads, along the tile grid's columns and along its rows
-  const int run = (tiles_m * tiles_n + 7) / 8;
-  const int down = std::min(run, tiles_m) * BM + (run / tiles_m + 1) * BN, across = std::min(run, tiles_n) * BN + (run / tiles_n + 1) * BM;
-  hipLaunchKernelGGL(kern, grid, dim3(64 * WGM * WGN), smem, stream, a, tiles_m, tiles_n, across < down ? 1 : 0);
+  const int bands = order_of(tiles_m, tiles_n, BM, BN, SYM, EPI, batch, (a.K + BK - 1) / BK * a.nseg);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * WGM * WGN), smem, stream, a, tiles_m, tiles_n, bands);
   return hipGetLastError();
 }
 
@@ -1052,6 +1098,14 @@ extern "C" __attribute__((visibility("default"))) void conqur_gemm_tile_for_test
   const Choice c = choose(a, (GemmEpilogue)epi, batch);
   const Tile& u = kTiles[c.tile];
   out[0] = u.bm; out[1] = u.bn; out[2] = u.wgm * u.wgn; out[3] = (int)c.tiles; out[4] = c.sym;
+}
+
+// For tests (host code only): the tile of every workgroup of such a grid, in the order the launcher takes for it.
+extern "C" __attribute__((visibility("default"))) void conqur_gemm_order_for_tests(int epi, int symmetric, int tiles_m, int tiles_n, int bm, int bn,
+                                                                                   int batch, int steps, int* tm, int* tn) {
+  const int bands = order_of(tiles_m, tiles_n, bm, bn, symmetric != 0, epi, batch, steps);
+  const int n = symmetric ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
+  for (int i = 0; i < n; ++i) tile_of(i, tiles_m, tiles_n, symmetric != 0, bands, tm + i, tn + i);
 }
 
 int gemm_num_workgroups(const GemmArgs& a, GemmEpilogue epi, int batch) { return (int)(choose(a, epi, batch).tiles * batch); }

@@ -2,6 +2,7 @@
 import ctypes
 import random
 
+import numpy as np
 import pytest
 
 from paper_2605_10793_amd import binding
@@ -48,3 +49,23 @@ def test_workgroups_cover_the_output():
         bm, bn, waves, wg, mirrored = tile(EPI_GRAMW, 1, 1, N, N, N)
         side = -(-N // bm)
         assert wg == (side * (side + 1) // 2 if mirrored else side * -(-N // bn)) and (not mirrored or (bm == bn and side >= 8))
+
+
+@pytest.mark.parametrize("sym", [0, 1])
+def test_every_tile_of_a_grid_is_one_workgroups(sym):
+    """Whole and mirrored grids, along lines and in bands: each tile is computed by exactly one workgroup."""
+    L = binding.load()
+    rng = np.random.default_rng(0)
+    grids = [(1, 1), (1, 9), (9, 1), (7, 8), (16, 16), (43, 16), (13, 17), (33, 5), (64, 64), (65536, 1), (3000, 700)]
+    grids += [tuple(int(v) for v in rng.integers(1, 70, 2)) for _ in range(60)]
+    for m, n in grids:
+        if sym:
+            m = n = min(m, 1000)
+        count = m * (m + 1) // 2 if sym else m * n
+        for epi in (1, 4):
+            for batch, steps in ((1, 4), (1, 64), (32, 64)):
+                tm, tn = np.full(count, -1, np.int32), np.full(count, -1, np.int32)
+                L.conqur_gemm_order_for_tests(epi, sym, m, n, 128, 192, batch, steps, tm.ctypes.data_as(ctypes.c_void_p), tn.ctypes.data_as(ctypes.c_void_p))
+                assert tm.min() >= 0 and tm.max() < m and tn.min() >= 0 and tn.max() < n
+                assert not sym or (tm <= tn).all()
+                assert np.unique(tm.astype(np.int64) * n + tn).size == count
