@@ -76,6 +76,11 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// A value for the host, in pinned memory: stored through every cache, so that it is there once the kernel (and an event behind it)
+// has completed, whatever that event releases.
+template <typename T>
+__device__ __forceinline__ void store_for_host(T* p, T v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM); }
+
 static inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }
 
 // The accumulate operand holds the unit rows x^ = x / ||x|| times this power of two, in fp16.  |x^| <= 1, and on

@@ -41,6 +41,12 @@ constexpr int kTimingSlots = 12;
 
 }  // namespace
 
+struct HostScalars {
+  unsigned long long stamp[2];   // the device's wall clock (100 MHz ticks) at the update's first and last launch
+  double score[2];               // squared error and energy of a scored batch
+  int nonfinite;
+};
+
 struct conqur_ctx {
   conqur_config cfg{};
   int d = 0, heads = 0, dh = 0, np = 1;  // np: bf16 planes per activation operand (1 bf16, 3 fp32)
@@ -69,17 +75,15 @@ struct conqur_ctx {
   int* nonfinite = nullptr;
   void* Y = nullptr;           // [tmax][d] rotated activations (quantiser score)
   float *row_sse = nullptr, *row_en = nullptr;
-  double* qsum = nullptr;      // [2]
   // polar workspaces
   float* Rprev = nullptr;                            // narrow heads: the rotation the running update started from
   float* PX = nullptr;                               // polar iterate, fp32 [heads][dh][dh]
   bf16_bits *PXn[2] = {nullptr, nullptr};            // iterate as bf16 split planes [3][heads][dh][dh], ping-pong
   bf16_bits *PXt[2] = {nullptr, nullptr};            // ... transposed
   bf16_bits *PW = nullptr, *PW2 = nullptr;           // polynomial factor planes [3][heads][dh][dh]
-  double* resid = nullptr;                           // [kResidSlots][heads] residual history of one update
   double* resid_part = nullptr;                      // [heads][parts] per-wavefront partials of one Gram GEMM
   double *fro2 = nullptr, *inner = nullptr;          // [heads]
-  double* dot_part = nullptr;                        // [heads][(dh/64)^2] per-tile partials of <R, M>
+  double* dot_part = nullptr;                        // [2][heads][(dh/64)^2] per-tile partials of <R_op, M> and of <R, M>
   int64_t last_T = 0;
   size_t stat_words = 0;
   double* fused_res = nullptr;                       // start of the result block: [2][heads] residuals of the one-launch update
@@ -102,8 +106,12 @@ struct conqur_ctx {
   bool ev_valid[ST_COUNT]{};
   hipEvent_t ev_resid = nullptr;   // behind the copy of a closing residual: the host waits for this, not for the stream
   hipEvent_t ev_sq = nullptr;      // behind the copy of ||D^2||_F^2 of the closing step's D^2 product
-  double* host_res = nullptr;      // pinned: [kResidSlots][heads] residual history, then the update's result block (from fused_res on)
-  float* host_rows = nullptr;      // pinned: per-row errors and energies of one score call (up to kHostSumRows rows)
+  // Pinned: what the kernels of a call leave for the host they write here themselves (dev_*: the device's addresses).
+  double* host_res = nullptr;      // [kResidSlots][heads] residual history, then the update's result block (5 heads, see UpdateEnd)
+  double* dev_res = nullptr;
+  HostScalars* host_scalars = nullptr;
+  HostScalars* dev_scalars = nullptr;
+  float* host_rows = nullptr;      // per-row results of one score or diagnostics call, copied (up to kHostSumRows rows)
   std::vector<void*> allocs;
 };
 
@@ -211,6 +219,7 @@ void conqur_destroy(conqur_ctx* ctx) {
   if (ctx->ev_resid) (void)hipEventDestroy(ctx->ev_resid);
   if (ctx->ev_sq) (void)hipEventDestroy(ctx->ev_sq);
   if (ctx->host_res) (void)hipHostFree(ctx->host_res);
+  if (ctx->host_scalars) (void)hipHostFree(ctx->host_scalars);
   if (ctx->host_rows) (void)hipHostFree(ctx->host_rows);
   delete ctx;
 }
@@ -283,7 +292,6 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   A(dev_alloc(ctx, reinterpret_cast<char**>(&ctx->Y), tmax * d * (ctx->f32 ? 4 : 2)));
   A(dev_alloc(ctx, &ctx->row_sse, 2 * tmax));   // per-row SSE, then per-row energy
   ctx->row_en = ctx->row_sse + tmax;
-  A(dev_alloc(ctx, &ctx->qsum, (size_t)2));
   A(dev_alloc(ctx, &ctx->PX, blk));
   if (dh <= (uint32_t)kHeadPolarMaxDh && cfg->polar_precision == 0) A(dev_alloc(ctx, &ctx->Rprev, blk));   // (read only by updates that take the one-launch path)
   for (int b = 0; b < 2; ++b) {
@@ -292,7 +300,6 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   }
   A(dev_alloc(ctx, &ctx->PW, 3 * blk));
   A(dev_alloc(ctx, &ctx->PW2, 3 * blk));
-  A(dev_alloc(ctx, &ctx->resid, (size_t)kResidSlots * ctx->heads));
   A(dev_alloc(ctx, &ctx->resid_part, (size_t)gemm_max_partials((int)dh) * ctx->heads));
   ctx->head_fused = ctx->dh == 128 && !ctx->f32;
   if (ctx->head_fused) {
@@ -307,15 +314,18 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
     if (ctx->ksplit_max > 1) A(dev_alloc(ctx, &ctx->Mpart, (size_t)ctx->ksplit_max * blk));
     else ctx->ksplit_max = 0;
   }
-  A(dev_alloc(ctx, &ctx->dot_part, (size_t)ctx->heads * pack_dot_partials(ctx->dh)));
+  A(dev_alloc(ctx, &ctx->dot_part, (size_t)2 * ctx->heads * pack_dot_partials(ctx->dh)));
   for (int k = 0; k < 2; ++k) A(dev_alloc(ctx, &ctx->clk[k], (size_t)4 * kClkMaxWorkgroups));
   for (int s = 0; s < ST_COUNT && e == hipSuccess; ++s)
     for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreate(&ctx->ev[s][k]);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_resid, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_sq, hipEventDisableTiming);
   if (e == hipSuccess)
-    e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host_res), ((size_t)kResidSlots * ctx->heads + 5 * ctx->heads + 1) * sizeof(double),
+    e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host_res), ((size_t)kResidSlots * ctx->heads + 5 * ctx->heads) * sizeof(double),
                       hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&ctx->dev_res), ctx->host_res, 0);
+  if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host_scalars), sizeof(HostScalars), hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&ctx->dev_scalars), ctx->host_scalars, 0);
   if (e == hipSuccess)
     e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host_rows), (size_t)2 * std::min<size_t>(tmax, kHostSumRows) * sizeof(float),
                       hipHostMallocDefault);
@@ -648,9 +658,12 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   hipStream_t s = ctx->stream;
   const int h = ctx->heads, dh = ctx->dh;
   const int64_t blk = (int64_t)dh * dh, plane = (int64_t)h * blk;
-  const bool timed = ctx->timing || out;
+  const bool timed = ctx->timing != 0;   // (the time the statistics report is taken by the first and the last launch themselves)
   const bool trace = std::getenv("CONQUR_TRACE") != nullptr;
   if (timed) HIP_TRY(hipEventRecord(ctx->ev[ST_UPDATE][0], s));
+  HostScalars* const scalars = ctx->host_scalars;   // (nothing is in flight that writes them: every call that asks for them waits)
+  scalars->nonfinite = 0;
+  unsigned long long* const stamp0 = &ctx->dev_scalars->stamp[0];
 
   const int np_main = 1 + (int)ctx->cfg.polar_precision;
   // Heads of width up to kHeadPolarMaxDh: the launch that runs the main phase also forms the start iterate (and, below, takes
@@ -659,13 +672,17 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   const bool one_launch = dh <= kHeadPolarMaxDh && np_main == 1;
   const bool one_launch_step = !one_launch && dh <= kPolarStepMaxDh && np_main == 1;   // (a launch a step: polar_step.hip)
   bool use_hstart = one_launch && ctx->cfg.polar_max_iters > 0;
+  int fro2_parts = 0;         // partial sums of ||M||_F^2 per head in dotrm_part
   if (ctx->parts_pending) {   // per-head step: M is summed from the token shares here, ||M||_F^2 from the same pass
-    HIP_TRY(launch_head_reduce(ctx->Mpart, ctx->parts_pending, h, ctx->M, 0, ctx->dotrm_part, s));
-    if (use_hstart) { hstart.fro2_parts = ctx->dotrm_part; hstart.nparts = kHeadReduceParts; }
-    else HIP_TRY(launch_sum_partials(ctx->dotrm_part, kHeadReduceParts, h, ctx->fro2, s));
+    HIP_TRY(launch_head_reduce(ctx->Mpart, ctx->parts_pending, h, ctx->M, 0, ctx->dotrm_part, s, stamp0));
+    fro2_parts = kHeadReduceParts;
+    if (use_hstart) { hstart.fro2_parts = ctx->dotrm_part; hstart.nparts = fro2_parts; }
     ctx->parts_pending = 0;
   } else if (!use_hstart) {
-    HIP_TRY(launch_fro2(ctx->M, h, blk, ctx->dotrm_part, ctx->fro2, s));
+    HIP_TRY(launch_fro2(ctx->M, h, blk, ctx->dotrm_part, stamp0, s));
+    fro2_parts = dot_rm_partials(blk);
+  } else {
+    hstart.stamp = stamp0;
   }
   if (use_hstart) {
     hstart.M = ctx->M; hstart.R = ctx->R; hstart.fro2_out = ctx->fro2; hstart.lambda = ctx->cfg.prox_lambda;
@@ -687,10 +704,12 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   // planes of the first step (no fp32 copy: at least one main step runs, and the last one writes the fp32 iterate)
   // The same pass evaluates the l1 term of the rows this update consumes (general path; the fused per-head step
   // keeps it as it goes): a copy of either is taken here, before the statistics are cleared.
+  double* const dot_end = ctx->dot_part + (size_t)h * pack_dot_partials(dh);   // partials of <R, M>, behind those of <R_op, M>
+  const bool ldot_parts = !use_hstart && !ctx->head_fused;
   if (!use_hstart) {
-    HIP_TRY(launch_polar_start_pack(ctx->M, ctx->R, h, dh, ctx->cfg.prox_lambda, ctx->fro2, np_main, nullptr,
+    HIP_TRY(launch_polar_start_pack(ctx->M, ctx->R, h, dh, ctx->cfg.prox_lambda, ctx->dotrm_part, fro2_parts, ctx->fro2, np_main,
                                     ctx->PXn[cur], ctx->PXt[cur], plane, ctx->f32 ? 0 : 1,
-                                    ctx->head_fused ? nullptr : ctx->dot_part, ctx->ldot, s, main_f16));
+                                    ctx->head_fused ? nullptr : ctx->dot_part, s, main_f16));
     if (ctx->head_fused) HIP_TRY(hipMemcpyAsync(ctx->ldot, ctx->L, h * sizeof(double), hipMemcpyDeviceToDevice, s));
   }
   int slot = 0;           // next residual-history slot
@@ -712,7 +731,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     hipError_t e = launch_gemm_nt(g, EPI_GRAMW, h, s);
     mfma_flop += gemm_issued_flop(g, EPI_GRAMW, h);
     if (e == hipSuccess && want_resid)
-      e = launch_sum_partials(ctx->resid_part, gemm_num_partials(g, EPI_GRAMW, h), h, ctx->resid + (size_t)slot * h, s);
+      e = launch_sum_partials(ctx->resid_part, gemm_num_partials(g, EPI_GRAMW, h), h, ctx->dev_res + (size_t)slot * h, s);
     return e;
   };
   // X' = X W (+ X): reads the planes in buffer `cur`, writes np_x planes (both layouts)
@@ -746,7 +765,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     return e;
   };
   // W2 = D + 1.5 D^2 from the planes of D = (I - G)/2 in PW (D is symmetric, so D D^T = D^2)
-  // keep_square: D^2 itself is kept as a plane and ||D^2||_F^2 goes to residual slot `slot` (copied to the host behind
+  // keep_square: D^2 itself is kept as a plane and ||D^2||_F^2 goes to residual slot `slot` (on the host behind
   // ev_sq): both serve the orthogonality bounds of the step that applies this correction.
   int sq_slot = -1;
   auto square_correction = [&](bool keep_square) -> hipError_t {
@@ -764,9 +783,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     mfma_flop += gemm_issued_flop(g, EPI_SQUARE, h);
     hipError_t e = launch_gemm_nt(g, EPI_SQUARE, h, s);
     if (!keep_square) return e;
-    if (e == hipSuccess) e = launch_sum_partials(ctx->resid_part, gemm_num_partials(g, EPI_SQUARE, h), h, ctx->resid + (size_t)slot * h, s);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(ctx->host_res + (size_t)slot * h, ctx->resid + (size_t)slot * h, h * sizeof(double), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = launch_sum_partials(ctx->resid_part, gemm_num_partials(g, EPI_SQUARE, h), h, ctx->dev_res + (size_t)slot * h, s);
     if (e == hipSuccess) e = hipEventRecord(ctx->ev_sq, s);
     if (e == hipSuccess) sq_slot = slot++;
     return e;
@@ -784,13 +801,12 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     g.resid_part = ctx->resid_part;
     hipError_t e = launch_gemm_nt(g, EPI_FRO2, h, s);
     mfma_flop += gemm_issued_flop(g, EPI_FRO2, h);
-    if (e == hipSuccess) e = launch_sum_partials(ctx->resid_part, gemm_num_partials(g, EPI_FRO2, h), h, ctx->resid + (size_t)slot * h, s);
+    if (e == hipSuccess) e = launch_sum_partials(ctx->resid_part, gemm_num_partials(g, EPI_FRO2, h), h, ctx->dev_res + (size_t)slot * h, s);
     return e;
   };
-  double* const hist = ctx->host_res;   // pinned, so that the copies below are asynchronous
-  // The copy of residual slot sl_idx and an event behind it; work enqueued after this does not delay the host's read.
-  auto post_resid = [&](int sl_idx) -> conqur_status {
-    HIP_TRY(hipMemcpyAsync(hist + (size_t)sl_idx * h, ctx->resid + (size_t)sl_idx * h, h * sizeof(double), hipMemcpyDeviceToHost, s));
+  double* const hist = ctx->host_res;   // (written by the kernels that sum a residual's partials)
+  // An event behind the sums of residual slot last filled; work enqueued after this does not delay the host's read.
+  auto post_resid = [&]() -> conqur_status {
     HIP_TRY(hipEventRecord(ctx->ev_resid, s));
     return CONQUR_OK;
   };
@@ -906,25 +922,37 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   const float* final_x = ctx->PX;   // where the final iterate lives (the lean closing step writes R directly)
   const bool keep_sq = !ctx->cfg.polar_verify || trace;
   bool finished = false;
-  auto enqueue_finish = [&]() -> conqur_status {
-    // R = final iterate (unless it is there already), <R, M>, and the rotate operand planes of R^T: one pass
-    HIP_TRY(launch_polar_finish_pack(final_x, ctx->M, h, dh, ctx->np, final_x == ctx->R ? nullptr : ctx->R, ctx->RopT, plane,
-                                     ctx->dot_part, ctx->inner, s));
-    // statistics restart empty (Alg. 1): M is overwritten by the next accumulate
-    HIP_TRY(launch_fill_zero(ctx->L, ctx->stat_words * sizeof(double), s));
+  double* const resblk = ctx->host_res + (size_t)kResidSlots * h;   // outcome of a closing step in the main phase's launch, if any | results
+  // The update's last launch: results to the host, statistics restart empty (Alg. 1: M is overwritten by the next accumulate).
+  auto enqueue_end = [&](const double* outcome, bool inner_parts) -> conqur_status {
+    UpdateEnd u{};
+    u.heads = h;
+    u.ldot_parts = ldot_parts ? ctx->dot_part : nullptr;
+    u.inner_parts = inner_parts ? dot_end : nullptr;
+    u.nparts = pack_dot_partials(dh);
+    u.scalars = ctx->ldot;
+    u.outcome = outcome;
+    u.nonfinite = ctx->nonfinite;
+    u.stats = ctx->L; u.stats_bytes = ctx->stat_words * sizeof(double);
+    u.host = ctx->dev_res + (size_t)kResidSlots * h + (outcome ? 0 : 2 * h);
+    u.host_nonfinite = &ctx->dev_scalars->nonfinite;
+    u.stamp = &ctx->dev_scalars->stamp[1];
+    HIP_TRY(launch_update_end(u, s));
     if (timed) HIP_TRY(hipEventRecord(ctx->ev[ST_UPDATE][1], s));
     return CONQUR_OK;
+  };
+  auto enqueue_finish = [&]() -> conqur_status {
+    // R = final iterate (unless it is there already), <R, M>, and the rotate operand planes of R^T: one pass
+    HIP_TRY(launch_polar_finish_pack(final_x, ctx->M, h, dh, ctx->np, final_x == ctx->R ? nullptr : ctx->R, ctx->RopT, plane, dot_end, s));
+    return enqueue_end(nullptr, true);
   };
   // Outcome of a closing step taken inside the main phase's launch (narrow heads): accepted if every head took it
   // and the bound from ||D^2||_F (see below) is within the tolerance; otherwise the general closing steps continue from
   // the hand-over state, which that launch wrote as well.  R and the operand of the heads that did take the step are replaced
   // by then; the launch has kept the previous rotation aside, for the nudge below and for an update that fails.  The
-  // statistics and the non-finite flag are cleared on the device, unless a residual is not finite: the outcome and the result
-  // block come in one copy, and the host waits once, with nothing left to enqueue behind the outcome it expects.
-  double* const resblk = ctx->host_res + (size_t)(kResidSlots + 2) * h;   // <R_op, M> | <R, M> | ||M||_F^2 | non-finite flag
-  const size_t resblk_bytes = ((size_t)3 * h + 1) * sizeof(double);
+  // statistics and the non-finite flag are cleared on the device, unless a residual is not finite: one small launch does that and
+  // brings the outcome and the results, and the host waits once, with nothing left to enqueue behind the outcome it expects.
   bool r_replaced = false, fused_done = false;
-  int nonfinite = 0;
   auto fail_nonfinite = [&]() -> conqur_status {   // the context is left as the update found it
     if (r_replaced) {
       HIP_TRY(hipMemcpyAsync(ctx->R, ctx->Rprev, (size_t)plane * sizeof(float), hipMemcpyDeviceToDevice, s));
@@ -934,14 +962,10 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     return fail(ctx, CONQUR_ENONFINITE, "update_rotation: non-finite polar iterate");
   };
   auto fused_outcome = [&]() -> conqur_status {
-    double* const outcome = resblk - 2 * h;
-    HIP_TRY(hipMemcpyAsync(outcome, ctx->fused_res, 2 * h * sizeof(double) + resblk_bytes, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipEventRecord(ctx->ev_resid, s));
-    HIP_TRY(launch_fill_zero_if_finite(ctx->fused_res, h, ctx->nonfinite, (1 + ctx->stat_words) * sizeof(double), s));
-    if (timed) HIP_TRY(hipEventRecord(ctx->ev[ST_UPDATE][1], s));
-    HIP_TRY(hipEventSynchronize(ctx->ev_resid));
-    std::memcpy(hist + (size_t)fused_slot * h, outcome, 2 * h * sizeof(double));
-    std::memcpy(&nonfinite, resblk + 3 * h, sizeof(int));
+    const conqur_status st_end = enqueue_end(ctx->fused_res, false);
+    if (st_end != CONQUR_OK) return st_end;
+    HIP_TRY(hipStreamSynchronize(s));
+    std::memcpy(hist + (size_t)fused_slot * h, resblk, 2 * h * sizeof(double));
     bool ok = true, finite = true;
     double worst_res = 0.0, worst_pred = 0.0;
     for (int q = 0; q < h; ++q) {
@@ -982,7 +1006,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     // The first check after a main phase practically always calls for the quintic step: enqueue its D^2 product
     // before the host waits for the residual, so that the device keeps working through the round trip.
     const bool spec_square = closing == 0;
-    st = post_resid(last_slot);   // before the D^2 product, so that the host reads the residual while that runs
+    st = post_resid();   // before the D^2 product, so that the host reads the residual while that runs
     if (st != CONQUR_OK) return st;
     if (spec_square) HIP_TRY(square_correction(keep_sq));
     st = wait_resid(last_slot, &res);
@@ -1052,7 +1076,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       }
       HIP_TRY(cube_norm());
       const int cslot = slot++;
-      st = post_resid(cslot);
+      st = post_resid();
       if (st != CONQUR_OK) return st;
       if (lean) {   // expected to be the end: the finishing kernels go in before the host waits for the norm
         st = enqueue_finish();
@@ -1086,24 +1110,15 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
     if (st != CONQUR_OK) return st;
   }
   ctx->ev_valid[ST_UPDATE] = timed;
-  if (!fused_done) {   // (else the result block came with the outcome)
-    HIP_TRY(hipMemcpyAsync(resblk, ctx->ldot, resblk_bytes, hipMemcpyDeviceToHost, s));
-    HIP_TRY(launch_fill_zero(ctx->nonfinite, sizeof(int), s));
-  }
-  HIP_TRY(hipStreamSynchronize(s));
-  const double *ldot = resblk, *inner = resblk + h, *fro2 = resblk + 2 * h;
-  if (!fused_done) {
-    int flag = 0;
-    std::memcpy(&flag, resblk + 3 * h, sizeof(int));
-    nonfinite |= flag;   // (an outcome that was not accepted has brought the flag, and cleared it, already)
-  }
+  if (!fused_done) HIP_TRY(hipStreamSynchronize(s));   // (else the results came with the outcome)
+  const double *ldot = resblk + 2 * h, *inner = resblk + 3 * h, *fro2 = resblk + 4 * h;
+  const bool nonfinite = scalars->nonfinite != 0;   // (rows of this update, whichever of its launches brought the flag)
   ctx->m_empty = true;
   ctx->have_rows = false;
   ctx->h_empty.assign(h, 1);
   ctx->h_rows.assign(h, 0);
   if (out) {
-    float ms = 0.0f;
-    HIP_TRY(hipEventElapsedTime(&ms, ctx->ev[ST_UPDATE][0], ctx->ev[ST_UPDATE][1]));
+    const double ms = 1e-5 * (double)(scalars->stamp[1] - scalars->stamp[0]);
     for (int q = 0; q < h; ++q) {
       out[q].iters = iters; out[q].accurate = closing; out[q].orth_measured = predicted ? 0u : 1u;
       out[q].orth_err = std::sqrt(hist[(size_t)last_slot * h + q]);
@@ -1137,23 +1152,25 @@ static conqur_status quant_error_impl(conqur_ctx* ctx, const void* X, uint64_t T
   {
     StageTimer tm(ctx, ST_QERR);
     // a batch's per-row results are small: the host adds them (fixed order) instead of one more kernel launch
-    // (the per-row energies directly behind the per-row errors: one copy brings both)
+    // (the per-row energies directly behind the per-row errors: one copy brings both; a summing launch that writes to the host takes
+    // as long as the copy and the additions: 2048 x 3072, three such calls 176 us, 175 so)
     HIP_TRY(launch_quant_error(ctx->Y, ctx->f32, T, ctx->d, ctx->d, (int)bits, zero_point, clip, ctx->row_sse, ctx->row_sse + T,
-                               T <= kHostSumRows ? nullptr : ctx->qsum, nullptr, 0, s));
+                               T <= kHostSumRows ? nullptr : ctx->dev_scalars->score, nullptr, 0, s));
   }
   }
-  double host[2] = {0.0, 0.0};
   if (T <= kHostSumRows) {
+    double host[2] = {0.0, 0.0};
     const float* rows = ctx->host_rows;   // pinned
     HIP_TRY(hipMemcpyAsync(ctx->host_rows, ctx->row_sse, (size_t)2 * T * sizeof(float), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
     for (int64_t i = 0; i < T; ++i) { host[0] += (double)rows[i]; host[1] += (double)rows[T + i]; }
+    *sse = host[0];
+    *energy = host[1];
   } else {
-    HIP_TRY(hipMemcpyAsync(host, ctx->qsum, sizeof(host), hipMemcpyDeviceToHost, s));
     HIP_TRY(hipStreamSynchronize(s));
+    *sse = ctx->host_scalars->score[0];
+    *energy = ctx->host_scalars->score[1];
   }
-  *sse = host[0];
-  *energy = host[1];
   return CONQUR_OK;
 }
 

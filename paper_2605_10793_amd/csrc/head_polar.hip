@@ -222,6 +222,7 @@ __global__ void __launch_bounds__(64 * NW, 2) k_head_polar(const bf16_bits* __re
   };
 
   Acc acc;
+  if (st.stamp && h == 0 && tid == 0) store_for_host(st.stamp, (unsigned long long)wall_clock64());
   if (st.M) {
     // The start of the update in this launch as well (what the packing pass does on the general path):
     // X0 = (M + lambda tau R_prev) / alpha, tau = ||M||_F / sqrt(dh), alpha = ||M||_F (1 + lambda); lambda = 0 stands for the

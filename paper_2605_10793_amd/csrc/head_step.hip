@@ -240,7 +240,9 @@ __global__ void __launch_bounds__(NTHREADS) k_head_step128(const bf16_bits* __re
 // update that follows needs no separate pass over M for ||M_h||_F.
 template <bool FRO2>
 __global__ void __launch_bounds__(256) k_head_reduce(const float* __restrict__ Mpart, int nsplit, int64_t n_total,
-                                                     float* __restrict__ M, int accumulate, double* __restrict__ fro2_part) {
+                                                     float* __restrict__ M, int accumulate, double* __restrict__ fro2_part,
+                                                     unsigned long long* __restrict__ stamp) {
+  if (stamp && blockIdx.x == 0 && threadIdx.x == 0) store_for_host(stamp, (unsigned long long)wall_clock64());
   const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;   // n_total is a multiple of 1024: no ragged block
   float4 acc = accumulate ? *reinterpret_cast<const float4*>(M + i) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   for (int s0 = 0; s0 < nsplit; s0 += 8) {   // eight shares' loads in flight, added in share order
@@ -302,17 +304,18 @@ hipError_t launch_head_step128(const bf16_bits* X, int64_t T, int64_t stride, in
 hipError_t launch_sum_shares(const float* part, int nsplit, int64_t n_total, float* M, int accumulate, hipStream_t s) {
   if (nsplit < 1 || n_total < 1024 || (n_total & 1023)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_head_reduce<false>, dim3((unsigned)(n_total / 1024)), dim3(256), 0, s, part, nsplit, n_total, M, accumulate,
-                     (double*)nullptr);
+                     (double*)nullptr, (unsigned long long*)nullptr);
   return hipGetLastError();
 }
 
-hipError_t launch_head_reduce(const float* Mpart, int nsplit, int heads, float* M, int accumulate, double* fro2_part, hipStream_t s) {
+hipError_t launch_head_reduce(const float* Mpart, int nsplit, int heads, float* M, int accumulate, double* fro2_part, hipStream_t s,
+                              unsigned long long* stamp) {
   const int64_t n_total = (int64_t)heads * DH * DH;
   const dim3 grid((unsigned)(n_total / 1024));
   if (fro2_part)
-    hipLaunchKernelGGL(k_head_reduce<true>, grid, dim3(256), 0, s, Mpart, nsplit, n_total, M, accumulate, fro2_part);
+    hipLaunchKernelGGL(k_head_reduce<true>, grid, dim3(256), 0, s, Mpart, nsplit, n_total, M, accumulate, fro2_part, stamp);
   else
-    hipLaunchKernelGGL(k_head_reduce<false>, grid, dim3(256), 0, s, Mpart, nsplit, n_total, M, accumulate, fro2_part);
+    hipLaunchKernelGGL(k_head_reduce<false>, grid, dim3(256), 0, s, Mpart, nsplit, n_total, M, accumulate, fro2_part, stamp);
   return hipGetLastError();
 }
 

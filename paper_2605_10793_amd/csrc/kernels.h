@@ -56,26 +56,46 @@ int dot_rm_partials(int64_t n);
 hipError_t launch_dot_rm(const float* R, const float* M, int heads, int64_t n, int round_bf16, double* part, double* out,
                          hipStream_t s);
 
-// fro2[h] = sum M_h^2 (overwritten).  part: heads * dot_rm_partials(n) doubles of scratch.
-hipError_t launch_fro2(const float* M, int heads, int64_t n, double* part, double* fro2, hipStream_t s);
+// part[h][dot_rm_partials(n)]: partial sums of M_h^2.  stamp: receives the device's wall clock at the start of the launch.
+hipError_t launch_fro2(const float* M, int heads, int64_t n, double* part, unsigned long long* stamp, hipStream_t s);
 
 // Start of the polar iteration, fused with the operand packing: X0 = (M + lambda*tau*R) / alpha with
 // tau = ||M||_F/sqrt(dh), alpha = ||M||_F (1 + lambda) (a head with M = 0 starts from R itself), written as np bf16
-// split planes in natural (outN) and transposed (outT) layout and, if X32 is not null, in fp32.
-// If dot_part is not null (heads * pack_dot_partials(dh) doubles), also dot_out[h] = <R_op,h , M_h> (R_op = R rounded to bf16 if
+// split planes in natural (outN) and transposed (outT) layout.  ||M_h||_F^2 is the sum of nparts partial sums per head
+// (fro2_parts[h * nparts + p]), which every workgroup adds up for itself, and goes to fro2_out[h].
+// If dot_part is not null, also pack_dot_partials(dh) partial sums per head of <R_op,h , M_h> (R_op = R rounded to bf16 if
 // round_bf16), the quantity of launch_dot_rm, from the same pass.
-hipError_t launch_polar_start_pack(const float* M, const float* R, int heads, int dh, float lambda, const double* fro2, int np,
-                                   float* X32, bf16_bits* outN, bf16_bits* outT, int64_t plane, int round_bf16,
-                                   double* dot_part, double* dot_out, hipStream_t s, int out_f16 = 0);
+hipError_t launch_polar_start_pack(const float* M, const float* R, int heads, int dh, float lambda, const double* fro2_parts, int nparts,
+                                   double* fro2_out, int np, bf16_bits* outN, bf16_bits* outT, int64_t plane, int round_bf16,
+                                   double* dot_part, hipStream_t s, int out_f16 = 0);
 
 // X += kappa * R over n elements (all heads).
 hipError_t launch_axpy(float* X, const float* R, int64_t n, float kappa, hipStream_t s);
 
-// End of the polar iteration, one pass over X: inner[h] = <X_h, M_h> (overwritten), the rotate operand outT =
-// np bf16 split planes of X^T, and, if R32 is not null, R32 = X.  dot_part: heads * pack_dot_partials(dh) doubles.
+// End of the polar iteration, one pass over X: pack_dot_partials(dh) partial sums per head of <X_h, M_h>, the rotate operand
+// outT = np bf16 split planes of X^T, and, if R32 is not null, R32 = X.
 int pack_dot_partials(int dh);
 hipError_t launch_polar_finish_pack(const float* X, const float* M, int heads, int dh, int np, float* R32, bf16_bits* outT,
-                                    int64_t plane, double* dot_part, double* inner, hipStream_t s);
+                                    int64_t plane, double* dot_part, hipStream_t s);
+
+// The last launch of an update: its scalar results to the host, the batch statistics and the non-finite flag cleared.
+struct UpdateEnd {
+  int heads;
+  // <R_op, M> and <R, M> per head: sums of nparts partial sums each, or, where the pointer is null, as they lie at scalars
+  const double* ldot_parts;
+  const double* inner_parts;
+  int nparts;
+  const double* scalars;       // device: [ldot heads | inner heads | fro2 heads]
+  const double* outcome;       // non-null: 2 heads residuals that go in front of the results; nothing is cleared unless all are finite
+  int* nonfinite;
+  void* stats;                 // stats_bytes, a multiple of 8
+  size_t stats_bytes;
+  // in host memory the device can write
+  double* host;                // [outcome 2 heads, if any | ldot | inner | fro2]
+  int* host_nonfinite;         // set if the flag is (never cleared here)
+  unsigned long long* stamp;   // the device's wall clock (100 MHz) near the end
+};
+hipError_t launch_update_end(const UpdateEnd& u, hipStream_t s);
 
 // Fused statistics step for heads of width 128 with bf16 activations (head_step.hip): one kernel rotates, normalises,
 // takes the corners and accumulates; every workgroup (head, share of the tokens) stores a partial M_h into
@@ -91,7 +111,9 @@ hipError_t launch_head_step128(const bf16_bits* X, int64_t T, int64_t stride, in
 // The same sum for any matrix of n_total floats (a multiple of 1024) held as nsplit shares [nsplit][n_total], fixed order.
 hipError_t launch_sum_shares(const float* part, int nsplit, int64_t n_total, float* M, int accumulate, hipStream_t s);
 constexpr int kHeadReduceParts = 16;
-hipError_t launch_head_reduce(const float* Mpart, int nsplit, int heads, float* M, int accumulate, double* fro2_part, hipStream_t s);
+// stamp non-null: receives the device's wall clock at the start of the launch.
+hipError_t launch_head_reduce(const float* Mpart, int nsplit, int heads, float* M, int accumulate, double* fro2_part, hipStream_t s,
+                              unsigned long long* stamp = nullptr);
 
 // Main phase of the polar iteration for heads of width up to kHeadPolarMaxDh (a multiple of 16) in one launch
 // (head_polar.hip): runs the composed cubics X <- X (a_k I + b_k X^T X), k < nsteps, on single fp16 operand planes held in
@@ -135,6 +157,7 @@ struct HeadPolarStart {
   int rop_dot;
   int round_bf16;
   float* R_keep;       // non-null: a copy of R, which the closing step may replace in the same launch
+  unsigned long long* stamp;   // non-null: receives the device's wall clock at the start of the launch
 };
 hipError_t launch_head_polar(const bf16_bits* Xt0, int heads, int dh, const PolarSchedule& sched, float* X32, bf16_bits* Pn, bf16_bits* Pt,
                              const HeadPolarClose* close, const HeadPolarStart* start, hipStream_t s);
@@ -158,11 +181,9 @@ hipError_t launch_quant_error(const void* Y, int y_is_f32, int64_t T, int64_t ld
 hipError_t launch_row_diag(const void* Y, int y_is_f32, int64_t T, int64_t ld, int d, float* row_pr, float* row_rho,
                            hipStream_t s);
 
-// out[h] = sum of part[h][0..n) for h < heads, fixed order.
+// out[h] = sum of part[h][0..n) for h < heads, fixed order.  out may be host memory the device can write.
 hipError_t launch_sum_partials(const double* part, int n, int heads, double* out, hipStream_t s);
 
-// p (bytes a multiple of 4) cleared if the n values at v are all finite.
-hipError_t launch_fill_zero_if_finite(const double* v, int n, void* p, size_t bytes, hipStream_t s);
 hipError_t launch_fill_zero(void* p, size_t bytes, hipStream_t s);
 
 // Device address, on the current device, of the static array conqur_score_rows_static keeps its per-row results in

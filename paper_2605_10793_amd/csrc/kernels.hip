@@ -36,6 +36,28 @@ __device__ __forceinline__ double block_sum_d(double v, double* sh) {
   return t;
 }
 
+// sum of p[0 .. n) by a workgroup of 256 in a fixed order, known to every thread
+__device__ __forceinline__ double sum_partials(const double* __restrict__ p, int n, double* sh) {
+  double s = 0.0;
+  // several loads in flight per lane (one at a time, 16384 partial sums took 14 us, now 5.2), summed in the order of one at a time;
+  // sixteen for the long sums only: clamped to the end, each costs a short one as much as a real load
+  int i0 = threadIdx.x;
+  auto some = [&](auto count) {
+    constexpr int U = decltype(count)::value;
+    double v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = p[i0 + u * 256 < n ? i0 + u * 256 : n - 1];   // (no branch around a load)
+#pragma unroll
+    for (int u = 0; u < U; ++u) s = i0 + u * 256 < n ? s + v[u] : s;
+    i0 += U * 256;
+  };
+  int left = n;
+  for (; left > 4 * 256; left -= 16 * 256) some(std::integral_constant<int, 16>{});
+  if (left > 256) some(std::integral_constant<int, 4>{});
+  else if (left > 0) some(std::integral_constant<int, 1>{});
+  return block_sum_d(s, sh);
+}
+
 // ---------------------------------------------------------------- row norms
 template <bool F32>
 __global__ void __launch_bounds__(256) k_row_norms(const void* __restrict__ X, int64_t T, int64_t stride, int heads, int dh,
@@ -251,12 +273,15 @@ __global__ void __launch_bounds__(256) k_split_rows(const float* __restrict__ X,
 // ---------------------------------------------------------------- fp32 matrix -> bf16 planes (natural / transposed)
 // One 64 x 64 tile per workgroup.  Optional fused work, so that the matrix is read once:
 //   START: the value packed is X0 = cm * src + cr * src2 (start of the polar iteration: src = M, src2 = R_prev,
-//          cm = 1/alpha, cr = lambda tau / alpha from fro2 = ||M||_F^2 of this batch entry);
+//          cm = 1/alpha, cr = lambda tau / alpha from ||M||_F^2 of this batch entry, the sum of the partial sums another
+//          launch has left: 8 KiB from the L2 behind the tile's own loads, instead of a launch for one number);
 //   DOT:   also the partial sum over the tile of value * dotwith (the inner product <X, M>), one per workgroup;
 //   out32: also the value itself in fp32.
 struct PackFused {
   const float* src2;      // START
-  const double* fro2;     // START
+  const double* fro2_parts;   // START: [batch][nparts]
+  int nparts;             // START
+  double* fro2_out;       // START: [batch]
   float lambda;           // START
   int dh;                 // START (tau = ||M||_F / sqrt(dh))
   const float* dotwith;   // DOT
@@ -275,8 +300,20 @@ __global__ void __launch_bounds__(256) k_pack(const float* __restrict__ src, int
   const int64_t boff = (int64_t)blockIdx.z * rows * cols;
   const int t = threadIdx.x;
   float cm = 1.0f, cr = 0.0f;
+  [[maybe_unused]] float4 m_tile[4], r_tile[4];   // START: in flight while the partial sums come
   if constexpr (START) {
-    const double f = sqrt(fx.fro2[blockIdx.z]);
+#pragma unroll
+    for (int pass = 0; pass < 4; ++pass) {
+      const int r = r0 + (t >> 4) + pass * 16, c = c0 + (t & 15) * 4;
+      m_tile[pass] = r_tile[pass] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      if (r < rows && c < cols) {
+        m_tile[pass] = *reinterpret_cast<const float4*>(src + boff + (int64_t)r * cols + c);
+        r_tile[pass] = *reinterpret_cast<const float4*>(fx.src2 + boff + (int64_t)r * cols + c);
+      }
+    }
+    const double f2 = sum_partials(fx.fro2_parts + (int64_t)blockIdx.z * fx.nparts, fx.nparts, sh);
+    if (t == 0 && blockIdx.x == 0 && blockIdx.y == 0) fx.fro2_out[blockIdx.z] = f2;
+    const double f = sqrt(f2);
     const bool empty = !(f > 0.0);
     // lambda = 0 is taken as the limit lambda -> 0+ at fp32 resolution: the floor ties the
     // update to R_prev on the null space of M (where every completion is optimal) and
@@ -295,10 +332,12 @@ __global__ void __launch_bounds__(256) k_pack(const float* __restrict__ src, int
     float f[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     if (r0 + r < rows && c0 + c < cols) {
       const int64_t off = boff + (int64_t)(r0 + r) * cols + c0 + c;
-      const float4 v = *reinterpret_cast<const float4*>(src + off);
+      float4 v;
+      if constexpr (START) v = m_tile[pass];
+      else v = *reinterpret_cast<const float4*>(src + off);
       f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
       if constexpr (START) {
-        float4 w = *reinterpret_cast<const float4*>(fx.src2 + off);
+        float4 w = r_tile[pass];
         const float m4[4] = {f[0], f[1], f[2], f[3]};
         f[0] = fmaf(cm, f[0], cr * w.x); f[1] = fmaf(cm, f[1], cr * w.y); f[2] = fmaf(cm, f[2], cr * w.z); f[3] = fmaf(cm, f[3], cr * w.w);
         if (fx.dot_part) {   // <R_op, M> on the way (the l1 term of the rows this update consumes; see k_dot_rm)
@@ -383,8 +422,10 @@ __global__ void __launch_bounds__(256) k_dot_rm(const float* __restrict__ R, con
   if (threadIdx.x == 0) part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = acc;
 }
 
-__global__ void __launch_bounds__(256) k_fro2(const float* __restrict__ M, int64_t n, double* __restrict__ part) {
+__global__ void __launch_bounds__(256) k_fro2(const float* __restrict__ M, int64_t n, double* __restrict__ part,
+                                              unsigned long long* __restrict__ stamp) {
   __shared__ double sh[4];
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) store_for_host(stamp, (unsigned long long)wall_clock64());
   const float* m = M + (int64_t)blockIdx.y * n;
   double acc = 0.0;
   for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < n; i += (int64_t)gridDim.x * 1024) {
@@ -640,46 +681,52 @@ __global__ void __launch_bounds__(1024) k_sum_rows(const float* __restrict__ a, 
   sa = block_sum_d(sa, sh);
   sb = block_sum_d(sb, sh);
   if (threadIdx.x == 0) {
-    out[0] = sa;
-    out[1] = sb;
+    store_for_host(out, sa);
+    store_for_host(out + 1, sb);
   }
 }
 
 // out[h] = sum_i part[h][i], i < n (one workgroup per h).
 __global__ void __launch_bounds__(256) k_sum_partials(const double* __restrict__ part, int n, double* __restrict__ out) {
   __shared__ double sh[4];
-  const double* p = part + (int64_t)blockIdx.x * n;
-  double s = 0.0;
-  // several loads in flight per lane (one at a time, 16384 partial sums took 14 us, now 5.2), summed in the order of one at a time;
-  // sixteen for the long sums only: clamped to the end, each costs a short one as much as a real load
-  int i0 = threadIdx.x;
-  auto some = [&](auto count) {
-    constexpr int U = decltype(count)::value;
-    double v[U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) v[u] = p[i0 + u * 256 < n ? i0 + u * 256 : n - 1];   // (no branch around a load)
-#pragma unroll
-    for (int u = 0; u < U; ++u) s = i0 + u * 256 < n ? s + v[u] : s;
-    i0 += U * 256;
-  };
-  int left = n;
-  for (; left > 4 * 256; left -= 16 * 256) some(std::integral_constant<int, 16>{});
-  if (left > 256) some(std::integral_constant<int, 4>{});
-  else if (left > 0) some(std::integral_constant<int, 1>{});
-  s = block_sum_d(s, sh);
-  if (threadIdx.x == 0) out[blockIdx.x] = s;
+  const double s = sum_partials(part + (int64_t)blockIdx.x * n, n, sh);
+  if (threadIdx.x == 0) store_for_host(out + blockIdx.x, s);
+}
+
+// The end of an update (see UpdateEnd): a workgroup per head for its sums, one more for what the heads share.  One launch and
+// one synchronisation instead of two sums, two fills, a copy and a second wait; the residuals' sums go to the host's memory as
+// well, and the time stamps replace two events.  A calibration pass, us, before and with all of these: 32 heads of width 64
+// 103.6 and 76.7, of 128 135 and 104, fp32 at 256 267 and 246, 1104 354 and 336, 3072 1997 and 1975.
+__global__ void __launch_bounds__(256) k_update_end(const UpdateEnd u) {
+  __shared__ double sh[4];
+  const int t = threadIdx.x, h = blockIdx.x, n = u.heads;
+  double* const results = u.outcome ? u.host + 2 * n : u.host;
+  if (h < n) {
+    const double ldot = u.ldot_parts ? sum_partials(u.ldot_parts + (int64_t)h * u.nparts, u.nparts, sh) : u.scalars[h];
+    const double inner = u.inner_parts ? sum_partials(u.inner_parts + (int64_t)h * u.nparts, u.nparts, sh) : u.scalars[n + h];
+    if (t == 0) {
+      store_for_host(results + h, ldot);
+      store_for_host(results + n + h, inner);
+      store_for_host(results + 2 * n + h, u.scalars[2 * n + h]);
+      if (h == 0) store_for_host(u.stamp, (unsigned long long)wall_clock64());
+    }
+    return;
+  }
+  int bad = 0;
+  if (u.outcome)
+    for (int i = t; i < 2 * n; i += 256) {
+      const double v = u.outcome[i];
+      store_for_host(u.host + i, v);
+      bad |= isfinite(v) ? 0 : 1;
+    }
+  if (t == 0 && *u.nonfinite) store_for_host(u.host_nonfinite, 1);
+  if (__syncthreads_or(bad)) return;
+  if (t == 0) *u.nonfinite = 0;
+  for (size_t i = t; i < u.stats_bytes / 8; i += 256) reinterpret_cast<uint64_t*>(u.stats)[i] = 0;
 }
 
 __global__ void __launch_bounds__(256) k_fill_zero(uint32_t* p, size_t n) {
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = 0u;
-}
-
-// p cleared if all n values are finite; every workgroup looks at all of them (a few hundred doubles at most).
-__global__ void __launch_bounds__(256) k_fill_zero_if_finite(const double* __restrict__ v, int n, uint32_t* __restrict__ p, size_t words) {
-  int bad = 0;
-  for (int i = threadIdx.x; i < n; i += 256) bad |= isfinite(v[i]) ? 0 : 1;
-  if (__syncthreads_or(bad)) return;
-  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < words; i += (size_t)gridDim.x * 256) p[i] = 0u;
 }
 
 inline int grid_for(int64_t items, int cap = 4096) {
@@ -761,26 +808,22 @@ hipError_t launch_pack(const float* src, int batch, int rows, int cols, int np, 
 
 int pack_dot_partials(int dh) { return ((dh + 63) / 64) * ((dh + 63) / 64); }
 
-hipError_t launch_polar_start_pack(const float* M, const float* R, int heads, int dh, float lambda, const double* fro2, int np,
-                                   float* X32, bf16_bits* outN, bf16_bits* outT, int64_t plane, int round_bf16,
-                                   double* dot_part, double* dot_out, hipStream_t s, int out_f16) {
-  if (out_f16 && np != 1) return hipErrorInvalidValue;
+hipError_t launch_polar_start_pack(const float* M, const float* R, int heads, int dh, float lambda, const double* fro2_parts, int nparts,
+                                   double* fro2_out, int np, bf16_bits* outN, bf16_bits* outT, int64_t plane, int round_bf16,
+                                   double* dot_part, hipStream_t s, int out_f16) {
+  if ((out_f16 && np != 1) || !fro2_parts || nparts < 1 || !fro2_out) return hipErrorInvalidValue;
   PackFused fx{};
   fx.out_f16 = out_f16;
-  fx.src2 = R; fx.fro2 = fro2; fx.lambda = lambda; fx.dh = dh; fx.out32 = X32;
+  fx.src2 = R; fx.fro2_parts = fro2_parts; fx.nparts = nparts; fx.fro2_out = fro2_out; fx.lambda = lambda; fx.dh = dh;
   fx.dot_part = dot_part; fx.round_bf16 = round_bf16;
-  hipError_t e = launch_pack_impl<true, false>(M, heads, dh, dh, np, outN, outT, plane, fx, s);
-  if (e != hipSuccess || !dot_part) return e;
-  return launch_sum_partials(dot_part, pack_dot_partials(dh), heads, dot_out, s);
+  return launch_pack_impl<true, false>(M, heads, dh, dh, np, outN, outT, plane, fx, s);
 }
 
 hipError_t launch_polar_finish_pack(const float* X, const float* M, int heads, int dh, int np, float* R32, bf16_bits* outT,
-                                    int64_t plane, double* dot_part, double* inner, hipStream_t s) {
+                                    int64_t plane, double* dot_part, hipStream_t s) {
   PackFused fx{};
   fx.dotwith = M; fx.dot_part = dot_part; fx.out32 = R32;
-  hipError_t e = launch_pack_impl<false, true>(X, heads, dh, dh, np, nullptr, outT, plane, fx, s);
-  if (e != hipSuccess) return e;
-  return launch_sum_partials(dot_part, pack_dot_partials(dh), heads, inner, s);
+  return launch_pack_impl<false, true>(X, heads, dh, dh, np, nullptr, outT, plane, fx, s);
 }
 
 int dot_rm_partials(int64_t n) { return grid_for(n / 4, 1024); }
@@ -794,12 +837,9 @@ hipError_t launch_dot_rm(const float* R, const float* M, int heads, int64_t n, i
   return launch_sum_partials(part, blocks, heads, out, s);
 }
 
-hipError_t launch_fro2(const float* M, int heads, int64_t n, double* part, double* fro2, hipStream_t s) {
-  const int blocks = dot_rm_partials(n);
-  hipLaunchKernelGGL(k_fro2, dim3(blocks, heads), dim3(256), 0, s, M, n, part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return launch_sum_partials(part, blocks, heads, fro2, s);
+hipError_t launch_fro2(const float* M, int heads, int64_t n, double* part, unsigned long long* stamp, hipStream_t s) {
+  hipLaunchKernelGGL(k_fro2, dim3(dot_rm_partials(n), heads), dim3(256), 0, s, M, n, part, stamp);
+  return hipGetLastError();
 }
 
 hipError_t launch_axpy(float* X, const float* R, int64_t n, float kappa, hipStream_t s) {
@@ -849,9 +889,11 @@ hipError_t launch_sum_partials(const double* part, int n, int heads, double* out
   return hipGetLastError();
 }
 
-hipError_t launch_fill_zero_if_finite(const double* v, int n, void* p, size_t bytes, hipStream_t s) {
-  const size_t words = bytes / 4;
-  hipLaunchKernelGGL(k_fill_zero_if_finite, dim3(grid_for((int64_t)words, 64)), dim3(256), 0, s, v, n, reinterpret_cast<uint32_t*>(p), words);
+hipError_t launch_update_end(const UpdateEnd& u, hipStream_t s) {
+  if (u.heads < 1 || !u.scalars || !u.nonfinite || !u.host || !u.host_nonfinite || !u.stamp || (u.stats_bytes & 7) ||
+      ((u.ldot_parts || u.inner_parts) && u.nparts < 1))
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_update_end, dim3(u.heads + 1), dim3(256), 0, s, u);
   return hipGetLastError();
 }
 

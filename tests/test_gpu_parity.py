@@ -1663,3 +1663,34 @@ def test_one_launch_step_is_the_two_products_bit_for_bit(B, dh, heads):
             ref = a * x + b * torch.bmm(x, torch.bmm(x.transpose(1, 2).contiguous(), x))
             # W and the result each rounded once to 11 bits (the hand-over to 8): 2^-10 (2^-8) of the matrix's norm
             assert float((nxt - ref).norm()) <= 2.0 ** (-8 if last else -10) * float(ref.norm())
+
+
+@pytest.mark.parametrize("heads,dh,precision,lam", [(1, 16, 0, 0.1), (3, 64, 0, 0.0), (2, 128, 0, 0.1), (2, 128, 1, 0.1), (1, 256, 0, 0.0), (2, 272, 0, 0.1),
+                                                    (1, 1040, 0, 0.1)])
+def test_an_update_reports_and_clears_its_own_statistics(B, heads, dh, precision, lam):
+    """The scalars an update's launches leave in host memory, update after update: those of the rows it consumed.  ||M||_F and <R, M>
+    are sums of dh^2 fp32 products in fp64 (1e-6: the products' own rounding); a skipped row is reported once; a head's clock moves."""
+    d, T = heads * dh, 200
+    w = I.small_workload(d, T, n_batches=2, heads=heads, seed=31, prox_lambda=lam)
+    cal = B.Calibrator(d, heads, "bf16", I.initial_rotation(w), max_tokens=T, prox_lambda=lam, polar_precision=precision)
+    try:
+        for b in range(3):
+            X = I.batch(w, b % 2).copy()
+            if b == 1:
+                X[7, :] = np.nan
+            cal.step_batch(B.to_device(X, w.dtype))
+            _, M, n = cal.get_state(want_R=False)
+            l1 = [s["l1"] for s in cal.batch_stats()]
+            assert (n == T - (b == 1)).all()
+            st, out = cal.update_rotation(allow=(B.ENONFINITE,))
+            assert st == (B.ENONFINITE if b == 1 else B.OK)
+            R, _, n = cal.get_state(want_M=False)
+            assert (n == 0).all() and all(s["rows"] == 0 and s["skipped"] == 0 for s in cal.batch_stats())
+            for h in range(heads):
+                m64, r64 = M[h].astype(np.float64), R[h].astype(np.float64)
+                assert abs(out[h]["m_fro"] / np.linalg.norm(m64) - 1) <= 1e-6
+                assert abs(out[h]["inner"] / (m64 * r64).sum() - 1) <= 1e-6
+                assert abs(out[h]["l1"] / l1[h] - 1) <= 1e-9
+                assert 0 < out[h]["ms"] < 1000
+    finally:
+        cal.close()
