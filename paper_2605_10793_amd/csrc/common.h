@@ -60,21 +60,52 @@ __device__ __forceinline__ bf16_bits f32_to_f16(float f) {
 }
 __device__ __forceinline__ float bf16_to_f32(bf16_bits b) { return __uint_as_float(((uint32_t)b) << 16); }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+// Sums and maxima over lanes, known to every lane afterwards: the butterfly with offsets 32, 16, 8, 4, 2, 1 (or 8, 4, 2, 1 within
+// rows of 16 lanes), one VALU operation per offset.  Swapping the halves (odd and even rows) of a register with itself leaves either
+// half in both; behind offset 8 the values of a row repeat every 8 lanes, so that a rotation by 4 meets the same partner as the
+// XOR, and so on.  A lane exchange through LDS (ds_bpermute) instead takes some 60 cycles per offset and another half dozen instructions
+// for a workgroup that reads one row: see k_quant_error.
+template <int N>
+__device__ __forceinline__ uint32_t row_rotated(uint32_t v) {   // by N lanes within rows of 16
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x120 + N, 0xf, 0xf, true);
 }
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+template <int N>
+__device__ __forceinline__ float row_rotated(float v) { return __uint_as_float(row_rotated<N>(__float_as_uint(v))); }
+template <int N>
+__device__ __forceinline__ double row_rotated(double v) {
+  const uint2 u = __builtin_bit_cast(uint2, v);
+  return __builtin_bit_cast(double, make_uint2(row_rotated<N>(u.x), row_rotated<N>(u.y)));
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+template <typename T, typename Op>
+__device__ __forceinline__ T row16_reduce(T v, Op op) {
+  v = op(v, row_rotated<8>(v));
+  v = op(v, row_rotated<4>(v));
+  v = op(v, row_rotated<2>(v));
+  return op(v, row_rotated<1>(v));
 }
+template <typename Op>
+__device__ __forceinline__ float wave_reduce(float v, Op op) {
+  const uint32_t u = __float_as_uint(v);
+  const auto a = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  const uint32_t w = __float_as_uint(op(__uint_as_float(a[0]), __uint_as_float(a[1])));
+  const auto b = __builtin_amdgcn_permlane16_swap(w, w, false, false);
+  return row16_reduce(op(__uint_as_float(b[0]), __uint_as_float(b[1])), op);
+}
+template <typename Op>
+__device__ __forceinline__ double wave_reduce(double v, Op op) {
+  auto both = [&](auto swap) {
+    const uint2 u = __builtin_bit_cast(uint2, v);
+    const auto x = swap(u.x), y = swap(u.y);
+    v = op(__builtin_bit_cast(double, make_uint2(x[0], y[0])), __builtin_bit_cast(double, make_uint2(x[1], y[1])));
+  };
+  both([](uint32_t u) { return __builtin_amdgcn_permlane32_swap(u, u, false, false); });
+  both([](uint32_t u) { return __builtin_amdgcn_permlane16_swap(u, u, false, false); });
+  return row16_reduce(v, op);
+}
+__device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ double wave_sum_d(double v) { return wave_reduce(v, [](double a, double b) { return a + b; }); }
+__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); }); }
+__device__ __forceinline__ float row16_sum(float v) { return row16_reduce(v, [](float a, float b) { return a + b; }); }
 
 // A value for the host, in pinned memory: stored through every cache, so that it is there once the kernel (and an event behind it)
 // has completed, whatever that event releases.

@@ -104,8 +104,7 @@ __global__ void __launch_bounds__(NTHREADS) k_head_step128(const bf16_bits* __re
           ss += a * a + b * b;
         }
       }
-#pragma unroll
-      for (int o = 8; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);   // over the 16 lanes of the row
+      ss = row16_sum(ss);   // over the 16 lanes of the row
       *reinterpret_cast<uint4*>(sX + xoff(r, lchunk)) = v;
       if (lchunk == 0) {
         float n = 0.0f, w = 0.0f;

@@ -529,7 +529,9 @@ __global__ void __launch_bounds__(256) k_quant_error(const void* __restrict__ Y,
   // Zero-point levels without the shift: clamp(r + zeta, 0, qmax) - zeta = clamp(r, -zeta, qmax - zeta), the same integer as long as
   // every sum is one fp32 holds exactly.  A row whose values lie 2^22 steps or more from 0 keeps the shifted form, a
   // constant row (delta = 0, the single level lo) has its own: both are row-wide choices.  This kernel is nearly bound by its
-  // arithmetic (14 instructions per value; 16384 x 4096 bf16: 36 us zero-point, 29 symmetric, 27 for reading Y once).
+  // arithmetic (some 9 instructions per value and 60 per row and lane; 16384 x 4096 bf16: 31 us zero-point, 26 symmetric, 27 for copying
+  // half as much; with the lanes' extremes and sums exchanged through LDS 32 and 27).  Workgroups that take one row after another and
+  // fetch the next ahead lose: 8 a compute unit 36 and 32.
   [[maybe_unused]] const bool plain = ZP && delta > 0.0f && fmaxf(fabsf(amax), fabsf(amin)) * inv_delta < 4194304.0f;
   const float code_lo = ZP ? -zeta : -qmax, code_hi = ZP ? qmax - zeta : qmax;
   auto score = [&](const uint4& v, int c, auto is_plain) {
@@ -654,36 +656,28 @@ __global__ void __launch_bounds__(256) k_row_diag(const void* __restrict__ Y, in
   }
 }
 
-// out[0] = sum a, out[1] = sum b in a fixed order (one workgroup).  Results of many
+// out[0] = sum a, out[1] = sum b in a fixed order (one workgroup each).  Results of many
 // workgroups are combined this way rather than with atomics on one address, which the
 // XCDs would serialise at the memory side.
 __global__ void __launch_bounds__(1024) k_sum_rows(const float* __restrict__ a, const float* __restrict__ b, int64_t T,
                                                    double* __restrict__ out) {
   __shared__ double sh[16];
-  double sa = 0.0, sb = 0.0;
-  // eight loads of either array in flight per lane: one at a time, 16384 rows were 16 trips to memory in a row (7.3 us)
-  for (int64_t i0 = threadIdx.x; i0 < T; i0 += 8 * 1024) {
-    float va[8], vb[8];
+  const float* const p = blockIdx.x ? b : a;
+  double sum = 0.0;
+  // sixteen loads in flight per lane: one at a time, 16384 rows were 16 trips to memory in a row.  (Both arrays in one workgroup, eight
+  // loads of each at a time, took 5.2 us for them; this, with the sum over the lanes in the VALU, 4.4.)
+  for (int64_t i0 = threadIdx.x; i0 < T; i0 += 16 * 1024) {
+    float v[16];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < 16; ++u) {
       const int64_t i = i0 + u * 1024;
-      const int64_t at = i < T ? i : T - 1;   // (no branch around a load: those would wait for one another)
-      va[u] = a[at];
-      vb[u] = b[at];
+      v[u] = p[i < T ? i : T - 1];   // (no branch around a load: those would wait for one another)
     }
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const bool in = i0 + u * 1024 < T;
-      sa += in ? (double)va[u] : 0.0;
-      sb += in ? (double)vb[u] : 0.0;
-    }
+    for (int u = 0; u < 16; ++u) sum += i0 + u * 1024 < T ? (double)v[u] : 0.0;
   }
-  sa = block_sum_d(sa, sh);
-  sb = block_sum_d(sb, sh);
-  if (threadIdx.x == 0) {
-    store_for_host(out, sa);
-    store_for_host(out + 1, sb);
-  }
+  sum = block_sum_d(sum, sh);
+  if (threadIdx.x == 0) store_for_host(out + blockIdx.x, sum);
 }
 
 // out[h] = sum_i part[h][i], i < n (one workgroup per h).
@@ -870,7 +864,7 @@ hipError_t launch_quant_error(const void* Y, int y_is_f32, int64_t T, int64_t ld
   else launch_quant_kernel<false>(Y, y_is_f32, T, ld, d, qmax, zero_point, clip, row_sse, row_en, nullptr, 0, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !out) return e;   // out == null: the caller sums the per-row results itself
-  hipLaunchKernelGGL(k_sum_rows, dim3(1), dim3(1024), 0, s, row_sse, row_en, T, out);
+  hipLaunchKernelGGL(k_sum_rows, dim3(2), dim3(1024), 0, s, row_sse, row_en, T, out);
   return hipGetLastError();
 }
 
