@@ -469,6 +469,24 @@ static conqur_status step_general(conqur_ctx* ctx, const void* X, int64_t T, int
   // kernel for a few rows, which saves the transposing launch; fp32 activations (split planes) and the GEMM variant that
   // also emits Y keep that launch.
   const bool xt_in_rotate = !ctx->f32 && (few || !keep_y);
+  // Several narrow heads: one launch for the whole step, the same bits (of one rotation the accumulate GEMM splits the token range).
+  if (!ctx->f32 && ctx->heads > 1 && ctx->dh <= kHeadStepNarrowMaxDh && !few && !keep_y) {
+    HeadStepNarrow a{};
+    a.X = reinterpret_cast<const bf16_bits*>(X); a.T = T; a.stride = stride; a.heads = ctx->heads; a.RopT = ctx->RopT;
+    a.M = ctx->M; a.accumulate = ctx->m_empty ? 0 : 1;
+    a.nrm = ctx->nrm; a.ldn = ctx->tmax; a.cnt = ctx->cnt; a.cnt_slots = kCountSlots; a.nonfinite = ctx->nonfinite;
+    a.St = ctx->St; a.pitch = ctx->pitch;
+    ctx->clk_wg[0] = ctx->clk_wg[1] = 0;
+    ctx->ev_valid[ST_PREP] = ctx->ev_valid[ST_ACCUM] = false;
+    {
+      StageTimer tm(ctx, ST_ROTATE);   // (all of it)
+      HIP_TRY(launch_head_step_narrow(a, ctx->dh, s));
+    }
+    ctx->m_empty = false;
+    ctx->have_rows = true;
+    ctx->last_T = T;
+    return CONQUR_OK;
+  }
   {
     StageTimer tm(ctx, ST_PREP);
     HIP_TRY(launch_row_norms(X, ctx->f32, T, stride, ctx->heads, ctx->dh, ctx->nrm, ctx->w, ctx->tmax, ctx->nonfinite, s));

@@ -115,6 +115,28 @@ constexpr int kHeadReduceParts = 16;
 hipError_t launch_head_reduce(const float* Mpart, int nsplit, int heads, float* M, int accumulate, double* fro2_part, hipStream_t s,
                               unsigned long long* stamp = nullptr);
 
+// The statistics step of heads of width 16 .. 112 with bf16 activations in one launch (head_step_narrow.hip), bit for bit what the row
+// norms, the rotate GEMM's signs and operand and the accumulate GEMM leave: the row norms, the corner signs St (fp16 +-1,
+// transposed [heads * dh][pitch], pitch at least T rounded up to 32), the row counters cnt [heads][cnt_slots][2], and M
+// [heads][dh][dh], set or added to.
+constexpr int kHeadStepNarrowMaxDh = 112;
+struct HeadStepNarrow {
+  const bf16_bits* X;
+  int64_t T, stride;
+  int heads;
+  const bf16_bits* RopT;
+  float* M;
+  int accumulate;
+  float* nrm;
+  int64_t ldn;
+  unsigned long long* cnt;
+  int cnt_slots;
+  int* nonfinite;
+  bf16_bits* St;
+  int64_t pitch;
+};
+hipError_t launch_head_step_narrow(const HeadStepNarrow& a, int dh, hipStream_t s);
+
 // Main phase of the polar iteration for heads of width up to kHeadPolarMaxDh (a multiple of 16) in one launch
 // (head_polar.hip): runs the composed cubics X <- X (a_k I + b_k X^T X), k < nsteps, on single fp16 operand planes held in
 // LDS (11 significant bits).  Xt0: the start iterate as one transposed fp16 plane [heads][dh][dh].

@@ -1694,3 +1694,28 @@ def test_an_update_reports_and_clears_its_own_statistics(B, heads, dh, precision
                 assert 0 < out[h]["ms"] < 1000
     finally:
         cal.close()
+
+
+@pytest.mark.parametrize("dh,heads,T", [(16, 5, 33), (16, 300, 129), (32, 3, 2041), (48, 2, 127), (48, 75, 161), (64, 32, 2048), (64, 2, 4000), (80, 3, 128),
+                                        (80, 70, 257), (96, 5, 1025), (96, 90, 300), (112, 2, 33), (112, 33, 255)])
+def test_step_of_narrow_heads_in_one_launch(B, dh, heads, T):
+    """The one-launch statistics step, by channel blocks and not: tokens that end inside a wavefront's 32 or inside 256, heads whose
+    channels fill no K block, a zero row and a row with an infinity, a first batch and a second.  step_batch_quant runs the
+    general launches (norms, rotation, transposed operand, accumulation): bit for bit the same M, signs, norms and counts."""
+    d = dh * heads
+    w = I.small_workload(d, T, n_batches=1, heads=heads, seed=dh + T, prox_lambda=0.1)
+    X = B.to_device(I.batch(w, 0), "bf16")
+    X[T // 2, :] = 0.0
+    X[T - 1, dh - 1] = float("inf")
+    got = []
+    for general in (False, True):
+        cal = B.Calibrator(d, heads, "bf16", I.initial_rotation(w), max_tokens=T, prox_lambda=0.1)
+        try:
+            for _ in range(2):
+                cal.step_batch_quant(X, 4, True, 0.9) if general else cal.step_batch(X)
+                got.append((cal.get_state(want_R=False)[1], *cal.last_corners(T), [(s["rows"], s["skipped"]) for s in cal.batch_stats()]))
+        finally:
+            cal.close()
+    for a, b in zip(got[:2], got[2:]):
+        assert all(np.array_equal(x, y) for x, y in zip(a[:3], b[:3])) and a[3] == b[3]
+    assert got[0][3] == [(T - 2, 2)] + [(T - 1, 1)] * (heads - 1) and np.isfinite(got[1][0]).all()
