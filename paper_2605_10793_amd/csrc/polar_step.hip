@@ -9,9 +9,12 @@
 // by transposing reads (the apply).  Beyond kPolarStepMaxDh it does not fit and would be fetched twice.
 //
 // What bounds it: launch, one fetch of X^T (up to 128 KiB per workgroup, from memory: the step before wrote it on other XCDs)
-// and a short chain of MFMAs behind it.  16 columns per workgroup while that gives at most one workgroup per compute unit,
-// else 32.  A whole update by events, two launches a step and one, us: width 256, 23 iterations, one head 276 and 179, 32 heads
-// 434 and 226; 24 x 208 422 and 200; 10 iterations of 3 x 192 143 and 99, 8 x 176 146 and 95; 40 x 160, 9 iterations 182 and 104.
+// and a short chain of MFMAs behind it.  So a workgroup fetches the rows its columns are first, and every wavefront then takes the rows
+// of G that it has fetched itself, as they land; all of a product's LDS reads are in flight before its MFMAs.  16 columns per
+// workgroup while that gives at most one workgroup per compute unit, else 32.  A whole update by events, 23 iterations, us, with two
+// launches a step; with one that waited for all of X^T and had 4 wavefronts; and so, with 8 (squares of 192: 12): one head of 256
+// 276, 166 .. 173, 141 .. 145; 32 of 256 434, 211, 191; 24 of 208 422, 185, 166; 3 of 192 - , 139, 120; 8 of 176 - , 133, 117.
+// (In 4, 6 wavefronts a square of 192 took 132 and 129 in the fourth case; 16 for 256 are no faster than 8.)
 //
 // Roundings are those of the two GEMM launches it stands for (K in ascending blocks of 32, W and X' once to fp16), bit for bit.
 #include "gemm_nt.h"
@@ -24,18 +27,20 @@ namespace conqur {
 namespace {
 
 constexpr int kRowB = 512;   // bytes of an LDS row, whatever the width: the rows' bank pattern is head_polar.hip's
-constexpr int kNW = 4;
 
-// N: width of the square the head is taken as (zero beyond the head); P: columns of a workgroup.
-template <int N, int P>
-__global__ void __launch_bounds__(64 * kNW, 2) k_polar_step(const bf16_bits* __restrict__ Xt, const int dh, const int panels, const float ci,
+// s_waitcnt's operand for vmcnt(n) only
+constexpr int vmcnt(int n) { return 0x0F70 | (n & 15) | ((n >> 4) << 14); }
+
+// N: width of the square the head is taken as (zero beyond the head); P: columns of a workgroup; kNW: its wavefronts.
+template <int N, int P, int kNW>
+__global__ void __launch_bounds__(64 * kNW) k_polar_step(const bf16_bits* __restrict__ Xt, const int dh, const int panels, const float ci,
                                                            const float cg, bf16_bits* __restrict__ Xt_out, const int last,
                                                            float* __restrict__ X32, bf16_bits* __restrict__ Pn) {
   static_assert(N % (16 * kNW) == 0 && N <= kPolarStepMaxDh && P % 16 == 0, "whole row tiles per wavefront");
   constexpr int TM = N / (16 * kNW), TN = P / 16, KB = N / 32;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   unsigned char* const sX = smem;                  // X^T: row c, K = row of X
-  unsigned char* const sW = smem + N * kRowB;      // columns p of W: row = column, K = row of W
+  unsigned char* const sW = smem + N * kRowB;      // columns p of W: row = column, K = row of W; before that, rows p of X^T
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int kg = lane >> 4, col = lane & 15;
   // a head's workgroups on one XCD (bid % 8), where its L2 fetches X^T once
@@ -55,21 +60,22 @@ __global__ void __launch_bounds__(64 * kNW, 2) k_polar_step(const bf16_bits* __r
   const uint32_t l_tr = t * kRowB + ((((col >> 1) & 1) ^ swz(t)) << 4) + 8 * (col & 1);              // row 8 kg + col / 4, element 4 (col % 4)
   const uint32_t l_put = col * kRowB + (((kg >> 1) ^ s) << 4) + 8 * (kg & 1);                        // row col, element 4 kg
 
-  auto fetch = [&](__amdgpu_buffer_rsrc_t r, int row0, uint32_t off) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(sX + row0 * kRowB), 16, off, 0, 0, 0);
+  // X^T to LDS, 2 rows per instruction; what lies beyond the head reads zero.  Rows p first, into the place of W: the right operand
+  // of every wavefront's G.  Then each wavefront the row tiles it takes of G, which it can start on one by one as they land.
+  const auto rx = rsrc(Xt, 2);
+  const int half = lane >> 5, pc = lane & 31;
+  auto fetch = [&](__amdgpu_buffer_rsrc_t r, unsigned char* to, int row0, int from) {
+    const int row = from + half, chunk = pc ^ swz(row0 + half);
+    const uint32_t off = row < dh && 8 * chunk < dh ? (uint32_t)(row * dh + 8 * chunk) * 2u : kOob;
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(to + row0 * kRowB), 16, off, 0, 0, 0);
   };
-  {   // X^T to LDS, 2 rows per instruction; what lies beyond the head reads zero
-    const auto rx = rsrc(Xt, 2);
-    const int half = lane >> 5, pc = lane & 31;
 #pragma unroll
-    for (int q = 0; q < N / 2 / kNW; ++q) {
-      const int row0 = 2 * (q * kNW + wave), row = row0 + half, chunk = pc ^ swz(row);
-      const uint32_t off = row < dh && 8 * chunk < dh ? (uint32_t)(row * dh + 8 * chunk) * 2u : kOob;
-      fetch(rx, row0, off);
-    }
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): they have landed
-  }
-  __syncthreads();
+  for (int q = 0; q < (P / 2 + kNW - 1) / kNW; ++q)
+    if (q * kNW + wave < P / 2) fetch(rx, sW, 2 * (q * kNW + wave), n0 + 2 * (q * kNW + wave));
+#pragma unroll
+  for (int q = 0; q < 8 * TM; ++q) fetch(rx, sX, 16 * TM * wave + 2 * q, 16 * TM * wave + 2 * q);
+  __builtin_amdgcn_s_waitcnt(vmcnt(8 * TM));
+  asm volatile("s_barrier" ::: "memory");   // (without the fence of __syncthreads, which would wait for the rows as well)
 
   // rows row .. row + 15 of an LDS matrix, K elements 32 kk + 8 kg .. + 7
   auto frag = [&](const unsigned char* base, int row, int kk) {
@@ -95,24 +101,33 @@ __global__ void __launch_bounds__(64 * kNW, 2) k_polar_step(const bf16_bits* __r
 #pragma unroll
       for (int j = 0; j < TN; ++j) acc[i][j] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   };
-  auto product = [&](auto&& fa, auto&& fb) {
-    zero();
+  // G[:, p]
+  zero();
+  {
+    f16x8 b[TN][KB];
 #pragma unroll
-    for (int kk = 0; kk < KB; ++kk) {
-      f16x8 a[TM], b[TN];
+    for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int j = 0; j < TN; ++j) b[j] = fb(j, kk);
+      for (int kk = 0; kk < KB; ++kk) b[j][kk] = frag(sW, 16 * j, kk);
+    static_assert(TM <= 3, "row tiles of a wavefront");
 #pragma unroll
-      for (int i = 0; i < TM; ++i) a[i] = fa(i0 + i, kk);
+    for (int i = 0; i < TM; ++i) {
+      if (TM - i == 3) __builtin_amdgcn_s_waitcnt(vmcnt(16));
+      else if (TM - i == 2) __builtin_amdgcn_s_waitcnt(vmcnt(8));
+      else __builtin_amdgcn_s_waitcnt(vmcnt(0));
+      asm volatile("" ::: "memory");   // (the tile's reads stay behind the wait)
+      f16x8 a[KB];
 #pragma unroll
-      for (int i = 0; i < TM; ++i)
+      for (int kk = 0; kk < KB; ++kk) a[kk] = frag(sX, 16 * (i0 + i), kk);
+      __builtin_amdgcn_sched_barrier(0);   // (all reads in flight: left alone, the compiler waits for one at a time)
 #pragma unroll
-        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[i], b[j], acc[i][j], 0, 0, 0);
+      for (int kk = 0; kk < KB; ++kk)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[kk], b[j][kk], acc[i][j], 0, 0, 0);
     }
-  };
-
-  // G[:, p], then W[:, p] (as the general path's epilogue rounds it)
-  product([&](int i, int kk) { return frag(sX, 16 * i, kk); }, [&](int j, int kk) { return frag(sX, n0 + 16 * j < N ? n0 + 16 * j : 0, kk); });
+  }
+  __syncthreads();   // everyone has rows p, whose place W takes
+  // W[:, p] (as the general path's epilogue rounds it)
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -125,7 +140,34 @@ __global__ void __launch_bounds__(64 * kNW, 2) k_polar_step(const bf16_bits* __r
     }
   __syncthreads();
   // X'[:, p]
-  product([&](int i, int kk) { return frag_tr(i, kk); }, [&](int j, int kk) { return frag(sW, 16 * j, kk); });
+  zero();
+  {
+    constexpr int KH = KB / 2;   // half of K at a time in registers, the other half's reads on the way
+    f16x8 a[2][KH][TM], b[2][KH][TN];
+    auto read = [&](int half) {
+#pragma unroll
+      for (int k = 0; k < KH; ++k) {
+        const int kk = half * KH + k;
+#pragma unroll
+        for (int j = 0; j < TN; ++j) b[half][k][j] = frag(sW, 16 * j, kk);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) a[half][k][i] = frag_tr(i0 + i, kk);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    auto multiply = [&](int half) {
+#pragma unroll
+      for (int k = 0; k < KH; ++k)
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+          for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[half][k][i], b[half][k][j], acc[i][j], 0, 0, 0);
+    };
+    read(0);
+    read(1);
+    multiply(0);
+    multiply(1);
+  }
 
   typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
   const auto rt = rsrc(Xt_out, 2);
@@ -164,13 +206,14 @@ hipError_t launch_one(const bf16_bits* Xt, int heads, int dh, float a, float b, 
                       hipStream_t s) {
   constexpr int smem = (N + P) * kRowB;
   static PerDeviceOnce configured;
-  auto kern = k_polar_step<N, P>;
+  constexpr int NW = N == 256 ? 8 : 12;   // whole row tiles each (see above)
+  auto kern = k_polar_step<N, P, NW>;
   hipError_t e = configured.run([&] {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
   });
   if (e != hipSuccess) return e;
   const int panels = (dh + P - 1) / P;
-  hipLaunchKernelGGL(kern, dim3(panels * heads), dim3(64 * kNW), smem, s, Xt, dh, panels, a, b, Xt_out, last, X32, Pn);
+  hipLaunchKernelGGL(kern, dim3(panels * heads), dim3(64 * NW), smem, s, Xt, dh, panels, a, b, Xt_out, last, X32, Pn);
   return hipGetLastError();
 }
 
