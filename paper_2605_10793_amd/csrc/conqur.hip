@@ -76,17 +76,17 @@ struct conqur_ctx {
   void* Y = nullptr;           // [tmax][d] rotated activations (quantiser score)
   float *row_sse = nullptr, *row_en = nullptr;
   // polar workspaces
+  unsigned long long* stats_keep = nullptr;          // narrow heads: the statistics that update consumes, [stat_words]
   float* Rprev = nullptr;                            // narrow heads: the rotation the running update started from
   float* PX = nullptr;                               // polar iterate, fp32 [heads][dh][dh]
   bf16_bits *PXn[2] = {nullptr, nullptr};            // iterate as bf16 split planes [3][heads][dh][dh], ping-pong
   bf16_bits *PXt[2] = {nullptr, nullptr};            // ... transposed
   bf16_bits *PW = nullptr, *PW2 = nullptr;           // polynomial factor planes [3][heads][dh][dh]
   double* resid_part = nullptr;                      // [heads][parts] per-wavefront partials of one Gram GEMM
-  double *fro2 = nullptr, *inner = nullptr;          // [heads]
+  double* fro2 = nullptr;                             // [heads]
   double* dot_part = nullptr;                        // [2][heads][(dh/64)^2] per-tile partials of <R_op, M> and of <R, M>
   int64_t last_T = 0;
   size_t stat_words = 0;
-  double* fused_res = nullptr;                       // start of the result block: [2][heads] residuals of the one-launch update
   // heads of width 128 with bf16 activations take the fused step kernel (head_step.hip)
   bool head_fused = false;
   float* Mpart = nullptr;                            // [head_splits][heads][128][128] partial M of the token shares
@@ -273,17 +273,14 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   // L, rows, skipped (fused per-head step) and the slot counters (general path) share one allocation so that one
   // fill clears the batch statistics
   ctx->stat_words = (size_t)3 * ctx->heads + (size_t)2 * kCountSlots * ctx->heads;
-  // The update's scalar results lie in front of them (one copy brings them to the host): ||I - G||_F^2 | ||D^2||_F^2 of a
-  // closing step in the main phase's launch, <R_op, M> | <R, M> | ||M||_F^2, all per head, then the non-finite flag, which is
-  // cleared with the statistics
-  A(dev_alloc(ctx, &ctx->fused_res, (size_t)5 * ctx->heads + 1 + ctx->stat_words));
-  ctx->ldot = ctx->fused_res + 2 * ctx->heads;
-  ctx->L = ctx->ldot + 3 * ctx->heads + 1;
+  // The update's scalar results that its launches hand on lie in front of them: <R_op, M> | ||M||_F^2 per head, then the non-finite
+  // flag, which is cleared with the statistics
+  A(dev_alloc(ctx, &ctx->ldot, (size_t)2 * ctx->heads + 1 + ctx->stat_words));
+  ctx->L = ctx->ldot + 2 * ctx->heads + 1;
   ctx->rows = reinterpret_cast<unsigned long long*>(ctx->L + ctx->heads);
   ctx->skipped = ctx->rows + ctx->heads;
   ctx->cnt = ctx->skipped + ctx->heads;
-  ctx->inner = ctx->ldot + ctx->heads;
-  ctx->fro2 = ctx->inner + ctx->heads;
+  ctx->fro2 = ctx->ldot + ctx->heads;
   ctx->nonfinite = reinterpret_cast<int*>(ctx->fro2 + ctx->heads);
   A(dev_alloc(ctx, &ctx->dotrm_part, (size_t)ctx->heads * dot_rm_partials((int64_t)dh * dh)));
   ctx->l_base.assign(ctx->heads, 0.0);
@@ -293,7 +290,10 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   A(dev_alloc(ctx, &ctx->row_sse, 2 * tmax));   // per-row SSE, then per-row energy
   ctx->row_en = ctx->row_sse + tmax;
   A(dev_alloc(ctx, &ctx->PX, blk));
-  if (dh <= (uint32_t)kHeadPolarMaxDh && cfg->polar_precision == 0) A(dev_alloc(ctx, &ctx->Rprev, blk));   // (read only by updates that take the one-launch path)
+  if (dh <= (uint32_t)kHeadPolarMaxDh && cfg->polar_precision == 0) {   // (for updates that take the one-launch path)
+    A(dev_alloc(ctx, &ctx->Rprev, blk));
+    A(dev_alloc(ctx, &ctx->stats_keep, ctx->stat_words));
+  }
   for (int b = 0; b < 2; ++b) {
     A(dev_alloc(ctx, &ctx->PXn[b], 3 * blk));
     A(dev_alloc(ctx, &ctx->PXt[b], 3 * blk));
@@ -321,7 +321,7 @@ conqur_status conqur_init(const conqur_config* cfg, const float* R0_host, conqur
   if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_resid, hipEventDisableTiming);
   if (e == hipSuccess) e = hipEventCreateWithFlags(&ctx->ev_sq, hipEventDisableTiming);
   if (e == hipSuccess)
-    e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host_res), ((size_t)kResidSlots * ctx->heads + 5 * ctx->heads) * sizeof(double),
+    e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host_res), ((size_t)kResidSlots * ctx->heads + 6 * ctx->heads) * sizeof(double),
                       hipHostMallocDefault);
   if (e == hipSuccess) e = hipHostGetDevicePointer(reinterpret_cast<void**>(&ctx->dev_res), ctx->host_res, 0);
   if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&ctx->host_scalars), sizeof(HostScalars), hipHostMallocDefault);
@@ -848,7 +848,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   bool allow_fuse = true;    // (only the first main phase of an update: not the one after a nudge)
   int fused_slot = -1;       // narrow heads: the launch of the main phase also took the closing step (per head, if
                              // its residual allowed); residual slots fused_slot (||I - G||_F^2) and fused_slot + 1 (||D^2||_F^2)
-                             // of the history on the host (fused_res on the device)
+                             // of the history on the host
   auto main_phase = [&](double l0, bool planes_ready) -> conqur_status {
     if (!planes_ready) HIP_TRY(launch_pack(ctx->PX, h, dh, dh, np_main, ctx->PXn[cur], ctx->PXt[cur], plane, s, main_f16));
     const double e_stop = np_main == 1 ? 4e-3 : 5e-4;   // the safety margins below floor the ripple near 2e-4
@@ -873,7 +873,10 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       const bool fuse = allow_fuse && !ctx->cfg.polar_verify && iters + sc.nsteps + 1 <= cap && slot + 2 < kResidSlots - 8;
       if (fuse) {
         hc.R = ctx->R; hc.RopT = ctx->RopT; hc.rop_planes = ctx->np; hc.rop_plane = plane; hc.M = ctx->M;
-        hc.res_out = ctx->fused_res; hc.sq_out = ctx->fused_res + h; hc.inner_out = ctx->inner;
+        hc.host = ctx->dev_res + (size_t)kResidSlots * h;
+        hc.host_stamps = reinterpret_cast<unsigned long long*>(hc.host + 5 * h);
+        hc.stats = reinterpret_cast<unsigned long long*>(ctx->L); hc.stats_keep = ctx->stats_keep;
+        hc.nonfinite = ctx->nonfinite; hc.host_nonfinite = &ctx->dev_scalars->nonfinite;
         hc.res_max = (float)(1e-2 * std::sqrt((double)dh));
         fused_slot = slot;
         slot += 2;
@@ -940,19 +943,18 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   const float* final_x = ctx->PX;   // where the final iterate lives (the lean closing step writes R directly)
   const bool keep_sq = !ctx->cfg.polar_verify || trace;
   bool finished = false;
-  double* const resblk = ctx->host_res + (size_t)kResidSlots * h;   // outcome of a closing step in the main phase's launch, if any | results
+  double* const resblk = ctx->host_res + (size_t)kResidSlots * h;   // outcome of a closing step in the main phase's launch, if any | results | its heads' stamps
   // The update's last launch: results to the host, statistics restart empty (Alg. 1: M is overwritten by the next accumulate).
-  auto enqueue_end = [&](const double* outcome, bool inner_parts) -> conqur_status {
+  auto enqueue_end = [&]() -> conqur_status {
     UpdateEnd u{};
     u.heads = h;
     u.ldot_parts = ldot_parts ? ctx->dot_part : nullptr;
-    u.inner_parts = inner_parts ? dot_end : nullptr;
+    u.inner_parts = dot_end;
     u.nparts = pack_dot_partials(dh);
     u.scalars = ctx->ldot;
-    u.outcome = outcome;
     u.nonfinite = ctx->nonfinite;
     u.stats = ctx->L; u.stats_bytes = ctx->stat_words * sizeof(double);
-    u.host = ctx->dev_res + (size_t)kResidSlots * h + (outcome ? 0 : 2 * h);
+    u.host = ctx->dev_res + (size_t)kResidSlots * h + 2 * h;
     u.host_nonfinite = &ctx->dev_scalars->nonfinite;
     u.stamp = &ctx->dev_scalars->stamp[1];
     HIP_TRY(launch_update_end(u, s));
@@ -962,26 +964,31 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   auto enqueue_finish = [&]() -> conqur_status {
     // R = final iterate (unless it is there already), <R, M>, and the rotate operand planes of R^T: one pass
     HIP_TRY(launch_polar_finish_pack(final_x, ctx->M, h, dh, ctx->np, final_x == ctx->R ? nullptr : ctx->R, ctx->RopT, plane, dot_end, s));
-    return enqueue_end(nullptr, true);
+    return enqueue_end();
   };
   // Outcome of a closing step taken inside the main phase's launch (narrow heads): accepted if every head took it
   // and the bound from ||D^2||_F (see below) is within the tolerance; otherwise the general closing steps continue from
   // the hand-over state, which that launch wrote as well.  R and the operand of the heads that did take the step are replaced
-  // by then; the launch has kept the previous rotation aside, for the nudge below and for an update that fails.  The
-  // statistics and the non-finite flag are cleared on the device, unless a residual is not finite: one small launch does that and
-  // brings the outcome and the results, and the host waits once, with nothing left to enqueue behind the outcome it expects.
-  bool r_replaced = false, fused_done = false;
+  // by then; the launch has kept the previous rotation and the statistics aside, for the nudge below and for an update that fails.  It
+  // has also brought the outcome and the results and cleared the statistics of the heads whose residuals are finite, and the host waits
+  // once, with nothing left to enqueue behind the outcome it expects.  (A last launch for that took 5 us: a calibration pass of 32 heads
+  // of width 64 62.2 us with it and 60.8 without, of 128 102 and 98.5.)
+  bool r_replaced = false, fused_done = false, stats_cleared = false;
   auto fail_nonfinite = [&]() -> conqur_status {   // the context is left as the update found it
     if (r_replaced) {
       HIP_TRY(hipMemcpyAsync(ctx->R, ctx->Rprev, (size_t)plane * sizeof(float), hipMemcpyDeviceToDevice, s));
       const conqur_status st_op = refresh_operand(ctx);
       if (st_op != CONQUR_OK) return st_op;
     }
+    if (stats_cleared) {
+      HIP_TRY(hipMemcpyAsync(ctx->L, ctx->stats_keep, ctx->stat_words * sizeof(double), hipMemcpyDeviceToDevice, s));
+      if (scalars->nonfinite) HIP_TRY(hipMemcpyAsync(ctx->nonfinite, &scalars->nonfinite, sizeof(int), hipMemcpyHostToDevice, s));
+      HIP_TRY(hipStreamSynchronize(s));
+    }
     return fail(ctx, CONQUR_ENONFINITE, "update_rotation: non-finite polar iterate");
   };
   auto fused_outcome = [&]() -> conqur_status {
-    const conqur_status st_end = enqueue_end(ctx->fused_res, false);
-    if (st_end != CONQUR_OK) return st_end;
+    if (timed) HIP_TRY(hipEventRecord(ctx->ev[ST_UPDATE][1], s));
     HIP_TRY(hipStreamSynchronize(s));
     std::memcpy(hist + (size_t)fused_slot * h, resblk, 2 * h * sizeof(double));
     bool ok = true, finite = true;
@@ -997,6 +1004,7 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
       worst_pred = std::max(worst_pred, b);
       if (!(std::isfinite(b) && b <= tol)) ok = false;
     }
+    stats_cleared = true;   // (of the heads whose residuals are finite)
     if (!finite) return fail_nonfinite();
     if (trace) std::fprintf(stderr, "[conqur] polar closing in the main phase's launch: resid_F=%.6e bound on resid_F=%.4e accepted=%d\n",
                             worst_res, worst_pred, (int)ok);
@@ -1136,7 +1144,9 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   ctx->h_empty.assign(h, 1);
   ctx->h_rows.assign(h, 0);
   if (out) {
-    const double ms = 1e-5 * (double)(scalars->stamp[1] - scalars->stamp[0]);
+    unsigned long long end = scalars->stamp[1];
+    if (fused_done) end = *std::max_element(reinterpret_cast<unsigned long long*>(resblk + 5 * h), reinterpret_cast<unsigned long long*>(resblk + 5 * h) + h);
+    const double ms = 1e-5 * (double)(end - scalars->stamp[0]);
     for (int q = 0; q < h; ++q) {
       out[q].iters = iters; out[q].accurate = closing; out[q].orth_measured = predicted ? 0u : 1u;
       out[q].orth_err = std::sqrt(hist[(size_t)last_slot * h + q]);

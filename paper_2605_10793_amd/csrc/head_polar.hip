@@ -221,6 +221,8 @@ __global__ void __launch_bounds__(64 * NW, 2) k_head_polar(const bf16_bits* __re
     return t;
   };
 
+  // word q of this head's batch statistics: L, rows, skipped, then its counters
+  auto stat_at = [&](int q) { return q < 3 ? (int64_t)q * gridDim.x + h : (int64_t)(3 * gridDim.x) + (int64_t)h * (2 * kCountSlots) + q - 3; };
   Acc acc;
   if (st.stamp && h == 0 && tid == 0) store_for_host(st.stamp, (unsigned long long)wall_clock64());
   if (st.M) {
@@ -254,8 +256,16 @@ __global__ void __launch_bounds__(64 * NW, 2) k_head_polar(const bf16_bits* __re
       dot = block_sum(dot, 1);
     }
     if (tid == 0) {
+      const double l = st.rop_dot || !st.ldot ? dot : st.L[h];
       st.fro2_out[h] = f2;
-      if (st.ldot) st.ldot[h] = st.rop_dot ? dot : st.L[h];   // kept before the statistics restart
+      if (st.ldot) st.ldot[h] = l;   // kept before the statistics restart
+      if constexpr (CLOSE) {         // (here, where the way to the host is covered by the steps)
+        store_for_host(cl.host + 2 * gridDim.x + h, l);
+        store_for_host(cl.host + 4 * gridDim.x + h, f2);
+      }
+    }
+    if constexpr (CLOSE) {
+      for (int q = tid; q < 3 + 2 * kCountSlots; q += NT) cl.stats_keep[stat_at(q)] = cl.stats[stat_at(q)];
     }
     if (st.R_keep) store_block(st.R_keep, prev);
     const double f = sqrt(f2);
@@ -449,8 +459,21 @@ __global__ void __launch_bounds__(64 * NW, 2) k_head_polar(const bf16_bits* __re
       part += (double)p32;
     });
     const double res2 = block_sum(part, 2);
+    auto report = [&](double sq2) {
+      if (isfinite(res2))
+        for (int q = tid; q < 3 + 2 * kCountSlots; q += NT) cl.stats[stat_at(q)] = 0;
+      if (tid == 0) {
+        store_for_host(cl.host + h, res2);
+        store_for_host(cl.host + gridDim.x + h, sq2);
+        if (h == 0 && *cl.nonfinite) {
+          store_for_host(cl.host_nonfinite, 1);
+          if (isfinite(res2)) *cl.nonfinite = 0;
+        }
+        store_for_host(cl.host_stamps + h, (unsigned long long)wall_clock64());
+      }
+    };
     if (!(res2 <= (double)cl.res_max * cl.res_max)) {   // (also a non-finite residual)
-      if (tid == 0) { cl.res_out[h] = res2; cl.sq_out[h] = -1.0; }
+      report(-1.0);
       return;
     }
     const Lanes ld = lanes();
@@ -529,7 +552,8 @@ __global__ void __launch_bounds__(64 * NW, 2) k_head_polar(const bf16_bits* __re
         return t;
       });
     const double inner = block_sum(part, 4);
-    if (tid == 0) { cl.res_out[h] = res2; cl.sq_out[h] = sq2; cl.inner_out[h] = inner; }
+    if (tid == 0) store_for_host(cl.host + 3 * gridDim.x + h, inner);
+    report(sq2);
   }
 }
 
@@ -552,7 +576,8 @@ hipError_t launch_one(const bf16_bits* Xt0, int heads, int dh, const PolarSchedu
 hipError_t launch_head_polar(const bf16_bits* Xt0, int heads, int dh, const PolarSchedule& sched, float* X32, bf16_bits* Pn, bf16_bits* Pt,
                              const HeadPolarClose* close, const HeadPolarStart* start, hipStream_t s) {
   if (heads < 1 || dh < 16 || dh > kHeadPolarMaxDh || (dh & 15) || sched.nsteps < 1 || sched.nsteps > kPolarScheduleMax) return hipErrorInvalidValue;
-  if (close && (!close->R || !close->RopT || !close->M || !close->res_out || !close->sq_out || !close->inner_out || close->rop_planes < 1))
+  if (close && (!start || !close->R || !close->RopT || !close->M || !close->host || !close->host_stamps || !close->stats || !close->stats_keep ||
+                !close->nonfinite || !close->host_nonfinite || close->rop_planes < 1))
     return hipErrorInvalidValue;
   if (start && (!start->M || !start->R || (start->nparts > 0 && !start->fro2_parts) || !start->fro2_out ||
                 (start->ldot && !start->rop_dot && !start->L)))

@@ -78,20 +78,19 @@ int pack_dot_partials(int dh);
 hipError_t launch_polar_finish_pack(const float* X, const float* M, int heads, int dh, int np, float* R32, bf16_bits* outT,
                                     int64_t plane, double* dot_part, hipStream_t s);
 
-// The last launch of an update: its scalar results to the host, the batch statistics and the non-finite flag cleared.
+// The last launch of an update that is not one launch: its scalar results to the host, the batch statistics and the non-finite flag cleared.
 struct UpdateEnd {
   int heads;
-  // <R_op, M> and <R, M> per head: sums of nparts partial sums each, or, where the pointer is null, as they lie at scalars
+  // <R_op, M> and <R, M> per head: sums of nparts partial sums each; ldot_parts null: <R_op, M> as it lies at scalars
   const double* ldot_parts;
   const double* inner_parts;
   int nparts;
-  const double* scalars;       // device: [ldot heads | inner heads | fro2 heads]
-  const double* outcome;       // non-null: 2 heads residuals that go in front of the results; nothing is cleared unless all are finite
+  const double* scalars;       // device: [ldot heads | fro2 heads]
   int* nonfinite;
   void* stats;                 // stats_bytes, a multiple of 8
   size_t stats_bytes;
   // in host memory the device can write
-  double* host;                // [outcome 2 heads, if any | ldot | inner | fro2]
+  double* host;                // [ldot | inner | fro2]
   int* host_nonfinite;         // set if the flag is (never cleared here)
   unsigned long long* stamp;   // the device's wall clock (100 MHz) near the end
 };
@@ -148,20 +147,26 @@ struct PolarSchedule {
   int nsteps;
   float a[kPolarScheduleMax], b[kPolarScheduleMax];
 };
-// close non-null: each head whose residual ||I - X^T X||_F at the hand-over is at most res_max also takes the closing
-// step X <- X + X (D + 1.5 D^2), D = (I - X^T X)/2, in the same launch and writes R (fp32), RopT (bf16 plane of R^T) and
-// inner_out[h] = <R, M>; res_out[h] = ||I - X^T X||_F^2 at the hand-over, sq_out[h] = ||D^2||_F^2, or < 0 if the head did
-// not take the step (then R, RopT and inner_out of that head are untouched).  The hand-over outputs are written either way.
+// close non-null (start as well): each head whose residual ||I - X^T X||_F at the hand-over is at most res_max also takes the closing
+// step X <- X + X (D + 1.5 D^2), D = (I - X^T X)/2, in the same launch and writes R (fp32) and RopT (bf16 plane of R^T).  Of a head that
+// did not take the step R and RopT are untouched and ||D^2||_F^2 is reported < 0.  The hand-over outputs are written either way.
 struct HeadPolarClose {
   float* R;
   bf16_bits* RopT;     // rop_planes split planes of R^T, rop_plane elements apart
   int rop_planes;
   int64_t rop_plane;
   const float* M;
-  double* res_out;
-  double* sq_out;
-  double* inner_out;
   float res_max;
+  // The update's report, by each head for itself: its results to host memory the device can write, [||I - X^T X||_F^2 | ||D^2||_F^2 |
+  // <R_op, M> | <R, M> | ||M||_F^2] of `heads` values each (<R, M>: if the step was taken), and the device's wall clock behind them to
+  // host_stamps[h]; its batch statistics copied to stats_keep and, if its residual is finite, cleared (both [L | rows | skipped |
+  // counters [kCountSlots][2]] of 8 bytes per value, `heads` of each); by head 0 the non-finite flag, likewise.
+  double* host;
+  unsigned long long* host_stamps;
+  unsigned long long* stats;
+  unsigned long long* stats_keep;
+  int* nonfinite;
+  int* host_nonfinite;
 };
 // start non-null: the launch forms the start iterate itself, X0 = (M + lambda tau R) / alpha per head (Xt0 unused, may
 // be null), from M and R (fp32 [heads][dh][dh]).  ||M_h||_F^2 is the sum of nparts partial sums per head

@@ -687,35 +687,28 @@ __global__ void __launch_bounds__(256) k_sum_partials(const double* __restrict__
   if (threadIdx.x == 0) store_for_host(out + blockIdx.x, s);
 }
 
-// The end of an update (see UpdateEnd): a workgroup per head for its sums, one more for what the heads share.  One launch and
-// one synchronisation instead of two sums, two fills, a copy and a second wait; the residuals' sums go to the host's memory as
-// well, and the time stamps replace two events.  A calibration pass, us, before and with all of these: 32 heads of width 64
-// 103.6 and 76.7, of 128 135 and 104, fp32 at 256 267 and 246, 1104 354 and 336, 3072 1997 and 1975.
+// The end of an update of several launches (see UpdateEnd): a workgroup per head for its sums, one more for what the heads share.  One
+// launch and one synchronisation instead of two sums, two fills, a copy and a second wait; the residuals' sums go to the host's memory as
+// well, and the time stamps replace two events.  A calibration pass, us, before and with all of these: fp32 at 256 267 and 246,
+// 1104 354 and 336, 3072 1997 and 1975.
 __global__ void __launch_bounds__(256) k_update_end(const UpdateEnd u) {
   __shared__ double sh[4];
   const int t = threadIdx.x, h = blockIdx.x, n = u.heads;
-  double* const results = u.outcome ? u.host + 2 * n : u.host;
   if (h < n) {
     const double ldot = u.ldot_parts ? sum_partials(u.ldot_parts + (int64_t)h * u.nparts, u.nparts, sh) : u.scalars[h];
-    const double inner = u.inner_parts ? sum_partials(u.inner_parts + (int64_t)h * u.nparts, u.nparts, sh) : u.scalars[n + h];
+    const double inner = sum_partials(u.inner_parts + (int64_t)h * u.nparts, u.nparts, sh);
     if (t == 0) {
-      store_for_host(results + h, ldot);
-      store_for_host(results + n + h, inner);
-      store_for_host(results + 2 * n + h, u.scalars[2 * n + h]);
+      store_for_host(u.host + h, ldot);
+      store_for_host(u.host + n + h, inner);
+      store_for_host(u.host + 2 * n + h, u.scalars[n + h]);
       if (h == 0) store_for_host(u.stamp, (unsigned long long)wall_clock64());
     }
     return;
   }
-  int bad = 0;
-  if (u.outcome)
-    for (int i = t; i < 2 * n; i += 256) {
-      const double v = u.outcome[i];
-      store_for_host(u.host + i, v);
-      bad |= isfinite(v) ? 0 : 1;
-    }
-  if (t == 0 && *u.nonfinite) store_for_host(u.host_nonfinite, 1);
-  if (__syncthreads_or(bad)) return;
-  if (t == 0) *u.nonfinite = 0;
+  if (t == 0 && *u.nonfinite) {
+    store_for_host(u.host_nonfinite, 1);
+    *u.nonfinite = 0;
+  }
   for (size_t i = t; i < u.stats_bytes / 8; i += 256) reinterpret_cast<uint64_t*>(u.stats)[i] = 0;
 }
 
@@ -885,7 +878,7 @@ hipError_t launch_sum_partials(const double* part, int n, int heads, double* out
 
 hipError_t launch_update_end(const UpdateEnd& u, hipStream_t s) {
   if (u.heads < 1 || !u.scalars || !u.nonfinite || !u.host || !u.host_nonfinite || !u.stamp || (u.stats_bytes & 7) ||
-      ((u.ldot_parts || u.inner_parts) && u.nparts < 1))
+      !u.inner_parts || u.nparts < 1)
     return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_update_end, dim3(u.heads + 1), dim3(256), 0, s, u);
   return hipGetLastError();
