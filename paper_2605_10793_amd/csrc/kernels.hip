@@ -454,15 +454,26 @@ __global__ void __launch_bounds__(256) k_axpy(float* __restrict__ X, const float
 // {0 .. qmax}, D = range / qmax, integer zero point zeta = -rint(lo / D), code = clamp(rint(y / D) + zeta, 0, qmax).
 // EMIT: the quantised rows q are also written out in the activation dtype (Q, row stride ldq): what a linear layer with
 // quantised input receives during quantisation-aware calibration (Sec. 3.4).
-template <bool F32, bool ZP, bool EMIT>
+// WAVE: a wavefront per row, for many short rows, where what every wavefront does once per row (extremes, divisions, sums: some 60
+// instructions) weighs more than its values.  Scores of both quantisers, us, a workgroup per row and a wavefront: 30000 x 256
+// 25.7 and 33.8, 17.5 and 20.2; 12000 x 1024 13.9 and 17.4, 11.7 and 12.9; 9000 x 1040 12.4 and 15.4, 11.9 and 13.1; 12000 x 2560 17.9 and
+// 21.5, 18.2 and 19.4; 8192 x 4096 17.0 and 19.1, 20.3 and 22.0.  Fewer than some 4000 rows are bound by the launch either way.  The
+// lane that takes four lanes' chunks keeps their sums apart: same bits.
+constexpr int kWaveRowChunks = 5;
+constexpr bool wave_per_row(int64_t T, int chunks, bool zero_point) { return T >= 4096 && chunks <= 64 * (zero_point ? kWaveRowChunks : 3); }
+
+template <bool F32, bool ZP, bool EMIT, bool WAVE>
 __global__ void __launch_bounds__(256) k_quant_error(const void* __restrict__ Y, int64_t T, int64_t ld, int d, float qmax,
                                                      float clip, float* __restrict__ row_sse, float* __restrict__ row_en,
                                                      void* __restrict__ Q, int64_t ldq) {
   constexpr int EPC = F32 ? 4 : 8;  // elements per 16-byte chunk
-  constexpr int NC = 4;             // chunks cached per thread
+  constexpr int LANES = WAVE ? 64 : 256, NC = WAVE ? kWaveRowChunks : 4;   // lanes of a row, chunks cached per lane
+  constexpr int NS = WAVE ? 4 : 1;  // sums of a lane: those of the four lanes that would have its chunks in a workgroup
   __shared__ float shm[4], shn[4], shs[4], she[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int64_t row = blockIdx.x;
+  const int at = WAVE ? lane : (int)threadIdx.x;
+  const int64_t row = WAVE ? (int64_t)blockIdx.x * 4 + wave : (int64_t)blockIdx.x;
+  if (WAVE && row >= T) return;
   const int nch = d / EPC;
   auto expand = [](const uint4& v, float* f) {
     if constexpr (F32) {
@@ -496,20 +507,23 @@ __global__ void __launch_bounds__(256) k_quant_error(const void* __restrict__ Y,
   };
 #pragma unroll
   for (int q = 0; q < NC; ++q) {
-    const int c = threadIdx.x + 256 * q;
+    const int c = at + LANES * q;
     cache[q] = make_uint4(0, 0, 0, 0);
     if (c < nch) {
       cache[q] = y[c];
       track(cache[q]);
     }
   }
-  for (int c = threadIdx.x + 256 * NC; c < nch; c += 256) track(y[c]);
+  if constexpr (!WAVE)
+    for (int c = at + LANES * NC; c < nch; c += LANES) track(y[c]);
   amax = wave_max(amax);
   if constexpr (ZP) amin = wave_max(amin);
-  if (lane == 0) { shm[wave] = amax; shn[wave] = amin; }
-  __syncthreads();
-  amax = fmaxf(fmaxf(shm[0], shm[1]), fmaxf(shm[2], shm[3]));
-  if constexpr (ZP) amin = fmaxf(fmaxf(shn[0], shn[1]), fmaxf(shn[2], shn[3]));
+  if constexpr (!WAVE) {
+    if (lane == 0) { shm[wave] = amax; shn[wave] = amin; }
+    __syncthreads();
+    amax = fmaxf(fmaxf(shm[0], shm[1]), fmaxf(shm[2], shm[3]));
+    if constexpr (ZP) amin = fmaxf(fmaxf(shn[0], shn[1]), fmaxf(shn[2], shn[3]));
+  }
   // D = max / qmax; the code is decided in fp32 as round-half-even(y * (1/D)) with the
   // correctly rounded reciprocal (a division per element would make this kernel
   // ALU bound instead of HBM bound); it can differ from round(y / D) only within an
@@ -524,7 +538,7 @@ __global__ void __launch_bounds__(256) k_quant_error(const void* __restrict__ Y,
     delta = amax / qmax;
     inv_delta = amax > 0.0f ? 1.0f / delta : 0.0f;
   }
-  float sse = 0.0f, en = 0.0f;
+  float sum_sse[NS] = {}, sum_en[NS] = {};
   uint4* const qrow = EMIT ? reinterpret_cast<uint4*>(reinterpret_cast<char*>(Q) + row * ldq * (F32 ? 4 : 2)) : nullptr;
   // Zero-point levels without the shift: clamp(r + zeta, 0, qmax) - zeta = clamp(r, -zeta, qmax - zeta), the same integer as long as
   // every sum is one fp32 holds exactly.  A row whose values lie 2^22 steps or more from 0 keeps the shifted form, a
@@ -534,7 +548,7 @@ __global__ void __launch_bounds__(256) k_quant_error(const void* __restrict__ Y,
   // fetch the next ahead lose: 8 a compute unit 36 and 32.
   [[maybe_unused]] const bool plain = ZP && delta > 0.0f && fmaxf(fabsf(amax), fabsf(amin)) * inv_delta < 4194304.0f;
   const float code_lo = ZP ? -zeta : -qmax, code_hi = ZP ? qmax - zeta : qmax;
-  auto score = [&](const uint4& v, int c, auto is_plain) {
+  auto score = [&](const uint4& v, int c, float& sse, float& en, auto is_plain) {
     float f[EPC], qv[EPC];
     expand(v, f);
 #pragma unroll
@@ -569,18 +583,25 @@ __global__ void __launch_bounds__(256) k_quant_error(const void* __restrict__ Y,
   auto score_row = [&](auto is_plain) {
 #pragma unroll
     for (int q = 0; q < NC; ++q)
-      if ((int)threadIdx.x + 256 * q < nch) score(cache[q], (int)threadIdx.x + 256 * q, is_plain);
-    for (int c = threadIdx.x + 256 * NC; c < nch; c += 256) score(y[c], c, is_plain);
+      if (at + LANES * q < nch) score(cache[q], at + LANES * q, sum_sse[q % NS], sum_en[q % NS], is_plain);
+    if constexpr (!WAVE)
+      for (int c = at + LANES * NC; c < nch; c += LANES) score(y[c], c, sum_sse[0], sum_en[0], is_plain);
   };
   if (!ZP || plain) score_row(std::true_type{});
   else score_row(std::false_type{});
-  sse = wave_sum(sse);
-  en = wave_sum(en);
-  if (lane == 0) { shs[wave] = sse; she[wave] = en; }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    row_sse[row] = (float)((double)shs[0] + (double)shs[1] + (double)shs[2] + (double)shs[3]);
-    row_en[row] = (float)((double)she[0] + (double)she[1] + (double)she[2] + (double)she[3]);
+  // the four partial sums of a workgroup's wavefronts, wherever they are, in their order
+  float s4[4], e4[4];
+#pragma unroll
+  for (int q = 0; q < NS; ++q) { s4[q] = wave_sum(sum_sse[q]); e4[q] = wave_sum(sum_en[q]); }
+  if constexpr (!WAVE) {
+    if (lane == 0) { shs[wave] = s4[0]; she[wave] = e4[0]; }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { s4[q] = shs[q]; e4[q] = she[q]; }
+  }
+  if (at == 0) {
+    row_sse[row] = (float)((double)s4[0] + (double)s4[1] + (double)s4[2] + (double)s4[3]);
+    row_en[row] = (float)((double)e4[0] + (double)e4[1] + (double)e4[2] + (double)e4[3]);
   }
 }
 
@@ -835,26 +856,28 @@ hipError_t launch_axpy(float* X, const float* R, int64_t n, float kappa, hipStre
 }
 
 namespace {
-template <bool EMIT>
+template <bool EMIT, bool WAVE>
 void launch_quant_kernel(const void* Y, int y_is_f32, int64_t T, int64_t ld, int d, float qmax, int zero_point, float clip,
                          float* row_sse, float* row_en, void* Q, int64_t ldq, hipStream_t s) {
-  const dim3 grid((unsigned)T);
-  if (y_is_f32 && zero_point)
-    hipLaunchKernelGGL((k_quant_error<true, true, EMIT>), grid, dim3(256), 0, s, Y, T, ld, d, qmax, clip, row_sse, row_en, Q, ldq);
-  else if (y_is_f32)
-    hipLaunchKernelGGL((k_quant_error<true, false, EMIT>), grid, dim3(256), 0, s, Y, T, ld, d, qmax, clip, row_sse, row_en, Q, ldq);
-  else if (zero_point)
-    hipLaunchKernelGGL((k_quant_error<false, true, EMIT>), grid, dim3(256), 0, s, Y, T, ld, d, qmax, clip, row_sse, row_en, Q, ldq);
-  else
-    hipLaunchKernelGGL((k_quant_error<false, false, EMIT>), grid, dim3(256), 0, s, Y, T, ld, d, qmax, clip, row_sse, row_en, Q, ldq);
+  const dim3 grid((unsigned)(WAVE ? (T + 3) / 4 : T));
+  auto go = [&](auto f32, auto zp) {
+    hipLaunchKernelGGL((k_quant_error<decltype(f32)::value, decltype(zp)::value, EMIT, WAVE>), grid, dim3(256), 0, s, Y, T, ld, d, qmax, clip, row_sse,
+                       row_en, Q, ldq);
+  };
+  if (y_is_f32 && zero_point) go(std::true_type{}, std::true_type{});
+  else if (y_is_f32) go(std::true_type{}, std::false_type{});
+  else if (zero_point) go(std::false_type{}, std::true_type{});
+  else go(std::false_type{}, std::false_type{});
 }
 }  // namespace
 
 hipError_t launch_quant_error(const void* Y, int y_is_f32, int64_t T, int64_t ld, int d, int bits, int zero_point, float clip,
                               float* row_sse, float* row_en, double* out, void* Q, int64_t ldq, hipStream_t s) {
   const float qmax = zero_point ? (float)((1 << bits) - 1) : (float)((1 << (bits - 1)) - 1);
-  if (Q) launch_quant_kernel<true>(Y, y_is_f32, T, ld, d, qmax, zero_point, clip, row_sse, row_en, Q, ldq, s);
-  else launch_quant_kernel<false>(Y, y_is_f32, T, ld, d, qmax, zero_point, clip, row_sse, row_en, nullptr, 0, s);
+  if (Q) launch_quant_kernel<true, false>(Y, y_is_f32, T, ld, d, qmax, zero_point, clip, row_sse, row_en, Q, ldq, s);
+  else if (wave_per_row(T, d / (y_is_f32 ? 4 : 8), zero_point))
+    launch_quant_kernel<false, true>(Y, y_is_f32, T, ld, d, qmax, zero_point, clip, row_sse, row_en, nullptr, 0, s);
+  else launch_quant_kernel<false, false>(Y, y_is_f32, T, ld, d, qmax, zero_point, clip, row_sse, row_en, nullptr, 0, s);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || !out) return e;   // out == null: the caller sums the per-row results itself
   hipLaunchKernelGGL(k_sum_rows, dim3(2), dim3(1024), 0, s, row_sse, row_en, T, out);

@@ -1719,3 +1719,28 @@ def test_step_of_narrow_heads_in_one_launch(B, dh, heads, T):
     for a, b in zip(got[:2], got[2:]):
         assert all(np.array_equal(x, y) for x, y in zip(a[:3], b[:3])) and a[3] == b[3]
     assert got[0][3] == [(T - 2, 2)] + [(T - 1, 1)] * (heads - 1) and np.isfinite(got[1][0]).all()
+
+
+@pytest.mark.parametrize("d,dtype", [(16, "bf16"), (528, "bf16"), (1536, "bf16"), (2064, "bf16"), (2560, "bf16"), (16, "f32"), (784, "f32"), (1280, "f32")])
+def test_scores_of_many_short_rows(B, d, dtype):
+    """Calls of 4096 rows and more take a wavefront per row where the row is short, smaller ones a workgroup: the same row results to the
+    bit, so the sums differ by their fp64 additions alone.  Both ends of the range of widths; zero, constant and non-finite rows."""
+    import torch
+    T = 4099
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d)
+    Y = torch.randn((T, d), generator=g, device="cuda:0") * torch.exp(2 * torch.randn((T, 1), generator=g, device="cuda:0"))
+    Y[5], Y[6], Y[T - 1] = 0.0, -3.25, 1e-3
+    Y = Y.to(torch.bfloat16) if dtype == "bf16" else Y
+    out = torch.empty((4, 2), dtype=torch.float64, device="cuda:0")
+    for zp, clip in ((False, 1.0), (True, 0.9), (True, 1.0)):
+        B.score_rows_static(Y, out[0], 4, zp, clip)
+        for i, (a, b) in enumerate(((0, 2000), (2000, 4090), (4090, T))):
+            B.score_rows_static(Y[a:b].contiguous(), out[1 + i], 4, zp, clip)
+        torch.cuda.synchronize()
+        whole, pieces = out[0], out[1:].sum(0)
+        assert float(((whole - pieces).abs() / pieces).max()) <= T * 2.0 ** -53
+    Y[77, d - 1] = float("nan")
+    B.score_rows_static(Y, out[0], 4, True, 0.9)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(out[0]).all())
