@@ -299,7 +299,7 @@ conqur_status conqur_score_rows_static(const void* Y_dev, uint32_t dtype, uint64
  * pair per stage -- the records between the kernels keep one kernel's launch from
  * overlapping the previous kernel's tail, so the stages sum to more than the whole call --
  * and the clock probes of conqur_get_clock_probe.  out_host: HOST, 12 floats:
- * [0] step: prepare (norms + transposed operand)  [1] step: rotate+corner GEMM
+ * [0] step: prepare (norms + transposed operand)  [1] step: rotate+corner GEMM (a per-head step of one launch: all of it)
  * [2] step: accumulate GEMM                       [3] step: statistics reduction
  * [4] update: whole polar update                  [5] quant: rotate GEMM
  * [6] quant: error kernel                         [7] whole conqur_step_batch
