@@ -469,8 +469,9 @@ static conqur_status step_general(conqur_ctx* ctx, const void* X, int64_t T, int
   // kernel for a few rows, which saves the transposing launch; fp32 activations (split planes) and the GEMM variant that
   // also emits Y keep that launch.
   const bool xt_in_rotate = !ctx->f32 && (few || !keep_y);
-  // Several narrow heads: one launch for the whole step, the same bits (of one rotation the accumulate GEMM splits the token range).
-  if (!ctx->f32 && ctx->heads > 1 && ctx->dh <= kHeadStepNarrowMaxDh && !few && !keep_y) {
+  // Several narrow heads: one launch for the whole step where that is faster, the same bits (of one rotation the accumulate GEMM splits
+  // the token range).
+  if (!ctx->f32 && !few && !keep_y && head_step_narrow_pays(ctx->dh, ctx->heads, T)) {
     HeadStepNarrow a{};
     a.X = reinterpret_cast<const bf16_bits*>(X); a.T = T; a.stride = stride; a.heads = ctx->heads; a.RopT = ctx->RopT;
     a.M = ctx->M; a.accumulate = ctx->m_empty ? 0 : 1;

@@ -11,12 +11,15 @@
 //              the scaled rows (fp16) times an identity leave accumulators that hold them, exactly, in Y's layout, turned the same way.
 //   M          The operands of the 256 tokens meet in LDS (two buffers, one barrier), and one wavefront per tile of M takes them in order.
 // What bounds it: the arithmetic of the operands (some 330 VALU instructions per 32 tokens), half of which, the norms, every
-// workgroup of a head repeats; 256 tokens take 1.5 us whatever the number of heads.  Statistics step, us, as norms, rotation with signs and operand,
+// workgroup of a head repeats, in series over the tokens: 256 tokens take 0.8 us at width 16 and 2.2 to 2.9 at 112, whatever the number of
+// heads up to a round of workgroups.  Statistics step, us, as norms, rotation with signs and operand,
 // and accumulation in a launch each, and so: 32 heads of width 64, 2048 tokens 29.2 and 16.6; 24 of 64, 700 tokens 16.3 and 8.5; 32 of 16, 2048
-// 22.5 and 10.2; 16 of 48, 3000 27.9 and 19.5; 32 of 96, 2048 30.9 and 24.1; 8 of 112, 2500 27.8 and 26.3.  Not faster: 16
+// 22.5 and 10.2; 16 of 48, 3000 27.9 and 19.5; 32 of 96, 2048 30.9 and 24.1; 8 of 112, 2500 27.8 and 26.3.  Where the three launches are the
+// faster ones (long batches of few heads 48 wide and more, a second round of workgroups) they stay: head_step_narrow_pays.  Not faster: 16
 // wavefronts, rows fetched 512 tokens ahead (17.5 .. 19.2 for the first), wavefronts of their own for M (18.1).
 #include "kernels.h"
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -216,15 +219,20 @@ __global__ void __launch_bounds__(64 * NW) k_head_step_narrow(const HeadStepNarr
   }
 }
 
+// By channel blocks where that still gives every workgroup a compute unit of its own: 32 heads of width 64, 2048 tokens 16.6 us (18.0
+// without), 8 of 112, 2500 tokens 26.3 (32.4); but 32 of 80, 2000 tokens, 480 workgroups 32.4 (22.8), 16 of 96, 400 tokens 11.7 (8.9).
+bool by_channel_blocks(int dh, int heads) {
+  const int kb = (dh + 31) / 32;
+  return kb > 1 && heads * (dh / 16) * kb <= 256;
+}
+
 template <int DH>
 hipError_t launch_one(const HeadStepNarrow& a, hipStream_t s) {
   constexpr int KB = (DH + 31) / 32, NT = DH / 16;
   const float out_scale = 1.0f / (kXhatScale * std::sqrt((float)DH));
   const dim3 grid(8 * NT * ((a.heads + 7) / 8));
-  // By channel blocks where that still gives every workgroup a compute unit of its own: 32 heads of width 64, 2048 tokens 16.6 us (18.0
-  // without), 8 of 112, 2500 tokens 26.3 (32.4); but 32 of 80, 2000 tokens, 480 workgroups 32.4 (22.8), 16 of 96, 400 tokens 11.7 (8.9).
   if constexpr (KB > 1) {
-    if (a.heads * NT * KB <= 256) {
+    if (by_channel_blocks(DH, a.heads)) {
       hipLaunchKernelGGL((k_head_step_narrow<DH, true>), dim3(grid.x, KB), dim3(64 * NW), 0, s, a, out_scale);
       return hipGetLastError();
     }
@@ -234,6 +242,32 @@ hipError_t launch_one(const HeadStepNarrow& a, hipStream_t s) {
 }
 
 }  // namespace
+
+// The expected times of this launch and of the general path's three, us.  Here: a fixed 3 and `per_block` for every 256 tokens, as many
+// times over as the workgroups, of which a compute unit holds what its LDS does, are rounds.  There: 12 for the launches, the
+// accumulate GEMM's chain over the tokens and the passes over the elements.  Fitted to 1140 steps, 2 to 256 heads, 33 to 65536
+// tokens, both ways each: the way taken is 0.2 % slower than the faster one on average, at worst 1.18 times, and slower than the three
+// launches by more than 2 % in 8 (1.09 at worst; without the rule in 154, 1.96 at worst).  One launch and three, us: 32 heads of
+// width 64, 2048 tokens 16 and 27; 2 of 112, 1024 tokens 12 and 16, 4096 35 and 27, 65536 500 and 265; 16 of 96, 2048 23 and 27, 8192 77 and
+// 66; 40 of 112, 512 17 and 19, 2048 52 and 42.  Heads up to 32 wide are faster in one launch throughout.
+bool head_step_narrow_pays(int dh, int heads, int64_t T) {
+  if (heads < 2 || dh < 16 || (dh & 15) || dh > kHeadStepNarrowMaxDh) return false;
+  static constexpr double kWhole[] = {0.85, 0.95, 1.45, 1.7, 2.2, 2.3, 2.9}, kSplit[] = {0.85, 0.95, 1.3, 1.4, 1.7, 1.75, 2.2};
+  const bool split = by_channel_blocks(dh, heads);
+  const int nt = dh / 16, tiles = split ? 2 : nt;
+  const int64_t workgroups = (int64_t)heads * nt * (split ? (dh + 31) / 32 : 1);
+  const bool share = 160 / (2 * NW * (tiles + 1)) > 1;   // of 160 KiB of LDS (nt == 1 is never split)
+  const double rounds = share ? std::max(1.0, (double)workgroups / 256) : (double)((workgroups + 255) / 256);
+  const double per_block = (split ? kSplit : kWhole)[nt - 1];
+  const double one = rounds * (3.0 + per_block * (double)T / 256);
+  const double three = 12.0 + 0.9 * (double)T / 256 + 2.4e-6 * (double)T * dh * heads;
+  return one < three;
+}
+
+// For tests (host code only).
+extern "C" __attribute__((visibility("default"))) int conqur_head_step_narrow_for_tests(int dh, int heads, int64_t T) {
+  return head_step_narrow_pays(dh, heads, T);
+}
 
 hipError_t launch_head_step_narrow(const HeadStepNarrow& a, int dh, hipStream_t s) {
   if (a.heads < 1 || a.T < 1 || a.cnt_slots < 1 || a.pitch < round_up(a.T, kBlock) || (a.pitch & 7)) return hipErrorInvalidValue;

@@ -135,6 +135,8 @@ struct HeadStepNarrow {
   int64_t pitch;
 };
 hipError_t launch_head_step_narrow(const HeadStepNarrow& a, int dh, hipStream_t s);
+// Whether that is the faster way for these sizes (several heads of a width it takes; T tokens of a batch).
+bool head_step_narrow_pays(int dh, int heads, int64_t T);
 
 // Main phase of the polar iteration for heads of width up to kHeadPolarMaxDh (a multiple of 16) in one launch
 // (head_polar.hip): runs the composed cubics X <- X (a_k I + b_k X^T X), k < nsteps, on single fp16 operand planes held in

@@ -69,3 +69,14 @@ def test_every_tile_of_a_grid_is_one_workgroups(sym):
                 assert tm.min() >= 0 and tm.max() < m and tn.min() >= 0 and tn.max() < n
                 assert not sym or (tm <= tn).all()
                 assert np.unique(tm.astype(np.int64) * n + tn).size == count
+
+
+@pytest.mark.parametrize("dh,heads,T,one_launch", [
+    (16, 2, 65536, 1), (32, 256, 16384, 1), (64, 32, 2048, 1), (48, 2, 65536, 0), (64, 2, 1024, 1), (64, 4, 16384, 0), (80, 4, 8192, 0), (80, 40, 8192, 1),
+    (96, 2, 512, 1), (96, 16, 16384, 0), (96, 48, 512, 1), (96, 48, 4096, 0), (96, 128, 4096, 1), (112, 2, 1024, 1), (112, 2, 4096, 0), (112, 4, 65536, 0),
+    (112, 8, 8192, 0), (112, 40, 200, 1), (112, 40, 2048, 0), (112, 40, 8192, 0), (112, 256, 64, 0), (64, 1, 2048, 0), (128, 8, 512, 0)])
+def test_narrow_heads_take_the_faster_statistics_step(dh, heads, T, one_launch):
+    """One launch or the general path's three, as measured: each of these is at least 1.1 times as fast the way stated.  (One head
+    and heads of width 128 have other ways.)"""
+    L = binding.load()
+    assert L.conqur_head_step_narrow_for_tests(dh, heads, ctypes.c_int64(T)) == one_launch

@@ -1721,6 +1721,28 @@ def test_step_of_narrow_heads_in_one_launch(B, dh, heads, T):
     assert got[0][3] == [(T - 2, 2)] + [(T - 1, 1)] * (heads - 1) and np.isfinite(got[1][0]).all()
 
 
+@pytest.mark.parametrize("dh,heads,short,long", [(112, 2, 700, 4001), (64, 3, 500, 9000), (96, 48, 300, 3001)])
+def test_narrow_steps_on_both_sides_of_the_rule(B, dh, heads, short, long):
+    """A short batch (one launch) and a long one (the general launches) into one M, in either order: the bits of the general launches."""
+    import ctypes
+    d = dh * heads
+    assert [B.load().conqur_head_step_narrow_for_tests(dh, heads, ctypes.c_int64(T)) for T in (short, long)] == [1, 0]
+    w = I.small_workload(d, long, n_batches=1, heads=heads, seed=dh, prox_lambda=0.1)
+    X = B.to_device(I.batch(w, 0), "bf16")
+    got = []
+    for order in ((short, long), (long, short)):
+        for general in (False, True):
+            cal = B.Calibrator(d, heads, "bf16", I.initial_rotation(w), max_tokens=long, prox_lambda=0.1)
+            try:
+                for T in order:
+                    cal.step_batch_quant(X[:T], 4, True, 0.9) if general else cal.step_batch(X[:T])
+                got.append((cal.get_state(want_R=False)[1], *cal.last_corners(order[-1]), [s["rows"] for s in cal.batch_stats()]))
+            finally:
+                cal.close()
+    for a, b in (got[:2], got[2:]):
+        assert all(np.array_equal(x, y) for x, y in zip(a[:3], b[:3])) and a[3] == b[3] == [short + long] * heads
+
+
 @pytest.mark.parametrize("d,dtype", [(16, "bf16"), (528, "bf16"), (1536, "bf16"), (2064, "bf16"), (2560, "bf16"), (16, "f32"), (784, "f32"), (1280, "f32")])
 def test_scores_of_many_short_rows(B, d, dtype):
     """Calls of 4096 rows and more take a wavefront per row where the row is short, smaller ones a workgroup: the same row results to the
