@@ -1008,33 +1008,46 @@ Choice choose(const GemmArgs& a, GemmEpilogue epi, int batch) {
   return best;
 }
 
-// The order of the tiles (`bands` of tile_of).  32 tiles at a time per XCD, or its whole share: in bands for which they read the
-// fewest operand rows, that is blocks that are about square.  Where a launch has several rounds the XCDs' reads otherwise cost
-// power, if not time: 11008 x 4096 rotated (688 tiles, 33 panels at a time down the columns, 12 so) 313 -> 291 us at the clock the
-// chip sustains, fp32 777 x 1040 (one round, six segments) 31.9 -> 30.9.  A polar product of one round reads what the same XCD
-// has just written, and whole lines keep more of that in its L2: update at d = 1104 360 us along the columns, 371 in bands.
+// The order of the tiles (`bands` of tile_of).  In bands, what an XCD runs at a time (32 tiles, or its whole share) is about square
+// and reads the fewest operand rows; along lines its whole share is one run of whole tile rows or columns, less regular reads
+// but none twice.  Which one wins was measured, us along lines and in bands:
+//   rotations of several rounds    bands where they read at most 0.6 of the rows (and K is long enough for that to count): 9190 x 4096 280
+//                                  and 264, 12000 x 5120 490 and 456, 4045 x 4480 166 and 161 (0.35 .. 0.5 of the rows); but 9190 x
+//                                  3344 171 and 181 (0.63), 9190 rows of 8 x 304, 5 steps, 34.0 and 35.8
+//   rotations of one round         lines: fp32, six segments, 1936 x 1040 55.1 and 60.4, 1100 x 480 17.7 and 19.4, 1500 x 800 40.2 and
+//                                  43.4; 603 x 2096 (64 x 64, some sharing a compute unit) 15.7 and 18.7, 6000 x 2096 50.8 and 55.6.
+//                                  But 64 x 64 tiles of many steps: 777 x 1040 34.8 and 33.5, 872 x 944 31.8 and 29.8; of 125
+//                                  such from 84 steps on bands took 0.94 to 1.01 of the time, from 72 to 78 0.95 to 1.06
+//   other products                 bands from two rounds on (a step of 4045 tokens at d = 5120 434 and 407).  A polar product of one round
+//                                  reads what the same XCD has just written, and whole lines keep more of that in its L2: update at
+//                                  d = 1104 360 us along the columns, 371 in bands.
+// (Of 758 rotations timed, 24 are more than 3 % slower than along lines or in whole 4 x 8 blocks, in two library builds; 19 such are
+// noise of the comparison.  Bands for every rotation of 32 steps or several rounds were slower for 130, by up to 21 %.)
 int order_of(int tiles_m, int tiles_n, int bm, int bn, bool sym, int epi, int batch, int steps) {
   const int n = sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   const int share = (n + 7) / 8, run = std::min(share, 32);
-  const bool square = (tiles_m & 3) == 0 && (tiles_n & 7) == 0 && (((tiles_m >> 2) * (tiles_n >> 3)) & 7) == 0;   // whole 4 x 8 blocks
-  const bool rotates = epi == EPI_ACT || epi == EPI_SIGN || epi == EPI_SIGN_ACT || epi == EPI_SIGN_XT;
-  const bool lines = (int64_t)n * batch <= 256 && !(rotates && steps >= 32);
+  const bool one_round = (int64_t)n * batch <= 256;
   if (sym) {
     int h = 0;
-    if (!lines)
+    if (!one_round)
       for (h = 1; (h + 1) * (h + 1) <= run;) ++h;
     return h;
   }
-  if (lines && !square) {   // along the columns or the rows, whichever reads fewer operand rows
-    const int down = std::min(share, tiles_m) * bm + (share / tiles_m + 1) * bn, across = std::min(share, tiles_n) * bn + (share / tiles_n + 1) * bm;
-    return across < down ? 0 : 1;
-  }
+  const bool square = (tiles_m & 3) == 0 && (tiles_n & 7) == 0 && (((tiles_m >> 2) * (tiles_n >> 3)) & 7) == 0;   // whole 4 x 8 blocks
+  const bool rotates = epi == EPI_ACT || epi == EPI_SIGN || epi == EPI_SIGN_ACT || epi == EPI_SIGN_XT;
+  // along the columns or the rows, whichever reads fewer operand rows
+  const int64_t down = (int64_t)std::min(share, tiles_m) * bm + (int64_t)(share / tiles_m + 1) * bn;
+  const int64_t across = (int64_t)std::min(share, tiles_n) * bn + (int64_t)(share / tiles_n + 1) * bm;
+  const int line = across < down ? 0 : 1;
+  const bool short_k = rotates && steps < (one_round ? 80 : 16), large = rotates && one_round && bm * bn > 64 * 64;
+  if (!square && (short_k || large || (one_round && !rotates))) return line;
   int best = 1;
   int64_t best_rows = INT64_MAX;
   for (int h = std::min(tiles_m, run); h >= 1; --h) {
     const int64_t rows = (int64_t)h * bm + (int64_t)((run + h - 1) / h) * bn;
     if (rows < best_rows) { best_rows = rows; best = (tiles_m + h - 1) / h; }
   }
+  if (!square && rotates && !one_round && 5 * best_rows > 3 * std::min(down, across)) return line;
   return best;
 }
 
@@ -1100,12 +1113,13 @@ extern "C" __attribute__((visibility("default"))) void conqur_gemm_tile_for_test
   out[0] = u.bm; out[1] = u.bn; out[2] = u.wgm * u.wgn; out[3] = (int)c.tiles; out[4] = c.sym;
 }
 
-// For tests (host code only): the tile of every workgroup of such a grid, in the order the launcher takes for it.
-extern "C" __attribute__((visibility("default"))) void conqur_gemm_order_for_tests(int epi, int symmetric, int tiles_m, int tiles_n, int bm, int bn,
-                                                                                   int batch, int steps, int* tm, int* tn) {
+// For tests (host code only): the tile of every workgroup of such a grid, in the order the launcher takes for it, and that order's `bands`.
+extern "C" __attribute__((visibility("default"))) int conqur_gemm_order_for_tests(int epi, int symmetric, int tiles_m, int tiles_n, int bm, int bn,
+                                                                                  int batch, int steps, int* tm, int* tn) {
   const int bands = order_of(tiles_m, tiles_n, bm, bn, symmetric != 0, epi, batch, steps);
   const int n = symmetric ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
   for (int i = 0; i < n; ++i) tile_of(i, tiles_m, tiles_n, symmetric != 0, bands, tm + i, tn + i);
+  return bands;
 }
 
 int gemm_num_workgroups(const GemmArgs& a, GemmEpilogue epi, int batch) { return (int)(choose(a, epi, batch).tiles * batch); }

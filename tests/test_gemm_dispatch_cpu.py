@@ -80,3 +80,21 @@ def test_narrow_heads_take_the_faster_statistics_step(dh, heads, T, one_launch):
     and heads of width 128 have other ways.)"""
     L = binding.load()
     assert L.conqur_head_step_narrow_for_tests(dh, heads, ctypes.c_int64(T)) == one_launch
+
+
+def in_bands(T, d, heads, nseg):
+    """Whether a rotation's tiles are taken in bands, not along the rows or columns of its grid."""
+    bm, bn = tile(EPI_ACT, 0, 0, T, d, d, nseg, heads)[:2]
+    m, n = -(-T // bm), -(-d // bn)
+    buf = np.empty((2, m * n), np.int32)
+    return binding.load().conqur_gemm_order_for_tests(EPI_ACT, 0, m, n, bm, bn, heads, -(-d // 64) * nseg, buf[0].ctypes.data_as(ctypes.c_void_p),
+                                                      buf[1].ctypes.data_as(ctypes.c_void_p)) > 1
+
+
+@pytest.mark.parametrize("T,d,heads,nseg,bands", [
+    (1936, 1040, 1, 6, 0), (4000, 1040, 1, 6, 0), (1100, 480, 1, 6, 0), (1500, 800, 1, 6, 0), (1936, 400, 1, 6, 0), (6000, 2096, 1, 1, 0), (603, 2096, 1, 1, 0),
+    (9190, 3344, 1, 1, 0), (9190, 304, 8, 1, 0), (12000, 304, 8, 1, 0), (777, 1040, 1, 6, 1), (872, 944, 1, 6, 1), (868, 1152, 1, 6, 1), (9190, 4096, 1, 1, 1),
+    (11008, 4096, 1, 1, 1), (4045, 4480, 1, 1, 1), (12000, 5120, 1, 1, 1)])
+def test_rotations_take_the_faster_order_of_tiles(T, d, heads, nseg, bands):
+    """As measured: each of these rotations is 3 to 18 % faster in the order stated than in the other."""
+    assert in_bands(T, d, heads, nseg) == bool(bands)
