@@ -78,65 +78,81 @@ __device__ __forceinline__ float again(float x) {
 // the hardware returns zeros (also for loads whose destination is LDS).
 constexpr uint32_t kOobOffset = 0x80000000u;
 
-// a / b for 0 <= a, 0 < b.  Below 2^21 by the fp32 reciprocal: (a + 1/2) / b lies at least 1 / 2b from a whole number, its
-// relative error is below 2^-22.  (The division ahead of a kernel's first loads is the latency of the launch: an integer one takes
-// several times as long.)
-__host__ __device__ inline int quotient(int a, int b) {
-#ifdef __HIP_DEVICE_COMPILE__
-  if (a < (1 << 21)) return (int)(((float)a + 0.5f) * __builtin_amdgcn_rcpf((float)b));
-#else
-  if (a < (1 << 21)) return (int)(((float)a + 0.5f) * (1.0f / (float)b));
-#endif
-  return a / b;
+// a / b for 0 <= a < 2^30, by one multiplication: m = ceil(2^(31 + l) / b) with l = floor(log2 b), so that a m / 2^(31 + l) exceeds a / b by
+// less than a / 2^(31 + l) < 1 / b.  (The division ahead of a kernel's first loads is the latency of the launch.)
+struct Divisor { uint32_t b, m, l; };
+inline Divisor divisor(int b) {
+  uint32_t l = 0;
+  while ((2u << l) <= (uint32_t)b) ++l;
+  return Divisor{(uint32_t)b, (uint32_t)(((1ull << (31 + l)) + b - 1) / b), l};
+}
+__host__ __device__ inline int quotient(int a, const Divisor& d) { return (int)((uint32_t)(((uint64_t)(2u * (uint32_t)a) * d.m) >> 32) >> d.l); }
+
+// The order of a launch's tiles.  Workgroups are dealt round-robin to the 8 XCDs (bid % 8), each with its own L2; every XCD
+// takes a run of consecutive tiles (the first n % 8 of them one tile more), numbered
+//   whole grids      in `bands` bands of tile rows of equal height (+- 1, the first ones higher), down the columns of one band after another;
+//                    1: down the columns of the grid, tiles_m: along its rows
+//   mirrored grids   (the tiles on and above the diagonal, tiles_m == tiles_n) the same in bands of `bands` rows; 0: tile rows r and T-1-r,
+//                    which hold T + 1 tiles between them, after one another
+// What the tiles that an XCD runs at a time read together is one panel per tile row and column they span: see order_of.
+struct TileOrder {
+  int tiles_m, tiles_n, bands;
+  int high_tiles, high_rows;   // whole grids: tiles and rows of the higher bands
+  Divisor high_band, high;     // ... tiles of such a band, its rows
+  Divisor band, rows;          // ... of the others; mirrored grids, rows: `bands`, or T + 1
+};
+
+inline TileOrder tile_order(int tiles_m, int tiles_n, bool sym, int bands) {
+  TileOrder o{tiles_m, tiles_n, bands, 0, 0, divisor(1), divisor(1), divisor(1), divisor(1)};
+  if (sym) {
+    o.rows = divisor(bands ? bands : tiles_m + 1);
+  } else {
+    const int h = tiles_m / bands, higher = tiles_m - h * bands;
+    o.high_rows = higher * (h + 1);
+    o.high_tiles = o.high_rows * tiles_n;
+    o.high_band = divisor((h + 1) * tiles_n); o.high = divisor(h + 1);
+    o.band = divisor(h * tiles_n); o.rows = divisor(h);
+  }
+  return o;
 }
 
-// Which tile workgroup bid computes.  Workgroups are dealt round-robin to the 8 XCDs (bid % 8), each with its own L2; every XCD
-// takes a run of consecutive tiles (the first n % 8 of them one tile more) in the order of the grid:
-//   bands > 0   whole grids: `bands` bands of tile rows of equal height (+- 1), down the columns of one band after another;
-//               mirrored grids (the tiles on and above the diagonal, tiles_m == tiles_n): the same in bands of `bands` rows
-//   0           along the rows; mirrored grids: tile rows r and T-1-r, which hold T + 1 tiles between them, after one another
-// What the tiles that an XCD runs at a time read together is one panel per tile row and column they span: see order_of.
-__host__ __device__ inline void tile_of(int bid, int tiles_m, int tiles_n, bool sym, int bands, int* tm, int* tn) {
-  const int n = sym ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
+// The tile workgroup bid computes.
+template <bool SYM>
+__host__ __device__ inline void tile_of(int bid, const TileOrder& o, int* tm, int* tn) {
+  const int T = o.tiles_m, n = SYM ? T * (T + 1) / 2 : T * o.tiles_n;
   const int x = bid & 7, rest = n & 7;
   int at = x * (n >> 3) + (x < rest ? x : rest) + (bid >> 3);
-  if (sym && bands == 0) {
-    const int pair = quotient(at, tiles_m + 1), within = at - pair * (tiles_m + 1);
-    const bool first = within < tiles_m - pair;
-    *tm = first ? pair : tiles_m - 1 - pair;
+  if constexpr (!SYM) {
+    const bool high = at < o.high_tiles;
+    const Divisor in_band = high ? o.high_band : o.band, rows = high ? o.high : o.rows;
+    if (!high) at -= o.high_tiles;
+    const int band = quotient(at, in_band);
+    at -= band * (int)in_band.b;
+    *tn = quotient(at, rows);
+    *tm = (high ? 0 : o.high_rows) + band * (int)rows.b + at - *tn * (int)rows.b;
+  } else if (o.bands == 0) {
+    const int pair = quotient(at, o.rows), within = at - pair * (T + 1);
+    const bool first = within < T - pair;
+    *tm = first ? pair : T - 1 - pair;
     *tn = first ? pair + within : within - 1;
-  } else if (sym) {
+  } else {
     int r0 = 0, h;
     for (;; r0 += h) {
-      h = bands < tiles_m - r0 ? bands : tiles_m - r0;
-      const int in_band = h * (tiles_m - r0) - h * (h - 1) / 2;
+      h = o.bands < T - r0 ? o.bands : T - r0;
+      const int in_band = h * (T - r0) - h * (h - 1) / 2;
       if (at < in_band) break;
       at -= in_band;
     }
     int c = 0;   // the band's columns: 1, 2 .. h tiles (its triangle), then h each
     while (c < h && at > c) { at -= c + 1; ++c; }
-    const int right = c < h ? 0 : quotient(at, h);
+    const int right = c < h ? 0 : quotient(at, o.rows);   // (h == bands: a lower band, the last one, is all triangle)
     *tm = r0 + at - right * h;
     *tn = r0 + c + right;
-  } else if (bands == 0) {
-    *tm = quotient(at, tiles_n);
-    *tn = at - *tm * tiles_n;
-  } else if (bands == 1) {
-    *tn = quotient(at, tiles_m);
-    *tm = at - *tn * tiles_m;
-  } else {
-    const int q = quotient(tiles_m, bands), r = tiles_m - q * bands;   // the first r bands have q + 1 rows
-    const int tall = r * (q + 1) * tiles_n;
-    const bool in_tall = at < tall;
-    const int h = in_tall ? q + 1 : q, local = in_tall ? at : at - tall;
-    const int band = quotient(local, h * tiles_n), in_band = local - band * (h * tiles_n);
-    *tn = quotient(in_band, h);
-    *tm = (in_tall ? 0 : r * (q + 1)) + band * h + in_band - *tn * h;
   }
 }
 
 template <int BM, int BN, int WGM, int WGN, int NSTAGE, int EPI, bool F16, bool SYM>
-__global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs g, const int tiles_m, const int tiles_n, const int bands) {
+__global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs g, const TileOrder order) {
   static_assert(!SYM || (BM == BN && (EPI == EPI_GRAMW || EPI == EPI_SQUARE || EPI == EPI_FRO2)),
                 "mirrored tiles: square tiles, symmetric results");
   constexpr int NW = WGM * WGN;                 // wavefronts per workgroup
@@ -157,10 +173,8 @@ __global__ void __launch_bounds__(64 * WGM * WGN) gemm_nt_kernel(const GemmArgs 
   const int kg = lane >> 4, col = lane & 15;    // operand fragments: row (or column) col, K elements 8 kg .. 8 kg + 7 of 32
 
   int tm, tn;
-  tile_of(blockIdx.x, tiles_m, tiles_n, SYM, bands, &tm, &tn);
-  tm = __builtin_amdgcn_readfirstlane(tm);   // (the reciprocal is a vector instruction)
-  tn = __builtin_amdgcn_readfirstlane(tn);
-  [[maybe_unused]] const int ntiles = tiles_m * tiles_n;
+  tile_of<SYM>(blockIdx.x, order, &tm, &tn);
+  [[maybe_unused]] const int tiles_m = order.tiles_m, ntiles = order.tiles_m * order.tiles_n;
   const int m0 = tm * BM, n0 = tn * BN;
   const int bz = blockIdx.z;
   const bf16_bits* Ab = g.A + (int64_t)bz * g.batchA;
@@ -1038,7 +1052,7 @@ int order_of(int tiles_m, int tiles_n, int bm, int bn, bool sym, int epi, int ba
   // along the columns or the rows, whichever reads fewer operand rows
   const int64_t down = (int64_t)std::min(share, tiles_m) * bm + (int64_t)(share / tiles_m + 1) * bn;
   const int64_t across = (int64_t)std::min(share, tiles_n) * bn + (int64_t)(share / tiles_n + 1) * bm;
-  const int line = across < down ? 0 : 1;
+  const int line = across < down ? tiles_m : 1;
   const bool short_k = rotates && steps < (one_round ? 80 : 16), large = rotates && one_round && bm * bn > 64 * 64;
   if (!square && (short_k || large || (one_round && !rotates))) return line;
   int best = 1;
@@ -1064,7 +1078,7 @@ hipError_t launch_one(const GemmArgs& a, int batch, hipStream_t stream) {
   const int tiles_m = (a.M + BM - 1) / BM, tiles_n = (a.N + BN - 1) / BN;
   dim3 grid(SYM ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n, 1, batch);
   const int bands = order_of(tiles_m, tiles_n, BM, BN, SYM, EPI, batch, (a.K + BK - 1) / BK * a.nseg);
-  hipLaunchKernelGGL(kern, grid, dim3(64 * WGM * WGN), smem, stream, a, tiles_m, tiles_n, bands);
+  hipLaunchKernelGGL(kern, grid, dim3(64 * WGM * WGN), smem, stream, a, tile_order(tiles_m, tiles_n, SYM, bands));
   return hipGetLastError();
 }
 
@@ -1118,7 +1132,8 @@ extern "C" __attribute__((visibility("default"))) int conqur_gemm_order_for_test
                                                                                   int batch, int steps, int* tm, int* tn) {
   const int bands = order_of(tiles_m, tiles_n, bm, bn, symmetric != 0, epi, batch, steps);
   const int n = symmetric ? tiles_m * (tiles_m + 1) / 2 : tiles_m * tiles_n;
-  for (int i = 0; i < n; ++i) tile_of(i, tiles_m, tiles_n, symmetric != 0, bands, tm + i, tn + i);
+  const TileOrder o = tile_order(tiles_m, tiles_n, symmetric != 0, bands);
+  for (int i = 0; i < n; ++i) symmetric ? tile_of<true>(i, o, tm + i, tn + i) : tile_of<false>(i, o, tm + i, tn + i);
   return bands;
 }
 

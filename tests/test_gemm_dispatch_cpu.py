@@ -87,8 +87,9 @@ def in_bands(T, d, heads, nseg):
     bm, bn = tile(EPI_ACT, 0, 0, T, d, d, nseg, heads)[:2]
     m, n = -(-T // bm), -(-d // bn)
     buf = np.empty((2, m * n), np.int32)
-    return binding.load().conqur_gemm_order_for_tests(EPI_ACT, 0, m, n, bm, bn, heads, -(-d // 64) * nseg, buf[0].ctypes.data_as(ctypes.c_void_p),
-                                                      buf[1].ctypes.data_as(ctypes.c_void_p)) > 1
+    bands = binding.load().conqur_gemm_order_for_tests(EPI_ACT, 0, m, n, bm, bn, heads, -(-d // 64) * nseg, buf[0].ctypes.data_as(ctypes.c_void_p),
+                                                       buf[1].ctypes.data_as(ctypes.c_void_p))
+    return 1 < bands < m   # (1: down the columns; m: along the rows)
 
 
 @pytest.mark.parametrize("T,d,heads,nseg,bands", [
