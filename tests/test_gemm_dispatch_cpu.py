@@ -99,3 +99,15 @@ def in_bands(T, d, heads, nseg):
 def test_rotations_take_the_faster_order_of_tiles(T, d, heads, nseg, bands):
     """As measured: each of these rotations is 3 to 18 % faster in the order stated than in the other."""
     assert in_bands(T, d, heads, nseg) == bool(bands)
+
+
+@pytest.mark.parametrize("epi,m,n,bm,bn,rows", [(EPI_F32, 16, 16, 256, 256, 4), (EPI_F32, 32, 32, 256, 256, 4), (EPI_F32, 16, 16, 128, 128, 4),
+                                                (EPI_F32, 16, 16, 64, 64, 4), (EPI_F32, 16, 16, 192, 192, 4), (EPI_XOUT, 32, 32, 256, 256, 4),
+                                                (EPI_ACT, 32, 8, 256, 256, 4), (EPI_ACT, 16, 32, 64, 64, 8)])
+def test_the_wider_of_two_blocks_that_read_the_same(epi, m, n, bm, bn, rows):
+    """Whole 4 x 8 or 8 x 4 blocks: the tiles an XCD takes at a time span so many tile rows (as measured, 1 to 6 % of a launch)."""
+    buf = np.empty((2, m * n), np.int32)
+    binding.load().conqur_gemm_order_for_tests(epi, 0, m, n, bm, bn, 1, 32, buf[0].ctypes.data_as(ctypes.c_void_p), buf[1].ctypes.data_as(ctypes.c_void_p))
+    for xcd in range(8):
+        mine = buf[:, xcd::8][:, :32]
+        assert len(set(mine[0])) == rows and len(set(mine[1])) == 32 // rows
