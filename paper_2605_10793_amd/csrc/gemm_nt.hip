@@ -1055,10 +1055,11 @@ int order_of(int tiles_m, int tiles_n, int bm, int bn, bool sym, int epi, int ba
   const int line = across < down ? tiles_m : 1;
   const bool short_k = rotates && steps < (one_round ? 80 : 16), large = rotates && one_round && bm * bn > 64 * 64;
   if (!square && (short_k || large || (one_round && !rotates))) return line;
-  // Of two blocks that read the same, accumulating and 256 x 256 tiles take the wider one, whose rows of the result are longer: 4 x 8
-  // tiles instead of 8 x 4.  A step of 512 tokens at d = 4096 66.3 us in 4 x 8, 69.9 in 8 x 4, of 2048 124 and 128, of 512 at 8192
-  // 258 and 270; 64 x 64 tiles of rotations are the other way round, 1024 x 2048 14.4 and 13.5.
-  const bool wide = epi == EPI_F32 || (bm == 256 && bn == 256);
+  // Of two blocks that read the same, accumulating and 256 x 256 tiles of whole blocks take the wider one, whose rows of the result are
+  // longer: 4 x 8 tiles instead of 8 x 4.  A step of 512 tokens at d = 4096 66.3 us in 4 x 8, 69.9 in 8 x 4, of 2048 124 and 128, of
+  // 512 at 8192 258 and 270, 8192 x 8192 rotated 717 and 730.  The others are the other way round: 11008 x 4096 (43 x 16 tiles of
+  // 256 x 256) 292 and 288, 1024 x 2048 in 64 x 64 14.4 and 13.5.
+  const bool wide = epi == EPI_F32 || (square && bm == 256 && bn == 256);
   int best = 1;
   int64_t best_rows = INT64_MAX;
   for (int h = std::min(tiles_m, run); h >= 1; --h) {

@@ -111,3 +111,10 @@ def test_the_wider_of_two_blocks_that_read_the_same(epi, m, n, bm, bn, rows):
     for xcd in range(8):
         mine = buf[:, xcd::8][:, :32]
         assert len(set(mine[0])) == rows and len(set(mine[1])) == 32 // rows
+
+
+def test_a_grid_of_no_whole_blocks_keeps_the_taller_one():
+    """11008 x 4096 rotated in 256 x 256 tiles: bands of 7 and 8 rows (as measured, 1.5 % of the launch)."""
+    buf = np.empty((2, 43 * 16), np.int32)
+    assert binding.load().conqur_gemm_order_for_tests(EPI_ACT, 0, 43, 16, 256, 256, 1, 64, buf[0].ctypes.data_as(ctypes.c_void_p),
+                                                      buf[1].ctypes.data_as(ctypes.c_void_p)) == 6
