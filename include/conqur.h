@@ -91,7 +91,10 @@ typedef struct {
                            estimate of it (see polar_verify)                                         */
   double inner;         /* <R_new, M>, the Procrustes objective value (nuclear norm at the optimum)  */
   double m_fro;         /* ||M||_F                                                                  */
-  double ms;            /* device time of this update in milliseconds (all heads together)          */
+  double ms;            /* device time of this update in milliseconds (all heads together): from the start of
+                           its first launch to the report of its results, by the device's 100 MHz clock.
+                           conqur_get_timing's event times hold the launch's latency and its end as
+                           well, 2 to 5 us more                                                       */
   uint32_t orth_measured; /* 1: orth_err was measured; 0: it is the estimate                          */
   uint32_t reserved;
   double l1;            /* L of the rows this update consumed (as conqur_batch_stats.l1 just before it)   */

@@ -104,8 +104,8 @@ struct conqur_ctx {
   int clk_wg[2] = {0, 0};                            // workgroups that wrote them in the last step (0: none)
   hipEvent_t ev[ST_COUNT][2]{};
   bool ev_valid[ST_COUNT]{};
-  hipEvent_t ev_resid = nullptr;   // behind the copy of a closing residual: the host waits for this, not for the stream
-  hipEvent_t ev_sq = nullptr;      // behind the copy of ||D^2||_F^2 of the closing step's D^2 product
+  hipEvent_t ev_resid = nullptr;   // behind the launch that sums a closing residual: the host waits for this, not for the stream
+  hipEvent_t ev_sq = nullptr;      // behind the one that sums ||D^2||_F^2 of the closing step's D^2 product
   // Pinned: what the kernels of a call leave for the host they write here themselves (dev_*: the device's addresses).
   double* host_res = nullptr;      // [kResidSlots][heads] residual history, then the update's result block (5 heads, see UpdateEnd)
   double* dev_res = nullptr;
@@ -975,7 +975,11 @@ conqur_status conqur_update_rotation(conqur_ctx* ctx, conqur_update_stats* out) 
   // once, with nothing left to enqueue behind the outcome it expects.  (A last launch for that took 5 us: a calibration pass of 32 heads
   // of width 64 62.2 us with it and 60.8 without, of 128 102 and 98.5.)
   bool r_replaced = false, fused_done = false, stats_cleared = false;
-  auto fail_nonfinite = [&]() -> conqur_status {   // the context is left as the update found it
+  // The context is left as the update found it.  Reached from the outcome of a closing step in the main phase's launch, whose
+  // replacements are put back here, or from a residual the general path measures ahead of the step that writes R and of the last
+  // launch's clearing.  (Behind that step there is none: it follows a residual of at most 1e-2 sqrt(dh), from which the closing
+  // products stay finite.)
+  auto fail_nonfinite = [&]() -> conqur_status {
     if (r_replaced) {
       HIP_TRY(hipMemcpyAsync(ctx->R, ctx->Rprev, (size_t)plane * sizeof(float), hipMemcpyDeviceToDevice, s));
       const conqur_status st_op = refresh_operand(ctx);

@@ -963,8 +963,8 @@ constexpr bool fits_largest_8(int epi) {
 //                       3072 210 tiles, 35.2 us (192 x 192 42.2), at 2832 33.2 (39.5), at 3328 38.9 (45.3)
 //  96 x 64              polar and accumulate products: 1104^3 216 tiles, 9.2 us (64 x 64, some sharing a compute unit, 10.0); among an
 //                       update's other launches 11.3 and 13.2, the correction 18.3 (128 x 128 24.0)
-//  128 x 64             signs and operand of heads up to 64 wide: 32 x 2048 x 64 8.4 us (256 x 128, half of it empty, 10.6).  (The steps of
-//                       several such heads have a kernel of their own, head_step_narrow.hip: one head is left.)
+//  128 x 64             signs and operand of heads up to 64 wide: 32 x 2048 x 64 8.4 us (256 x 128, half of it empty, 10.6).  (Long
+//                       batches of one head or a few: the other steps of such heads are one launch, head_step_narrow.hip.)
 //  128 x 192            rotations of at most 256 such tiles (4 wavefronts of 64 x 96 read 80 KiB of LDS a K step, 8 of 64 x 48 would 112)
 //                       and applies: 2048 x 3072 rotated 36.0 us (192 tiles of 256 x 128 39.3), 1842 x 2576 34.8 (40.0), 978 x 4464
 //                       50.4 (59.5), with signs and operand 2.5 to 10 us less a step; update at 2304 727 (746).  Two rounds lose:
@@ -1022,9 +1022,9 @@ Choice choose(const GemmArgs& a, GemmEpilogue epi, int batch) {
   return best;
 }
 
-// The order of the tiles (`bands` of tile_of).  In bands, what an XCD runs at a time (32 tiles, or its whole share) is about square
-// and reads the fewest operand rows; along lines its whole share is one run of whole tile rows or columns, less regular reads
-// but none twice.  Which one wins was measured, us along lines and in bands:
+// The order of the tiles (`bands` of tile_of).  In bands, what an XCD runs at a time (32 tiles, or its whole share; tiles that share a
+// compute unit are counted alike) is about square and reads the fewest operand rows; along lines its whole share is one run
+// of whole tile rows or columns.  Which one wins was measured, us along lines and in bands:
 //   rotations of several rounds    bands where they read at most 0.6 of the rows (and K is long enough for that to count): 9190 x 4096 280
 //                                  and 264, 12000 x 5120 490 and 456, 4045 x 4480 166 and 161 (0.35 .. 0.5 of the rows); but 9190 x
 //                                  3344 171 and 181 (0.63), 9190 rows of 8 x 304, 5 steps, 34.0 and 35.8

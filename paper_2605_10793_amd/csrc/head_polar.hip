@@ -440,7 +440,7 @@ __global__ void __launch_bounds__(64 * NW, 2) k_head_polar(const bf16_bits* __re
     // correction product and finishing pass, with the same operand planes): D = (I - X^T X)/2 from the exact bf16 iterate,
     // X <- X + X (D + 1.5 D^2) with the correction as two bf16 planes, then R, the rotate operand R^T and <R, M>.
     // The step is taken only if this head's residual allows the quintic form (cl.res_max); otherwise the head reports
-    // its residual, marks the step as not taken (sq_out < 0) and the host continues on the general path from the
+    // its residual and a negative ||D^2||_F^2, which says that it did not, and the host continues on the general path from the
     // hand-over state written above.
     unsigned char* const sD = buf0;    // first plane of D (symmetric)
     // G = X^T X (products of bf16 values are exact in fp32), D = (I - G) / 2, ||I - G||_F^2

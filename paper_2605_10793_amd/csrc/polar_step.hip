@@ -109,11 +109,10 @@ __global__ void __launch_bounds__(64 * kNW) k_polar_step(const bf16_bits* __rest
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int kk = 0; kk < KB; ++kk) b[j][kk] = frag(sW, 16 * j, kk);
-    static_assert(TM <= 3, "row tiles of a wavefront");
+    static_assert(TM <= 2, "row tiles of a wavefront");
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
-      if (TM - i == 3) __builtin_amdgcn_s_waitcnt(vmcnt(16));
-      else if (TM - i == 2) __builtin_amdgcn_s_waitcnt(vmcnt(8));
+      if (TM - i == 2) __builtin_amdgcn_s_waitcnt(vmcnt(8));
       else __builtin_amdgcn_s_waitcnt(vmcnt(0));
       asm volatile("" ::: "memory");   // (the tile's reads stay behind the wait)
       f16x8 a[KB];
