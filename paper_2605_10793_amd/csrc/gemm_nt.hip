@@ -963,8 +963,9 @@ constexpr bool fits_largest_8(int epi) {
 //                       3072 210 tiles, 35.2 us (192 x 192 42.2), at 2832 33.2 (39.5), at 3328 38.9 (45.3)
 //  96 x 64              polar and accumulate products: 1104^3 216 tiles, 9.2 us (64 x 64, some sharing a compute unit, 10.0); among an
 //                       update's other launches 11.3 and 13.2, the correction 18.3 (128 x 128 24.0)
-//  128 x 64             signs and operand of heads up to 64 wide: 32 x 2048 x 64 8.4 us (256 x 128, half of it empty, 10.6).  (Long
-//                       batches of one head or a few: the other steps of such heads are one launch, head_step_narrow.hip.)
+//  128 x 64             signs and operand of heads up to 64 wide: 32 x 2048 x 64 8.4 us (256 x 128, half of it empty, 10.6).  What is
+//                       left to it are long batches of one head or a few (the other steps are one launch, head_step_narrow.hip): step of
+//                       4 heads of 64, 16384 tokens 80.4 and 77.3 us, of 8, 60000 285 and 266, of one, 65536 56.4 and 54.5
 //  128 x 192            rotations of at most 256 such tiles (4 wavefronts of 64 x 96 read 80 KiB of LDS a K step, 8 of 64 x 48 would 112)
 //                       and applies: 2048 x 3072 rotated 36.0 us (192 tiles of 256 x 128 39.3), 1842 x 2576 34.8 (40.0), 978 x 4464
 //                       50.4 (59.5), with signs and operand 2.5 to 10 us less a step; update at 2304 727 (746).  Two rounds lose:
